@@ -52,12 +52,14 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
     const int lane = threadIdx.x & 63;
     const int kBlock = blockDim.x;
 
-    for (int64_t w0 = blockIdx.x; w0 < work_items; w0 += gridDim.x) {
+    // order 1: blocks b, b + 8, b + 16, ... (they run on the same one of the 8 dies) take
+    // consecutive work items: each die streams through an eighth of the list.  The eighths are
+    // rounded up, so there are 8 * per places and the last ones may hold no item.
+    const int64_t per = (work_items + 7) >> 3;
+    const int64_t places = order == 1 ? 8 * per : work_items;
+    for (int64_t w0 = blockIdx.x; w0 < places; w0 += gridDim.x) {
         int64_t w = w0;
         if (order == 1) {
-            // blocks b, b + 8, b + 16, ... (they run on the same one of the 8 dies) take
-            // consecutive work items: each die streams through an eighth of the list
-            const int64_t per = (work_items + 7) >> 3;
             w = (w0 & 7) * per + (w0 >> 3);
             if (w >= work_items) continue;
         }
