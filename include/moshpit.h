@@ -117,10 +117,10 @@ int moshpit_create(int64_t N, int64_t P, int32_t M, int32_t d, int32_t dtype, mo
 int moshpit_destroy(moshpit_ctx *h);
 
 /* Attach the peer-state matrix.  state_dev: device, borrowed, must stay valid
- * while the handle uses it.  row_stride_elems >= P.  Rows that start on 16-byte
- * boundaries (state_dev and row_stride_elems*elem_size multiples of 16) take
- * the 128-bit path; anything else is still correct through an element-wise
- * path.  hip_stream: a hipStream_t, or NULL for the default stream. */
+ * while the handle uses it.  row_stride_elems >= P.  Rows may start on any
+ * element; rows of at least 16 bytes take 128-bit accesses, which cost least
+ * where rows start on 16-byte boundaries.  hip_stream: a hipStream_t, or NULL
+ * for the default stream. */
 int moshpit_bind_state(moshpit_ctx *h, void *state_dev, int64_t row_stride_elems, void *hip_stream);
 
 /* One averaging round t >= 0 (Alg. 1, one pass of its loop body; App. C.3's

@@ -401,7 +401,7 @@ int moshpit_bind_state(moshpit_ctx *h, void *state_dev, int64_t row_stride_elems
         return fail(h, MOSHPIT_EINVAL, "state pointer is not device memory");
     }
     if (h->X) HIP_TRY(h, hipStreamSynchronize(h->stream));
-    const int64_t need = dist_partials_count(h->dtype, h->P, row_stride_elems, state_dev);
+    const int64_t need = dist_partials_count(h->dtype, h->P);
     if (need > h->partials_cap) {
         if (h->d_partials) HIP_TRY(h, hipFree(h->d_partials));
         h->d_partials = nullptr;
@@ -568,7 +568,9 @@ int moshpit_dist_to_mean_static(const void *state_dev, int64_t N, int64_t P, int
         return fail(nullptr, MOSHPIT_EINVAL, "state pointer is not aligned to the element size");
     if (reinterpret_cast<uintptr_t>(out_dev) % sizeof(double) != 0)
         return fail(nullptr, MOSHPIT_EINVAL, "output pointer is not aligned to 8 bytes");
-    const int64_t need = dist_partials_count(dtype, P, row_stride_elems, state_dev);
+    // (one partial sum per 64 elements is reserved where rows are not 16-byte aligned)
+    const bool aligned = reinterpret_cast<uintptr_t>(state_dev) % 16 == 0 && (row_stride_elems * esize) % 16 == 0;
+    const int64_t need = aligned ? dist_partials_count(dtype, P) : (P + 63) / 64;
     if (need > kStaticPartials)
         return fail(nullptr, MOSHPIT_EINVAL,
                     "rows of %lld elements need %lld partial sums, the static scratch holds %lld "

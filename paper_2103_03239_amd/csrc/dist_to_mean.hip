@@ -17,6 +17,7 @@
 #include <mutex>
 
 #include "moshpit_internal.h"
+#include "row_vec.h"
 
 // Partial sums of the allocation-free entry point: one double per block of the
 // first kernel, kept in the code object so that no call ever allocates.  Every
@@ -27,9 +28,6 @@ static __device__ __align__(256) double scratch[moshpit::kStaticPartials];
 
 namespace moshpit {
 namespace {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -76,14 +74,16 @@ template <> struct Wide<1, 1> {
 };
 
 // X         byte pointer to element (row 0, first column of this launch)
-// nvec      vectors of VE elements per row covered by this launch
+// valid_bytes  bytes of a row; it has ceil(valid_bytes / vector size) vectors of VE elements.
+//           Rows may start on any element; where a row is not a whole number of vectors its last
+//           one ends with the row and the elements it shares with its neighbour count as 0 in it.
 // partials  one double per block: sum over the block's columns of s2 - s1^2/n
 // present   nullptr, or N bytes: rows with 0 are left out of mean and sum
 //           (vertices of a partly filled grid that hold no peer)
 // first     index of the first row that counts; n = number of rows that count
 template <int DT, int VE, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) void dist_partial_kernel(const char *__restrict__ X, int64_t row_bytes,
-                                                                    int64_t nvec, int64_t N,
+                                                                    int64_t valid_bytes, int64_t N,
                                                                     double *__restrict__ partials,
                                                                     const uint8_t *__restrict__ present,
                                                                     int64_t first, int64_t n)
@@ -96,13 +96,16 @@ __global__ __launch_bounds__(kWaves * 64) void dist_partial_kernel(const char *_
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int64_t v = static_cast<int64_t>(blockIdx.x) * 64 + lane;
-    const bool valid = v < nvec;
-    const char *col = X + v * static_cast<int64_t>(sizeof(mem_t));
+    constexpr int64_t kVec = sizeof(mem_t);
+    const bool valid = v * kVec < valid_bytes;
+    const int64_t at = v * kVec < valid_bytes - kVec ? v * kVec : valid_bytes - kVec;
+    const int shared = static_cast<int>((v * kVec - at) / (kVec / NE));      // elements that belong to the neighbour
+    const char *col = X + at;
 
     double x0[NE], s1[NE], s2[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) { x0[e] = 0.0; s1[e] = 0.0; s2[e] = 0.0; }
-    if (valid) V::widen(*reinterpret_cast<const mem_t *>(col + first * row_bytes), x0);
+    if (valid) V::widen(load_vec<false, mem_t>(col + first * row_bytes), x0);
 
     for (int64_t i0 = wave; i0 < N; i0 += kWaves * kRowsInFlight) {
         mem_t buf[kRowsInFlight];
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(kWaves * 64) void dist_partial_kernel(const char *_
         for (int u = 0; u < kRowsInFlight; ++u) {
             const int64_t i = i0 + static_cast<int64_t>(u) * kWaves;
             have[u] = valid && i < N && (present == nullptr || present[i] != 0);
-            if (have[u]) buf[u] = __builtin_nontemporal_load(reinterpret_cast<const mem_t *>(col + i * row_bytes));
+            if (have[u]) buf[u] = load_vec<true, mem_t>(col + i * row_bytes);
         }
 #pragma unroll
         for (int u = 0; u < kRowsInFlight; ++u) {
@@ -139,7 +142,7 @@ __global__ __launch_bounds__(kWaves * 64) void dist_partial_kernel(const char *_
             double t1 = 0.0, t2 = 0.0;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) { t1 += sh[0][w][lane]; t2 += sh[1][w][lane]; }
-            if (valid) colsum += t2 - t1 * t1 / static_cast<double>(n);
+            if (valid && e >= shared) colsum += t2 - t1 * t1 / static_cast<double>(n);
         }
         __syncthreads();
     }
@@ -165,63 +168,40 @@ __global__ __launch_bounds__(256) void dist_final_kernel(const double *__restric
     if (threadIdx.x == 0) out[0] = sh[0] / static_cast<double>(n);
 }
 
-struct Split {
-    int64_t nvec;       // 128-bit vectors per row
-    int64_t tail0;      // first element-wise column
-    int64_t blocks_vec, blocks_tail;
-};
-
-Split split_row(int dtype, int64_t P, int64_t row_stride, const void *X)
+int64_t row_blocks(int dtype, int64_t P)
 {
-    const int64_t esize = dtype == 0 ? 4 : 2;
-    const int64_t ve = dtype == 0 ? 4 : 8;
-    const bool aligned = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && ((row_stride * esize) % 16 == 0);
-    Split s;
-    s.nvec = aligned ? P / ve : 0;
-    s.tail0 = s.nvec * ve;
-    s.blocks_vec = (s.nvec + 63) / 64;
-    s.blocks_tail = (P - s.tail0 + 63) / 64;
-    return s;
+    const int64_t valid_bytes = P * (dtype == 0 ? 4 : 2);
+    const int64_t nvec = valid_bytes < 16 ? P : (valid_bytes + 15) / 16;
+    return (nvec + 63) / 64;
 }
 
 }  // namespace
 
-int64_t dist_partials_count(int dtype, int64_t P, int64_t row_stride, const void *X)
-{
-    const Split s = split_row(dtype, P, row_stride, X);
-    return s.blocks_vec + s.blocks_tail;
-}
+int64_t dist_partials_count(int dtype, int64_t P) { return row_blocks(dtype, P); }
 
 hipError_t launch_dist_to_mean(const void *X, int dtype, int64_t N, int64_t P, int64_t row_stride,
                                double *partials, double *out, const uint8_t *present, int64_t first, int64_t n,
                                hipStream_t stream)
 {
-    const Split s = split_row(dtype, P, row_stride, X);
-    if (s.blocks_vec > 0x7fffffffLL || s.blocks_tail > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int64_t blocks = row_blocks(dtype, P);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int64_t esize = dtype == 0 ? 4 : 2;
-    const int64_t row_bytes = row_stride * esize;
+    const int64_t row_bytes = row_stride * esize, valid_bytes = P * esize;
     const char *base = static_cast<const char *>(X);
     // about 256 rows per wave (measured best on MI355X for 64 <= N <= 4096)
     int waves = 1;
     while (waves < kMaxWaves && N / (waves * 2) >= 256) waves *= 2;
-    const char *tbase = base + s.tail0 * esize;
-    double *tpart = partials + s.blocks_vec;
+    const dim3 grid(static_cast<uint32_t>(blocks));
+#define MOSHPIT_DIST_CALL(DT, VE, W) \
+    dist_partial_kernel<DT, VE, W><<<grid, dim3(W * 64), 0, stream>>>(base, row_bytes, valid_bytes, N, partials, present, first, n)
 #define MOSHPIT_DIST(W)                                                                                        \
     if (waves == W) {                                                                                          \
-        const dim3 block(W * 64);                                                                              \
-        if (s.blocks_vec > 0) {                                                                                \
-            const dim3 grid(static_cast<uint32_t>(s.blocks_vec));                                              \
-            if (dtype == 0)                                                                                    \
-                dist_partial_kernel<0, 4, W><<<grid, block, 0, stream>>>(base, row_bytes, s.nvec, N, partials, present, first, n); \
-            else                                                                                               \
-                dist_partial_kernel<1, 8, W><<<grid, block, 0, stream>>>(base, row_bytes, s.nvec, N, partials, present, first, n); \
-        }                                                                                                      \
-        if (s.blocks_tail > 0) {                                                                               \
-            const dim3 grid(static_cast<uint32_t>(s.blocks_tail));                                             \
-            if (dtype == 0)                                                                                    \
-                dist_partial_kernel<0, 1, W><<<grid, block, 0, stream>>>(tbase, row_bytes, P - s.tail0, N, tpart, present, first, n); \
-            else                                                                                               \
-                dist_partial_kernel<1, 1, W><<<grid, block, 0, stream>>>(tbase, row_bytes, P - s.tail0, N, tpart, present, first, n); \
+        if (valid_bytes >= 16) {                                                                               \
+            if (dtype == 0) MOSHPIT_DIST_CALL(0, 4, W);                                                        \
+            else MOSHPIT_DIST_CALL(1, 8, W);                                                                   \
+        } else {                                                                                               \
+            if (dtype == 0) MOSHPIT_DIST_CALL(0, 1, W);                                                        \
+            else MOSHPIT_DIST_CALL(1, 1, W);                                                                   \
         }                                                                                                      \
     }
     MOSHPIT_DIST(1)
@@ -230,11 +210,12 @@ hipError_t launch_dist_to_mean(const void *X, int dtype, int64_t N, int64_t P, i
     MOSHPIT_DIST(8)
     MOSHPIT_DIST(16)
 #undef MOSHPIT_DIST
+#undef MOSHPIT_DIST_CALL
     {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    dist_final_kernel<<<dim3(1), dim3(256), 0, stream>>>(partials, s.blocks_vec + s.blocks_tail, n, out);
+    dist_final_kernel<<<dim3(1), dim3(256), 0, stream>>>(partials, blocks, n, out);
     return hipGetLastError();
 }
 

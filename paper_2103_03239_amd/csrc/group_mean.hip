@@ -29,7 +29,12 @@ constexpr int kLdsPerCu = 160 * 1024;   // gfx950: LDS bytes per compute unit
 
 // X            state, byte pointer to element (row 0, first column of this launch)
 // row_bytes    distance between rows in bytes
-// nvec         vectors of VE elements per row covered by this launch
+// valid_bytes  bytes of a row; nvec = ceil(valid_bytes / vector size) vectors of VE elements.
+//              Rows may start on any element.  Where a row is not a whole number of vectors its
+//              last vector ends with the row and shares columns with its neighbour; both are
+//              averaged, with the same bits.  The two always belong to one work item of one wave
+//              (a work item that would start with that last vector starts one vector earlier),
+//              whose loads all come before its stores.
 // tiles        ceil(nvec / (blockDim.x * COLS))
 // work_items   groups * tiles
 // IDX          groups are consecutive chunks of M entries of the peer list
@@ -39,7 +44,7 @@ constexpr int kLdsPerCu = 160 * 1024;   // gfx950: LDS bytes per compute unit
 //              (rows g_row_bytes apart); a peer that is alone in its group still
 //              takes its local step
 template <int DT, int VE, int COLS, int U, bool NT, bool IDX, bool SGD>
-__global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t row_bytes, int64_t nvec,
+__global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t row_bytes, int64_t valid_bytes,
                                                             const uint8_t *__restrict__ alive, int32_t M,
                                                             int64_t S, int64_t tiles, int64_t work_items,
                                                             const int32_t *__restrict__ index, int64_t n_index,
@@ -51,6 +56,10 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
     constexpr int NE = V::NE;
     const int lane = threadIdx.x & 63;
     const int kBlock = blockDim.x;
+    constexpr int64_t kVec = sizeof(mem_t);
+    const int64_t nvec = (valid_bytes + kVec - 1) / kVec;
+    // the ragged last vector would be a work item of its own
+    const bool lone_last = valid_bytes % kVec != 0 && tiles > 1 && nvec == (tiles - 1) * kBlock * COLS + 1;
 
     // order 1: blocks b, b + 8, b + 16, ... (they run on the same one of the 8 dies) take
     // consecutive work items: each die streams through an eighth of the list.  The eighths are
@@ -80,14 +89,23 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
         const int cnt = __popcll(live);
         if (cnt < (SGD ? 1 : 2)) continue;           // nothing to do: rows stay as they are
 
-        const int64_t v0 = tile * (static_cast<int64_t>(kBlock) * COLS) + threadIdx.x;
+        int64_t v0 = tile * (static_cast<int64_t>(kBlock) * COLS) + threadIdx.x, v_end = nvec;
+        if (lone_last) {
+            if (tile == tiles - 1) v0 -= 1;
+            else if (tile == tiles - 2) v_end -= 2;
+        }
         bool in_row[COLS];
+        int64_t at[COLS];                            // byte of the row where this lane's vector starts
 #pragma unroll
-        for (int c = 0; c < COLS; ++c) in_row[c] = (v0 + c * kBlock) < nvec;
+        for (int c = 0; c < COLS; ++c) {
+            const int64_t v = v0 + c * kBlock;
+            in_row[c] = v < v_end;
+            at[c] = v * kVec < valid_bytes - kVec ? v * kVec : valid_bytes - kVec;
+        }
 
-        char *gbase = X + base * row_bytes + v0 * static_cast<int64_t>(sizeof(mem_t));
+        char *gbase = X + base * row_bytes;
         const int64_t jstep = S * row_bytes;
-        // address of this lane's first vector in the row of position j (j is wave-uniform)
+        // first byte of the row of position j (j is wave-uniform)
         auto row_ptr = [&](int j) -> char * {
             if constexpr (IDX)
                 return gbase + static_cast<int64_t>(__builtin_amdgcn_readlane(my_row, j)) * row_bytes;
@@ -118,16 +136,15 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
                     if constexpr (SGD) gbuf[u][c] = V::zero();
                 }
                 if ((bits >> u) & 1ull) {
-                    const mem_t *src = reinterpret_cast<const mem_t *>(row_ptr(j0 + u));
+                    const char *src = row_ptr(j0 + u);
 #pragma unroll
                     for (int c = 0; c < COLS; ++c)
-                        if (in_row[c]) buf[u][c] = load_vec<NT>(src + c * kBlock);
+                        if (in_row[c]) buf[u][c] = load_vec<NT, mem_t>(src + at[c]);
                     if constexpr (SGD) {
-                        const mem_t *gsrc = reinterpret_cast<const mem_t *>(
-                            G + (base + (j0 + u) * S) * g_row_bytes + v0 * static_cast<int64_t>(sizeof(mem_t)));
+                        const char *gsrc = G + (base + (j0 + u) * S) * g_row_bytes;
 #pragma unroll
                         for (int c = 0; c < COLS; ++c)
-                            if (in_row[c]) gbuf[u][c] = load_vec<NT>(gsrc + c * kBlock);
+                            if (in_row[c]) gbuf[u][c] = load_vec<NT, mem_t>(gsrc + at[c]);
                     }
                 }
             }
@@ -168,10 +185,10 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
         while (rem != 0) {
             const int j = __builtin_ctzll(rem);
             rem &= rem - 1;
-            mem_t *dst = reinterpret_cast<mem_t *>(row_ptr(j));
+            char *dst = row_ptr(j);
 #pragma unroll
             for (int c = 0; c < COLS; ++c)
-                if (in_row[c]) store_vec<NT>(dst + c * kBlock, mean[c]);
+                if (in_row[c]) store_vec<NT, mem_t>(dst + at[c], mean[c]);
         }
     }
 }
@@ -180,10 +197,13 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
 // throttle: a block that reserves lds bytes lets floor(160 KiB / lds) blocks
 // share a compute unit, which bounds the number of row loads in flight.
 template <int DT, int VE, int COLS, int U, bool NT, bool IDX = false, bool SGD = false>
-hipError_t launch_one(char *X, int64_t row_bytes, int64_t nvec, const uint8_t *alive, const RoundGeom &geom,
+hipError_t launch_one(char *X, int64_t row_bytes, int64_t valid_bytes, const uint8_t *alive, const RoundGeom &geom,
                       int block, int waves_per_cu, int order, hipStream_t stream)
 {
-    if (nvec <= 0) return hipSuccess;
+    constexpr int64_t kVec = VE * (DT == 0 ? 4 : 2);
+    if (valid_bytes < kVec) return hipErrorInvalidValue;
+    const int64_t nvec = (valid_bytes + kVec - 1) / kVec;
+    if (valid_bytes % kVec != 0) block = 64;         // the last two vectors of a row belong to one wave
     const int64_t per_tile = static_cast<int64_t>(block) * COLS;
     const int64_t tiles = (nvec + per_tile - 1) / per_tile;
     const int64_t groups = IDX ? (geom.n_index + geom.M - 1) / geom.M : geom.N / geom.M;
@@ -203,7 +223,7 @@ hipError_t launch_one(char *X, int64_t row_bytes, int64_t nvec, const uint8_t *a
         hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsPerCu);
         if (e != hipSuccess) return e;
     }
-    kernel<<<dim3(static_cast<uint32_t>(grid)), dim3(block), lds, stream>>>(X, row_bytes, nvec, alive, geom.M,
+    kernel<<<dim3(static_cast<uint32_t>(grid)), dim3(block), lds, stream>>>(X, row_bytes, valid_bytes, alive, geom.M,
                                                                             geom.S, tiles, work, geom.index,
                                                                             geom.n_index, geom.grad, geom.grad_row_bytes,
                                                                             geom.gamma, order);
@@ -211,29 +231,37 @@ hipError_t launch_one(char *X, int64_t row_bytes, int64_t nvec, const uint8_t *a
 }
 
 template <int DT, int VE>
-hipError_t launch_shape(int cols, int unroll, bool nt, char *X, int64_t row_bytes, int64_t nvec,
+hipError_t launch_shape(int cols, int unroll, bool nt, char *X, int64_t row_bytes, int64_t valid_bytes,
                         const uint8_t *alive, const RoundGeom &geom, int block, int wpc, int order, hipStream_t stream)
 {
     if (geom.index != nullptr) {
-        // peer-list groups: the default shapes only, streaming accesses
-        if (cols == 1 && unroll == 16) return launch_one<DT, VE, 1, 16, true, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
-        if (cols == 2 && unroll == 8) return launch_one<DT, VE, 2, 8, true, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
-        if (cols == 4 && unroll == 4) return launch_one<DT, VE, 4, 4, true, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
-        if (cols == 4 && unroll == 2) return launch_one<DT, VE, 4, 2, true, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
+        // peer-list groups: the default shapes only
+        if (cols == 1 && unroll == 16) return nt ? launch_one<DT, VE, 1, 16, true, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 1, 16, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        if (cols == 2 && unroll == 8) return nt ? launch_one<DT, VE, 2, 8, true, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 2, 8, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        if (cols == 4 && unroll == 4) return nt ? launch_one<DT, VE, 4, 4, true, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 4, 4, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        if (cols == 4 && unroll == 2) return nt ? launch_one<DT, VE, 4, 2, true, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 4, 2, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
         return hipErrorInvalidValue;
     }
     if (geom.grad != nullptr) {
-        // Moshpit SGD step: the default shapes only, streaming accesses
-        if (cols == 1 && unroll == 16) return launch_one<DT, VE, 1, 16, true, false, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
-        if (cols == 2 && unroll == 8) return launch_one<DT, VE, 2, 8, true, false, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
-        if (cols == 4 && unroll == 4) return launch_one<DT, VE, 4, 4, true, false, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
-        if (cols == 4 && unroll == 2) return launch_one<DT, VE, 4, 2, true, false, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
+        // Moshpit SGD step: the default shapes only
+        if (cols == 1 && unroll == 16) return nt ? launch_one<DT, VE, 1, 16, true, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 1, 16, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        if (cols == 2 && unroll == 8) return nt ? launch_one<DT, VE, 2, 8, true, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 2, 8, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        if (cols == 4 && unroll == 4) return nt ? launch_one<DT, VE, 4, 4, true, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 4, 4, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        if (cols == 4 && unroll == 2) return nt ? launch_one<DT, VE, 4, 2, true, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                                                  : launch_one<DT, VE, 4, 2, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
         return hipErrorInvalidValue;
     }
 #define MOSHPIT_CASE(C, UU)                                                                          \
     if (cols == C && unroll == UU)                                                                   \
-        return nt ? launch_one<DT, VE, C, UU, true>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream)   \
-                  : launch_one<DT, VE, C, UU, false>(X, row_bytes, nvec, alive, geom, block, wpc, order, stream);
+        return nt ? launch_one<DT, VE, C, UU, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)   \
+                  : launch_one<DT, VE, C, UU, false>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
     MOSHPIT_CASE(1, 4)
     MOSHPIT_CASE(1, 8)
     MOSHPIT_CASE(1, 16)
@@ -256,12 +284,7 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
 {
     const int64_t esize = dtype == 0 ? 4 : 2;
     const int64_t row_bytes = row_stride * esize;
-    const bool aligned = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (row_bytes % 16 == 0) &&
-                         (geom.grad == nullptr || (reinterpret_cast<uintptr_t>(geom.grad) % 16 == 0 &&
-                                                   geom.grad_row_bytes % 16 == 0));
-    const int64_t ve = dtype == 0 ? 4 : 8;
-    const int64_t nvec = aligned ? P / ve : 0;          // 128-bit part of every row
-    const int64_t tail0 = nvec * ve;                    // first column of the element-wise part
+    const int64_t valid_bytes = P * esize;
 
     // Defaults (measured on MI355X over block sizes, rows in flight and resident waves):
     // one-wave blocks, each wave keeps about 16 KiB of row loads in flight
@@ -280,7 +303,18 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         }
         else { unroll = 2; cols = 4; }
     }
-    const bool nt = tune.nt != 0;
+    // Non-temporal or ordinary accesses (measured on MI355X; GB/s are bytes of one round over its time).
+    // Non-temporal ones are worth 3 - 17 % where a large state streams through (1 GiB, 16 x 16
+    // peers: 5.6 against 5.3 TB/s).  A state of up to 256 MiB stays in the last-level cache from
+    // round to round if the accesses are ordinary, and wants more waves in flight, since its latency
+    // is what limits: 256 MiB, 16 x 16 peers 5.4 -> 6.2 TB/s, 64 MiB 4.1 -> 4.7, 32 x 32 peers of
+    // 128 MiB 4.5 -> 5.7, 4 x 4 x 4 of 256 MiB 5.4 -> 6.4; at 512 MiB both are equal.  Rows that
+    // do not start on cache lines share their first and last lines with other work items: the parts
+    // have to meet in L2 (16 x 16 peers x 2,000,001 binary32: 4.5 -> 5.3 TB/s, x 1,200,007
+    // bfloat16: 4.3 -> 5.2, 4 x 4 x 4 x 9,000,001: 4.7 -> 5.6).
+    const bool cached = static_cast<double>(geom.N) * row_bytes * (geom.grad != nullptr ? 2 : 1) <= 256.0 * (1 << 20);
+    const bool whole_lines = reinterpret_cast<uintptr_t>(X) % 128 == 0 && row_bytes % 128 == 0;
+    const bool nt = tune.nt >= 0 ? tune.nt != 0 : (!cached && whole_lines);
     const int block = (tune.block == 64 || tune.block == 128 || tune.block == 256) ? tune.block : 64;
     // Block order (measured on MI355X over row sizes of 128 KiB .. 32 MiB, groups of 16 and of
     // 32 rows).  Work items go to the blocks tile-fastest, so the waves in flight stream a
@@ -292,7 +326,11 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     int order = tune.order;
     if (order < 0) {
         order = 0;
-        if (geom.index == nullptr) {
+        if (cached) {
+            order = geom.M > 8 ? 1 : 0;
+        } else if (!whole_lines) {
+            order = geom.M > (geom.grad != nullptr ? 8 : 16) ? 1 : 0;
+        } else if (geom.index == nullptr) {
             const int64_t member_stride = geom.S * row_bytes;
             const int64_t MiB = 1 << 20;
             if (geom.M <= 16 ? (member_stride >= 4 * MiB && member_stride <= 16 * MiB)
@@ -325,92 +363,83 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         }
         // groups of up to 4 rows with one vector per row and lane (4 KiB in flight per wave)
         if (rows * cols <= 4) wpc = full ? 14 : 21;
+        // ordinary accesses (see above): more in flight, 8 for bfloat16 rows off the cache lines
+        if (cached) wpc = geom.M > 8 ? 12 : 16;
+        else if (!whole_lines && rows * cols <= 4) wpc = 16;
+        else if (!whole_lines && rows == 16 && dtype == 1) wpc = 8;
         if (wpc > 32) wpc = 32;
     }
 
     char *base = static_cast<char *>(X);
-    hipError_t e = hipSuccess;
-    if (nvec > 0) {
-        e = dtype == 0 ? launch_shape<0, 4>(cols, unroll, nt, base, row_bytes, nvec, alive, geom, block, wpc, order, stream)
-                       : launch_shape<1, 8>(cols, unroll, nt, base, row_bytes, nvec, alive, geom, block, wpc, order, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (tail0 < P) {
-        char *tbase = base + tail0 * esize;
-        if (geom.grad != nullptr) {
-            RoundGeom tg = geom;
-            tg.grad = geom.grad + tail0 * esize;
-            e = dtype == 0 ? launch_one<0, 1, 1, 8, false, false, true>(tbase, row_bytes, P - tail0, alive, tg, 256, 32, 0, stream)
-                           : launch_one<1, 1, 1, 8, false, false, true>(tbase, row_bytes, P - tail0, alive, tg, 256, 32, 0, stream);
-        } else if (geom.index != nullptr)
-            e = dtype == 0 ? launch_one<0, 1, 1, 8, false, true>(tbase, row_bytes, P - tail0, alive, geom, 256, 32, 0, stream)
-                           : launch_one<1, 1, 1, 8, false, true>(tbase, row_bytes, P - tail0, alive, geom, 256, 32, 0, stream);
-        else
-            e = dtype == 0 ? launch_one<0, 1, 1, 8, false>(tbase, row_bytes, P - tail0, alive, geom, 256, 32, 0, stream)
-                           : launch_one<1, 1, 1, 8, false>(tbase, row_bytes, P - tail0, alive, geom, 256, 32, 0, stream);
-    }
-    return e;
+    if (valid_bytes >= 16)
+        return dtype == 0 ? launch_shape<0, 4>(cols, unroll, nt, base, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
+                          : launch_shape<1, 8>(cols, unroll, nt, base, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+    // rows of less than one vector, element by element
+    if (geom.grad != nullptr)
+        return dtype == 0 ? launch_one<0, 1, 1, 16, false, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
+                          : launch_one<1, 1, 1, 16, false, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
+    if (geom.index != nullptr)
+        return dtype == 0 ? launch_one<0, 1, 1, 16, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
+                          : launch_one<1, 1, 1, 16, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
+    return dtype == 0 ? launch_one<0, 1, 1, 16, false>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
+                      : launch_one<1, 1, 1, 16, false>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
 }
 
 // ---- local iteration of Moshpit SGD (Alg. 2): theta_i <- theta_i - gamma * g_i ----
 
 namespace {
+// A lane takes one 16-byte vector of a row, or the elements after the row's last whole vector.
 template <int DT, int VE>
 __global__ __launch_bounds__(256) void local_step_kernel(char *X, int64_t row_bytes, const char *__restrict__ G,
-                                                         int64_t g_row_bytes, int64_t nvec,
+                                                         int64_t g_row_bytes, int64_t P,
                                                          const uint8_t *__restrict__ alive, float gamma, int64_t tiles)
 {
     typedef Vec<DT, VE> V;
     typedef typename V::mem_t mem_t;
+    typedef Vec<DT, 1> V1;
+    typedef typename V1::mem_t mem1_t;
     constexpr int NE = V::NE;
     const int64_t row = blockIdx.x / tiles;
     const int64_t tile = blockIdx.x - row * tiles;
     if (alive != nullptr && alive[row] == 0) return;
-    const int64_t v = tile * 256 + threadIdx.x;
-    if (v >= nvec) return;
-    mem_t *x = reinterpret_cast<mem_t *>(X + row * row_bytes) + v;
-    const mem_t *g = reinterpret_cast<const mem_t *>(G + row * g_row_bytes) + v;
-    float xf[NE], gf[NE];
-    V::widen(load_vec<true>(x), xf);
-    V::widen(load_vec<true>(g), gf);
+    const int64_t first = (tile * 256 + threadIdx.x) * VE;      // first column of this lane
+    if (first >= P) return;
+    char *x = X + row * row_bytes + first * static_cast<int64_t>(sizeof(mem1_t));
+    const char *g = G + row * g_row_bytes + first * static_cast<int64_t>(sizeof(mem1_t));
+    if (first + VE <= P) {
+        float xf[NE], gf[NE];
+        V::widen(load_vec<true, mem_t>(x), xf);
+        V::widen(load_vec<true, mem_t>(g), gf);
 #pragma unroll
-    for (int e = 0; e < NE; ++e) xf[e] = fmaf(-gamma, gf[e], xf[e]);
-    store_vec<true>(x, V::narrow(xf));
-}
-
-template <int DT, int VE>
-hipError_t launch_local(char *X, int64_t row_bytes, const char *G, int64_t g_row_bytes, int64_t nvec, int64_t N,
-                        const uint8_t *alive, float gamma, hipStream_t stream)
-{
-    if (nvec <= 0) return hipSuccess;
-    const int64_t tiles = (nvec + 255) / 256;
-    const int64_t blocks = tiles * N;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    local_step_kernel<DT, VE><<<dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, stream>>>(X, row_bytes, G, g_row_bytes,
-                                                                                              nvec, alive, gamma, tiles);
-    return hipGetLastError();
+        for (int e = 0; e < NE; ++e) xf[e] = fmaf(-gamma, gf[e], xf[e]);
+        store_vec<true, mem_t>(x, V::narrow(xf));
+    } else {
+        for (int64_t c = 0; first + c < P; ++c) {
+            float xf[1], gf[1];
+            V1::widen(reinterpret_cast<mem1_t *>(x)[c], xf);
+            V1::widen(reinterpret_cast<const mem1_t *>(g)[c], gf);
+            xf[0] = fmaf(-gamma, gf[0], xf[0]);
+            reinterpret_cast<mem1_t *>(x)[c] = V1::narrow(xf);
+        }
+    }
 }
 }  // namespace
 
 hipError_t launch_local_step(void *X, int dtype, int64_t N, int64_t P, int64_t row_stride, const void *G,
                              int64_t g_row_stride, const uint8_t *alive, float gamma, hipStream_t stream)
 {
-    const int64_t esize = dtype == 0 ? 4 : 2;
-    const int64_t row_bytes = row_stride * esize, g_row_bytes = g_row_stride * esize;
-    const bool aligned = reinterpret_cast<uintptr_t>(X) % 16 == 0 && row_bytes % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(G) % 16 == 0 && g_row_bytes % 16 == 0;
-    const int64_t ve = dtype == 0 ? 4 : 8;
-    const int64_t nvec = aligned ? P / ve : 0;
-    const int64_t tail0 = nvec * ve;
+    const int64_t esize = dtype == 0 ? 4 : 2, ve = 16 / esize;
+    const int64_t tiles = (P + ve * 256 - 1) / (ve * 256);
+    const int64_t blocks = tiles * N;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     char *x = static_cast<char *>(X);
     const char *g = static_cast<const char *>(G);
-    hipError_t e = dtype == 0 ? launch_local<0, 4>(x, row_bytes, g, g_row_bytes, nvec, N, alive, gamma, stream)
-                              : launch_local<1, 8>(x, row_bytes, g, g_row_bytes, nvec, N, alive, gamma, stream);
-    if (e != hipSuccess || tail0 >= P) return e;
-    return dtype == 0 ? launch_local<0, 1>(x + tail0 * esize, row_bytes, g + tail0 * esize, g_row_bytes, P - tail0, N,
-                                           alive, gamma, stream)
-                      : launch_local<1, 1>(x + tail0 * esize, row_bytes, g + tail0 * esize, g_row_bytes, P - tail0, N,
-                                           alive, gamma, stream);
+    const dim3 grid(static_cast<uint32_t>(blocks)), block(256);
+    if (dtype == 0)
+        local_step_kernel<0, 4><<<grid, block, 0, stream>>>(x, row_stride * esize, g, g_row_stride * esize, P, alive, gamma, tiles);
+    else
+        local_step_kernel<1, 8><<<grid, block, 0, stream>>>(x, row_stride * esize, g, g_row_stride * esize, P, alive, gamma, tiles);
+    return hipGetLastError();
 }
 
 }  // namespace moshpit

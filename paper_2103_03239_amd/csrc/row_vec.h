@@ -72,16 +72,22 @@ template <> struct Vec<1, 1> {
     }
 };
 
-template <bool NT, typename T> __device__ __forceinline__ T load_vec(const T *p)
+// T at any address a row element can have: global memory takes 128-bit accesses at
+// element-aligned addresses (they cost an extra cache line where they straddle one).
+template <bool NT, typename T> __device__ __forceinline__ T load_vec(const void *p)
 {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
+    typedef T any_t __attribute__((aligned(2)));
+    const any_t *q = reinterpret_cast<const any_t *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(q);
+    else return *q;
 }
 
-template <bool NT, typename T> __device__ __forceinline__ void store_vec(T *p, const T &v)
+template <bool NT, typename T> __device__ __forceinline__ void store_vec(void *p, const T &v)
 {
-    if constexpr (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
+    typedef T any_t __attribute__((aligned(2)));
+    any_t *q = reinterpret_cast<any_t *>(p);
+    if constexpr (NT) __builtin_nontemporal_store(v, q);
+    else *q = v;
 }
 
 }  // namespace moshpit

@@ -11,13 +11,11 @@
 // waves keep 16 loads in flight each).  The row copy reaches 6.3 TB/s with about a
 // million blocks that walk the work items; fewer, longer-running blocks are slower
 // (5.3 TB/s with 64 per compute unit).
-#include "bf16_round.h"
 #include "moshpit_internal.h"
+#include "row_vec.h"
 
 namespace moshpit {
 namespace {
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLdsPerCu = 160 * 1024;
 
@@ -53,10 +51,10 @@ __global__ __launch_bounds__(256) void copy_probe_kernel(u32x4 *__restrict__ dst
 
 // Work item w = (returning peer r = w / chunks, chunk c = w % chunks of blockDim * VECS
 // vectors of its row); the blocks walk the items grid-stride, the number of items is
-// read on the device (counts[1] returning peers).  VEC: rows are 16-byte aligned
-// (128-bit copies, the ragged end of a row element by element by the block that has the
-// row's last chunk); otherwise everything element by element.
-template <int ESIZE, bool VEC, int VECS>
+// read on the device (counts[1] returning peers).  128-bit copies at element-aligned addresses
+// (non-temporal where rows are 16-byte aligned), the ragged end of a row element by element by
+// the block that has the row's last chunk.
+template <int ESIZE, bool NT, int VECS>
 __global__ __launch_bounds__(256) void refresh_copy_kernel(char *__restrict__ X, int64_t row_bytes, int64_t valid_bytes,
                                                            int64_t chunks, const int32_t *__restrict__ donor,
                                                            const int32_t *__restrict__ returning,
@@ -72,34 +70,29 @@ __global__ __launch_bounds__(256) void refresh_copy_kernel(char *__restrict__ X,
         char *dst = X + i * row_bytes;
         const int64_t c0 = c * chunk_bytes;
         const int64_t c1 = c0 + chunk_bytes < valid_bytes ? c0 + chunk_bytes : valid_bytes;
-        if (VEC) {
-            const int64_t v_end = c1 / 16 * 16;
-            u32x4 val[VECS];
+        const int64_t v_end = c0 + (c1 - c0) / 16 * 16;
+        u32x4 val[VECS];
 #pragma unroll
-            for (int k = 0; k < VECS; ++k) {
-                const int64_t o = c0 + (static_cast<int64_t>(k) * blockDim.x + threadIdx.x) * 16;
-                if (o < v_end) val[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + o));
-            }
-#pragma unroll
-            for (int k = 0; k < VECS; ++k) {
-                const int64_t o = c0 + (static_cast<int64_t>(k) * blockDim.x + threadIdx.x) * 16;
-                if (o < v_end) __builtin_nontemporal_store(val[k], reinterpret_cast<u32x4 *>(dst + o));
-            }
-            for (int64_t o = v_end + static_cast<int64_t>(threadIdx.x) * ESIZE; o < c1; o += blockDim.x * ESIZE)
-                *reinterpret_cast<elem_t *>(dst + o) = *reinterpret_cast<const elem_t *>(src + o);
-        } else {
-            for (int64_t o = c0 + static_cast<int64_t>(threadIdx.x) * ESIZE; o < c1; o += blockDim.x * ESIZE)
-                *reinterpret_cast<elem_t *>(dst + o) = *reinterpret_cast<const elem_t *>(src + o);
+        for (int k = 0; k < VECS; ++k) {
+            const int64_t o = c0 + (static_cast<int64_t>(k) * blockDim.x + threadIdx.x) * 16;
+            if (o < v_end) val[k] = load_vec<NT, u32x4>(src + o);
         }
+#pragma unroll
+        for (int k = 0; k < VECS; ++k) {
+            const int64_t o = c0 + (static_cast<int64_t>(k) * blockDim.x + threadIdx.x) * 16;
+            if (o < v_end) store_vec<NT, u32x4>(dst + o, val[k]);
+        }
+        for (int64_t o = v_end + static_cast<int64_t>(threadIdx.x) * ESIZE; o < c1; o += blockDim.x * ESIZE)
+            *reinterpret_cast<elem_t *>(dst + o) = *reinterpret_cast<const elem_t *>(src + o);
     }
 }
 
-template <int ESIZE, bool VEC, int VECS>
+template <int ESIZE, bool NT, int VECS>
 hipError_t launch_refresh_shape(const CopyShape &s, uint32_t grid, char *X, int64_t row_bytes, int64_t valid,
                                 const int32_t *donor, const int32_t *returning, const int32_t *counts,
                                 hipStream_t stream)
 {
-    auto kernel = refresh_copy_kernel<ESIZE, VEC, VECS>;
+    auto kernel = refresh_copy_kernel<ESIZE, NT, VECS>;
     const size_t lds = throttle_lds(s);
     if (lds > 0) {
         hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsPerCu);
@@ -111,16 +104,16 @@ hipError_t launch_refresh_shape(const CopyShape &s, uint32_t grid, char *X, int6
     return hipGetLastError();
 }
 
-template <int ESIZE, bool VEC>
+template <int ESIZE, bool NT>
 hipError_t launch_refresh_vecs(const CopyShape &s, uint32_t grid, char *X, int64_t row_bytes, int64_t valid,
                                const int32_t *donor, const int32_t *returning, const int32_t *counts,
                                hipStream_t stream)
 {
     switch (s.vecs) {
-    case 1: return launch_refresh_shape<ESIZE, VEC, 1>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
-    case 2: return launch_refresh_shape<ESIZE, VEC, 2>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
-    case 4: return launch_refresh_shape<ESIZE, VEC, 4>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
-    default: return launch_refresh_shape<ESIZE, VEC, 8>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
+    case 1: return launch_refresh_shape<ESIZE, NT, 1>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
+    case 2: return launch_refresh_shape<ESIZE, NT, 2>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
+    case 4: return launch_refresh_shape<ESIZE, NT, 4>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
+    default: return launch_refresh_shape<ESIZE, NT, 8>(s, grid, X, row_bytes, valid, donor, returning, counts, stream);
     }
 }
 
@@ -148,13 +141,13 @@ hipError_t launch_refresh_copy(void *X, int dtype, int64_t N, int64_t P, int64_t
     if (grid < static_cast<int64_t>(cus) * 64) grid = static_cast<int64_t>(cus) * 64;
     if (grid > static_cast<int64_t>(cus) * s.grid_per_cu) grid = static_cast<int64_t>(cus) * s.grid_per_cu;
     if (grid > N * chunks) grid = N * chunks;
-    const bool vec = reinterpret_cast<uintptr_t>(X) % 16 == 0 && row_bytes % 16 == 0;
+    const bool nt = reinterpret_cast<uintptr_t>(X) % 16 == 0 && row_bytes % 16 == 0;
     char *base = static_cast<char *>(X);
     const uint32_t g = static_cast<uint32_t>(grid);
     if (dtype == 0)
-        return vec ? launch_refresh_vecs<4, true>(s, g, base, row_bytes, valid, donor, returning, counts, stream)
+        return nt ? launch_refresh_vecs<4, true>(s, g, base, row_bytes, valid, donor, returning, counts, stream)
                    : launch_refresh_vecs<4, false>(s, g, base, row_bytes, valid, donor, returning, counts, stream);
-    return vec ? launch_refresh_vecs<2, true>(s, g, base, row_bytes, valid, donor, returning, counts, stream)
+    return nt ? launch_refresh_vecs<2, true>(s, g, base, row_bytes, valid, donor, returning, counts, stream)
                : launch_refresh_vecs<2, false>(s, g, base, row_bytes, valid, donor, returning, counts, stream);
 }
 
