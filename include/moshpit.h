@@ -88,20 +88,25 @@ typedef struct {
     int32_t  refresh;               /* 1: before every round of a run but its
                                        first, a peer that returns takes the
                                        parameters of an up-to-date peer (see
-                                       moshpit_refresh), drawn with `seed`; such
-                                       a run is never fused                      */
+                                       moshpit_refresh), drawn with `seed`       */
 } moshpit_schedule;
 
 /* Flags of moshpit_run.
- * MOSHPIT_RUN_FUSED allows consecutive rounds to run in one pass over HBM: a
- * tile made of the M^F rows of an F-dimensional sub-grid (F distinct axes) and
- * a slice of columns is closed under rounds on those axes, so it is loaded
- * once, averaged F times on chip (any number of times when F = d) and stored
- * once.  The state after a fused pass is bit-identical to the state after the
- * same rounds run one by one.  Where fusion does not apply or does not pay
- * (rows not 16-byte aligned, a sub-grid too tall for on-chip memory, a single
- * round left, two rounds on a sub-grid so tall that its rows get only 128
- * bytes on chip) the rounds run one by one. */
+ * The library may run consecutive rounds in one pass over HBM: a tile made of
+ * the M^F rows of an F-dimensional sub-grid (F distinct axes) and a slice of
+ * columns is closed under rounds on those axes, so it is loaded once, averaged
+ * F times on chip (any number of times when F = d) and stored once.  The state
+ * after a pass is bit-identical to the state after the same rounds run one by
+ * one.  On grids of up to 4096 peers with M <= 32 and rows of at least 16 bytes
+ * a pass covers the whole grid, with the distortion after every round and the
+ * refresh of returning peers computed on the way, whatever the flags; only a
+ * run that asks for the time of every single round (round_ms_out_host without
+ * MOSHPIT_RUN_FUSED) goes round by round there.
+ * MOSHPIT_RUN_FUSED allows passes on larger grids too (rows 16-byte aligned, no
+ * refresh, a sub-grid that fits on-chip memory, at least two rounds; three
+ * where its rows get only 128 bytes on chip), shares the time of a pass out
+ * evenly over its rounds, and leaves the distortion between the rounds of such
+ * a pass NaN. */
 enum {
     MOSHPIT_RUN_DEFAULT = 0,
     MOSHPIT_RUN_FUSED   = 1

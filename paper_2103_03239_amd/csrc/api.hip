@@ -33,6 +33,10 @@ struct moshpit_ctx {
     int32_t *d_refresh = nullptr;      // 3 N + 2 int32: candidates, donors, returning peers, counts
     uint8_t *d_refresh_masks = nullptr;  // 2 N bytes, for moshpit_refresh(host masks)
     int32_t *d_keys = nullptr;         // N
+    void *d_grid = nullptr;            // tables of whole-grid passes (see grid_tables): grid_rounds_cap rounds
+    int64_t grid_rounds_cap = 0;
+    double *d_grid_partials = nullptr; // their distortion sums: grid_partials_cap doubles
+    int64_t grid_partials_cap = 0;
     double *d_partials = nullptr;      // partials_cap doubles
     int64_t partials_cap = 0;
     double *d_dist = nullptr;          // dist_cap doubles
@@ -53,7 +57,9 @@ struct moshpit_ctx {
 
     // Die-and-rejoin schedule carried between calls: d_away[i] = rounds peer i still sits
     // out at the start of round away_t under (away_seed, away_threshold, away_down).
+    // (two buffers of N: a whole-grid plan reads one while it writes the other)
     int32_t *d_away = nullptr;
+    int away_half = 0;
     bool away_valid = false;
     uint64_t away_seed = 0;
     uint32_t away_threshold = 0;
@@ -195,6 +201,41 @@ int reserve_events(moshpit_ctx *h, size_t count)
     return MOSHPIT_OK;
 }
 
+uint32_t schedule_threshold(const moshpit_schedule *s)
+{
+    return static_cast<uint32_t>(std::floor((s ? s->p : 0.0) * 16777216.0));
+}
+
+// Die-and-rejoin state of the handle: where a schedule's walk to round t0 may start (from the
+// state a previous call left, when it belongs to this schedule and is not past t0) and where the
+// state at the end of the rounds goes.
+int away_before(moshpit_ctx *h, uint64_t seed, uint32_t threshold, int32_t down, int64_t t0, int64_t *s_begin,
+                const int32_t **away_in, int32_t **away_out)
+{
+    if (!h->d_away)
+        HIP_TRY(h, hipMalloc(reinterpret_cast<void **>(&h->d_away), 2 * sizeof(int32_t) * static_cast<size_t>(h->N)));
+    *s_begin = 0;
+    *away_in = nullptr;
+    if (h->away_valid && h->away_seed == seed && h->away_threshold == threshold && h->away_down == down &&
+        h->away_t <= t0 && h->away_t > 0) {
+        *s_begin = h->away_t;
+        *away_in = h->d_away + h->away_half * h->N;
+    }
+    *away_out = h->d_away + (h->away_half ^ 1) * h->N;
+    h->away_valid = false;
+    return MOSHPIT_OK;
+}
+
+void away_after(moshpit_ctx *h, uint64_t seed, uint32_t threshold, int32_t down, int64_t t)
+{
+    h->away_half ^= 1;
+    h->away_valid = true;
+    h->away_seed = seed;
+    h->away_threshold = threshold;
+    h->away_down = down;
+    h->away_t = t;
+}
+
 // Fill d_masks[0..rounds) for rounds t0.. under schedule s (s may be NULL).
 int queue_masks(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t rounds)
 {
@@ -205,32 +246,19 @@ int queue_masks(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t r
         if (rc != MOSHPIT_OK) return rc;
     } else {
         const int kind = s ? s->kind : MOSHPIT_SCHED_NONE;
-        const double p = s ? s->p : 0.0;
-        const uint32_t threshold = static_cast<uint32_t>(std::floor(p * 16777216.0));
+        const uint32_t threshold = schedule_threshold(s);
         const uint64_t seed = s ? s->seed : 0;
         const int32_t down = s ? s->down_rounds : 0;
         int64_t s_begin = 0;
         const int32_t *away_in = nullptr;
+        int32_t *away_out = nullptr;
         if (kind == MOSHPIT_SCHED_REJOIN) {
-            // go on from the state a previous call left, when it belongs to this schedule and is not past t0
-            if (!h->d_away)
-                HIP_TRY(h, hipMalloc(reinterpret_cast<void **>(&h->d_away), sizeof(int32_t) * static_cast<size_t>(h->N)));
-            if (h->away_valid && h->away_seed == seed && h->away_threshold == threshold && h->away_down == down &&
-                h->away_t <= t0 && h->away_t > 0) {
-                s_begin = h->away_t;
-                away_in = h->d_away;
-            }
-            h->away_valid = false;
+            rc = away_before(h, seed, threshold, down, t0, &s_begin, &away_in, &away_out);
+            if (rc != MOSHPIT_OK) return rc;
         }
-        HIP_TRY(h, launch_schedule(kind, threshold, seed, down, h->N, t0, rounds, h->d_masks, s_begin, away_in,
-                                   kind == MOSHPIT_SCHED_REJOIN ? h->d_away : nullptr, h->stream));
-        if (kind == MOSHPIT_SCHED_REJOIN) {
-            h->away_valid = true;
-            h->away_seed = seed;
-            h->away_threshold = threshold;
-            h->away_down = down;
-            h->away_t = t0 + rounds;
-        }
+        HIP_TRY(h, launch_schedule(kind, threshold, seed, down, h->N, t0, rounds, h->d_masks, s_begin, away_in, away_out,
+                                   h->stream));
+        if (kind == MOSHPIT_SCHED_REJOIN) away_after(h, seed, threshold, down, t0 + rounds);
     }
     if (s && s->group_skip) {
         if (s->refresh) {
@@ -313,6 +341,60 @@ int queue_round(moshpit_ctx *h, int64_t t, const uint8_t *alive_dev, float prese
     return MOSHPIT_OK;
 }
 
+// Tables of whole-grid passes over `rounds` rounds, one allocation:
+// [bitmaps rounds x N/M][copies rounds x N][copy counts rounds][flags N].
+GridTables grid_tables(const moshpit_ctx *h, int64_t rounds)
+{
+    GridTables g;
+    g.bitmaps = static_cast<uint32_t *>(h->d_grid);
+    g.copies = g.bitmaps + rounds * (h->N / h->M);
+    g.copy_counts = reinterpret_cast<int32_t *>(g.copies + rounds * h->N);
+    g.flags = reinterpret_cast<uint8_t *>(g.copy_counts + rounds);
+    return g;
+}
+
+// Queue the tables for rounds t0 .. t0+rounds-1 under schedule s (which has failures).
+int queue_grid_plan(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t rounds, GridTables *tables)
+{
+    if (rounds > h->grid_rounds_cap) {
+        if (h->d_grid) {
+            HIP_TRY(h, hipStreamSynchronize(h->stream));
+            HIP_TRY(h, hipFree(h->d_grid));
+            h->d_grid = nullptr;
+            h->grid_rounds_cap = 0;
+        }
+        const size_t words = static_cast<size_t>(rounds) * static_cast<size_t>(h->N / h->M + h->N + 1);
+        HIP_TRY(h, hipMalloc(&h->d_grid, words * 4 + static_cast<size_t>(h->N)));
+        h->grid_rounds_cap = rounds;
+    }
+    *tables = grid_tables(h, h->grid_rounds_cap);
+    GridSchedule g{};
+    g.kind = s->kind;
+    g.N = static_cast<int32_t>(h->N);
+    g.M = h->M;
+    g.d = h->d;
+    g.rounds = rounds;
+    g.down = s->down_rounds;
+    g.group_skip = s->group_skip != 0;
+    g.refresh = s->refresh != 0;
+    g.threshold = schedule_threshold(s);
+    g.seed = s->seed;
+    g.t0 = t0;
+    if (s->kind == MOSHPIT_SCHED_EXPLICIT) {
+        int rc = reserve_masks(h, rounds);
+        if (rc != MOSHPIT_OK) return rc;
+        rc = stage_to_device(h, h->d_masks, s->explicit_masks, static_cast<size_t>(rounds) * h->N);
+        if (rc != MOSHPIT_OK) return rc;
+        g.masks = h->d_masks;
+    } else if (s->kind == MOSHPIT_SCHED_REJOIN) {
+        int rc = away_before(h, g.seed, g.threshold, g.down, t0, &g.begin, &g.away_in, &g.away_out);
+        if (rc != MOSHPIT_OK) return rc;
+    }
+    HIP_TRY(h, launch_grid_plan(g, *tables, h->stream));
+    if (s->kind == MOSHPIT_SCHED_REJOIN) away_after(h, g.seed, g.threshold, g.down, t0 + rounds);
+    return MOSHPIT_OK;
+}
+
 int queue_dist(moshpit_ctx *h, double *out_dev)
 {
     HIP_TRY(h, launch_dist_to_mean(h->X, h->dtype, h->N, h->P, h->row_stride, h->d_partials, out_dev, nullptr, 0,
@@ -380,6 +462,8 @@ int moshpit_destroy(moshpit_ctx *h)
     if (h->d_refresh_masks) (void)hipFree(h->d_refresh_masks);
     if (h->d_keys) (void)hipFree(h->d_keys);
     if (h->d_partials) (void)hipFree(h->d_partials);
+    if (h->d_grid) (void)hipFree(h->d_grid);
+    if (h->d_grid_partials) (void)hipFree(h->d_grid_partials);
     if (h->d_dist) (void)hipFree(h->d_dist);
     delete h;
     return MOSHPIT_OK;
@@ -437,6 +521,148 @@ int moshpit_round_dev(moshpit_ctx *h, int64_t t, const uint8_t *alive_dev)
 }
 
 namespace {
+// Rounds t0 .. t0+rounds-1 in passes over the whole grid, when the shape allows it and a pass is
+// the better way: *done says whether the run has been queued (and waited for, with outputs).
+int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedule *s, int32_t flags,
+                double *dist_out_host, float *round_ms_out_host, const void *grad, int64_t grad_row_stride, float gamma,
+                bool *done)
+{
+    *done = false;
+    const bool failures = s && s->kind != MOSHPIT_SCHED_NONE;
+    const bool fused = (flags & MOSHPIT_RUN_FUSED) != 0;
+    // the time of every single round is asked for: round by round (a fused run's times are shared out)
+    if (round_ms_out_host && !fused) return MOSHPIT_OK;
+    if (rounds < 2 && !dist_out_host) return MOSHPIT_OK;
+    GridPlan plan;
+    if (!plan_grid(h->dtype, h->N, h->M, h->d, h->P, h->row_stride, h->X, t0, &plan)) return MOSHPIT_OK;
+    const bool refresh = failures && s->refresh != 0;
+
+    // A bfloat16 local step is rounded before the first round only where a fused pass is documented
+    // to do so; elsewhere the first round is the single-round kernel's.
+    const auto documented_pass = [&](int32_t r, FusedPlan *fp) {
+        const bool grad_fits = grad == nullptr || r > 0 ||
+                               (grad_row_stride == h->row_stride && reinterpret_cast<uintptr_t>(grad) % 16 == 0);
+        return fused && !refresh && grad_fits &&
+               plan_fused(h->dtype, h->N, h->M, h->d, h->P, h->row_stride, h->X, t0 + r, rounds - r, fp);
+    };
+    FusedPlan fp;
+    const bool step_in_pass = grad != nullptr && (h->dtype == MOSHPIT_F32 || documented_pass(0, &fp));
+    const bool step_first = grad != nullptr && !step_in_pass;
+    if (step_first && rounds < 2) return MOSHPIT_OK;
+
+    int rc = MOSHPIT_OK;
+    GridTables tables{};
+    if (failures && rounds > 0) {
+        if (step_first) rc = queue_masks(h, s, t0, rounds);          // (the first round reads the masks themselves)
+        if (rc == MOSHPIT_OK) rc = queue_grid_plan(h, s, t0, rounds, &tables);
+        if (rc != MOSHPIT_OK) return rc;
+    }
+    const int64_t entry_tiles = plan.tiles * plan.phases;
+    if (dist_out_host) {
+        rc = reserve_dist(h, static_cast<int64_t>(rounds) + 1);
+        if (rc != MOSHPIT_OK) return rc;
+        const int64_t need = (static_cast<int64_t>(rounds) + 1) * entry_tiles;
+        if (need > h->grid_partials_cap) {
+            if (h->d_grid_partials) {
+                HIP_TRY(h, hipStreamSynchronize(h->stream));
+                HIP_TRY(h, hipFree(h->d_grid_partials));
+                h->d_grid_partials = nullptr;
+                h->grid_partials_cap = 0;
+            }
+            HIP_TRY(h, hipMalloc(reinterpret_cast<void **>(&h->d_grid_partials), static_cast<size_t>(need) * sizeof(double)));
+            h->grid_partials_cap = need;
+        }
+    }
+    if (round_ms_out_host) {
+        rc = reserve_events(h, 2 * static_cast<size_t>(rounds));
+        if (rc != MOSHPIT_OK) return rc;
+    }
+    // with a local step the first entry (the distortion before it) is measured on its own
+    int32_t first_entry = 0;                                        // first entry the passes' partials hold
+    if (dist_out_host && grad != nullptr) {
+        rc = queue_dist(h, h->d_dist);
+        if (rc != MOSHPIT_OK) return rc;
+        first_entry = 1;
+    }
+    std::vector<int32_t> pass_rounds;
+    int32_t r = 0;
+    do {
+        const size_t pass = pass_rounds.size();
+        if (round_ms_out_host) HIP_TRY(h, hipEventRecord(h->events[2 * pass], h->stream));
+        int32_t now = 1;
+        if (step_first && r == 0) {
+            RoundGeom geom{h->N, h->M, axis_stride(h, t0)};
+            geom.grad = static_cast<const char *>(grad);
+            geom.grad_row_bytes = grad_row_stride * (h->dtype == MOSHPIT_F32 ? 4 : 2);
+            geom.gamma = gamma;
+            HIP_TRY(h, launch_group_mean(h->X, h->dtype, h->P, h->row_stride, geom, failures ? h->d_masks : nullptr, h->tune,
+                                         h->stream));
+            if (dist_out_host) {
+                rc = queue_dist(h, h->d_dist + 1);
+                if (rc != MOSHPIT_OK) return rc;
+                first_entry = 2;
+            }
+        } else {
+            GridPlan p = plan;
+            now = rounds - r < p.max_rounds ? rounds - r : p.max_rounds;
+            p.rounds = now;
+            p.axis0 = static_cast<int32_t>((t0 + r) % h->d);
+            if (failures && rounds > 0) {
+                p.bitmaps = tables.bitmaps + static_cast<int64_t>(r) * (h->N / h->M);
+                p.flags = tables.flags;
+                if (refresh) {
+                    p.copies = tables.copies + static_cast<int64_t>(r) * h->N;
+                    p.copy_counts = tables.copy_counts + r;
+                    p.refresh_first = r > 0;
+                }
+            }
+            if (grad != nullptr && r == 0) {
+                p.grad = static_cast<const char *>(grad);
+                p.grad_row_bytes = grad_row_stride * (h->dtype == MOSHPIT_F32 ? 4 : 2);
+                p.gamma = gamma;
+            }
+            if (dist_out_host) {
+                p.partials = h->d_grid_partials + static_cast<int64_t>(r) * entry_tiles;
+                p.dist_before = r == 0 && grad == nullptr;
+            }
+            HIP_TRY(h, launch_grid_rounds(h->X, h->dtype, p, h->stream));
+        }
+        if (round_ms_out_host) HIP_TRY(h, hipEventRecord(h->events[2 * pass + 1], h->stream));
+        r += now;
+        pass_rounds.push_back(now);
+    } while (r < rounds);
+    if (dist_out_host && first_entry <= rounds)
+        HIP_TRY(h, launch_grid_dist(h->d_grid_partials + first_entry * entry_tiles, entry_tiles, rounds + 1 - first_entry,
+                                    h->N, h->d_dist + first_entry, h->stream));
+    *done = true;
+    if (!dist_out_host && !round_ms_out_host) return MOSHPIT_OK;
+    if (dist_out_host)
+        HIP_TRY(h, hipMemcpyAsync(dist_out_host, h->d_dist, sizeof(double) * (static_cast<size_t>(rounds) + 1),
+                                  hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (dist_out_host) {
+        // with MOSHPIT_RUN_FUSED the entries inside what the header documents as one pass are NaN
+        int32_t q = 0;
+        while (q < rounds) {
+            int32_t len = 1;
+            if (documented_pass(q, &fp)) len = fp.rounds;
+            for (int32_t k = 1; k < len; ++k) dist_out_host[q + k] = std::nan("");
+            q += len;
+        }
+    }
+    if (round_ms_out_host) {
+        int32_t first = 0;
+        for (size_t pass = 0; pass < pass_rounds.size(); ++pass) {
+            float ms = 0.f;
+            HIP_TRY(h, hipEventElapsedTime(&ms, h->events[2 * pass], h->events[2 * pass + 1]));
+            for (int32_t i = 0; i < pass_rounds[pass]; ++i)
+                round_ms_out_host[first + i] = ms / static_cast<float>(pass_rounds[pass]);
+            first += pass_rounds[pass];
+        }
+    }
+    return MOSHPIT_OK;
+}
+
 // Rounds t0 .. t0+rounds-1 under schedule s.  grad != nullptr: an iteration of Moshpit SGD -
 // the peers present in round t0 first take their local step theta - gamma * g (fused into
 // the first pass over the state).
@@ -451,6 +677,11 @@ int run_impl(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedule 
     const bool failures = s && s->kind != MOSHPIT_SCHED_NONE;
     const bool refresh = failures && s->refresh != 0;
     if (refresh && h->N > 0x7fffffffLL) return fail(h, MOSHPIT_EINVAL, "too many peers for 32-bit donor indices");
+    {
+        bool done = false;
+        rc = run_on_grid(h, t0, rounds, s, flags, dist_out_host, round_ms_out_host, grad, grad_row_stride, gamma, &done);
+        if (rc != MOSHPIT_OK || done) return rc;
+    }
     // a refresh between two rounds moves rows across tiles: such runs go round by round
     const bool fused = (flags & MOSHPIT_RUN_FUSED) != 0 && !refresh;
     if (failures) {

@@ -32,144 +32,18 @@
 // flags: rows bytes][tile offset of
 // the first row of every group per axis][pad][RN(1/k), k = 0..64][16 bytes of zeros][16 bytes
 // of write-only trash].
-#include "bf16_round.h"
 #include "moshpit_internal.h"
+#include "tile_math.h"
 
 namespace moshpit {
 namespace {
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // BPC = blocks per compute unit (1 or 2): a block has 1024 / BPC threads and
 // 160 / BPC KiB of LDS, so a compute unit always runs 16 waves on one or two tiles.
 constexpr int threads_of(int bpc) { return 1024 / bpc; }
 constexpr int lds_of(int bpc) { return 160 * 1024 / bpc; }
-constexpr int kRcpBytes = 272;       // 65 reciprocals, padded to a multiple of 16 bytes
-constexpr int kNormalOrZero = 0x168;  // v_cmp_class mask: -normal, -0, +0, +normal
 constexpr int kMinSeg = 128;          // fewest bytes of a row in a tile
 constexpr int kPrefetch = 8;          // 128-bit vectors per thread: 1024 * 8 * 16 B = 128 KiB of tile
-
-// Block barrier that orders LDS traffic only.  __syncthreads() also waits for
-// every outstanding global load and store of the wave (its fence covers global
-// memory), which would serialise the tile prefetch and the store drain with
-// the rounds running in LDS.  Threads of a block exchange data through LDS
-// only, so waiting for the LDS counter before the barrier is sufficient.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Lane exchanges without a trip through LDS.  With rows of 16 lanes r0..r3,
-//   swap16(a, b) = ([a.r0, b.r0, a.r2, b.r2], [a.r1, b.r1, a.r3, b.r3])
-//   swap32(a, b) = ([a.r0, a.r1, b.r0, b.r1], [a.r2, a.r3, b.r2, b.r3])
-// (v_permlane16_swap / v_permlane32_swap).  Adding the two results of a swap of
-// two DIFFERENT values reduces both across a pair of rows at once and leaves
-// one of them in each row of the pair: the transposing reduction used below.
-struct LanePair { float first, second; };
-__device__ __forceinline__ LanePair swap16(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return LanePair{__uint_as_float(r[0]), __uint_as_float(r[1])};
-}
-__device__ __forceinline__ LanePair swap32(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return LanePair{__uint_as_float(r[0]), __uint_as_float(r[1])};
-}
-
-// CV consecutive columns of one row in LDS, widened to binary32.
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-template <int DT, int CV> struct Cols;
-template <> struct Cols<0, 4> {
-    typedef float elem_t;
-    static __device__ __forceinline__ void load(const elem_t *p, float (&f)[4])
-    {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(p);
-        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
-    }
-    static __device__ __forceinline__ void store(elem_t *p, const float (&f)[4])
-    {
-        *reinterpret_cast<f32x4 *>(p) = f32x4{f[0], f[1], f[2], f[3]};
-    }
-};
-template <> struct Cols<0, 2> {
-    typedef float elem_t;
-    static __device__ __forceinline__ void load(const elem_t *p, float (&f)[2])
-    {
-        const f32x2 v = *reinterpret_cast<const f32x2 *>(p);
-        f[0] = v.x; f[1] = v.y;
-    }
-    static __device__ __forceinline__ void store(elem_t *p, const float (&f)[2])
-    {
-        *reinterpret_cast<f32x2 *>(p) = f32x2{f[0], f[1]};
-    }
-};
-template <> struct Cols<0, 1> {
-    typedef float elem_t;
-    static __device__ __forceinline__ void load(const elem_t *p, float (&f)[1]) { f[0] = *p; }
-    static __device__ __forceinline__ void store(elem_t *p, const float (&f)[1]) { *p = f[0]; }
-};
-template <> struct Cols<1, 4> {
-    typedef uint16_t elem_t;
-    static __device__ __forceinline__ void load(const elem_t *p, float (&f)[4])
-    {
-        const u32x2 v = *reinterpret_cast<const u32x2 *>(p);
-        f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
-        f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
-    }
-    static __device__ __forceinline__ void store(elem_t *p, const float (&f)[4])
-    {
-        *reinterpret_cast<u32x2 *>(p) = u32x2{bf16_pair(f[0], f[1]), bf16_pair(f[2], f[3])};
-    }
-};
-template <> struct Cols<1, 2> {
-    typedef uint16_t elem_t;
-    static __device__ __forceinline__ void load(const elem_t *p, float (&f)[2])
-    {
-        const uint32_t v = *reinterpret_cast<const uint32_t *>(p);
-        f[0] = __uint_as_float(v << 16); f[1] = __uint_as_float(v & 0xffff0000u);
-    }
-    static __device__ __forceinline__ void store(elem_t *p, const float (&f)[2])
-    {
-        *reinterpret_cast<uint32_t *>(p) = bf16_pair(f[0], f[1]);
-    }
-};
-template <> struct Cols<1, 1> {
-    typedef uint16_t elem_t;
-    static __device__ __forceinline__ void load(const elem_t *p, float (&f)[1])
-    {
-        f[0] = __uint_as_float(static_cast<uint32_t>(*p) << 16);
-    }
-    static __device__ __forceinline__ void store(elem_t *p, const float (&f)[1])
-    {
-        *p = bf16_one(f[0]);
-    }
-};
-
-// One 16-byte tile slot (4 binary32 or 8 bfloat16 values) after a local step of
-// Moshpit SGD (Alg. 2): x - gamma * g, formed in binary32 with one fused multiply-add
-// per value and rounded to the storage type.
-template <int DT> __device__ __forceinline__ u32x4 local_step(const u32x4 &x, const u32x4 &g, float gamma)
-{
-    if constexpr (DT == 0) {
-        u32x4 out;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            out[e] = __float_as_uint(__fmaf_rn(-gamma, __uint_as_float(g[e]), __uint_as_float(x[e])));
-        return out;
-    } else {
-        u32x4 out;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float lo = __fmaf_rn(-gamma, __uint_as_float(g[e] << 16), __uint_as_float(x[e] << 16));
-            const float hi = __fmaf_rn(-gamma, __uint_as_float(g[e] & 0xffff0000u), __uint_as_float(x[e] & 0xffff0000u));
-            out[e] = bf16_pair(lo, hi);
-        }
-        return out;
-    }
-}
 
 // global row of local row lr: base + sum_f digit_f(lr) * gstride[f]
 __device__ __forceinline__ int64_t global_row(const FusedPlan &p, int64_t base, int32_t lr)
@@ -207,42 +81,6 @@ __device__ __forceinline__ TileRef tile_ref(const FusedPlan &p, int64_t w)
     const int64_t left = p.row_valid_bytes - t.col0_bytes;
     t.seg_bytes = static_cast<int32_t>(left < p.Wb ? left : p.Wb);
     return t;
-}
-
-// Sum of TREE positions j0..j0+TREE-1 of CV columns of a group, as the balanced
-// tree ((x0+x1)+(x2+x3))+...; positions whose bit is clear (absent peers, and
-// positions past the group, whose bits are never set) contribute an exact 0:
-// their read is redirected to `zeros`, 16 bytes of LDS that hold 0, which costs
-// one select per position instead of one per value.  Blocks of up to FLAT
-// positions are read at once; larger trees are the sum of their two balanced
-// halves, which bounds the register footprint.
-template <int DT, int CV, int TREE, int FLAT>
-__device__ __forceinline__ void tree_block(const typename Cols<DT, CV>::elem_t *col, int32_t step, int32_t j0,
-                                           const typename Cols<DT, CV>::elem_t *zeros, uint32_t bits,
-                                           float (&out)[CV])
-{
-    if constexpr (TREE > FLAT) {
-        float lo[CV], hi[CV];
-        tree_block<DT, CV, TREE / 2, FLAT>(col, step, j0, zeros, bits & ((1u << (TREE / 2)) - 1u), lo);
-        tree_block<DT, CV, TREE / 2, FLAT>(col, step, j0 + TREE / 2, zeros, bits >> (TREE / 2), hi);
-#pragma unroll
-        for (int e = 0; e < CV; ++e) out[e] = lo[e] + hi[e];
-    } else {
-        float f[TREE][CV];
-#pragma unroll
-        for (int u = 0; u < TREE; ++u) {
-            const bool on = (bits >> u) & 1u;
-            Cols<DT, CV>::load(on ? col + (j0 + u) * step : zeros, f[u]);
-        }
-#pragma unroll
-        for (int s = 1; s < TREE; s *= 2)
-#pragma unroll
-            for (int u = 0; u + s < TREE; u += 2 * s)
-#pragma unroll
-                for (int e = 0; e < CV; ++e) f[u][e] += f[u + s][e];
-#pragma unroll
-        for (int e = 0; e < CV; ++e) out[e] = f[0][e];
-    }
 }
 
 // TREE = size of the summation block actually needed: 16 for M > 8, else the
@@ -437,31 +275,8 @@ __global__ __launch_bounds__(threads_of(BPC)) __attribute__((amdgpu_waves_per_eu
                             for (int u = 0; u + w2 < PER; u += 2 * w2)
 #pragma unroll
                                 for (int e = 0; e < CV; ++e) f[u][e] += f[u + w2][e];
-                        // The SPLIT lanes of an item hold partial sums of its 4 columns.  They
-                        // are added across lanes so that each lane ends with the total of ONE
-                        // column (same order as the full tree: (s0 + s1) + (s2 + s3)), divides
-                        // that one, and the quotients are handed round: 6 (4) exchanges and 1
-                        // (2) divisions per lane instead of 8 (4) exchanges and 4 divisions.
                         static_assert(CV == 4, "lane-split items work on 4 columns");
-                        const float k = static_cast<float>(cnt);
-                        if constexpr (SPLIT == 4) {
-                            const LanePair a = swap16(f[0][0], f[0][1]);    // rows 0, 2: column 0; rows 1, 3: column 1
-                            const LanePair b = swap16(f[0][2], f[0][3]);    // rows 0, 2: column 2; rows 1, 3: column 3
-                            const LanePair c = swap32(a.first + a.second, b.first + b.second);
-                            const float mean = (0.f + (c.first + c.second)) / k;    // row r: column r
-                            const LanePair eo = swap16(mean, mean);         // columns 0|2 and 1|3 of my half
-                            const LanePair m02 = swap32(eo.first, eo.first);
-                            const LanePair m13 = swap32(eo.second, eo.second);
-                            acc[0] = m02.first; acc[1] = m13.first; acc[2] = m02.second; acc[3] = m13.second;
-                        } else {
-                            const LanePair a = swap32(f[0][0], f[0][1]);    // lower half: column 0, upper: column 1
-                            const LanePair b = swap32(f[0][2], f[0][3]);    // lower half: column 2, upper: column 3
-                            const float q01 = (0.f + (a.first + a.second)) / k;
-                            const float q23 = (0.f + (b.first + b.second)) / k;
-                            const LanePair m01 = swap32(q01, q01);
-                            const LanePair m23 = swap32(q23, q23);
-                            acc[0] = m01.first; acc[1] = m01.second; acc[2] = m23.first; acc[3] = m23.second;
-                        }
+                        mean_over_lanes<SPLIT>(f[0], static_cast<float>(cnt), acc);
                     } else if constexpr (TREE < 16) {
                         float t0[CV];
                         tree_block<DT, CV, TREE, FLAT>(col, step, 0, zeros, static_cast<uint32_t>(live), t0);
@@ -478,30 +293,7 @@ __global__ __launch_bounds__(threads_of(BPC)) __attribute__((amdgpu_waves_per_eu
                         }
                     }
                     if constexpr (SPLIT == 1 && CV > 1) {
-                        // acc / k for CV columns, sharing the reciprocal y = RN(1/k) (a table in
-                        // LDS, filled by true divisions): q0 = RN(acc * y), the exact remainder
-                        // r = acc - k * q0 (one fma), q = RN(q0 + r * y) is the correctly rounded
-                        // quotient whenever nothing underflows.  A q that is not a normal number
-                        // or zero (NaN from an infinite sum, subnormal) is redone with a true
-                        // division.  With this guard the sequence was compared with the division
-                        // for every count k <= 64 and all 2^32 binary32 numerators: the only
-                        // difference is -0 / k, and acc is never -0 (it starts from +0).
-                        const float k = static_cast<float>(cnt);
-                        float quo[CV];
-                        bool redo = false;
-#pragma unroll
-                        for (int e = 0; e < CV; ++e) {
-                            const float q0 = __fmul_rn(acc[e], y);
-                            const float r = __fmaf_rn(-k, q0, acc[e]);
-                            quo[e] = __fmaf_rn(r, y, q0);
-                            redo = redo || !__builtin_amdgcn_classf(quo[e], kNormalOrZero);
-                        }
-                        if (redo) {
-#pragma unroll
-                            for (int e = 0; e < CV; ++e) quo[e] = acc[e] / k;
-                        }
-#pragma unroll
-                        for (int e = 0; e < CV; ++e) acc[e] = quo[e];
+                        divide_columns<CV>(acc, static_cast<float>(cnt), y);
                     } else if constexpr (SPLIT == 1) {
                         acc[0] = acc[0] / static_cast<float>(cnt);
                     }

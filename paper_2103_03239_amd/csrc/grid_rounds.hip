@@ -1,0 +1,708 @@
+// Consecutive averaging rounds on a WHOLE grid of up to 4096 peers in one pass over HBM, for
+// gfx950: the loop of Alg. 1 with everything a run may ask for in between - the distortion after
+// every round (left-hand side of the equation of Thm 3.2), the refresh of returning peers (App.
+// "Training with a dynamic number of peers") and the local step of Moshpit SGD (Alg. 2).
+//
+// Columns never interact (the convergence argument of App. C.2 is component-wise), so a tile made
+// of ALL N rows and Wb bytes of each is closed under every one of these steps: it is read from HBM
+// once, the rounds run on it in LDS, and it is written back once.  Values live in LDS in the
+// storage type and a round uses the arithmetic of the single-round kernel (same balanced tree of
+// 16-position blocks, one correctly rounded division, one rounding to the storage type), so the
+// state after a pass has the bits of the same rounds run one by one.
+//
+// Tiles.  Wb is a power of two: as wide as 32 KiB of tile allow (1 KiB at most), 256 bytes up to
+// 64 KiB, 128 bytes for up to 1024 peers and 32 bytes above.  A block holds its tile 16 bytes at a
+// time in the registers of its threads and works on it in LDS, at most 64 KiB at once, so that two
+// blocks or more share a compute unit: one block's loads and stores overlap another's rounds.  (A
+// wave that issues vector memory instructions faster than its compute unit's share of HBM delivers
+// is held at the issue; with one block of 128 KiB per compute unit that prefetched its next tile
+// the memory time and the time of the rounds added up.)  Tiles of 128 KiB wait in the registers
+// and pass through LDS in two column parts, so that HBM still sees the full width.
+//
+// What bounds it (MI355X).  Up to about 6 rounds the memory side: 64 rows of 102 MB in tiles of
+// 512 bytes 5.1 TB/s, 256 rows of 4 MiB in tiles of 256 bytes 5.4 TB/s (a copy in that pattern
+// gives 5.3 and 5.5); 1024 rows of 16 MiB in tiles of 128 bytes 4.2 TB/s (copy: 4.2 - 4.5).  Then
+// LDS: a round reads and rewrites the tile, 35 us per GiB of state and round on 16 x 16 peers (the
+// LDS of the chip reads a GiB in 14 us and writes it in 23 us).
+// Measured against the persistent kernel of fused_rounds.hip, which serves the larger grids:
+// 4 x 4 x 4 peers x 25,557,032 binary32, 6 rounds 2.92 -> 2.56 ms; 32 x 32 x 4,194,304, 8 rounds
+// 10.6 -> 9.3 ms; 16 x 16 x 16 x 262,144 bfloat16, 12 rounds 5.15 -> 2.08 ms (one pass instead
+// of six over planes of 256 rows; 32-byte rows move at 3.7 TB/s, see tile_of).
+//
+// Row ends and alignment.  Rows need no alignment beyond the element's: the loads and stores are
+// 128-bit accesses at element-aligned addresses.  Where a row does not end on a 16-byte boundary
+// the tile's last vector starts early enough to end with the row; the columns it shares with its
+// neighbour are averaged twice, with the same bits.
+#include <type_traits>
+
+#include "mix64.h"
+#include "moshpit_internal.h"
+#include "tile_math.h"
+
+namespace moshpit {
+namespace {
+
+constexpr int kPhaseSlots = 8;               // 16-byte slots of the tile in LDS per thread
+constexpr int kLdsPerBlock = 80 * 1024;      // two blocks share a compute unit
+constexpr int64_t kGridMaxPeers = 4096;
+
+template <int DT> __device__ __forceinline__ void widen16(const u32x4 &m, float (&f)[DT == 0 ? 4 : 8])
+{
+    if constexpr (DT == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(m[e]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            f[2 * e] = __uint_as_float(m[e] << 16);
+            f[2 * e + 1] = __uint_as_float(m[e] & 0xffff0000u);
+        }
+    }
+}
+
+// n / d for n < 2^16 and magic = ceil(2^32 / d), d >= 2
+__device__ __forceinline__ int32_t quotient(int32_t n, uint32_t magic)
+{
+    return static_cast<int32_t>(__umulhi(static_cast<uint32_t>(n), magic));
+}
+
+struct TileSpan {
+    int64_t col0;          // first byte of the tile within a row
+    int32_t seg;           // bytes of every row in it (>= 16)
+};
+
+// Tile w covers bytes [w * Wb, (w + 1) * Wb) of every row.  A last tile of fewer than 16 bytes
+// takes the last vector of its neighbour as well.
+__device__ __forceinline__ TileSpan tile_span(const GridPlan &p, int64_t w)
+{
+    TileSpan t;
+    const int64_t left = p.valid_bytes - w * p.Wb;
+    t.col0 = w * p.Wb;
+    t.seg = static_cast<int32_t>(left < p.Wb ? left : p.Wb);
+    if (t.seg < 16) {
+        t.col0 -= 16;
+        t.seg += 16;
+    } else if (left > p.Wb && left < p.Wb + 16) {
+        t.seg -= 16;
+    }
+    return t;
+}
+
+// Position i of the work list -> tile.  Blocks b, b + 8, b + 16, ... run on the same one of the 8
+// dies; each die takes `run` consecutive tiles of every 8 * run, so that tiles that share cache
+// lines or DRAM pages meet in one die's L2.  A copy of 4096 rows x 32 bytes moves 1.4 TB/s dealt in
+// order, 3.7 TB/s in runs of 32 (ordinary loads and stores: they have to stay in L2; 1.3 TB/s with
+// non-temporal ones).
+__device__ __forceinline__ int64_t tile_of(const GridPlan &p, int64_t i)
+{
+    if (p.die_run <= 1) return i;
+    const int64_t span = 8 * static_cast<int64_t>(p.die_run);
+    const int64_t q = i / span;
+    if ((q + 1) * span > p.tiles) return i;
+    const int64_t r = i - q * span;
+    return q * span + (r & 7) * p.die_run + (r >> 3);
+}
+
+// TREE, SPLIT, PER as chosen from M: TREE = summation block (power of two >= M, at most 16);
+// SPLIT lanes of a wave share the positions of a group, PER positions each (SPLIT = 1: one lane
+// takes them all).  PHASES: column parts of the tile that take turns in LDS.  NT: non-temporal
+// loads and stores.  DIST: distortions are wanted.
+template <int DT, int TREE, int SPLIT, int PER, int PHASES, bool NT, bool DIST>
+__global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kernel(char *X, GridPlan p)
+{
+    constexpr int kSlots = kPhaseSlots * PHASES;
+    constexpr int CV = 4;                                    // columns per item
+    typedef Cols<DT, CV> Q;
+    typedef typename Q::elem_t elem_t;
+    typedef typename std::conditional<SPLIT == 4, uint32_t, uint16_t>::type bits_t;      // M <= 16 but for SPLIT == 4
+    constexpr int kEs = sizeof(elem_t);
+    constexpr int NE = 16 / kEs;
+    constexpr int FLAT = 16 / CV;
+    extern __shared__ __align__(16) char lds[];
+    char *tile = lds;
+    bits_t *bitmaps = reinterpret_cast<bits_t *>(lds + p.tile_bytes);
+    uint8_t *flags = reinterpret_cast<uint8_t *>(bitmaps + p.rounds * p.groups);
+    double *red = reinterpret_cast<double *>(lds + p.red_offset);      // DIST: [waves][columns], then 2 x [waves]
+    float *rcp_tab = reinterpret_cast<float *>(lds + p.lds_bytes - 32 - kRcpBytes);
+    elem_t *zeros = reinterpret_cast<elem_t *>(lds + p.lds_bytes - 32);
+    elem_t *trash = reinterpret_cast<elem_t *>(lds + p.lds_bytes - 16);
+
+    const int32_t tid = threadIdx.x, T = blockDim.x;
+    // The tile has 2^full_shift vectors per row, the part of it that is in LDS 2^wv_shift.
+    const int32_t full_shift = p.wv_shift, full_mask = (1 << full_shift) - 1;
+    const int32_t wv_shift = full_shift - (PHASES == 2 ? 1 : 0), wv_mask = (1 << wv_shift) - 1;
+    const int32_t Wb = 16 << wv_shift;               // bytes of a row in LDS
+
+    // slot b of this thread: vector idx & full_mask of row idx >> full_shift, idx = tid + b * T
+    u32x4 pre[kSlots];
+    auto slot_valid = [&](const TileSpan &t, int32_t idx) -> bool {
+        return (idx >> full_shift) < p.N && (idx & full_mask) * 16 < t.seg;
+    };
+    // where slot idx lives in a matrix whose rows are row_bytes apart (a slot outside the tile: its first vector)
+    auto slot_offset = [&](const TileSpan &t, int32_t idx, int64_t row_bytes) -> int64_t {
+        if (!slot_valid(t, idx)) idx = 0;
+        const int32_t row = idx >> full_shift, v16 = (idx & full_mask) * 16;
+        const int32_t last = t.seg - 16;
+        return static_cast<int64_t>(row) * row_bytes + (v16 < last ? v16 : last);
+    };
+    // vector v of row `row` of the part in LDS
+    auto lds_vec = [&](int32_t row, int32_t v) -> u32x4 * {
+        const int32_t pad = p.pad == 0 ? 0 : quotient(row, p.magic_m) * p.pad;
+        return reinterpret_cast<u32x4 *>(tile + row * Wb + v * 16 + pad);
+    };
+    auto fetch = [&](const TileSpan &t) {
+        const char *origin = X + t.col0;
+        int32_t t_ = tid;
+        asm volatile("" : "+v"(t_));                 // keeps the address arithmetic out of registers that live across the rounds
+#pragma unroll
+        for (int b = 0; b < kSlots; ++b)
+            pre[b] = load_vec<NT, u32x4>(origin + slot_offset(t, t_ + b * T, p.row_bytes));
+    };
+
+    const int64_t w = tile_of(p, blockIdx.x);
+    const TileSpan cur = tile_span(p, w);
+    fetch(cur);
+
+    for (int32_t q = tid; q < p.rounds * p.groups; q += T) bitmaps[q] = static_cast<bits_t>(p.bitmaps != nullptr ? p.bitmaps[q] : p.full_bitmap);
+    for (int32_t q = tid; q < p.N; q += T) flags[q] = p.flags != nullptr ? p.flags[q] : 3;
+    if (tid < 4) reinterpret_cast<uint32_t *>(zeros)[tid] = 0u;
+    for (int32_t q = tid; q <= 64; q += T) rcp_tab[q] = q == 0 ? 0.f : 1.f / static_cast<float>(q);
+    if (p.grad != nullptr) lds_barrier();            // the local step reads the flags
+
+    // One round on axis `axis`, with the participant bitmaps bm[], of the part in LDS (seg bytes wide).
+    auto round = [&](int32_t seg, int32_t axis, const bits_t *bm) {
+        const int32_t chunk_shift = wv_shift + (kEs == 4 ? 0 : 1);              // log2 of CV-column chunks per row
+        const int32_t chunk_mask = (1 << chunk_shift) - 1;
+        const int32_t seg16 = (seg + 15) & ~15;            // (the last vector fills its slot)
+        const int32_t S = p.S[axis];
+        const uint32_t magic_s = p.magic_s[axis];
+        const int32_t step = axis == 0 ? Wb : S * Wb + p.pad_step[axis];    // bytes between the rows of a group
+        constexpr int kLanes = 64 / SPLIT;
+        const int32_t sub = (tid & 63) / kLanes;
+        int32_t it = (tid >> 6) * kLanes + (tid & (kLanes - 1));
+        const int32_t it_step = T / SPLIT;
+        for (; it < (p.groups << chunk_shift); it += it_step) {
+            const int32_t gl = it >> chunk_shift, cc = it & chunk_mask;
+            const uint32_t live = bm[gl];
+            const int cnt = __popc(live);
+            if (cnt < 2 || cc * (CV * kEs) >= seg16) continue;
+            [[maybe_unused]] float y = 0.f;
+            if constexpr (SPLIT == 1) y = rcp_tab[cnt];
+            const int32_t row0 = axis == 0 ? gl * p.M : gl + quotient(gl, magic_s) * S * (p.M - 1);
+            int32_t at = row0 * Wb + cc * (CV * kEs);
+            if (p.pad != 0) at += (axis == 0 ? gl : quotient(row0, p.magic_m)) * p.pad;
+            char *col = tile + at;
+            float acc[CV];
+            if constexpr (SPLIT > 1) {
+                int32_t st = step;
+                asm volatile("" : "+s"(st));
+                const int32_t j0 = sub * PER;
+                const uint32_t pbits = (live >> j0) & ((1u << PER) - 1u);
+                char *q = col + __mul24(j0, st);
+                elem_t *pos[PER];
+                float f[PER][CV];
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    const bool on = (pbits >> u) & 1u;
+                    elem_t *e = reinterpret_cast<elem_t *>(q);
+                    Q::load(on ? e : zeros, f[u]);
+                    pos[u] = on ? e : trash;
+                    q += st;
+                }
+#pragma unroll
+                for (int s = 1; s < PER; s *= 2)
+#pragma unroll
+                    for (int u = 0; u + s < PER; u += 2 * s)
+#pragma unroll
+                        for (int e = 0; e < CV; ++e) f[u][e] += f[u + s][e];
+                mean_over_lanes<SPLIT>(f[0], static_cast<float>(cnt), acc);
+#pragma unroll
+                for (int u = 0; u < PER; ++u) Q::store(pos[u], acc);
+            } else {
+                elem_t *base = reinterpret_cast<elem_t *>(col);
+                const int32_t estep = step / kEs;
+                float sum[CV];
+                tree_block<DT, CV, TREE, FLAT>(base, estep, 0, zeros, live, sum);
+#pragma unroll
+                for (int e = 0; e < CV; ++e) acc[e] = 0.f + sum[e];
+                divide_columns<CV>(acc, static_cast<float>(cnt), y);
+                if constexpr (TREE < 16) {
+#pragma unroll
+                    for (int u = 0; u < TREE; ++u)
+                        if ((live >> u) & 1u) Q::store(base + u * estep, acc);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < TREE; ++u) Q::store(((live >> u) & 1u) ? base + u * estep : trash, acc);
+                }
+            }
+        }
+    };
+
+    // Distortion of the tile: sum over its columns of s2 - s1^2 / N, s1 and s2 the sums of the
+    // differences from row 0 and of their squares in binary64 (the differences are exact).
+    // Thread (part, vector c) takes every parts-th row; the lanes and waves that share a column
+    // are added in a fixed order.
+    [[maybe_unused]] auto distortion = [&](int32_t seg, int64_t out_at) {
+        if constexpr (DIST) {
+            const int32_t waves = T >> 6, lane = tid & 63, wave = tid >> 6;
+            const int32_t c = tid & wv_mask, parts = T >> wv_shift;
+            const int32_t columns = NE << wv_shift;
+            const bool in = c * 16 < seg;
+            const int32_t early = c * 16 - (seg - 16);             // > 0: the row's last vector, first `early` bytes not its own
+            const int32_t dup = early > 0 ? early / kEs : 0;
+            double s1[NE], s2 = 0.0;
+            float x0[NE];
+            widen16<DT>(*lds_vec(0, c), x0);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) s1[e] = 0.0;
+            if (in) {
+                for (int32_t row = tid >> wv_shift; row < p.N; row += parts) {
+                    float x[NE];
+                    widen16<DT>(*lds_vec(row, c), x);
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) {
+                        double dlt = static_cast<double>(x[e]) - static_cast<double>(x0[e]);
+                        if (e < dup) dlt = 0.0;
+                        s1[e] += dlt;
+                        s2 = fma(dlt, dlt, s2);
+                    }
+                }
+            }
+            for (int32_t off = 1 << wv_shift; off < 64; off <<= 1)
+#pragma unroll
+                for (int e = 0; e < NE; ++e) s1[e] += __shfl_xor(s1[e], off, 64);
+#pragma unroll
+            for (int32_t off = 1; off < 64; off <<= 1) s2 += __shfl_xor(s2, off, 64);
+            if (lane <= wv_mask)
+#pragma unroll
+                for (int e = 0; e < NE; ++e) red[wave * columns + c * NE + e] = s1[e];
+            double *sq = red + waves * columns, *tot = sq + waves;
+            if (lane == 0) sq[wave] = s2;
+            lds_barrier();
+            double part = 0.0;
+            for (int32_t col = tid; col < columns; col += T) {
+                double t1 = 0.0;
+                for (int32_t k = 0; k < waves; ++k) t1 += red[k * columns + col];
+                part -= t1 * t1 / static_cast<double>(p.N);          // (columns outside the tile hold 0)
+            }
+#pragma unroll
+            for (int32_t off = 1; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
+            if (lane == 0) tot[wave] = sq[wave] + part;
+            lds_barrier();
+            if (tid == 0) {
+                double sum = 0.0;
+                for (int32_t k = 0; k < waves; ++k) sum += tot[k];
+                p.partials[out_at] = sum;
+            }
+        }
+    };
+
+    // Moshpit SGD: rows present in the first round enter as theta - gamma * g
+    if (p.grad != nullptr) {
+        const char *origin = p.grad + cur.col0;
+        int32_t t_ = tid;
+        asm volatile("" : "+v"(t_));
+        constexpr int kBatch = PHASES == 1 ? kSlots : 4;     // (few registers are free next to 16 slots)
+#pragma unroll
+        for (int b0 = 0; b0 < kSlots; b0 += kBatch) {
+            u32x4 g[kBatch];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b)
+                g[b] = load_vec<NT, u32x4>(origin + slot_offset(cur, t_ + (b0 + b) * T, p.grad_row_bytes));
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const int32_t idx = t_ + (b0 + b) * T;
+                if (slot_valid(cur, idx) && (flags[idx >> full_shift] & 2))
+                    pre[b0 + b] = local_step<DT>(pre[b0 + b], g[b], p.gamma);
+            }
+        }
+    }
+
+#pragma unroll 1
+    for (int32_t phase = 0; phase < PHASES; ++phase) {
+        // bytes of this part; with two parts half the lanes hold one, half the other (T is a multiple of a row's vectors)
+        const int32_t left = cur.seg - phase * Wb;
+        const int32_t seg = left < Wb ? left : Wb;
+        const int64_t tiles = p.tiles * PHASES;
+        if (seg <= 0) {
+            if constexpr (DIST)
+                for (int32_t e = tid; e <= p.rounds; e += T)
+                    if (e > 0 || p.dist_before) p.partials[e * tiles + w * PHASES + phase] = 0.0;
+            break;
+        }
+        const bool mine = PHASES == 1 || ((tid & full_mask) >> wv_shift) == phase;
+        int32_t t_ = tid;
+        asm volatile("" : "+v"(t_));
+#pragma unroll
+        for (int b = 0; b < kSlots; ++b) {
+            const int32_t idx = t_ + b * T;
+            if (mine && slot_valid(cur, idx)) *lds_vec(idx >> full_shift, idx & wv_mask) = pre[b];
+        }
+        lds_barrier();
+
+        if constexpr (DIST)
+            if (p.dist_before) distortion(seg, w * PHASES + phase);
+        int32_t axis = p.axis0;
+        for (int32_t r = 0; r < p.rounds; ++r) {
+            if (p.copies != nullptr && (r > 0 || p.refresh_first)) {
+                // returning peers copy their donors (who do not return themselves)
+                const uint32_t *list = p.copies + static_cast<int64_t>(r) * p.N;
+                const int32_t items = p.copy_counts[r] << wv_shift;
+                for (int32_t it = tid; it < items; it += T) {
+                    const uint32_t pair = list[it >> wv_shift];
+                    const int32_t v = it & wv_mask;
+                    *lds_vec(static_cast<int32_t>(pair & 0xffffu), v) = *lds_vec(static_cast<int32_t>(pair >> 16), v);
+                }
+                lds_barrier();
+            }
+            round(seg, axis, bitmaps + r * p.groups);
+            lds_barrier();
+            if constexpr (DIST) distortion(seg, (r + 1) * tiles + w * PHASES + phase);
+            axis = axis + 1 == p.d ? 0 : axis + 1;
+        }
+        if constexpr (PHASES == 2) {
+            // back into the registers; the next part enters LDS when everybody is done with this one
+            t_ = tid;
+            asm volatile("" : "+v"(t_));
+#pragma unroll
+            for (int b = 0; b < kSlots; ++b) {
+                const int32_t idx = t_ + b * T;
+                if (mine && slot_valid(cur, idx)) pre[b] = *lds_vec(idx >> full_shift, idx & wv_mask);
+            }
+            if (phase == 0) lds_barrier();
+        }
+    }
+
+    if (p.rounds > 0) {
+        char *origin = X + cur.col0;
+        int32_t t_ = tid;
+        asm volatile("" : "+v"(t_));
+        constexpr int kBatch = 4;
+#pragma unroll
+        for (int b0 = 0; b0 < kSlots; b0 += kBatch) {
+            uint8_t used[kBatch];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                int32_t idx = t_ + (b0 + b) * T;
+                if (!slot_valid(cur, idx)) idx = 0;
+                if constexpr (PHASES == 1) pre[b0 + b] = *lds_vec(idx >> full_shift, idx & full_mask);
+                used[b] = flags[idx >> full_shift];
+            }
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const int32_t idx = t_ + (b0 + b) * T;
+                if (used[b] != 0 && slot_valid(cur, idx)) store_vec<NT, u32x4>(origin + slot_offset(cur, idx, p.row_bytes), pre[b0 + b]);
+            }
+        }
+    }
+}
+
+// out[e] = (sum of partials[e][0 .. tiles)) / n, entry e = blockIdx.x, in a fixed order
+__global__ __launch_bounds__(256) void grid_dist_kernel(const double *__restrict__ partials, int64_t tiles, double n,
+                                                        double *__restrict__ out)
+{
+    __shared__ double sh[256];
+    const double *mine = partials + blockIdx.x * tiles;
+    double acc = 0.0;
+    for (int64_t k = threadIdx.x; k < tiles; k += 256) acc += mine[k];
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (static_cast<int>(threadIdx.x) < s) sh[threadIdx.x] += sh[threadIdx.x + s];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = sh[0] / n;
+}
+
+// ---- what a pass needs to know about the peers: one launch per run ----------------------------
+
+constexpr int kPlanThreads = 1024;
+constexpr int kPerThread = kGridMaxPeers / kPlanThreads;
+
+__device__ __forceinline__ bool failure_event(uint64_t seed, int64_t s, int64_t i, uint32_t threshold)
+{
+    const uint64_t round_key = mix64(seed + 0x9E3779B97F4A7C15ull * static_cast<uint64_t>(s + 1));
+    return static_cast<uint32_t>(mix64(round_key ^ static_cast<uint64_t>(i)) >> 40) < threshold;
+}
+
+// Stable compaction step of one block: number of set flags of the threads before this one; *total the block's.
+__device__ __forceinline__ int32_t block_rank(bool flag, int32_t *wave_sums, int32_t *total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned long long ballot = __ballot(flag);
+    if (lane == 0) wave_sums[wave] = __popcll(ballot);
+    __syncthreads();
+    int32_t base = 0, all = 0;
+    for (int k = 0; k < kPlanThreads / 64; ++k) {
+        const int32_t c = wave_sums[k];
+        if (k < wave) base += c;
+        all += c;
+    }
+    __syncthreads();
+    *total = all;
+    return base + __popcll(ballot & ((1ull << lane) - 1ull));
+}
+
+// Is peer i present in round t (and in round t - 1, for t > t0)?  Walks a die-and-rejoin schedule from s.begin.
+__device__ __forceinline__ void presence(const GridSchedule &s, int32_t i, int64_t t, bool &before, bool &now)
+{
+    before = true;
+    if (s.kind == 3) {                               // explicit masks, device
+        now = s.masks[(t - s.t0) * s.N + i] != 0;
+        if (t > s.t0) before = s.masks[(t - 1 - s.t0) * s.N + i] != 0;
+    } else if (s.kind == 1) {
+        now = !failure_event(s.seed, t, i, s.threshold);
+        if (s.refresh && t > s.t0) before = !failure_event(s.seed, t - 1, i, s.threshold);
+    } else {
+        int32_t away = s.away_in != nullptr ? s.away_in[i] : 0;
+        now = true;
+        for (int64_t q = s.begin; q <= t; ++q) {
+            before = now;
+            if (away == 0 && failure_event(s.seed, q, i, s.threshold)) away = s.down;
+            now = away == 0;
+            if (away > 0) --away;
+        }
+    }
+}
+
+// Blocks 0 .. rounds-1: round r = blockIdx.x: bitmaps[r][g] (bit j: position j of group g takes
+// part) and, with refresh, the (donor << 16 | returning peer) pairs of the round.  Blocks after
+// that: flags[i] for 1024 peers each (bit 0: takes part in some round or is refreshed; bit 1: in
+// the first one), and the state of a die-and-rejoin schedule at the end.
+__global__ __launch_bounds__(kPlanThreads) void grid_plan_kernel(GridSchedule s, GridTables o)
+{
+    __shared__ uint8_t here[kGridMaxPeers];
+    __shared__ uint16_t candidates[kGridMaxPeers];
+    __shared__ int32_t wave_sums[kPlanThreads / 64];
+    const int32_t N = s.N, tid = threadIdx.x;
+    if (static_cast<int32_t>(blockIdx.x) < s.rounds) {
+        const int32_t r = blockIdx.x;
+        const int64_t t = s.t0 + r;
+        const bool refresh = s.refresh && r > 0;
+        bool was[kPerThread], is[kPerThread];
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            const int32_t i = tid + k * kPlanThreads;
+            was[k] = is[k] = false;
+            if (i < N) {
+                presence(s, i, t, was[k], is[k]);
+                here[i] = is[k] ? 1 : 0;
+            }
+        }
+        __syncthreads();
+        int64_t S = 1;
+        for (int64_t q = 0; q < t % s.d; ++q) S *= s.M;
+        const int32_t groups = N / s.M;
+        for (int32_t g = tid; g < groups; g += kPlanThreads) {
+            const int32_t base = static_cast<int32_t>((g / S) * S * s.M + g % S);
+            uint32_t bits = 0;
+            for (int32_t j = 0; j < s.M; ++j) bits |= static_cast<uint32_t>(here[base + j * S]) << j;
+            if (s.group_skip && static_cast<int32_t>(__popc(bits)) != s.M) bits = 0;
+            o.bitmaps[r * groups + g] = bits;
+        }
+        if (!refresh) {
+            if (s.refresh && tid == 0) o.copy_counts[r] = 0;
+            return;
+        }
+        int32_t c = 0;
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            int32_t total = 0;
+            const bool cand = was[k] && is[k];
+            const int32_t rank = block_rank(cand, wave_sums, &total);
+            if (cand) candidates[c + rank] = static_cast<uint16_t>(tid + k * kPlanThreads);
+            c += total;
+        }
+        __syncthreads();
+        const uint64_t round_key = mix64(s.seed + 0xA0761D6478BD642Full * static_cast<uint64_t>(t + 1));
+        int32_t n = 0;
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            int32_t total = 0;
+            const int32_t i = tid + k * kPlanThreads;
+            const bool returns = c > 0 && is[k] && !was[k];
+            const int32_t rank = block_rank(returns, wave_sums, &total);
+            if (returns) {
+                const uint64_t u = mix64(round_key ^ static_cast<uint64_t>(i));
+                const uint32_t donor = candidates[u % static_cast<uint64_t>(c)];
+                o.copies[static_cast<int64_t>(r) * N + n + rank] = donor << 16 | static_cast<uint32_t>(i);
+            }
+            n += total;
+        }
+        if (tid == 0) o.copy_counts[r] = n;
+    } else {
+        const int32_t i = (static_cast<int32_t>(blockIdx.x) - s.rounds) * kPlanThreads + tid;
+        if (i >= N) return;
+        uint8_t flag = 0;
+        if (s.kind == 2) {
+            int32_t away = s.away_in != nullptr ? s.away_in[i] : 0;
+            for (int64_t q = s.begin; q < s.t0 + s.rounds; ++q) {
+                if (away == 0 && failure_event(s.seed, q, i, s.threshold)) away = s.down;
+                if (q >= s.t0 && away == 0) flag |= q == s.t0 ? 3 : 1;
+                if (away > 0) --away;
+            }
+            s.away_out[i] = away;
+        } else {
+            for (int32_t r = 0; r < s.rounds; ++r) {
+                const bool now = s.kind == 3 ? s.masks[static_cast<int64_t>(r) * N + i] != 0
+                                             : !failure_event(s.seed, s.t0 + r, i, s.threshold);
+                if (now) flag |= r == 0 ? 3 : 1;
+            }
+        }
+        o.flags[i] = flag;
+    }
+}
+
+// Group-skip schedules without refresh: a peer whose groups all sit out is not touched.
+__global__ __launch_bounds__(256) void grid_skip_flags_kernel(GridSchedule s, GridTables o)
+{
+    const int32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= s.N) return;
+    const int32_t groups = s.N / s.M;
+    uint8_t flag = 0;
+    for (int32_t r = 0; r < s.rounds; ++r) {
+        int32_t S = 1;
+        for (int64_t q = 0; q < (s.t0 + r) % s.d; ++q) S *= s.M;
+        const int32_t g = i / (S * s.M) * S + i % S, j = i / S % s.M;
+        if ((o.bitmaps[r * groups + g] >> j) & 1u) flag |= r == 0 ? 3 : 1;
+    }
+    if (s.refresh) flag |= o.flags[i] & 1;           // a refreshed peer is written although its group sits out
+    o.flags[i] = flag;
+}
+
+}  // namespace
+
+namespace {
+int64_t bitmap_bytes(int32_t M) { return M <= 16 ? 2 : 4; }
+}  // namespace
+
+hipError_t launch_grid_plan(const GridSchedule &s, const GridTables &tables, hipStream_t stream)
+{
+    if (s.rounds <= 0) return hipSuccess;
+    const uint32_t blocks = static_cast<uint32_t>(s.rounds + (s.N + kPlanThreads - 1) / kPlanThreads);
+    grid_plan_kernel<<<dim3(blocks), dim3(kPlanThreads), 0, stream>>>(s, tables);
+    if (s.group_skip)
+        grid_skip_flags_kernel<<<dim3((s.N + 255) / 256), dim3(256), 0, stream>>>(s, tables);
+    return hipGetLastError();
+}
+
+bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
+               GridPlan *out)
+{
+    const int64_t esize = dtype == 0 ? 4 : 2;
+    GridPlan p{};
+    p.valid_bytes = P * esize;
+    p.row_bytes = row_stride * esize;
+    if (N > kGridMaxPeers || M > 32 || p.valid_bytes < 16) return false;
+    p.N = static_cast<int32_t>(N);
+    p.M = M;
+    p.d = d;
+    p.groups = static_cast<int32_t>(N / M);
+    p.full_bitmap = M == 32 ? ~0u : (1u << M) - 1u;
+    p.axis0 = static_cast<int32_t>(t0 % d);
+    int32_t S = 1;
+    const auto magic = [](int64_t n) { return static_cast<uint32_t>(((int64_t(1) << 32) + n - 1) / n); };
+    p.magic_m = magic(M);
+    // Widest tile: rows of 512 bytes beat 1 KiB on 64 rows (2.55 against 2.73 ms), 256 bytes beat
+    // 128 on 256 rows (0.40 against 0.46 ms for 3 rounds).  Short rows: enough blocks for the chip.
+    int32_t wb = 1024;
+    while (wb > 256 && N * wb > 32 * 1024) wb >>= 1;
+    while (wb > 128 && N * wb > 64 * 1024) wb >>= 1;
+    while (wb > 32 && N * wb > 128 * 1024) wb >>= 1;
+    while (wb > 128 && (p.valid_bytes + wb - 1) / wb < 1024) wb >>= 1;
+    while (wb > 32 && wb / 2 >= p.valid_bytes) wb >>= 1;
+    p.Wb = wb;
+    p.wv_shift = 0;
+    while ((16 << p.wv_shift) < wb) ++p.wv_shift;
+    p.phases = N * wb > 72 * 1024 ? 2 : 1;
+    const int32_t part = wb / p.phases;              // bytes of a row in LDS
+    p.threads = static_cast<int32_t>((N * part / (16 * kPhaseSlots) + 63) / 64 * 64);
+    if (p.threads < 64) p.threads = 64;
+    if (p.threads > (p.phases == 1 ? 1024 : 512)) return false;
+    p.pad = part < 256 && M >= 8 && (M * part) % 256 == 0 ? part : 0;
+    for (int32_t a = 0; a < d; ++a) {
+        p.S[a] = S;
+        p.magic_s[a] = S > 1 ? magic(S) : 0;
+        p.pad_step[a] = a == 0 ? 0 : S / M * p.pad;
+        S *= M;
+    }
+    p.tile_bytes = static_cast<int32_t>(N * part + p.groups * p.pad);
+    p.tiles = (p.valid_bytes + wb - 1) / wb;
+    // Tiles of whole cache lines are not seen again: non-temporal (256 rows of 4 MiB: 5.5 TB/s
+    // against 5.1 with ordinary accesses).  Others share lines with their neighbours in the row.
+    // Runs per die: where tiles share lines, and for rows of one line (1024 rows of 16 MiB, 8
+    // rounds: 9.43 -> 9.33 ms, 4 rounds: 10.2 -> 8.3 ms); wider ones lose 1 % to them.
+    const bool whole_lines = wb >= 128 && reinterpret_cast<uintptr_t>(X) % 128 == 0 && p.row_bytes % 128 == 0;
+    p.streaming = whole_lines ? 1 : 0;
+    p.die_run = whole_lines && wb > 128 ? 1 : 32;
+    // rounds of one pass: as many bitmaps as fit next to the tile
+    const int64_t waves = p.threads / 64, columns = part / esize;
+    const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + 2 * waves) * 8 - kRcpBytes - 64;
+    const int64_t most = room / (static_cast<int64_t>(p.groups) * bitmap_bytes(M));
+    p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
+    if (p.max_rounds < 4) return false;
+    *out = p;
+    return true;
+}
+
+namespace {
+
+typedef void (*grid_kernel_t)(char *, GridPlan);
+
+template <int DT, int TREE, int SPLIT, int PER> grid_kernel_t pick_mode(bool two, bool nt, bool dist)
+{
+    if (two) return nt ? (dist ? grid_rounds_kernel<DT, TREE, SPLIT, PER, 2, true, true> : grid_rounds_kernel<DT, TREE, SPLIT, PER, 2, true, false>)
+                       : (dist ? grid_rounds_kernel<DT, TREE, SPLIT, PER, 2, false, true> : grid_rounds_kernel<DT, TREE, SPLIT, PER, 2, false, false>);
+    return nt ? (dist ? grid_rounds_kernel<DT, TREE, SPLIT, PER, 1, true, true> : grid_rounds_kernel<DT, TREE, SPLIT, PER, 1, true, false>)
+              : (dist ? grid_rounds_kernel<DT, TREE, SPLIT, PER, 1, false, true> : grid_rounds_kernel<DT, TREE, SPLIT, PER, 1, false, false>);
+}
+
+grid_kernel_t pick_kernel(int dtype, const GridPlan &p, bool dist)
+{
+    const bool two = p.phases == 2, nt = p.streaming != 0;
+    if (dtype == 0) {
+        if (p.M <= 2) return pick_mode<0, 2, 1, 0>(two, nt, dist);
+        if (p.M <= 4) return pick_mode<0, 4, 1, 0>(two, nt, dist);
+        if (p.M <= 8) return pick_mode<0, 8, 1, 0>(two, nt, dist);
+        if (p.M <= 16) return pick_mode<0, 16, 2, 8>(two, nt, dist);
+        return pick_mode<0, 16, 4, 8>(two, nt, dist);
+    }
+    if (p.M <= 2) return pick_mode<1, 2, 1, 0>(two, nt, dist);
+    if (p.M <= 4) return pick_mode<1, 4, 1, 0>(two, nt, dist);
+    if (p.M <= 8) return pick_mode<1, 8, 1, 0>(two, nt, dist);
+    if (p.M <= 16) return pick_mode<1, 16, 1, 0>(two, nt, dist);
+    return pick_mode<1, 16, 4, 8>(two, nt, dist);
+}
+
+}  // namespace
+
+hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStream_t stream)
+{
+    GridPlan p = plan;
+    const bool dist = p.partials != nullptr;
+    int64_t at = p.tile_bytes + static_cast<int64_t>(p.rounds) * p.groups * bitmap_bytes(p.M) + p.N;
+    at = (at + 15) / 16 * 16;
+    p.red_offset = static_cast<int32_t>(at);
+    if (dist) {
+        const int64_t waves = p.threads / 64, columns = p.Wb / p.phases / (dtype == 0 ? 4 : 2);
+        at += (waves * columns + 2 * waves) * 8;
+        at = (at + 15) / 16 * 16;
+    }
+    p.lds_bytes = static_cast<int32_t>(at + kRcpBytes + 32);
+    if (p.lds_bytes > kLdsPerBlock || p.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    const grid_kernel_t kernel = pick_kernel(dtype, p, dist);
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsPerBlock);
+    if (e != hipSuccess) return e;
+    kernel<<<dim3(static_cast<uint32_t>(p.tiles)), dim3(p.threads), p.lds_bytes, stream>>>(static_cast<char *>(X), p);
+    return hipGetLastError();
+}
+
+hipError_t launch_grid_dist(const double *partials, int64_t tiles, int32_t entries, int64_t N, double *out,
+                            hipStream_t stream)
+{
+    grid_dist_kernel<<<dim3(static_cast<uint32_t>(entries)), dim3(256), 0, stream>>>(partials, tiles,
+                                                                                    static_cast<double>(N), out);
+    return hipGetLastError();
+}
+
+}  // namespace moshpit

@@ -182,6 +182,58 @@ bool plan_fused(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t r
 hipError_t launch_fused_rounds(void *X, int dtype, const FusedPlan &plan, const uint8_t *masks,
                                hipStream_t stream);
 
+// Several rounds on a whole grid of up to 4096 peers in one pass over HBM (grid_rounds.hip).
+// plan_grid: does the shape qualify, and how is it cut into tiles (a pure function of its
+// arguments; depends on t0 through the first axis only).  The caller fills in the rest.
+constexpr int kGridMaxAxes = 12;
+struct GridPlan {
+    int32_t N, M, d, groups;
+    int32_t Wb, wv_shift;            // bytes of a row per tile; log2 of its 16-byte vectors
+    int32_t threads, tile_bytes, lds_bytes, red_offset;
+    int32_t pad;                     // LDS bytes added after every M rows (bank conflicts of axis 0)
+    int32_t die_run;                 // consecutive tiles per die (1 = tiles dealt in order)
+    int32_t streaming;               // 1 = non-temporal loads and stores
+    int32_t phases, max_rounds;      // column parts of a tile (1 or 2); most rounds of one pass
+    int32_t axis0;                   // axis of the pass's first round
+    uint32_t full_bitmap, magic_m;
+    int32_t S[kGridMaxAxes], pad_step[kGridMaxAxes];
+    uint32_t magic_s[kGridMaxAxes];
+    int64_t row_bytes, valid_bytes, tiles;
+    // filled in by the caller
+    int32_t rounds;
+    int32_t dist_before, refresh_first;   // distortion before the first round; refresh before it
+    float gamma;
+    const uint32_t *bitmaps;         // [rounds][groups], device; nullptr = everybody takes part
+    const uint8_t *flags;            // [N], device: bit 0 written back, bit 1 takes the local step; nullptr = 3
+    const uint32_t *copies;          // [rounds][N] pairs donor << 16 | returning peer; nullptr = no refresh
+    const int32_t *copy_counts;      // [rounds]
+    const char *grad;                // gradients (SGD) or nullptr
+    int64_t grad_row_bytes;
+    double *partials;                // [rounds + 1][tiles * phases] or nullptr (no distortion wanted)
+};
+bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
+               GridPlan *out);
+hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStream_t stream);
+hipError_t launch_grid_dist(const double *partials, int64_t tiles, int32_t entries, int64_t N, double *out,
+                            hipStream_t stream);
+
+// Tables of a run under a failure schedule, for the kernel above.
+struct GridSchedule {
+    int32_t kind, N, M, d, rounds, down, group_skip, refresh;
+    uint32_t threshold;
+    uint64_t seed;
+    int64_t t0, begin;               // begin: round from which a die-and-rejoin schedule is walked
+    const int32_t *away_in;          // its state at round `begin` (nullptr: nobody away)
+    int32_t *away_out;               // its state at round t0 + rounds (not away_in)
+    const uint8_t *masks;            // kind 3: device [rounds][N]
+};
+struct GridTables {
+    uint32_t *bitmaps, *copies;
+    uint8_t *flags;
+    int32_t *copy_counts;
+};
+hipError_t launch_grid_plan(const GridSchedule &s, const GridTables &tables, hipStream_t stream);
+
 // Queue a plain 128-bit copy of nbytes (multiple of 16) from src to dst.
 hipError_t launch_copy_probe(void *dst, const void *src, int64_t nbytes, hipStream_t stream);
 

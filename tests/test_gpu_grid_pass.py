@@ -1,0 +1,137 @@
+"""Passes over a whole grid (several rounds in one call) against the same rounds taken one at a
+time through moshpit_round, bit for bit: every summation shape (groups of 2 to 32, both types),
+tiles in one and two column parts, row ends on every remainder of 16 bytes, rows that are not
+aligned, rows shorter than a tile; failures, refresh, group-skip and explicit masks, the
+distortion after every round, and the local step of Moshpit SGD."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moshpit_oracle as orc
+from paper_2103_03239_amd import binding, inputs
+from parity_util import TOL, assert_dist_close, dist_floor
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+TD = {0: torch.float32, 1: torch.bfloat16}
+
+
+def state(N, P, stride, offset, dtype, seed, scale=1.0):
+    """[N, P] view at element `offset` of a buffer whose other elements hold 512."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    buf = torch.full((offset + N * stride + 16,), 512.0, dtype=TD[dtype], device=DEV)
+    view = buf[offset: offset + N * stride].view(N, stride)[:, :P]
+    view.copy_(torch.randn(N, P, generator=gen, device=DEV) * scale + torch.arange(N, device=DEV)[:, None] % 7)
+    return buf, view
+
+
+def cases():
+    out = []
+    # (M, d, P, pad, offset, dtype): one per summation shape and tile form ...
+    grids = [(2, 4), (3, 3), (4, 3), (5, 3), (8, 2), (8, 3), (12, 2), (16, 2), (24, 2), (32, 2), (16, 3), (17, 1), (2, 9)]
+    for k, (M, d) in enumerate(grids):
+        for dtype in (0, 1):
+            es = 4 if dtype == 0 else 2
+            for j, extra in enumerate((0, 1, 16 // es - 1)):          # row end: whole vectors, one element over, one short
+                P = (2 * 1024 if M ** d <= 64 else 300) // es * (1 + j) // (16 // es) * (16 // es) + extra
+                out.append((M, d, max(P, 16 // es), (j * 3) % 5, (k + j) % 4, dtype))
+    # ... and last tiles of 2 to 30 bytes next to a 1 KiB, 128- and 32-byte wide one
+    for M, d, wb in ((4, 2, 128), (32, 2, 128), (16, 3, 32)):
+        for left in (2, 8, 14, 16, 18, 30):
+            out.append((M, d, (3 * wb + left) // 2, 0, 1, 1))
+    return out
+
+
+@pytest.mark.parametrize("M,d,P,pad,offset,dtype", cases())
+def test_pass_equals_single_rounds(M, d, P, pad, offset, dtype):
+    N, rounds, t0, seed = M ** d, 2 * d + 1, 1, 40 + P
+    print(f"grid pass M={M} d={d} P={P} pad={pad} offset={offset} dtype={dtype}", flush=True)
+    masks = orc.schedule_masks(2, 0.2, seed, 2, N, t0, rounds)
+    sched = binding.Schedule(kind=binding.SCHED_REJOIN, p=0.2, seed=seed, down_rounds=2)
+    bufA, A = state(N, P, P + pad, offset, dtype, seed)
+    bufB, B = state(N, P, P + pad, offset, dtype, seed)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        m.bind_state(A)
+        want = [m.dist_to_mean()]
+        for r in range(rounds):
+            m.round(t0 + r, masks[r])
+            want.append(m.dist_to_mean())
+        m.bind_state(B)
+        dist, _ = m.run(t0, rounds, sched, want_dist=True)
+        assert torch.equal(bufA, bufB)
+        # same state, binary64 sums in another order: a few ulp per value added, times how much of s2 cancels (N at most)
+        assert np.abs(dist - np.array(want)).max() <= 1e-11 * max(want)
+        m.run(t0, rounds, sched)                                     # and without the distortion
+        for r in range(rounds):
+            m.sync()
+        m.bind_state(A)
+        for r in range(rounds):
+            m.round(t0 + r, masks[r])
+        m.sync()
+    assert torch.equal(bufA, bufB)
+
+
+@pytest.mark.parametrize("M,d,P,dtype,kind,skip", [(4, 3, 1_001, 0, 1, False), (16, 3, 77, 1, 2, False), (32, 2, 130, 0, 2, True),
+                                                   (8, 2, 515, 1, 3, True), (8, 2, 515, 1, 3, False), (2, 4, 9, 0, 1, False)])
+def test_refresh_pass_equals_refresh_and_round(M, d, P, dtype, kind, skip):
+    N, rounds, seed = M ** d, 7, 77
+    print(f"refresh pass M={M} d={d} P={P} dtype={dtype} kind={kind} skip={skip}", flush=True)
+    presence = orc.schedule_masks(2 if kind == 3 else kind, 0.25, seed, 2, N, 0, rounds)
+    bufA, A = state(N, P, P + 3, 1, dtype, 5)
+    bufB, B = state(N, P, P + 3, 1, dtype, 5)
+    sched = binding.Schedule(kind=kind, p=0.25, seed=seed, down_rounds=2, group_skip=skip, refresh=True,
+                             explicit_masks=presence if kind == 3 else None)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        m.bind_state(A)
+        for t in range(rounds):
+            if t > 0:
+                m.refresh(t, seed, presence[t - 1], presence[t])
+            m.round(t, orc.skip_filter(N, M, d, t, presence[t]) if skip else presence[t])
+        m.bind_state(B)
+        m.run(0, rounds, sched)
+        m.sync()
+    assert torch.equal(bufA, bufB)
+
+
+@pytest.mark.parametrize("M,d,P,pad,gpad", [(8, 2, 1_027, 0, 0), (4, 3, 999, 1, 2), (32, 2, 70, 0, 1), (16, 3, 40, 0, 0)])
+def test_sgd_pass_equals_step_and_rounds(M, d, P, pad, gpad):
+    N, rounds, seed = M ** d, 3, 9
+    print(f"sgd pass M={M} d={d} P={P} pad={pad} gpad={gpad}", flush=True)
+    masks = orc.schedule_masks(1, 0.2, seed, 0, N, 0, rounds)
+    sched = binding.Schedule(kind=binding.SCHED_IID, p=0.2, seed=seed)
+    bufA, A = state(N, P, P + pad, 0, 0, 3)
+    bufB, B = state(N, P, P + pad, 0, 0, 3)
+    _, G = state(N, P, P + gpad, 1, 0, 4)
+    with binding.Moshpit(N, P, M, d, 0) as m:
+        m.bind_state(A)
+        m.sgd_round(0, G, 0.05, masks[0])
+        for r in range(1, rounds):
+            m.round(r, masks[r])
+        for flags in (0, binding.RUN_FUSED):
+            Y = bufB.clone()
+            m.bind_state(Y[: N * (P + pad)].view(N, P + pad)[:, :P])
+            dist, _ = m.sgd_run(0, rounds, G, 0.05, sched, want_dist=flags == 0, flags=flags)
+            m.sync()
+            assert torch.equal(bufA, Y)
+    ref = orc.dist_to_mean(A.cpu().double().numpy())
+    assert np.isfinite(dist if dist is not None else 0.0).all() and ref >= 0.0
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_distortion_of_a_converged_state_with_an_outlier_first_row(dtype):
+    """Row 0 (which the sums are shifted by) far from everybody else, rounds that nobody takes part in."""
+    M, d, P = 8, 2, 1_001
+    N = M ** d
+    w = inputs.Workload("outlier", N, M, d, P, dtype, "normal", 0, 0.0, 0, 2, 21, 22)
+    X = torch.ones(N, P, device=DEV).to(TD[dtype])
+    X[0] = 512.0
+    print(f"outlier {w}", flush=True)
+    sched = binding.Schedule(kind=binding.SCHED_EXPLICIT, explicit_masks=np.zeros((2, N), dtype=np.uint8))
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        m.bind_state(X)
+        dist, _ = m.run(0, 2, sched, want_dist=True)
+    want = orc.dist_to_mean(X.cpu().double().numpy())
+    assert_dist_close(dist, np.full(3, want), TOL[dtype] * 1e-3, dist_floor(P, dtype, 1.0) * 1e-3, w.name)
+    assert bool((X[1:] == 1).all()) and bool((X[0] == 512).all())
