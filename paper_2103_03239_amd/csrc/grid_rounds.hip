@@ -604,12 +604,25 @@ bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t ro
     const auto magic = [](int64_t n) { return static_cast<uint32_t>(((int64_t(1) << 32) + n - 1) / n); };
     p.magic_m = magic(M);
     // Widest tile: rows of 512 bytes beat 1 KiB on 64 rows (2.55 against 2.73 ms), 256 bytes beat
-    // 128 on 256 rows (0.40 against 0.46 ms for 3 rounds).  Short rows: enough blocks for the chip.
+    // 128 on 256 rows (0.40 against 0.46 ms for 3 rounds).
     int32_t wb = 1024;
     while (wb > 256 && N * wb > 32 * 1024) wb >>= 1;
     while (wb > 128 && N * wb > 64 * 1024) wb >>= 1;
     while (wb > 32 && N * wb > 128 * 1024) wb >>= 1;
-    while (wb > 128 && (p.valid_bytes + wb - 1) / wb < 1024) wb >>= 1;
+    // A state of up to 256 MiB stays in the last-level cache and is bound by latency more than by
+    // the width of its accesses: 256 bytes at most (250 MiB, 4 x 4 x 4 peers: 103 against 109 us at
+    // 512), one part in LDS for up to 1024 peers (32 x 32, 4 rounds: 8 MiB 22 -> 14 us, 250 MiB
+    // 115 -> 97) and, above, while that gives a compute unit no second tile to run (16 x 16 x 16,
+    // 6 rounds: 16 MiB 46 -> 29 us, but 128 MiB 96 -> 127) ...
+    const double state_bytes = static_cast<double>(N) * p.row_bytes;
+    const bool cached = state_bytes <= 256.0 * (1 << 20);
+    if (cached && wb > 256) wb = 256;
+    if (cached && N * wb > 64 * 1024 && (N <= 1024 || (p.valid_bytes % 16 == 0 && p.valid_bytes <= 256 * wb))) wb >>= 1;
+    // ... and narrow tiles, so that every compute unit gets several blocks (8 MiB, 4 x 4 x 4 peers,
+    // 6 rounds: 15.3 -> 13.3 us; 5 x 5 x 5, 32 MiB: 31.9 -> 25.1), but not below 4 KiB or one
+    // cache line of 256 rows and more.
+    const int32_t least = N >= 256 ? 128 : 64;
+    while (wb > least && N * wb > 4096 && (p.valid_bytes + wb - 1) / wb < 2048) wb >>= 1;
     while (wb > 32 && wb / 2 >= p.valid_bytes) wb >>= 1;
     p.Wb = wb;
     p.wv_shift = 0;
@@ -633,8 +646,12 @@ bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t ro
     // Runs per die: where tiles share lines, and for rows of one line (1024 rows of 16 MiB, 8
     // rounds: 9.43 -> 9.33 ms, 4 rounds: 10.2 -> 8.3 ms); wider ones lose 1 % to them.
     const bool whole_lines = wb >= 128 && reinterpret_cast<uintptr_t>(X) % 128 == 0 && p.row_bytes % 128 == 0;
-    p.streaming = whole_lines ? 1 : 0;
+    // States in the last-level cache stay there with ordinary accesses (16 x 16 peers, 4 rounds:
+    // 128 MiB 58.6 -> 52.8 us, 250 MiB 113 -> 89); below the L2s' 32 MiB the non-temporal ones are
+    // ahead again (16 MiB: 12.5 against 13.8), they leave no dirty lines to be written back at the end.
+    p.streaming = whole_lines && (!cached || state_bytes <= 24.0 * (1 << 20)) ? 1 : 0;
     p.die_run = whole_lines && wb > 128 ? 1 : 32;
+    if (p.tiles < 8 * p.die_run) p.die_run = p.tiles >= 16 ? static_cast<int32_t>(p.tiles / 8) : 1;
     // rounds of one pass: as many bitmaps as fit next to the tile
     const int64_t waves = p.threads / 64, columns = part / esize;
     const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + 2 * waves) * 8 - kRcpBytes - 64;

@@ -308,13 +308,15 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // peers: 5.6 against 5.3 TB/s).  A state of up to 256 MiB stays in the last-level cache from
     // round to round if the accesses are ordinary, and wants more waves in flight, since its latency
     // is what limits: 256 MiB, 16 x 16 peers 5.4 -> 6.2 TB/s, 64 MiB 4.1 -> 4.7, 32 x 32 peers of
-    // 128 MiB 4.5 -> 5.7, 4 x 4 x 4 of 256 MiB 5.4 -> 6.4; at 512 MiB both are equal.  Rows that
+    // 128 MiB 4.5 -> 5.7, 4 x 4 x 4 of 256 MiB 5.4 -> 6.4; at 512 MiB both are equal, and below
+    // the L2s' 32 MiB the non-temporal ones are ahead by 5 %.  Rows that
     // do not start on cache lines share their first and last lines with other work items: the parts
     // have to meet in L2 (16 x 16 peers x 2,000,001 binary32: 4.5 -> 5.3 TB/s, x 1,200,007
     // bfloat16: 4.3 -> 5.2, 4 x 4 x 4 x 9,000,001: 4.7 -> 5.6).
-    const bool cached = static_cast<double>(geom.N) * row_bytes * (geom.grad != nullptr ? 2 : 1) <= 256.0 * (1 << 20);
+    const double touched = static_cast<double>(geom.N) * row_bytes * (geom.grad != nullptr ? 2 : 1);
+    const bool cached = touched <= 256.0 * (1 << 20);
     const bool whole_lines = reinterpret_cast<uintptr_t>(X) % 128 == 0 && row_bytes % 128 == 0;
-    const bool nt = tune.nt >= 0 ? tune.nt != 0 : (!cached && whole_lines);
+    const bool nt = tune.nt >= 0 ? tune.nt != 0 : whole_lines && (!cached || touched <= 24.0 * (1 << 20));
     const int block = (tune.block == 64 || tune.block == 128 || tune.block == 256) ? tune.block : 64;
     // Block order (measured on MI355X over row sizes of 128 KiB .. 32 MiB, groups of 16 and of
     // 32 rows).  Work items go to the blocks tile-fastest, so the waves in flight stream a

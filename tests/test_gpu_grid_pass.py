@@ -135,3 +135,23 @@ def test_distortion_of_a_converged_state_with_an_outlier_first_row(dtype):
     want = orc.dist_to_mean(X.cpu().double().numpy())
     assert_dist_close(dist, np.full(3, want), TOL[dtype] * 1e-3, dist_floor(P, dtype, 1.0) * 1e-3, w.name)
     assert bool((X[1:] == 1).all()) and bool((X[0] == 512).all())
+
+
+@pytest.mark.parametrize("M,d,P,dtype", [(16, 3, 2_048, 1), (16, 3, 2_056, 1), (16, 3, 8_192, 0), (32, 2, 65_536, 0), (32, 2, 70_000, 0),
+                                         (4, 3, 1_200_000, 0), (16, 2, 30_000, 0), (24, 2, 120_000, 0)])
+def test_pass_on_either_side_of_the_size_rules(M, d, P, dtype):
+    """Tile widths, parts and access kinds that change with the size of the state: 16- and 32-byte
+    tiles of 4096 rows, one or two parts for 1024, states below and above 24 and 256 MiB."""
+    N, rounds = M ** d, d + 1
+    print(f"grid size M={M} d={d} P={P} dtype={dtype}", flush=True)
+    A = torch.randn(N, P, device=DEV).to(TD[dtype])
+    B = A.clone()
+    masks = orc.schedule_masks(1, 0.1, 3, 0, N, 0, rounds)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        m.bind_state(A)
+        for r in range(rounds):
+            m.round(r, masks[r])
+        m.bind_state(B)
+        m.run(0, rounds, binding.Schedule(kind=binding.SCHED_IID, p=0.1, seed=3))
+        m.sync()
+    assert torch.equal(A, B)
