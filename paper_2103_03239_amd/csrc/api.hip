@@ -153,8 +153,16 @@ int stage_to_device(moshpit_ctx *h, void *dst_dev, const void *src_host, size_t 
 // by int32: 2^24 peers (a 256 MiB sort buffer) is where this library stops.
 constexpr int64_t kMaxOrderedPeers = int64_t(1) << 24;
 
+PeerBits pack_bits(const uint8_t *alive_host, int64_t N)
+{
+    PeerBits b{};
+    for (int64_t i = 0; i < N; ++i) b.word[i >> 5] |= static_cast<uint32_t>(alive_host[i] != 0) << (i & 31);
+    return b;
+}
+
 int reserve_sort(moshpit_ctx *h)
 {
+    if (h->N <= kSmallOrderPeers) return MOSHPIT_OK;           // (their orders need no scratch)
     if (h->N > kMaxOrderedPeers)
         return fail(h, MOSHPIT_EINVAL, "rounds over a random order of the peers support at most %lld peers",
                     (long long)kMaxOrderedPeers);
@@ -977,11 +985,18 @@ int moshpit_dynamic_round(moshpit_ctx *h, int64_t t, uint64_t seed, const uint8_
     if (t < 0) return fail(h, MOSHPIT_EINVAL, "round index must be >= 0");
     rc = dyn_ensure(h);
     if (rc != MOSHPIT_OK) return rc;
-    const uint8_t *alive_dev = stage_mask(h, alive_host, &rc);
-    if (rc != MOSHPIT_OK) return rc;
     const DynLayout L = dyn_layout(h);
-    HIP_TRY(h, launch_dynamic_grouping(h->N, h->M, h->d, seed, t, alive_dev, L.keys, L.packed, L.count, L.first,
-                                       L.index, L.n_index, h->d_sort, h->stream));
+    if (h->N <= kSmallOrderPeers) {
+        PeerBits bits;
+        if (alive_host) bits = pack_bits(alive_host, h->N);
+        HIP_TRY(h, launch_small_grouping(h->N, h->M, h->d, seed, t, alive_host ? &bits : nullptr, L.keys, L.index, L.n_index,
+                                         h->stream));
+    } else {
+        const uint8_t *alive_dev = stage_mask(h, alive_host, &rc);
+        if (rc != MOSHPIT_OK) return rc;
+        HIP_TRY(h, launch_dynamic_grouping(h->N, h->M, h->d, seed, t, alive_dev, L.keys, L.packed, L.count, L.first,
+                                           L.index, L.n_index, h->d_sort, h->stream));
+    }
     RoundGeom geom{h->N, h->M, 1, L.index, L.n_index};
     HIP_TRY(h, launch_group_mean(h->X, h->dtype, h->P, h->row_stride, geom, nullptr, h->tune, h->stream));
     return MOSHPIT_OK;
@@ -1007,7 +1022,10 @@ int moshpit_random_permutation(moshpit_ctx *h, int64_t t, uint64_t seed, int32_t
     if (t < 0 || !perm_host) return fail(h, MOSHPIT_EINVAL, "bad round index or NULL output");
     int rc = reserve_sort(h);
     if (rc != MOSHPIT_OK) return rc;
-    HIP_TRY(h, launch_random_permutation(seed, t, h->N, h->d_keys, h->d_sort, h->stream));
+    if (h->N <= kSmallOrderPeers)
+        HIP_TRY(h, launch_small_permutation(seed, t, h->N, nullptr, h->d_keys, h->stream));
+    else
+        HIP_TRY(h, launch_random_permutation(seed, t, h->N, h->d_keys, h->d_sort, h->stream));
     HIP_TRY(h, hipMemcpyAsync(perm_host, h->d_keys, sizeof(int32_t) * static_cast<size_t>(h->N),
                               hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -1024,6 +1042,12 @@ int moshpit_random_groups_round(moshpit_ctx *h, int64_t t, uint64_t seed, int32_
     rc = reserve_sort(h);
     if (rc != MOSHPIT_OK) return rc;
     if (!h->d_perm) HIP_TRY(h, hipMalloc(reinterpret_cast<void **>(&h->d_perm), sizeof(int32_t) * static_cast<size_t>(h->N)));
+    if (h->N <= kSmallOrderPeers) {
+        PeerBits bits;
+        if (alive_host) bits = pack_bits(alive_host, h->N);
+        HIP_TRY(h, launch_small_permutation(seed, t, h->N, alive_host ? &bits : nullptr, h->d_perm, h->stream));
+        return queue_list_round(h, h->d_perm, h->N, group_size, nullptr);
+    }
     HIP_TRY(h, launch_random_permutation(seed, t, h->N, h->d_perm, h->d_sort, h->stream));
     return queue_list_round(h, h->d_perm, h->N, group_size, alive_host);
 }

@@ -138,6 +138,21 @@ hipError_t launch_refresh_copy(void *X, int dtype, int64_t N, int64_t P, int64_t
                                const int32_t *returning, const int32_t *counts, int64_t expected_rows,
                                hipStream_t stream);
 
+// One bit per peer of a host mask, as a kernel argument (no copy to the device, nothing to keep
+// until it has been read).
+constexpr int64_t kSmallOrderPeers = 4096;
+struct PeerBits {
+    uint32_t word[kSmallOrderPeers / 32];
+};
+
+// The two below for up to 4096 peers, in one launch, without scratch.  bits: host, who takes part
+// (nullptr: everybody); peers that do not are left out of the groups (chunk-index rounds) or get
+// an entry of -1 in place of their index (permutation).
+hipError_t launch_small_permutation(uint64_t seed, int64_t t, int64_t N, const PeerBits *bits, int32_t *perm,
+                                    hipStream_t stream);
+hipError_t launch_small_grouping(int64_t N, int32_t M, int32_t d, uint64_t seed, int64_t t, const PeerBits *bits,
+                                 int32_t *keys, int32_t *index, int64_t n_index, hipStream_t stream);
+
 // Queue the random-permutation kernels: perm[r] = peer of rank r when the peers
 // are ordered by their 64-bit key of (seed, t), ties by index (device, N int32).
 // items: device scratch, sort_padded_count(N) entries.
