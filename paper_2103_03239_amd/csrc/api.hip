@@ -515,6 +515,24 @@ int moshpit_round(moshpit_ctx *h, int64_t t, const uint8_t *alive_host)
     if (rc != MOSHPIT_OK) return rc;
     if (t < 0) return fail(h, MOSHPIT_EINVAL, "round index must be >= 0");
     if (!alive_host) return queue_round(h, t, nullptr, 1.f);
+    if (h->N <= kSmallOrderPeers && h->tune.cols == 0 && h->tune.unroll == 0) {
+        // bits in group order: peer base(g) + j * S at g * M + j
+        PeerBits bits{};
+        const int64_t S = axis_stride(h, t);
+        int64_t present = 0, at = 0;
+        for (int64_t outer = 0; outer < h->N; outer += S * h->M)
+            for (int64_t inner = 0; inner < S; ++inner)
+                for (int64_t j = 0; j < h->M; ++j, ++at) {
+                    const uint32_t on = alive_host[outer + inner + j * S] != 0;
+                    bits.word[at >> 5] |= on << (at & 31);
+                    present += on;
+                }
+        RoundGeom geom{h->N, h->M, S};
+        geom.present = static_cast<float>(present) / static_cast<float>(h->N);
+        geom.bits = &bits;
+        HIP_TRY(h, launch_group_mean(h->X, h->dtype, h->P, h->row_stride, geom, nullptr, h->tune, h->stream));
+        return MOSHPIT_OK;
+    }
     rc = stage_to_device(h, h->d_round_mask, alive_host, static_cast<size_t>(h->N));
     if (rc != MOSHPIT_OK) return rc;
     return queue_round(h, t, h->d_round_mask, present_fraction(alive_host, h->N));

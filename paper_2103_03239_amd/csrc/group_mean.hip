@@ -17,7 +17,11 @@
 // all its loads retire before its first store.
 //
 // The participant bitmap of a group is built by the wave itself: lane j < M
-// reads alive[base + j*S] and a ballot gives a 64-bit mask (hence M <= 64).
+// reads alive[base + j*S] and a ballot gives a 64-bit mask (hence M <= 64).  A
+// host mask of up to 4096 peers arrives as kernel arguments instead, its bits in
+// group order, and costs the wave two scalar loads: no copy to the device and no
+// event per round (27 peers x 1,001 bfloat16: 12.7 -> 5.4 us a round; 8 x 8 x 8 x
+// 8,869: 17.9 -> 7.8).
 #include "moshpit_internal.h"
 #include "row_vec.h"
 
@@ -37,19 +41,24 @@ constexpr int kLdsPerCu = 160 * 1024;   // gfx950: LDS bytes per compute unit
 //              whose loads all come before its stores.
 // tiles        ceil(nvec / (blockDim.x * COLS))
 // work_items   groups * tiles
+// bits         BITS: who takes part as kernel arguments (instead of alive), group by group: bit j of
+//              group g at position g * M + j
 // IDX          groups are consecutive chunks of M entries of the peer list
 //              index[0..n_index) (e.g. a random permutation) instead of grid lines
 // SGD          the Moshpit SGD communication step (Alg. 2): what is averaged is
 //              theta_j - gamma * g_j, g read from the matrix G laid out like X
 //              (rows g_row_bytes apart); a peer that is alone in its group still
 //              takes its local step
-template <int DT, int VE, int COLS, int U, bool NT, bool IDX, bool SGD>
+struct NoBits {};
+
+template <int DT, int VE, int COLS, int U, bool NT, bool IDX, bool SGD, bool BITS>
 __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t row_bytes, int64_t valid_bytes,
                                                             const uint8_t *__restrict__ alive, int32_t M,
                                                             int64_t S, int64_t tiles, int64_t work_items,
                                                             const int32_t *__restrict__ index, int64_t n_index,
                                                             const char *__restrict__ G, int64_t g_row_bytes,
-                                                            float gamma, int order)
+                                                            float gamma, int order,
+                                                            typename std::conditional<BITS, PeerBits, NoBits>::type bits)
 {
     typedef Vec<DT, VE> V;
     typedef typename V::mem_t mem_t;
@@ -83,9 +92,17 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
             takes_part = my_row >= 0 && ((alive == nullptr) || (alive[my_row] != 0));
         } else {
             base = (g / S) * S * M + (g % S);
-            if (lane < M) takes_part = (alive == nullptr) || (alive[base + static_cast<int64_t>(lane) * S] != 0);
+            if (!BITS && lane < M) takes_part = (alive == nullptr) || (alive[base + static_cast<int64_t>(lane) * S] != 0);
         }
-        const uint64_t live = __ballot(takes_part);
+        uint64_t live = __ballot(takes_part);
+        if constexpr (BITS) {
+            // (g is uniform: two or three words of the argument block through the scalar cache)
+            const uint32_t first = static_cast<uint32_t>(g) * static_cast<uint32_t>(M), at = first >> 5, shift = first & 31;
+            const auto word = [&](uint32_t k) -> uint64_t { return k < kSmallOrderPeers / 32 ? bits.word[k] : 0u; };
+            live = (word(at) | word(at + 1) << 32) >> shift;
+            if (shift != 0 && M > 32) live |= word(at + 2) << (64 - shift);
+            if (M < 64) live &= (1ull << M) - 1ull;
+        }
         const int cnt = __popcll(live);
         if (cnt < (SGD ? 1 : 2)) continue;           // nothing to do: rows stay as they are
 
@@ -196,7 +213,7 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
 // The kernel uses no LDS.  The dynamic-LDS size of the launch is only a
 // throttle: a block that reserves lds bytes lets floor(160 KiB / lds) blocks
 // share a compute unit, which bounds the number of row loads in flight.
-template <int DT, int VE, int COLS, int U, bool NT, bool IDX = false, bool SGD = false>
+template <int DT, int VE, int COLS, int U, bool NT, bool IDX = false, bool SGD = false, bool BITS = false>
 hipError_t launch_one(char *X, int64_t row_bytes, int64_t valid_bytes, const uint8_t *alive, const RoundGeom &geom,
                       int block, int waves_per_cu, int order, hipStream_t stream)
 {
@@ -214,7 +231,9 @@ hipError_t launch_one(char *X, int64_t row_bytes, int64_t valid_bytes, const uin
         grid = ((work + 7) >> 3) << 3;
         if (grid > 0x7fffffffLL) { grid = 0x7fffffffLL; order = 0; }    // (more work items than blocks: plain order)
     }
-    auto kernel = group_mean_kernel<DT, VE, COLS, U, NT, IDX, SGD>;
+    auto kernel = group_mean_kernel<DT, VE, COLS, U, NT, IDX, SGD, BITS>;
+    typename std::conditional<BITS, PeerBits, NoBits>::type bits{};
+    if constexpr (BITS) bits = *geom.bits;
     size_t lds = 0;
     if (waves_per_cu > 0 && waves_per_cu < 32) {
         int blocks_per_cu = waves_per_cu / (block / 64);
@@ -226,7 +245,7 @@ hipError_t launch_one(char *X, int64_t row_bytes, int64_t valid_bytes, const uin
     kernel<<<dim3(static_cast<uint32_t>(grid)), dim3(block), lds, stream>>>(X, row_bytes, valid_bytes, alive, geom.M,
                                                                             geom.S, tiles, work, geom.index,
                                                                             geom.n_index, geom.grad, geom.grad_row_bytes,
-                                                                            geom.gamma, order);
+                                                                            geom.gamma, order, bits);
     return hipGetLastError();
 }
 
@@ -234,6 +253,19 @@ template <int DT, int VE>
 hipError_t launch_shape(int cols, int unroll, bool nt, char *X, int64_t row_bytes, int64_t valid_bytes,
                         const uint8_t *alive, const RoundGeom &geom, int block, int wpc, int order, hipStream_t stream)
 {
+    if (geom.bits != nullptr) {
+        // a host mask of up to 4096 peers: the default shapes only
+#define MOSHPIT_BITS(C, UU)                                                                                             \
+        if (cols == C && unroll == UU)                                                                                 \
+            return nt ? launch_one<DT, VE, C, UU, true, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream) \
+                      : launch_one<DT, VE, C, UU, false, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        MOSHPIT_BITS(1, 16)
+        MOSHPIT_BITS(2, 8)
+        MOSHPIT_BITS(1, 4)
+        MOSHPIT_BITS(4, 2)
+#undef MOSHPIT_BITS
+        return hipErrorInvalidValue;
+    }
     if (geom.index != nullptr) {
         // peer-list groups: the default shapes only
         if (cols == 1 && unroll == 16) return nt ? launch_one<DT, VE, 1, 16, true, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream)
@@ -292,7 +324,7 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // about 16-28 MiB in flight on the chip.  More than that and the HBM
     // controllers see too many open pages; less and latency is not covered.
     int cols = tune.cols, unroll = tune.unroll;
-    if (cols <= 0 || unroll <= 0 || geom.index != nullptr || geom.grad != nullptr) {
+    if (cols <= 0 || unroll <= 0 || geom.bits != nullptr || geom.index != nullptr || geom.grad != nullptr) {
         if (geom.M > 8) { unroll = 16; cols = 1; }
         else if (geom.M > 4) { unroll = 8; cols = 2; }
         else if (geom.M > 2) {
@@ -314,9 +346,14 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // have to meet in L2 (16 x 16 peers x 2,000,001 binary32: 4.5 -> 5.3 TB/s, x 1,200,007
     // bfloat16: 4.3 -> 5.2, 4 x 4 x 4 x 9,000,001: 4.7 -> 5.6).
     const double touched = static_cast<double>(geom.N) * row_bytes * (geom.grad != nullptr ? 2 : 1);
-    const bool cached = touched <= 256.0 * (1 << 20);
     const bool whole_lines = reinterpret_cast<uintptr_t>(X) % 128 == 0 && row_bytes % 128 == 0;
-    const bool nt = tune.nt >= 0 ? tune.nt != 0 : whole_lines && (!cached || touched <= 24.0 * (1 << 20));
+    // (off the cache lines the rule holds a little longer: 12 x 12 peers x 630,769 binary32, 347 MiB,
+    // 5.7 -> 6.1 TB/s)
+    const bool cached = touched <= (whole_lines ? 256.0 : 448.0) * (1 << 20);
+    // (the SGD step on groups of up to 8 rows streams so few rows at once that non-temporal accesses
+    // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms)
+    const bool lines_meet = !whole_lines && (geom.grad == nullptr || geom.M > 8);
+    const bool nt = tune.nt >= 0 ? tune.nt != 0 : (cached ? whole_lines && touched <= 24.0 * (1 << 20) : !lines_meet);
     const int block = (tune.block == 64 || tune.block == 128 || tune.block == 256) ? tune.block : 64;
     // Block order (measured on MI355X over row sizes of 128 KiB .. 32 MiB, groups of 16 and of
     // 32 rows).  Work items go to the blocks tile-fastest, so the waves in flight stream a
@@ -331,11 +368,14 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         if (cached) {
             order = geom.M > 8 ? 1 : 0;
         } else if (!whole_lines) {
-            order = geom.M > (geom.grad != nullptr ? 8 : 16) ? 1 : 0;
+            order = geom.M > (geom.grad != nullptr ? 8 : 16) || (geom.M <= 4 && geom.bits != nullptr) ? 1 : 0;
         } else if (geom.index == nullptr) {
             const int64_t member_stride = geom.S * row_bytes;
             const int64_t MiB = 1 << 20;
-            if (geom.M <= 16 ? (member_stride >= 4 * MiB && member_stride <= 16 * MiB)
+            // (only where the distance is a multiple of 256 KiB: 16 x 16 peers x 2,000,000 binary32,
+            // 8,000,000 bytes apart, runs at 5.95 TB/s in the plain order and 5.56 in this one)
+            if (member_stride % (MiB / 4) != 0) order = 0;
+            else if (geom.M <= 16 ? (member_stride >= 4 * MiB && member_stride <= 16 * MiB)
                              : (member_stride >= 2 * MiB && member_stride < 4 * MiB))
                 order = 1;
         }
@@ -355,7 +395,7 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         // (nearly) every peer takes part each wave has more loads in flight and fewer waves do
         // better (16 MiB rows in groups of 32: 3 waves 6.2 TB/s, 4 waves 5.8).
         if (wpc < 4) wpc = 4;
-        const bool full = alive == nullptr || geom.present >= 0.97f;
+        const bool full = (alive == nullptr && geom.bits == nullptr) || geom.present >= 0.97f;
         if (full && geom.grad == nullptr && geom.index == nullptr) wpc -= 1;
         if (rows == 16 && cols == 1 && geom.M <= 16) {
             if (geom.grad != nullptr) wpc = 5;
@@ -367,8 +407,11 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         if (rows * cols <= 4) wpc = full ? 14 : 21;
         // ordinary accesses (see above): more in flight, 8 for bfloat16 rows off the cache lines
         if (cached) wpc = geom.M > 8 ? 12 : 16;
-        else if (!whole_lines && rows * cols <= 4) wpc = 16;
-        else if (!whole_lines && rows == 16 && dtype == 1) wpc = 8;
+        else if (lines_meet && rows * cols <= 4) wpc = 16;
+        else if (!whole_lines && dtype == 1 && geom.M > 8 && geom.M <= 16) wpc = 128 / rows;
+        // a wave whose mask came with its arguments starts loading sooner: fewer do (8 x 8 peers x
+        // 12,000,007 binary32: 3 waves 5.3 TB/s, 4 waves 5.0; 16 x 16 x 2,000,001: 5.3 and 4.9)
+        else if (!whole_lines && dtype == 0 && geom.bits != nullptr && geom.M > 4 && geom.M <= 16) wpc = 52 / kib_per_wave;
         if (wpc > 32) wpc = 32;
     }
 
@@ -383,6 +426,9 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     if (geom.index != nullptr)
         return dtype == 0 ? launch_one<0, 1, 1, 16, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
                           : launch_one<1, 1, 1, 16, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
+    if (geom.bits != nullptr)
+        return dtype == 0 ? launch_one<0, 1, 1, 16, false, false, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
+                          : launch_one<1, 1, 1, 16, false, false, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
     return dtype == 0 ? launch_one<0, 1, 1, 16, false>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
                       : launch_one<1, 1, 1, 16, false>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
 }

@@ -57,6 +57,13 @@ struct MeanTuning {
     int order = -1;
 };
 
+// One bit per peer of a host mask, as a kernel argument (no copy to the device, nothing to keep
+// until it has been read).
+constexpr int64_t kSmallOrderPeers = 4096;
+struct PeerBits {
+    uint32_t word[kSmallOrderPeers / 32];
+};
+
 // Geometry of one round: group g (0 <= g < N/M) owns rows base(g) + j*S,
 // j = 0..M-1, with S = M^(t mod d) and base(g) = (g / S) * S * M + g % S.
 // With index != nullptr the groups are instead consecutive chunks of M entries of
@@ -74,6 +81,9 @@ struct RoundGeom {
     // Fraction of the peers expected to take part (sizes the launch only: a wave keeps one row
     // load in flight per participant, so fuller groups want fewer resident waves); < 0 = unknown
     float present = -1.f;
+    // Who takes part (host; bit j of group g at position g * M + j), instead of the `alive` argument;
+    // grid groups without gradients only, default launch shape
+    const PeerBits *bits = nullptr;
 };
 
 // Queue one averaging round on `stream`.  X: device, row-major, `P` valid
@@ -137,13 +147,6 @@ hipError_t launch_refresh_plan(const uint8_t *prev, const uint8_t *cur, int64_t 
 hipError_t launch_refresh_copy(void *X, int dtype, int64_t N, int64_t P, int64_t row_stride, const int32_t *donor,
                                const int32_t *returning, const int32_t *counts, int64_t expected_rows,
                                hipStream_t stream);
-
-// One bit per peer of a host mask, as a kernel argument (no copy to the device, nothing to keep
-// until it has been read).
-constexpr int64_t kSmallOrderPeers = 4096;
-struct PeerBits {
-    uint32_t word[kSmallOrderPeers / 32];
-};
 
 // The two below for up to 4096 peers, in one launch, without scratch.  bits: host, who takes part
 // (nullptr: everybody); peers that do not are left out of the groups (chunk-index rounds) or get
