@@ -187,13 +187,15 @@ def measure(cfg: int, steps: int, warmup: int, cpu_cols: int, cpu_budget_s: floa
     log(f"[bench] {steps} steps in {elapsed:.3f}s; group-mean kernel {k1_gbps:.0f} GB/s "
         f"({100 * k1_gbps / HBM_PEAK_GBPS:.1f}% of peak), step {value:.0f} GB/s")
 
-    # rounds only, queued back to back with no per-round events and one wait at the end
+    # rounds only, one call per round, queued back to back with no events and one wait at the end
+    # (a run without times takes all its rounds in one pass where it can)
     next_step = total_steps
     rsteps = max(steps, 4)
+    r_masks = m.schedule_mask(sched, next_step * w.rounds, rsteps * w.rounds)
     m.sync()
     tr = time.perf_counter()
-    for k in range(next_step, next_step + rsteps):
-        m.run(k * w.rounds, w.rounds, sched)
+    for k in range(rsteps * w.rounds):
+        m.round(next_step * w.rounds + k, r_masks[k])
     m.sync()
     r_elapsed = time.perf_counter() - tr
     next_step += rsteps
@@ -351,7 +353,7 @@ def measure_extras(m, X, w, all_masks, row_stride, dev, sgd_iteration=True):
         sched = binding.Schedule(kind=w.kind, p=w.p, seed=w.mask_seed, down_rounds=w.down)
         m.sgd_run(0, w.rounds, G, 1e-3, sched, flags=binding.RUN_FUSED)
         it_fused = timed(lambda r: m.sgd_run((r + 1) * w.rounds, w.rounds, G, 1e-3, sched, flags=binding.RUN_FUSED), 3)
-        it_plain = timed(lambda r: m.sgd_run((r + 4) * w.rounds, w.rounds, G, 1e-3, sched), 3)
+        it_plain = timed(lambda r: m.sgd_run((r + 4) * w.rounds, w.rounds, G, 1e-3, sched, want_times=True), 3)
         out["sgd_iteration"] = {"rounds": w.rounds, "ms_fused": round(it_fused, 4), "ms_round_by_round": round(it_plain, 4),
                                 "note": "theta - gamma*g for the peers present in the first round, then the rounds"}
         log(f"[bench] Moshpit SGD iteration with {w.rounds} rounds: {it_fused:.3f} ms fused, {it_plain:.3f} ms round by round")
