@@ -57,9 +57,7 @@ struct moshpit_ctx {
 
     // Die-and-rejoin schedule carried between calls: d_away[i] = rounds peer i still sits
     // out at the start of round away_t under (away_seed, away_threshold, away_down).
-    // (two buffers of N: a whole-grid plan reads one while it writes the other)
     int32_t *d_away = nullptr;
-    int away_half = 0;
     bool away_valid = false;
     uint64_t away_seed = 0;
     uint32_t away_threshold = 0;
@@ -214,36 +212,6 @@ uint32_t schedule_threshold(const moshpit_schedule *s)
     return static_cast<uint32_t>(std::floor((s ? s->p : 0.0) * 16777216.0));
 }
 
-// Die-and-rejoin state of the handle: where a schedule's walk to round t0 may start (from the
-// state a previous call left, when it belongs to this schedule and is not past t0) and where the
-// state at the end of the rounds goes.
-int away_before(moshpit_ctx *h, uint64_t seed, uint32_t threshold, int32_t down, int64_t t0, int64_t *s_begin,
-                const int32_t **away_in, int32_t **away_out)
-{
-    if (!h->d_away)
-        HIP_TRY(h, hipMalloc(reinterpret_cast<void **>(&h->d_away), 2 * sizeof(int32_t) * static_cast<size_t>(h->N)));
-    *s_begin = 0;
-    *away_in = nullptr;
-    if (h->away_valid && h->away_seed == seed && h->away_threshold == threshold && h->away_down == down &&
-        h->away_t <= t0 && h->away_t > 0) {
-        *s_begin = h->away_t;
-        *away_in = h->d_away + h->away_half * h->N;
-    }
-    *away_out = h->d_away + (h->away_half ^ 1) * h->N;
-    h->away_valid = false;
-    return MOSHPIT_OK;
-}
-
-void away_after(moshpit_ctx *h, uint64_t seed, uint32_t threshold, int32_t down, int64_t t)
-{
-    h->away_half ^= 1;
-    h->away_valid = true;
-    h->away_seed = seed;
-    h->away_threshold = threshold;
-    h->away_down = down;
-    h->away_t = t;
-}
-
 // Fill d_masks[0..rounds) for rounds t0.. under schedule s (s may be NULL).
 int queue_masks(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t rounds)
 {
@@ -259,14 +227,26 @@ int queue_masks(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t r
         const int32_t down = s ? s->down_rounds : 0;
         int64_t s_begin = 0;
         const int32_t *away_in = nullptr;
-        int32_t *away_out = nullptr;
         if (kind == MOSHPIT_SCHED_REJOIN) {
-            rc = away_before(h, seed, threshold, down, t0, &s_begin, &away_in, &away_out);
-            if (rc != MOSHPIT_OK) return rc;
+            // go on from the state a previous call left, when it belongs to this schedule and is not past t0
+            if (!h->d_away)
+                HIP_TRY(h, hipMalloc(reinterpret_cast<void **>(&h->d_away), sizeof(int32_t) * static_cast<size_t>(h->N)));
+            if (h->away_valid && h->away_seed == seed && h->away_threshold == threshold && h->away_down == down &&
+                h->away_t <= t0 && h->away_t > 0) {
+                s_begin = h->away_t;
+                away_in = h->d_away;
+            }
+            h->away_valid = false;
         }
-        HIP_TRY(h, launch_schedule(kind, threshold, seed, down, h->N, t0, rounds, h->d_masks, s_begin, away_in, away_out,
-                                   h->stream));
-        if (kind == MOSHPIT_SCHED_REJOIN) away_after(h, seed, threshold, down, t0 + rounds);
+        HIP_TRY(h, launch_schedule(kind, threshold, seed, down, h->N, t0, rounds, h->d_masks, s_begin, away_in,
+                                   kind == MOSHPIT_SCHED_REJOIN ? h->d_away : nullptr, h->stream));
+        if (kind == MOSHPIT_SCHED_REJOIN) {
+            h->away_valid = true;
+            h->away_seed = seed;
+            h->away_threshold = threshold;
+            h->away_down = down;
+            h->away_t = t0 + rounds;
+        }
     }
     if (s && s->group_skip) {
         if (s->refresh) {
@@ -377,29 +357,24 @@ int queue_grid_plan(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32
     }
     *tables = grid_tables(h, h->grid_rounds_cap);
     GridSchedule g{};
-    g.kind = s->kind;
     g.N = static_cast<int32_t>(h->N);
     g.M = h->M;
     g.d = h->d;
     g.rounds = rounds;
-    g.down = s->down_rounds;
     g.group_skip = s->group_skip != 0;
     g.refresh = s->refresh != 0;
     g.threshold = schedule_threshold(s);
     g.seed = s->seed;
     g.t0 = t0;
-    if (s->kind == MOSHPIT_SCHED_EXPLICIT) {
-        int rc = reserve_masks(h, rounds);
-        if (rc != MOSHPIT_OK) return rc;
-        rc = stage_to_device(h, h->d_masks, s->explicit_masks, static_cast<size_t>(rounds) * h->N);
+    if (s->kind != MOSHPIT_SCHED_IID) {
+        moshpit_schedule presence = *s;              // the masks before the group-skip filter
+        presence.group_skip = 0;
+        presence.refresh = 0;
+        const int rc = queue_masks(h, &presence, t0, rounds);
         if (rc != MOSHPIT_OK) return rc;
         g.masks = h->d_masks;
-    } else if (s->kind == MOSHPIT_SCHED_REJOIN) {
-        int rc = away_before(h, g.seed, g.threshold, g.down, t0, &g.begin, &g.away_in, &g.away_out);
-        if (rc != MOSHPIT_OK) return rc;
     }
     HIP_TRY(h, launch_grid_plan(g, *tables, h->stream));
-    if (s->kind == MOSHPIT_SCHED_REJOIN) away_after(h, g.seed, g.threshold, g.down, t0 + rounds);
     return MOSHPIT_OK;
 }
 
@@ -579,8 +554,9 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
     int rc = MOSHPIT_OK;
     GridTables tables{};
     if (failures && rounds > 0) {
-        if (step_first) rc = queue_masks(h, s, t0, rounds);          // (the first round reads the masks themselves)
-        if (rc == MOSHPIT_OK) rc = queue_grid_plan(h, s, t0, rounds, &tables);
+        rc = queue_grid_plan(h, s, t0, rounds, &tables);
+        // the single-round kernel of a first round reads the masks themselves (left by the plan, if it needed them unfiltered)
+        if (rc == MOSHPIT_OK && step_first && (s->kind == MOSHPIT_SCHED_IID || s->group_skip)) rc = queue_masks(h, s, t0, rounds);
         if (rc != MOSHPIT_OK) return rc;
     }
     const int64_t entry_tiles = plan.tiles * plan.phases;

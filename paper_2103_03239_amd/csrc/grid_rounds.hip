@@ -462,32 +462,24 @@ __device__ __forceinline__ int32_t block_rank(bool flag, int32_t *wave_sums, int
     return base + __popcll(ballot & ((1ull << lane) - 1ull));
 }
 
-// Is peer i present in round t (and in round t - 1, for t > t0)?  Walks a die-and-rejoin schedule from s.begin.
+// Is peer i present in round t (and in round t - 1, for t > t0)?
 __device__ __forceinline__ void presence(const GridSchedule &s, int32_t i, int64_t t, bool &before, bool &now)
 {
     before = true;
-    if (s.kind == 3) {                               // explicit masks, device
+    if (s.masks != nullptr) {
         now = s.masks[(t - s.t0) * s.N + i] != 0;
         if (t > s.t0) before = s.masks[(t - 1 - s.t0) * s.N + i] != 0;
-    } else if (s.kind == 1) {
+    } else {
         now = !failure_event(s.seed, t, i, s.threshold);
         if (s.refresh && t > s.t0) before = !failure_event(s.seed, t - 1, i, s.threshold);
-    } else {
-        int32_t away = s.away_in != nullptr ? s.away_in[i] : 0;
-        now = true;
-        for (int64_t q = s.begin; q <= t; ++q) {
-            before = now;
-            if (away == 0 && failure_event(s.seed, q, i, s.threshold)) away = s.down;
-            now = away == 0;
-            if (away > 0) --away;
-        }
     }
 }
 
 // Blocks 0 .. rounds-1: round r = blockIdx.x: bitmaps[r][g] (bit j: position j of group g takes
 // part) and, with refresh, the (donor << 16 | returning peer) pairs of the round.  Blocks after
 // that: flags[i] for 1024 peers each (bit 0: takes part in some round or is refreshed; bit 1: in
-// the first one), and the state of a die-and-rejoin schedule at the end.
+// the first one).  A die-and-rejoin schedule comes as masks: its walk over the rounds spreads over
+// the chip in the schedule kernel, while one block a round that walks for 4096 peers takes 42 us.
 __global__ __launch_bounds__(kPlanThreads) void grid_plan_kernel(GridSchedule s, GridTables o)
 {
     __shared__ uint8_t here[kGridMaxPeers];
@@ -553,20 +545,10 @@ __global__ __launch_bounds__(kPlanThreads) void grid_plan_kernel(GridSchedule s,
         const int32_t i = (static_cast<int32_t>(blockIdx.x) - s.rounds) * kPlanThreads + tid;
         if (i >= N) return;
         uint8_t flag = 0;
-        if (s.kind == 2) {
-            int32_t away = s.away_in != nullptr ? s.away_in[i] : 0;
-            for (int64_t q = s.begin; q < s.t0 + s.rounds; ++q) {
-                if (away == 0 && failure_event(s.seed, q, i, s.threshold)) away = s.down;
-                if (q >= s.t0 && away == 0) flag |= q == s.t0 ? 3 : 1;
-                if (away > 0) --away;
-            }
-            s.away_out[i] = away;
-        } else {
-            for (int32_t r = 0; r < s.rounds; ++r) {
-                const bool now = s.kind == 3 ? s.masks[static_cast<int64_t>(r) * N + i] != 0
-                                             : !failure_event(s.seed, s.t0 + r, i, s.threshold);
-                if (now) flag |= r == 0 ? 3 : 1;
-            }
+        for (int32_t r = 0; r < s.rounds; ++r) {
+            const bool now = s.masks != nullptr ? s.masks[static_cast<int64_t>(r) * N + i] != 0
+                                                : !failure_event(s.seed, s.t0 + r, i, s.threshold);
+            if (now) flag |= r == 0 ? 3 : 1;
         }
         o.flags[i] = flag;
     }

@@ -237,13 +237,11 @@ hipError_t launch_grid_dist(const double *partials, int64_t tiles, int32_t entri
 
 // Tables of a run under a failure schedule, for the kernel above.
 struct GridSchedule {
-    int32_t kind, N, M, d, rounds, down, group_skip, refresh;
+    int32_t N, M, d, rounds, group_skip, refresh;
     uint32_t threshold;
     uint64_t seed;
-    int64_t t0, begin;               // begin: round from which a die-and-rejoin schedule is walked
-    const int32_t *away_in;          // its state at round `begin` (nullptr: nobody away)
-    int32_t *away_out;               // its state at round t0 + rounds (not away_in)
-    const uint8_t *masks;            // kind 3: device [rounds][N]
+    int64_t t0;
+    const uint8_t *masks;            // who is present, device [rounds][N]; nullptr: independent failures
 };
 struct GridTables {
     uint32_t *bitmaps, *copies;
