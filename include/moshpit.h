@@ -9,8 +9,9 @@
  *   along coordinate a = t mod d: peers that agree in every other coordinate
  *   form a group (at most M members, row stride M^a), and every member that
  *   takes part in the round replaces its vector by the mean over the members
- *   that take part.  A peer that does not take part keeps its vector and is
- *   neither read nor written.  Rounds are numbered from 0.
+ *   that take part.  A peer that does not take part keeps its vector: its row is
+ *   never written (a pass over several rounds may read it).  Rounds are
+ *   numbered from 0.
  *
  * State layout.  X is row-major [N][row_stride] in device memory, P <=
  * row_stride valid elements per row, element type float (binary32) or
