@@ -533,6 +533,7 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
     const bool fused = (flags & MOSHPIT_RUN_FUSED) != 0;
     // the time of every single round is asked for: round by round (a fused run's times are shared out)
     if (round_ms_out_host && !fused) return MOSHPIT_OK;
+    if (rounds == 0) round_ms_out_host = nullptr;        // (one launch for the distortion alone, no round to time)
     if (rounds < 2 && !dist_out_host) return MOSHPIT_OK;
     GridPlan plan;
     if (!plan_grid(h->dtype, h->N, h->M, h->d, h->P, h->row_stride, h->X, t0, &plan)) return MOSHPIT_OK;

@@ -155,3 +155,21 @@ def test_pass_on_either_side_of_the_size_rules(M, d, P, dtype):
         m.run(0, rounds, binding.Schedule(kind=binding.SCHED_IID, p=0.1, seed=3))
         m.sync()
     assert torch.equal(A, B)
+
+
+@pytest.mark.parametrize("flags", [0, binding.RUN_FUSED])
+def test_zero_rounds_with_both_outputs_on_a_fresh_handle(flags):
+    """No round: one distortion value and no times, also before the handle has timed anything."""
+    M, d, P = 4, 2, 1_000
+    N = M ** d
+    X = torch.randn(N, P, device=DEV)
+    before = X.clone()
+    print(f"zero rounds flags={flags}", flush=True)
+    sched = binding.Schedule(kind=binding.SCHED_IID, p=0.2, seed=3)
+    with binding.Moshpit(N, P, M, d, 0) as m:
+        m.bind_state(X)
+        dist, ms = m.run(5, 0, sched, want_dist=True, want_times=True, flags=flags)
+    assert dist.shape == (1,) and ms.shape == (0,) and torch.equal(X, before)
+    want = orc.dist_to_mean(X.cpu().double().numpy())
+    # binary64 sums of N terms per column; s2 against s1^2/N cancels by N at most
+    assert abs(dist[0] - want) <= 4 * N * N * 2.0 ** -53 * want
