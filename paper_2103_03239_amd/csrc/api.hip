@@ -9,6 +9,7 @@
 
 #include "../../include/moshpit.h"
 #include "moshpit_internal.h"
+#include "pass_rules.h"
 
 using namespace moshpit;
 
@@ -33,8 +34,8 @@ struct moshpit_ctx {
     int32_t *d_refresh = nullptr;      // 3 N + 2 int32: candidates, donors, returning peers, counts
     uint8_t *d_refresh_masks = nullptr;  // 2 N bytes, for moshpit_refresh(host masks)
     int32_t *d_keys = nullptr;         // N
-    void *d_grid = nullptr;            // tables of whole-grid passes (see grid_tables): grid_rounds_cap rounds
-    int64_t grid_rounds_cap = 0;
+    void *d_grid = nullptr;            // tables of whole-grid passes (see queue_grid_plan): grid_cap bytes
+    int64_t grid_cap = 0;
     double *d_grid_partials = nullptr; // their distortion sums: grid_partials_cap doubles
     int64_t grid_partials_cap = 0;
     double *d_partials = nullptr;      // partials_cap doubles
@@ -329,52 +330,72 @@ int queue_round(moshpit_ctx *h, int64_t t, const uint8_t *alive_dev, float prese
     return MOSHPIT_OK;
 }
 
-// Tables of whole-grid passes over `rounds` rounds, one allocation:
-// [bitmaps rounds x N/M][copies rounds x N][copy counts rounds][flags N].
-GridTables grid_tables(const moshpit_ctx *h, int64_t rounds)
+// Memory for the tables of `rounds` rounds and the flags of the peers.
+int reserve_grid_tables(moshpit_ctx *h, bool refresh, int64_t rounds)
 {
-    GridTables g;
-    g.bitmaps = static_cast<uint32_t *>(h->d_grid);
-    g.copies = g.bitmaps + rounds * (h->N / h->M);
-    g.copy_counts = reinterpret_cast<int32_t *>(g.copies + rounds * h->N);
-    g.flags = reinterpret_cast<uint8_t *>(g.copy_counts + rounds);
-    return g;
+    const int64_t need = rounds * grid_table_round_bytes(h->N, h->M, refresh) + h->N;
+    if (need <= h->grid_cap) return MOSHPIT_OK;
+    if (h->d_grid) {
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        HIP_TRY(h, hipFree(h->d_grid));
+        h->d_grid = nullptr;
+        h->grid_cap = 0;
+    }
+    HIP_TRY(h, hipMalloc(&h->d_grid, static_cast<size_t>(need)));
+    h->grid_cap = need;
+    return MOSHPIT_OK;
 }
 
-// Queue the tables for rounds t0 .. t0+rounds-1 under schedule s (which has failures).
-int queue_grid_plan(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t rounds, GridTables *tables)
+// Queue the tables for rounds t0+r0 .. t0+r0+rounds-1 of a run that starts at round t0 under
+// schedule s (which has failures):
+// [bitmaps rounds x N/M][with refresh: copies rounds x N, copy counts rounds][flags N].
+// The presence of the whole run is in d_masks unless failures are independent.
+int queue_grid_plan(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t r0, int32_t rounds, GridTables *tables)
 {
-    if (rounds > h->grid_rounds_cap) {
-        if (h->d_grid) {
-            HIP_TRY(h, hipStreamSynchronize(h->stream));
-            HIP_TRY(h, hipFree(h->d_grid));
-            h->d_grid = nullptr;
-            h->grid_rounds_cap = 0;
-        }
-        const size_t words = static_cast<size_t>(rounds) * static_cast<size_t>(h->N / h->M + h->N + 1);
-        HIP_TRY(h, hipMalloc(&h->d_grid, words * 4 + static_cast<size_t>(h->N)));
-        h->grid_rounds_cap = rounds;
+    const bool refresh = s->refresh != 0;
+    GridTables o{};
+    o.bitmaps = static_cast<uint32_t *>(h->d_grid);
+    uint32_t *end = o.bitmaps + static_cast<int64_t>(rounds) * (h->N / h->M);
+    if (refresh) {
+        o.copies = end;
+        o.copy_counts = reinterpret_cast<int32_t *>(o.copies + static_cast<int64_t>(rounds) * h->N);
+        end = reinterpret_cast<uint32_t *>(o.copy_counts + rounds);
     }
-    *tables = grid_tables(h, h->grid_rounds_cap);
+    o.flags = reinterpret_cast<uint8_t *>(end);
     GridSchedule g{};
     g.N = static_cast<int32_t>(h->N);
     g.M = h->M;
     g.d = h->d;
     g.rounds = rounds;
     g.group_skip = s->group_skip != 0;
-    g.refresh = s->refresh != 0;
+    g.refresh = refresh;
+    g.continued = r0 > 0;
     g.threshold = schedule_threshold(s);
     g.seed = s->seed;
-    g.t0 = t0;
-    if (s->kind != MOSHPIT_SCHED_IID) {
-        moshpit_schedule presence = *s;              // the masks before the group-skip filter
-        presence.group_skip = 0;
-        presence.refresh = 0;
-        const int rc = queue_masks(h, &presence, t0, rounds);
-        if (rc != MOSHPIT_OK) return rc;
-        g.masks = h->d_masks;
+    g.t0 = t0 + r0;
+    if (s->kind != MOSHPIT_SCHED_IID) g.masks = h->d_masks + static_cast<int64_t>(r0) * h->N;
+    HIP_TRY(h, launch_grid_plan(g, o, h->stream));
+    *tables = o;
+    return MOSHPIT_OK;
+}
+
+// The mask of a run's first round, after the group-skip filter, for the single-round kernel: a run
+// that goes on in whole-grid passes keeps the presence before the filter in d_masks.
+int queue_first_mask(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, const uint8_t **mask)
+{
+    if (s->kind == MOSHPIT_SCHED_IID) {
+        moshpit_schedule one = *s;
+        one.refresh = 0;
+        *mask = nullptr;
+        const int rc = queue_masks(h, &one, t0, 1);
+        if (rc == MOSHPIT_OK) *mask = h->d_masks;
+        return rc;
     }
-    HIP_TRY(h, launch_grid_plan(g, *tables, h->stream));
+    *mask = h->d_masks;
+    if (!s->group_skip) return MOSHPIT_OK;
+    HIP_TRY(h, hipMemcpyAsync(h->d_round_mask, h->d_masks, static_cast<size_t>(h->N), hipMemcpyDeviceToDevice, h->stream));
+    HIP_TRY(h, launch_skip_filter(h->d_round_mask, h->N, h->M, h->d, t0, 1, h->stream));
+    *mask = h->d_round_mask;
     return MOSHPIT_OK;
 }
 
@@ -554,10 +575,18 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
 
     int rc = MOSHPIT_OK;
     GridTables tables{};
+    int32_t tables_first = 0, tables_end = 0;                       // the rounds they hold now
+    const int64_t tables_most = grid_table_rounds(h->N, h->M, refresh, plan.max_rounds);
+    const uint8_t *first_mask = nullptr;
     if (failures && rounds > 0) {
-        rc = queue_grid_plan(h, s, t0, rounds, &tables);
-        // the single-round kernel of a first round reads the masks themselves (left by the plan, if it needed them unfiltered)
-        if (rc == MOSHPIT_OK && step_first && (s->kind == MOSHPIT_SCHED_IID || s->group_skip)) rc = queue_masks(h, s, t0, rounds);
+        rc = reserve_grid_tables(h, refresh, rounds < tables_most ? rounds : tables_most);
+        if (rc == MOSHPIT_OK && s->kind != MOSHPIT_SCHED_IID) {
+            moshpit_schedule presence = *s;                         // the masks before the group-skip filter
+            presence.group_skip = 0;
+            presence.refresh = 0;
+            rc = queue_masks(h, &presence, t0, rounds);
+        }
+        if (rc == MOSHPIT_OK && step_first) rc = queue_first_mask(h, s, t0, &first_mask);
         if (rc != MOSHPIT_OK) return rc;
     }
     const int64_t entry_tiles = plan.tiles * plan.phases;
@@ -598,8 +627,7 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
             geom.grad = static_cast<const char *>(grad);
             geom.grad_row_bytes = grad_row_stride * (h->dtype == MOSHPIT_F32 ? 4 : 2);
             geom.gamma = gamma;
-            HIP_TRY(h, launch_group_mean(h->X, h->dtype, h->P, h->row_stride, geom, failures ? h->d_masks : nullptr, h->tune,
-                                         h->stream));
+            HIP_TRY(h, launch_group_mean(h->X, h->dtype, h->P, h->row_stride, geom, first_mask, h->tune, h->stream));
             if (dist_out_host) {
                 rc = queue_dist(h, h->d_dist + 1);
                 if (rc != MOSHPIT_OK) return rc;
@@ -611,11 +639,20 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
             p.rounds = now;
             p.axis0 = static_cast<int32_t>((t0 + r) % h->d);
             if (failures && rounds > 0) {
-                p.bitmaps = tables.bitmaps + static_cast<int64_t>(r) * (h->N / h->M);
+                if (r >= tables_end) {
+                    tables_first = r;
+                    tables_end = rounds - r < tables_most ? rounds : r + static_cast<int32_t>(tables_most);
+                    rc = queue_grid_plan(h, s, t0, tables_first, tables_end - tables_first, &tables);
+                    if (rc != MOSHPIT_OK) return rc;
+                }
+                if (now > tables_end - r) now = tables_end - r;
+                p.rounds = now;
+                const int64_t at = r - tables_first;
+                p.bitmaps = tables.bitmaps + at * (h->N / h->M);
                 p.flags = tables.flags;
                 if (refresh) {
-                    p.copies = tables.copies + static_cast<int64_t>(r) * h->N;
-                    p.copy_counts = tables.copy_counts + r;
+                    p.copies = tables.copies + at * h->N;
+                    p.copy_counts = tables.copy_counts + at;
                     p.refresh_first = r > 0;
                 }
             }

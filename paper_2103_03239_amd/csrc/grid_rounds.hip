@@ -462,16 +462,17 @@ __device__ __forceinline__ int32_t block_rank(bool flag, int32_t *wave_sums, int
     return base + __popcll(ballot & ((1ull << lane) - 1ull));
 }
 
-// Is peer i present in round t (and in round t - 1, for t > t0)?
-__device__ __forceinline__ void presence(const GridSchedule &s, int32_t i, int64_t t, bool &before, bool &now)
+// Is peer i present in round t0 + r (and in the round before it, if that belongs to the run)?
+__device__ __forceinline__ void presence(const GridSchedule &s, int32_t i, int64_t r, bool &before, bool &now)
 {
     before = true;
+    const bool earlier = r > 0 || s.continued;
     if (s.masks != nullptr) {
-        now = s.masks[(t - s.t0) * s.N + i] != 0;
-        if (t > s.t0) before = s.masks[(t - 1 - s.t0) * s.N + i] != 0;
+        now = s.masks[r * s.N + i] != 0;
+        if (earlier) before = s.masks[(r - 1) * s.N + i] != 0;
     } else {
-        now = !failure_event(s.seed, t, i, s.threshold);
-        if (s.refresh && t > s.t0) before = !failure_event(s.seed, t - 1, i, s.threshold);
+        now = !failure_event(s.seed, s.t0 + r, i, s.threshold);
+        if (s.refresh && earlier) before = !failure_event(s.seed, s.t0 + r - 1, i, s.threshold);
     }
 }
 
@@ -489,14 +490,14 @@ __global__ __launch_bounds__(kPlanThreads) void grid_plan_kernel(GridSchedule s,
     if (static_cast<int32_t>(blockIdx.x) < s.rounds) {
         const int32_t r = blockIdx.x;
         const int64_t t = s.t0 + r;
-        const bool refresh = s.refresh && r > 0;
+        const bool refresh = s.refresh && (r > 0 || s.continued);
         bool was[kPerThread], is[kPerThread];
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
             const int32_t i = tid + k * kPlanThreads;
             was[k] = is[k] = false;
             if (i < N) {
-                presence(s, i, t, was[k], is[k]);
+                presence(s, i, r, was[k], is[k]);
                 here[i] = is[k] ? 1 : 0;
             }
         }
@@ -509,7 +510,7 @@ __global__ __launch_bounds__(kPlanThreads) void grid_plan_kernel(GridSchedule s,
             uint32_t bits = 0;
             for (int32_t j = 0; j < s.M; ++j) bits |= static_cast<uint32_t>(here[base + j * S]) << j;
             if (s.group_skip && static_cast<int32_t>(__popc(bits)) != s.M) bits = 0;
-            o.bitmaps[r * groups + g] = bits;
+            o.bitmaps[static_cast<int64_t>(r) * groups + g] = bits;
         }
         if (!refresh) {
             if (s.refresh && tid == 0) o.copy_counts[r] = 0;
@@ -565,7 +566,7 @@ __global__ __launch_bounds__(256) void grid_skip_flags_kernel(GridSchedule s, Gr
         int32_t S = 1;
         for (int64_t q = 0; q < (s.t0 + r) % s.d; ++q) S *= s.M;
         const int32_t g = i / (S * s.M) * S + i % S, j = i / S % s.M;
-        if ((o.bitmaps[r * groups + g] >> j) & 1u) flag |= r == 0 ? 3 : 1;
+        if ((o.bitmaps[static_cast<int64_t>(r) * groups + g] >> j) & 1u) flag |= r == 0 ? 3 : 1;
     }
     if (s.refresh) flag |= o.flags[i] & 1;           // a refreshed peer is written although its group sits out
     o.flags[i] = flag;

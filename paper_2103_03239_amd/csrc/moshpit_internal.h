@@ -235,13 +235,14 @@ hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStrea
 hipError_t launch_grid_dist(const double *partials, int64_t tiles, int32_t entries, int64_t N, double *out,
                             hipStream_t stream);
 
-// Tables of a run under a failure schedule, for the kernel above.
+// Tables of rounds t0 .. t0+rounds-1 of a run under a failure schedule, for the kernel above.
 struct GridSchedule {
     int32_t N, M, d, rounds, group_skip, refresh;
+    int32_t continued;               // round t0 - 1 belongs to the run as well
     uint32_t threshold;
     uint64_t seed;
     int64_t t0;
-    const uint8_t *masks;            // who is present, device [rounds][N]; nullptr: independent failures
+    const uint8_t *masks;            // who is present, device, row r = round t0 + r (row -1 if continued); nullptr: independent failures
 };
 struct GridTables {
     uint32_t *bitmaps, *copies;

@@ -173,3 +173,61 @@ def test_zero_rounds_with_both_outputs_on_a_fresh_handle(flags):
     want = orc.dist_to_mean(X.cpu().double().numpy())
     # binary64 sums of N terms per column; s2 against s1^2/N cancels by N at most
     assert abs(dist[0] - want) <= 4 * N * N * 2.0 ** -53 * want
+
+
+@pytest.mark.parametrize("M,d,P,dtype,rounds,refresh", [(16, 3, 24, 1, 962, True), (2, 11, 8, 0, 4_104, False)])
+def test_run_longer_than_its_tables(M, d, P, dtype, rounds, refresh):
+    """More rounds than the tables of a pass are built for at once.  Nobody is present until shortly
+    before the tables change, so that the state still differs from peer to peer there."""
+    N, start = M ** d, (946 if refresh else 4_080)          # the tables change at round 952 (4,092)
+    print(f"long run M={M} d={d} rounds={rounds} refresh={refresh}", flush=True)
+    masks = np.zeros((rounds, N), dtype=np.uint8)
+    masks[start:] = (np.random.default_rng(rounds).random((rounds - start, N)) > 0.9).astype(np.uint8)
+    bufA, A = state(N, P, P, 0, dtype, 12)
+    bufB, B = state(N, P, P, 0, dtype, 12)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        m.bind_state(A)
+        for t in range(start, rounds):
+            if refresh:
+                m.refresh(t, 7, masks[t - 1], masks[t])
+            m.round(t, masks[t])
+        m.bind_state(B)
+        m.run(0, rounds, binding.Schedule(kind=binding.SCHED_EXPLICIT, seed=7, refresh=refresh, explicit_masks=masks))
+        m.sync()
+        assert torch.equal(bufA, bufB)
+        if not refresh:                       # the same length with drawn failures: groups of two that rarely meet
+            masks = orc.schedule_masks(1, 0.99, 5, 0, N, 3, rounds)
+            m.bind_state(A)
+            for r in range(rounds):
+                m.round(3 + r, masks[r])
+            m.bind_state(B)
+            m.run(3, rounds, binding.Schedule(kind=binding.SCHED_IID, p=0.99, seed=5))
+            m.sync()
+            assert torch.equal(bufA, bufB)
+    assert A.float().unique(dim=0).shape[0] > 1
+
+
+@pytest.mark.parametrize("kind,skip", [(1, False), (1, True), (2, False), (2, True), (3, True)])
+def test_bf16_step_then_passes(kind, skip):
+    """A bfloat16 iteration without RUN_FUSED: its first round is the single-round kernel's, which
+    sees the first round's mask after the group-skip filter; the passes after it see the presence."""
+    M, d, P, t0, rounds, seed = 4, 3, 333, 2, 5, 21
+    N = M ** d
+    print(f"bf16 step kind={kind} skip={skip}", flush=True)
+    presence = orc.schedule_masks(2 if kind == 3 else kind, 0.1, seed, 2, N, t0, rounds)
+    bufA, A = state(N, P, P, 0, 1, 3)
+    bufB, B = state(N, P, P, 0, 1, 3)
+    _, G = state(N, P, P, 0, 1, 4)
+    masks = [orc.skip_filter(N, M, d, t0 + r, presence[r]) if skip else presence[r] for r in range(rounds)]
+    sched = binding.Schedule(kind=kind, p=0.1, seed=seed, down_rounds=2, group_skip=skip, refresh=True,
+                             explicit_masks=presence if kind == 3 else None)
+    with binding.Moshpit(N, P, M, d, 1) as m:
+        m.bind_state(A)
+        m.sgd_round(t0, G, 0.05, masks[0])
+        for r in range(1, rounds):
+            m.refresh(t0 + r, seed, presence[r - 1], presence[r])
+            m.round(t0 + r, masks[r])
+        m.bind_state(B)
+        m.sgd_run(t0, rounds, G, 0.05, sched)
+        m.sync()
+    assert torch.equal(bufA, bufB)
