@@ -36,7 +36,7 @@ struct moshpit_ctx {
     int32_t *d_keys = nullptr;         // N
     void *d_grid = nullptr;            // tables of whole-grid passes (see queue_grid_plan): grid_cap bytes
     int64_t grid_cap = 0;
-    double *d_grid_partials = nullptr; // their distortion sums: grid_partials_cap doubles
+    void *d_grid_partials = nullptr;   // the distortion sums of one pass: grid_partials_cap bytes
     int64_t grid_partials_cap = 0;
     double *d_partials = nullptr;      // partials_cap doubles
     int64_t partials_cap = 0;
@@ -330,19 +330,27 @@ int queue_round(moshpit_ctx *h, int64_t t, const uint8_t *alive_dev, float prese
     return MOSHPIT_OK;
 }
 
-// Memory for the tables of `rounds` rounds and the flags of the peers.
-int reserve_grid_tables(moshpit_ctx *h, bool refresh, int64_t rounds)
+// Make a device buffer at least `need` bytes.  *fits = false when the device has no room for it,
+// which is no error: such a run goes round by round, without it.
+int grow_if_fits(moshpit_ctx *h, void **buffer, int64_t *cap, int64_t need, bool *fits)
 {
-    const int64_t need = rounds * grid_table_round_bytes(h->N, h->M, refresh) + h->N;
-    if (need <= h->grid_cap) return MOSHPIT_OK;
-    if (h->d_grid) {
+    *fits = true;
+    if (need <= *cap) return MOSHPIT_OK;
+    if (*buffer) {
         HIP_TRY(h, hipStreamSynchronize(h->stream));
-        HIP_TRY(h, hipFree(h->d_grid));
-        h->d_grid = nullptr;
-        h->grid_cap = 0;
+        HIP_TRY(h, hipFree(*buffer));
+        *buffer = nullptr;
+        *cap = 0;
     }
-    HIP_TRY(h, hipMalloc(&h->d_grid, static_cast<size_t>(need)));
-    h->grid_cap = need;
+    const hipError_t e = hipMalloc(buffer, static_cast<size_t>(need));
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        *buffer = nullptr;
+        *fits = false;
+        return MOSHPIT_OK;
+    }
+    HIP_TRY(h, e);
+    *cap = need;
     return MOSHPIT_OK;
 }
 
@@ -576,11 +584,29 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
     int rc = MOSHPIT_OK;
     GridTables tables{};
     int32_t tables_first = 0, tables_end = 0;                       // the rounds they hold now
-    const int64_t tables_most = grid_table_rounds(h->N, h->M, refresh, plan.max_rounds);
+    const int64_t entry_tiles = plan.tiles * plan.phases;           // partial sums of one distortion
+    const int32_t pass_most = grid_pass_rounds(plan.max_rounds, dist_out_host ? entry_tiles : 0);
+    const int64_t tables_most = grid_table_rounds(h->N, h->M, refresh, pass_most);
     const uint8_t *first_mask = nullptr;
+    {
+        bool fits = true;
+        if (failures && rounds > 0)
+            rc = grow_if_fits(h, &h->d_grid, &h->grid_cap,
+                              (rounds < tables_most ? rounds : tables_most) * grid_table_round_bytes(h->N, h->M, refresh) + h->N,
+                              &fits);
+        if (rc == MOSHPIT_OK && fits && dist_out_host)
+            rc = grow_if_fits(h, &h->d_grid_partials, &h->grid_partials_cap,
+                              ((rounds < pass_most ? rounds : pass_most) + 1) * entry_tiles * static_cast<int64_t>(sizeof(double)),
+                              &fits);
+        if (rc != MOSHPIT_OK || !fits) return rc;
+    }
+    double *partials = static_cast<double *>(h->d_grid_partials);
+    if (dist_out_host) {
+        rc = reserve_dist(h, static_cast<int64_t>(rounds) + 1);
+        if (rc != MOSHPIT_OK) return rc;
+    }
     if (failures && rounds > 0) {
-        rc = reserve_grid_tables(h, refresh, rounds < tables_most ? rounds : tables_most);
-        if (rc == MOSHPIT_OK && s->kind != MOSHPIT_SCHED_IID) {
+        if (s->kind != MOSHPIT_SCHED_IID) {
             moshpit_schedule presence = *s;                         // the masks before the group-skip filter
             presence.group_skip = 0;
             presence.refresh = 0;
@@ -589,32 +615,14 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
         if (rc == MOSHPIT_OK && step_first) rc = queue_first_mask(h, s, t0, &first_mask);
         if (rc != MOSHPIT_OK) return rc;
     }
-    const int64_t entry_tiles = plan.tiles * plan.phases;
-    if (dist_out_host) {
-        rc = reserve_dist(h, static_cast<int64_t>(rounds) + 1);
-        if (rc != MOSHPIT_OK) return rc;
-        const int64_t need = (static_cast<int64_t>(rounds) + 1) * entry_tiles;
-        if (need > h->grid_partials_cap) {
-            if (h->d_grid_partials) {
-                HIP_TRY(h, hipStreamSynchronize(h->stream));
-                HIP_TRY(h, hipFree(h->d_grid_partials));
-                h->d_grid_partials = nullptr;
-                h->grid_partials_cap = 0;
-            }
-            HIP_TRY(h, hipMalloc(reinterpret_cast<void **>(&h->d_grid_partials), static_cast<size_t>(need) * sizeof(double)));
-            h->grid_partials_cap = need;
-        }
-    }
     if (round_ms_out_host) {
         rc = reserve_events(h, 2 * static_cast<size_t>(rounds));
         if (rc != MOSHPIT_OK) return rc;
     }
     // with a local step the first entry (the distortion before it) is measured on its own
-    int32_t first_entry = 0;                                        // first entry the passes' partials hold
     if (dist_out_host && grad != nullptr) {
         rc = queue_dist(h, h->d_dist);
         if (rc != MOSHPIT_OK) return rc;
-        first_entry = 1;
     }
     std::vector<int32_t> pass_rounds;
     int32_t r = 0;
@@ -631,11 +639,10 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
             if (dist_out_host) {
                 rc = queue_dist(h, h->d_dist + 1);
                 if (rc != MOSHPIT_OK) return rc;
-                first_entry = 2;
             }
         } else {
             GridPlan p = plan;
-            now = rounds - r < p.max_rounds ? rounds - r : p.max_rounds;
+            now = rounds - r < pass_most ? rounds - r : pass_most;
             p.rounds = now;
             p.axis0 = static_cast<int32_t>((t0 + r) % h->d);
             if (failures && rounds > 0) {
@@ -662,18 +669,21 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
                 p.gamma = gamma;
             }
             if (dist_out_host) {
-                p.partials = h->d_grid_partials + static_cast<int64_t>(r) * entry_tiles;
+                p.partials = partials;
                 p.dist_before = r == 0 && grad == nullptr;
             }
             HIP_TRY(h, launch_grid_rounds(h->X, h->dtype, p, h->stream));
         }
         if (round_ms_out_host) HIP_TRY(h, hipEventRecord(h->events[2 * pass + 1], h->stream));
+        if (dist_out_host && !(step_first && r == 0)) {
+            // (summed before the next pass writes its own; entry 0 of a pass is the last of the one before it)
+            const int32_t skip = r == 0 && grad == nullptr ? 0 : 1;
+            HIP_TRY(h, launch_grid_dist(partials + skip * entry_tiles, entry_tiles, now + 1 - skip, h->N, h->d_dist + r + skip,
+                                        h->stream));
+        }
         r += now;
         pass_rounds.push_back(now);
     } while (r < rounds);
-    if (dist_out_host && first_entry <= rounds)
-        HIP_TRY(h, launch_grid_dist(h->d_grid_partials + first_entry * entry_tiles, entry_tiles, rounds + 1 - first_entry,
-                                    h->N, h->d_dist + first_entry, h->stream));
     *done = true;
     if (!dist_out_host && !round_ms_out_host) return MOSHPIT_OK;
     if (dist_out_host)

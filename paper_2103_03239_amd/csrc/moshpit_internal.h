@@ -227,7 +227,7 @@ struct GridPlan {
     const int32_t *copy_counts;      // [rounds]
     const char *grad;                // gradients (SGD) or nullptr
     int64_t grad_row_bytes;
-    double *partials;                // [rounds + 1][tiles * phases] or nullptr (no distortion wanted)
+    double *partials;                // [rounds + 1][tiles * phases], of this pass, or nullptr (no distortion wanted)
 };
 bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
                GridPlan *out);

@@ -26,4 +26,16 @@ inline int64_t grid_table_rounds(int64_t N, int32_t M, bool refresh, int64_t max
     return n < max_rounds ? max_rounds : n;
 }
 
+// A pass leaves one partial sum per tile for every distortion it computes; they are summed before
+// the next pass, so the buffer holds those of one pass, and a pass over a state so wide that they
+// would take more than 256 MiB takes fewer rounds.
+constexpr int64_t kGridPartialBytes = int64_t(256) << 20;
+
+inline int32_t grid_pass_rounds(int32_t max_rounds, int64_t entry_tiles)
+{
+    if (entry_tiles <= 0) return max_rounds;
+    const int64_t n = kGridPartialBytes / (8 * entry_tiles) - 1;
+    return n < 1 ? 1 : n < max_rounds ? static_cast<int32_t>(n) : max_rounds;
+}
+
 }  // namespace moshpit

@@ -231,3 +231,35 @@ def test_bf16_step_then_passes(kind, skip):
         m.sgd_run(t0, rounds, G, 0.05, sched)
         m.sync()
     assert torch.equal(bufA, bufB)
+
+
+def test_scratch_of_a_curve_does_not_grow_with_its_rounds():
+    """600 distortions of a state of 256 MiB in 524,288 tiles: the sums of all rounds would take 2.5 GB,
+    those of a pass are held to 256 MiB (63 rounds).  Every entry against the same rounds asked for in other pieces."""
+    M, d, P, rounds = 2, 1, 1 << 25, 600
+    N = M ** d
+    print("scratch of a curve", flush=True)
+    A = torch.randn(N, P, device=DEV)
+    B = A.clone()
+    masks = orc.schedule_masks(1, 0.9, 8, 0, N, 0, rounds)      # (two peers, both present once in 100 rounds)
+    sched = binding.Schedule(kind=binding.SCHED_EXPLICIT, explicit_masks=masks)
+    with binding.Moshpit(N, P, M, d, 0) as m:
+        m.bind_state(A)
+        m.run(0, 1, None)                                        # (what any run allocates)
+        A.copy_(B)
+        m.sync()
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        dist, _ = m.run(0, rounds, sched, want_dist=True)
+        assert free - torch.cuda.mem_get_info()[0] <= (256 + 16) << 20         # (16 MiB: the other outputs and masks)
+        m.bind_state(B)
+        first, pieces = 0, []
+        for part in (1, 63, 64, 65, 200, 207):
+            some = binding.Schedule(kind=binding.SCHED_EXPLICIT, explicit_masks=masks[first: first + part])
+            piece, _ = m.run(first, part, some, want_dist=True)
+            pieces += list(piece if first == 0 else piece[1:])
+            first += part
+        assert first == rounds and torch.equal(A, B)
+        assert np.array_equal(dist, np.array(pieces))
+        want = m.dist_to_mean()
+    assert dist[0] > 0.0 and abs(dist[-1] - want) <= 1e-11 * dist[0]

@@ -30,6 +30,16 @@ int main()
                         ++bad;
                     }
                 }
+    // a pass with distortions: at least one round, and either its sums fit the buffer or it is one round
+    for (int64_t tiles = 1; tiles < (int64_t(1) << 31); tiles *= 3)
+        for (int most = 4; most <= 64; most += 12) {
+            const int n = grid_pass_rounds(most, tiles);
+            const bool fits = (n + 1) * tiles * 8 <= kGridPartialBytes;
+            if (n < 1 || n > most || (!fits && n != 1) || (fits && n < most && (n + 2) * tiles * 8 <= kGridPartialBytes)) {
+                std::printf("tiles=%lld most=%d: %d rounds\n", (long long)tiles, most, n);
+                ++bad;
+            }
+        }
     return bad;
 }
 """
@@ -48,6 +58,7 @@ def run_host(tmp_path, source):
 
 def test_tables_of_a_long_run_are_bounded_and_hold_whole_passes(tmp_path):
     """Whatever the grid, the tables take at most 16 MiB (or one pass), their indexes stay below
-    2^31 and the launch that fills them below 2^32 threads."""
+    2^31 and the launch that fills them below 2^32 threads; the distortion sums take at most 256 MiB
+    (or one round)."""
     out = run_host(tmp_path, SOURCE)
     assert out.returncode == 0, out.stdout
