@@ -601,9 +601,17 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
         if (rc != MOSHPIT_OK || !fits) return rc;
     }
     double *partials = static_cast<double *>(h->d_grid_partials);
+    std::vector<uint8_t> wanted;                                    // which distortions the caller gets
     if (dist_out_host) {
         rc = reserve_dist(h, static_cast<int64_t>(rounds) + 1);
         if (rc != MOSHPIT_OK) return rc;
+        // with MOSHPIT_RUN_FUSED those inside what the header documents as one pass are NaN: not computed
+        wanted.assign(static_cast<size_t>(rounds) + 1, 1);
+        for (int32_t q = 0; q < rounds;) {
+            const int32_t len = documented_pass(q, &fp) ? fp.rounds : 1;
+            for (int32_t k = 1; k < len; ++k) wanted[q + k] = 0;
+            q += len;
+        }
     }
     if (failures && rounds > 0) {
         if (s->kind != MOSHPIT_SCHED_IID) {
@@ -669,18 +677,15 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
                 p.gamma = gamma;
             }
             if (dist_out_host) {
-                p.partials = partials;
                 p.dist_before = r == 0 && grad == nullptr;
+                for (int32_t k = 0; k < now; ++k) p.dist_after |= static_cast<uint64_t>(wanted[r + k + 1]) << k;
+                if (p.dist_before || p.dist_after != 0) p.partials = partials;
             }
             HIP_TRY(h, launch_grid_rounds(h->X, h->dtype, p, h->stream));
+            // (summed before the next pass writes its own)
+            if (p.partials != nullptr) HIP_TRY(h, launch_grid_dist(p, h->d_dist + r, h->stream));
         }
         if (round_ms_out_host) HIP_TRY(h, hipEventRecord(h->events[2 * pass + 1], h->stream));
-        if (dist_out_host && !(step_first && r == 0)) {
-            // (summed before the next pass writes its own; entry 0 of a pass is the last of the one before it)
-            const int32_t skip = r == 0 && grad == nullptr ? 0 : 1;
-            HIP_TRY(h, launch_grid_dist(partials + skip * entry_tiles, entry_tiles, now + 1 - skip, h->N, h->d_dist + r + skip,
-                                        h->stream));
-        }
         r += now;
         pass_rounds.push_back(now);
     } while (r < rounds);
@@ -690,16 +695,9 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
         HIP_TRY(h, hipMemcpyAsync(dist_out_host, h->d_dist, sizeof(double) * (static_cast<size_t>(rounds) + 1),
                                   hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    if (dist_out_host) {
-        // with MOSHPIT_RUN_FUSED the entries inside what the header documents as one pass are NaN
-        int32_t q = 0;
-        while (q < rounds) {
-            int32_t len = 1;
-            if (documented_pass(q, &fp)) len = fp.rounds;
-            for (int32_t k = 1; k < len; ++k) dist_out_host[q + k] = std::nan("");
-            q += len;
-        }
-    }
+    if (dist_out_host)
+        for (int32_t q = 0; q <= rounds; ++q)
+            if (!wanted[q]) dist_out_host[q] = std::nan("");
     if (round_ms_out_host) {
         int32_t first = 0;
         for (size_t pass = 0; pass < pass_rounds.size(); ++pass) {

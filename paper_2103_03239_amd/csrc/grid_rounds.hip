@@ -376,7 +376,8 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
             }
             round(seg, axis, bitmaps + r * p.groups);
             lds_barrier();
-            if constexpr (DIST) distortion(seg, (r + 1) * tiles + w * PHASES + phase);
+            if constexpr (DIST)
+                if ((p.dist_after >> r) & 1u) distortion(seg, (r + 1) * tiles + w * PHASES + phase);
             axis = axis + 1 == p.d ? 0 : axis + 1;
         }
         if constexpr (PHASES == 2) {
@@ -416,11 +417,13 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
     }
 }
 
-// out[e] = (sum of partials[e][0 .. tiles)) / n, entry e = blockIdx.x, in a fixed order
+// out[e] = (sum of partials[e][0 .. tiles)) / n, entry e = blockIdx.x, in a fixed order, for the entries
+// that the pass computed
 __global__ __launch_bounds__(256) void grid_dist_kernel(const double *__restrict__ partials, int64_t tiles, double n,
-                                                        double *__restrict__ out)
+                                                        int32_t before, uint64_t after, double *__restrict__ out)
 {
     __shared__ double sh[256];
+    if (blockIdx.x == 0 ? before == 0 : ((after >> (blockIdx.x - 1)) & 1u) == 0) return;
     const double *mine = partials + blockIdx.x * tiles;
     double acc = 0.0;
     for (int64_t k = threadIdx.x; k < tiles; k += 256) acc += mine[k];
@@ -716,11 +719,10 @@ hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_grid_dist(const double *partials, int64_t tiles, int32_t entries, int64_t N, double *out,
-                            hipStream_t stream)
+hipError_t launch_grid_dist(const GridPlan &p, double *out, hipStream_t stream)
 {
-    grid_dist_kernel<<<dim3(static_cast<uint32_t>(entries)), dim3(256), 0, stream>>>(partials, tiles,
-                                                                                    static_cast<double>(N), out);
+    grid_dist_kernel<<<dim3(static_cast<uint32_t>(p.rounds + 1)), dim3(256), 0, stream>>>(
+        p.partials, p.tiles * p.phases, static_cast<double>(p.N), p.dist_before, p.dist_after, out);
     return hipGetLastError();
 }
 

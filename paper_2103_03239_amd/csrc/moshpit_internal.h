@@ -228,12 +228,13 @@ struct GridPlan {
     const char *grad;                // gradients (SGD) or nullptr
     int64_t grad_row_bytes;
     double *partials;                // [rounds + 1][tiles * phases], of this pass, or nullptr (no distortion wanted)
+    uint64_t dist_after;             // bit r: the distortion after round r of the pass is wanted
 };
 bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
                GridPlan *out);
 hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStream_t stream);
-hipError_t launch_grid_dist(const double *partials, int64_t tiles, int32_t entries, int64_t N, double *out,
-                            hipStream_t stream);
+// The pass's distortions that were wanted, out[0] = before it .. out[rounds] = after its last round.
+hipError_t launch_grid_dist(const GridPlan &plan, double *out, hipStream_t stream);
 
 // Tables of rounds t0 .. t0+rounds-1 of a run under a failure schedule, for the kernel above.
 struct GridSchedule {

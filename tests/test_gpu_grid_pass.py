@@ -263,3 +263,34 @@ def test_scratch_of_a_curve_does_not_grow_with_its_rounds():
         assert np.array_equal(dist, np.array(pieces))
         want = m.dist_to_mean()
     assert dist[0] > 0.0 and abs(dist[-1] - want) <= 1e-11 * dist[0]
+
+
+def test_fused_curve_computes_only_what_it_returns():
+    """Ten rounds under RUN_FUSED return the first and the last distortion: the run must cost no more
+    than the rounds and two distortions on their own (a quarter allowed for the spread of timings;
+    computing all eleven takes half as long again)."""
+    import time
+    M, d, P, rounds = 16, 2, 1_048_576, 10
+    print("cost of a fused curve", flush=True)
+    X = torch.randn(M ** d, P, device=DEV)
+    sched = binding.Schedule(kind=binding.SCHED_IID, p=0.05, seed=3)
+
+    def fastest(call):
+        best = 1e9
+        for _ in range(8):
+            m.sync()
+            start = time.perf_counter()
+            call()
+            m.sync()
+            best = min(best, time.perf_counter() - start)
+        return best
+
+    with binding.Moshpit(M ** d, P, M, d, 0) as m:
+        m.bind_state(X)
+        dist, _ = m.run(0, rounds, sched, want_dist=True, flags=binding.RUN_FUSED)
+        assert not np.isnan(dist[[0, -1]]).any() and np.isnan(dist[1:-1]).all()
+        curve = fastest(lambda: m.run(0, rounds, sched, want_dist=True, flags=binding.RUN_FUSED))
+        plain = fastest(lambda: m.run(0, rounds, sched, flags=binding.RUN_FUSED))
+        alone = fastest(m.dist_to_mean)
+    print(f"  curve {1e6 * curve:.0f} us, rounds {1e6 * plain:.0f}, a distortion {1e6 * alone:.0f}", flush=True)
+    assert curve <= 1.25 * (plain + 2 * alone)
