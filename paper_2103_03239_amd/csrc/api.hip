@@ -322,6 +322,17 @@ float present_fraction(const moshpit_schedule *s)
     return static_cast<float>(1.0 - s->p);
 }
 
+// The same in the detail that the choice between passes and single rounds looks at.
+Participation participation(const moshpit_schedule *s, int64_t N, int32_t M, int32_t d, int64_t t0, int32_t rounds)
+{
+    if (!s || s->kind == MOSHPIT_SCHED_NONE) return Participation{};
+    const bool skip = s->group_skip != 0;
+    if (s->kind == MOSHPIT_SCHED_EXPLICIT) return sampled_presence(s->explicit_masks, rounds, N, M, d, t0, skip);
+    // a peer that stays away for several rounds is present between two absences for 1/p draws
+    const double away = s->kind == MOSHPIT_SCHED_REJOIN ? s->p * (s->down_rounds - 1) : 0.0;
+    return independent_presence((1.0 - s->p) / (1.0 + away), M, skip);
+}
+
 int queue_round(moshpit_ctx *h, int64_t t, const uint8_t *alive_dev, float present = -1.f)
 {
     RoundGeom geom{h->N, h->M, axis_stride(h, t)};
@@ -551,8 +562,8 @@ int moshpit_round_dev(moshpit_ctx *h, int64_t t, const uint8_t *alive_dev)
 }
 
 namespace {
-// Rounds t0 .. t0+rounds-1 in passes over the whole grid, when the shape allows it and a pass is
-// the better way: *done says whether the run has been queued (and waited for, with outputs).
+// Rounds t0 .. t0+rounds-1 in passes over the whole grid, when the shape allows it and passes are
+// the cheaper way: *done says whether the run has been queued (and waited for, with outputs).
 int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedule *s, int32_t flags,
                 double *dist_out_host, float *round_ms_out_host, const void *grad, int64_t grad_row_stride, float gamma,
                 bool *done)
@@ -580,6 +591,39 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
     const bool step_in_pass = grad != nullptr && (h->dtype == MOSHPIT_F32 || documented_pass(0, &fp));
     const bool step_first = grad != nullptr && !step_in_pass;
     if (step_first && rounds < 2) return MOSHPIT_OK;
+    if (rounds > 0) {
+        // both ways in microseconds (pass_rules.h); the cheaper one is taken
+        RunSize size;
+        size.N = h->N;
+        size.M = h->M;
+        size.element_bytes = h->dtype == MOSHPIT_F32 ? 4 : 2;
+        size.valid_bytes = plan.valid_bytes;
+        size.row_bytes = plan.row_bytes;
+        const Participation who = participation(s, h->N, h->M, h->d, t0, rounds);
+        const double single = single_round_us(size, who);
+        double by_rounds = 0.0;                                     // (masks and gradients cost either way the same)
+        int32_t distortions = 1;                                    // of the other way, and (fused) of a pass too
+        for (int32_t r = 0; r < rounds; ++distortions) {
+            const bool sub_grid = documented_pass(r, &fp);
+            by_rounds += sub_grid ? fused_pass_us(size, who, fp.rounds, fp.n_outer == 0, fp.blocks_per_cu) : single;
+            r += sub_grid ? fp.rounds : 1;
+            if (refresh && r < rounds) by_rounds += refresh_us(size);
+        }
+        GridTiles tiles;
+        tiles.row_bytes = plan.Wb;
+        tiles.parts = plan.phases;
+        tiles.threads = plan.threads;
+        tiles.lds_bytes = plan.tile_bytes + plan.N;
+        tiles.max_rounds = plan.max_rounds;
+        tiles.tiles = plan.tiles;
+        double by_passes = step_first ? single : 0.0;
+        by_passes += grid_passes_us(size, who, tiles, step_first ? rounds - 1 : rounds, dist_out_host ? distortions : 0);
+        if (dist_out_host) {
+            by_rounds += distortions * distortion_us(size);
+            if (grad != nullptr) by_passes += distortion_us(size);
+        }
+        if (by_rounds < by_passes) return MOSHPIT_OK;
+    }
 
     int rc = MOSHPIT_OK;
     GridTables tables{};

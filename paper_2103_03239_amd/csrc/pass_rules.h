@@ -1,6 +1,7 @@
 // Sizes and choices of multi-round passes: host arithmetic on plain numbers, without GPU types.
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 
 namespace moshpit {
@@ -36,6 +37,167 @@ inline int32_t grid_pass_rounds(int32_t max_rounds, int64_t entry_tiles)
     if (entry_tiles <= 0) return max_rounds;
     const int64_t n = kGridPartialBytes / (8 * entry_tiles) - 1;
     return n < 1 ? 1 : n < max_rounds ? static_cast<int32_t>(n) : max_rounds;
+}
+
+// ---- which way a run goes ---------------------------------------------------------------------
+//
+// On grids that whole-grid passes serve, a run can take one pass per max_rounds rounds (it reads
+// every row of the state and writes those that take part in some round of the pass), or the way
+// runs go elsewhere: round by round, a round touching only the rows of groups in which somebody
+// is averaged, or (MOSHPIT_RUN_FUSED) sub-grid passes, which touch the rows that take part in them.
+// Which is shorter depends on how many peers are away, on the number of rounds, and on the tile:
+// MI355X, times of the whole-grid pass against the other way,
+//   16 x 16 x 1,048,576 binary32:       2 rounds 408 us against 733 with everybody present, 401 : 597 with
+//                                       20 % absent, 260 : 166 with 90 %; 8 rounds, 90 %: 459 : 903
+//   32 x 32 x 4,194,304 binary32:       2 rounds, 50 %: 7.4 ms against 6.4; 8 rounds 9.3 : 25.3 ms; 8 rounds of
+//                                       group-skip at 20 % (hardly a group is whole): 5.1 : 2.5 ms
+//   16 x 16 x 16 x 262,144 bfloat16:    2 rounds, 20 %: 1.65 ms against 1.15; 4 rounds 1.87 : 2.29 ms;
+//                                       fused, 2 rounds: 1.65 : 0.86, 8 rounds: 2.2 : 3.2 ms
+//   3^7 x 131,072 binary32:             fused, 8 rounds, 20 %: 2.0 ms against 1.17 (tall tiles, narrow rows)
+// So both ways are priced and the cheaper one taken.  The figures below were fitted to 3,300 runs
+// on 46 grids of 16 to 4096 peers (rows of 0.1 KB to 64 MB, states of 50 KB to 4 GB; 2 to 10
+// rounds, 0 to 90 % absent; with and without curve, refresh, group-skip, local step and
+// MOSHPIT_RUN_FUSED) so that the choice comes out right: the way taken costs within 5 % of the
+// better one in 96 % of them and within 15 % in 98 %; half of the predicted times lie within 12 %
+// of the measured ones.  Times are in microseconds, sizes in megabytes (10^6 bytes).
+
+// Who takes part, as fractions: of the peers in a round, of the rows that lie in a group with an
+// average (`averaged`) and of the groups that have one.
+struct Participation {
+    double present = 1.0, averaged = 1.0, groups = 1.0;
+    bool failures = false, group_skip = false;
+    double ever_seen = -1.0;             // measured fraction of the peers that take part at some time; < 0: unknown
+    // of the peers that take part in some one of n rounds
+    double ever(double n) const
+    {
+        if (!failures) return 1.0;
+        const double e = 1.0 - pow(1.0 - (group_skip ? averaged : present), n);
+        return ever_seen >= 0.0 && ever_seen < e ? ever_seen : e;
+    }
+};
+
+// Peers present independently with probability q in groups of M.
+inline Participation independent_presence(double q, int32_t M, bool group_skip)
+{
+    Participation w;
+    w.failures = true;
+    w.group_skip = group_skip;
+    w.present = q;
+    if (group_skip) {
+        w.averaged = w.groups = pow(q, M);
+    } else {
+        const double others = pow(1.0 - q, M - 1);
+        w.averaged = q * (1.0 - others);
+        w.groups = 1.0 - (1.0 - q) * others - M * q * others;
+    }
+    return w;
+}
+
+// Masks given by the caller, [rounds][N] bytes: about 128 groups and 64 peers of them are looked at.
+inline Participation sampled_presence(const uint8_t *masks, int64_t rounds, int64_t N, int32_t M, int32_t d, int64_t t0,
+                                      bool group_skip)
+{
+    Participation w;
+    w.failures = true;
+    w.group_skip = group_skip;
+    const int64_t groups = N / M, all = groups * rounds, step = all / 128 > 0 ? (all / 128) | 1 : 1;
+    int64_t seen = 0, present = 0, averaged = 0, live = 0;
+    for (int64_t k = 0; k < all; k += step, ++seen) {
+        const int64_t r = k / groups, g = k % groups;
+        int64_t S = 1, on = 0;
+        for (int64_t q = 0; q < (t0 + r) % d; ++q) S *= M;
+        const uint8_t *first = masks + r * N + g / S * S * M + g % S;
+        for (int64_t j = 0; j < M; ++j) on += first[j * S] != 0 ? 1 : 0;
+        present += on;
+        if (on >= 2 && (!group_skip || on == M)) {
+            averaged += on;
+            ++live;
+        }
+    }
+    w.present = static_cast<double>(present) / static_cast<double>(seen * M);
+    w.averaged = static_cast<double>(averaged) / static_cast<double>(seen * M);
+    w.groups = static_cast<double>(live) / static_cast<double>(seen);
+    const int64_t peer_step = N / 64 > 0 ? N / 64 : 1, round_step = rounds / 64 > 0 ? rounds / 64 : 1;
+    int64_t peers = 0, ever = 0;
+    for (int64_t i = 0; i < N; i += peer_step, ++peers) {
+        bool on = false;
+        for (int64_t r = 0; r < rounds && !on; r += round_step) on = masks[r * N + i] != 0;
+        ever += on ? 1 : 0;
+    }
+    // (more rounds than were looked at can only add peers)
+    if (round_step == 1) w.ever_seen = static_cast<double>(ever) / static_cast<double>(peers);
+    return w;
+}
+
+struct RunSize {
+    int64_t N = 0, valid_bytes = 0, row_bytes = 0;
+    int32_t M = 0, element_bytes = 0;
+    double megabytes() const { return 1e-6 * static_cast<double>(N) * static_cast<double>(row_bytes); }
+    bool cached() const { return N * row_bytes <= (int64_t(256) << 20); }        // the last-level cache holds the state
+};
+
+// One round of the single-round kernel: a launch, a work item per KiB of a group's row (a wave that
+// finds nobody to average ends at once; one that does waits for its rows), and the traffic.
+inline double single_round_us(const RunSize &z, const Participation &w)
+{
+    const int32_t vectors = z.M <= 2 ? 4 : z.M > 4 && z.M <= 8 ? 2 : 1;      // KiB of a row per work item
+    const double items = 1e-3 * static_cast<double>(z.N / z.M) * static_cast<double>((z.valid_bytes + 1024 * vectors - 1) / (1024 * vectors));
+    const double dispatch = z.M <= 2 ? 0.47 : z.M <= 4 ? 0.22 : z.M <= 8 ? 0.63 : z.M <= 16 ? 0.44 : 0.72;
+    const double waits = z.M <= 4 ? 0.0 : z.M <= 8 ? 0.12 : z.M <= 16 ? 0.9 : 1.9;
+    const double us = items * (dispatch + waits * w.groups) + 2.0 * z.megabytes() * w.averaged * 0.14;
+    return 4.0 + us * (z.cached() ? 0.8 : 1.0);
+}
+
+// One sub-grid pass over `rounds` rounds.
+inline double fused_pass_us(const RunSize &z, const Participation &w, int32_t rounds, bool whole_grid, int32_t blocks_per_cu)
+{
+    const double bf16 = z.element_bytes == 2 ? 1.7 : 1.0, e = w.ever(rounds);
+    const double per_mb = blocks_per_cu == 2 ? 0.053 + 0.21 * e + bf16 * rounds * (0.03 + 0.031 * w.averaged)
+                                             : 0.11 + 0.38 * e + bf16 * rounds * 0.024;
+    const double cached = z.cached() && whole_grid && blocks_per_cu == 2 ? 0.77 : 1.0;
+    return 6.9 + 3.1 * rounds + z.megabytes() * cached * per_mb;
+}
+
+// A distortion on its own: the chain over the rows that a wave walks, and one read of the state.
+inline double distortion_us(const RunSize &z)
+{
+    return 21.0 + 0.098 * static_cast<double>(z.N < 1024 ? z.N : 1024) + 0.15 * z.megabytes();
+}
+
+// A refresh on its own: plan, and a copy whose launch is sized for the state.
+inline double refresh_us(const RunSize &z) { return 6.5 + 0.14 * z.megabytes(); }
+
+// Whole-grid passes over `rounds` rounds: the tiles' memory traffic by the bytes of a row in a tile
+// (narrow ones share cache lines and DRAM pages badly, rows left out of a write most of all), and
+// the rounds in LDS: every thread takes `items_per_thread` items a round, one after the other, on
+// as many blocks as share a compute unit.  The two hardly overlap.
+struct GridTiles {
+    int32_t row_bytes = 0, parts = 1, threads = 0, lds_bytes = 0, max_rounds = 1;
+    int64_t tiles = 0;
+};
+inline double grid_passes_us(const RunSize &z, const Participation &w, const GridTiles &t, int32_t rounds, int32_t distortions)
+{
+    const bool f32 = z.element_bytes == 4;
+    const int32_t split = z.M > 16 ? 4 : z.M > 8 && f32 ? 2 : 1;             // lanes that share an item
+    const double item_us = z.M > 16 ? 0.73 : z.M > 8 ? (f32 ? 0.69 : 1.2) : z.M > 4 ? (f32 ? 0.76 : 0.87) : z.M > 2 ? 0.48 : 0.22;
+    const int64_t items = z.N / z.M * (t.row_bytes / t.parts / (4 * z.element_bytes)) * split;
+    const double per_thread = static_cast<double>((items + t.threads - 1) / t.threads);
+    int64_t per_cu = 16 / (t.threads / 64);                                  // (16 waves: 128 registers each)
+    if (per_cu > 160 * 1024 / t.lds_bytes) per_cu = 160 * 1024 / t.lds_bytes;
+    if (per_cu < 1) per_cu = 1;
+    const double turns = static_cast<double>(t.tiles) / (256.0 * static_cast<double>(per_cu));
+    const double round_us = (turns > 1.0 ? turns : 1.0) * per_thread * item_us * (0.63 + 0.37 * w.groups) * t.parts;
+    const bool narrow = t.row_bytes <= 64;
+    const double read = t.row_bytes <= 32 ? 0.47 : narrow ? 0.36 : t.row_bytes <= 128 ? 0.25 : 0.17;
+    const double masked = t.row_bytes <= 32 ? 0.34 : narrow ? 0.25 : t.row_bytes <= 128 ? 0.12 : 0.13;
+    const double whole = t.row_bytes <= 32 ? 0.19 : narrow ? 0.17 : t.row_bytes <= 128 ? 0.13 : 0.11;
+    const double memory = z.megabytes() * (z.cached() ? (narrow ? 0.66 : 0.9) : 1.0);
+    double us = 0.0;
+    for (int32_t left = rounds; left > 0; left -= t.max_rounds) {
+        const int32_t n = left < t.max_rounds ? left : t.max_rounds;
+        us += 4.2 + 8.2 * static_cast<double>(z.N) / 4096.0 + memory * (read + (w.failures ? masked * w.ever(n) : whole)) + n * round_us;
+    }
+    return us + distortions * (6.3 + z.megabytes() * (t.parts == 1 ? 0.065 : 0.14) * (f32 ? 1.0 : 2.3));
 }
 
 }  // namespace moshpit

@@ -3,6 +3,8 @@ time through moshpit_round, bit for bit: every summation shape (groups of 2 to 3
 tiles in one and two column parts, row ends on every remainder of 16 bytes, rows that are not
 aligned, rows shorter than a tile; failures, refresh, group-skip and explicit masks, the
 distortion after every round, and the local step of Moshpit SGD."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -25,6 +27,18 @@ def state(N, P, stride, offset, dtype, seed, scale=1.0):
     view = buf[offset: offset + N * stride].view(N, stride)[:, :P]
     view.copy_(torch.randn(N, P, generator=gen, device=DEV) * scale + torch.arange(N, device=DEV)[:, None] % 7)
     return buf, view
+
+
+def fastest(m, call):
+    """Seconds of the fastest of 8 calls, each waited for."""
+    best = 1e9
+    for _ in range(8):
+        m.sync()
+        start = time.perf_counter()
+        call()
+        m.sync()
+        best = min(best, time.perf_counter() - start)
+    return best
 
 
 def cases():
@@ -269,28 +283,40 @@ def test_fused_curve_computes_only_what_it_returns():
     """Ten rounds under RUN_FUSED return the first and the last distortion: the run must cost no more
     than the rounds and two distortions on their own (a quarter allowed for the spread of timings;
     computing all eleven takes half as long again)."""
-    import time
     M, d, P, rounds = 16, 2, 1_048_576, 10
     print("cost of a fused curve", flush=True)
     X = torch.randn(M ** d, P, device=DEV)
     sched = binding.Schedule(kind=binding.SCHED_IID, p=0.05, seed=3)
-
-    def fastest(call):
-        best = 1e9
-        for _ in range(8):
-            m.sync()
-            start = time.perf_counter()
-            call()
-            m.sync()
-            best = min(best, time.perf_counter() - start)
-        return best
-
     with binding.Moshpit(M ** d, P, M, d, 0) as m:
         m.bind_state(X)
         dist, _ = m.run(0, rounds, sched, want_dist=True, flags=binding.RUN_FUSED)
         assert not np.isnan(dist[[0, -1]]).any() and np.isnan(dist[1:-1]).all()
-        curve = fastest(lambda: m.run(0, rounds, sched, want_dist=True, flags=binding.RUN_FUSED))
-        plain = fastest(lambda: m.run(0, rounds, sched, flags=binding.RUN_FUSED))
-        alone = fastest(m.dist_to_mean)
+        curve = fastest(m, lambda: m.run(0, rounds, sched, want_dist=True, flags=binding.RUN_FUSED))
+        plain = fastest(m, lambda: m.run(0, rounds, sched, flags=binding.RUN_FUSED))
+        alone = fastest(m, m.dist_to_mean)
     print(f"  curve {1e6 * curve:.0f} us, rounds {1e6 * plain:.0f}, a distortion {1e6 * alone:.0f}", flush=True)
     assert curve <= 1.25 * (plain + 2 * alone)
+
+
+@pytest.mark.parametrize("M,d,P,dtype,rounds,p,skip", [(16, 3, 262_144, 1, 2, 0.2, False), (32, 2, 524_288, 0, 8, 0.2, True),
+                                                       (16, 2, 1_048_576, 0, 2, 0.9, False), (7, 4, 131_072, 1, 2, 0.0, False)])
+def test_run_costs_no_more_than_its_rounds_one_by_one(M, d, P, dtype, rounds, p, skip):
+    """Runs that whole-grid passes would take 1.4 to 2 times as long for: few rounds on tall grids, hardly
+    anybody averaged.  (A quarter and a launch allowed for the spread of timings.)"""
+    print(f"cost of a run M={M} d={d} rounds={rounds} p={p} skip={skip}", flush=True)
+    X = torch.randn(M ** d, P, device=DEV).to(TD[dtype])
+    sched = binding.Schedule(kind=binding.SCHED_IID, p=p, seed=3, group_skip=skip) if p > 0 else None
+    masks = orc.schedule_masks(1, p, 3, 0, M ** d, 0, rounds) if p > 0 else None
+    if skip:
+        masks = np.stack([orc.skip_filter(M ** d, M, d, t, masks[t]) for t in range(rounds)])
+
+    def one_by_one():
+        for t in range(rounds):
+            m.round(t, None if masks is None else masks[t])
+
+    with binding.Moshpit(M ** d, P, M, d, dtype) as m:
+        m.bind_state(X)
+        run = fastest(m, lambda: m.run(0, rounds, sched))
+        alone = fastest(m, one_by_one)
+    print(f"  run {1e6 * run:.0f} us, its rounds {1e6 * alone:.0f}", flush=True)
+    assert run <= 1.25 * alone + 20e-6
