@@ -11,9 +11,16 @@
 //
 // Mapping.  A block owns a tile of 64 vectors (one 128-bit vector per lane,
 // 1 KiB per row); its W waves (W chosen so that a wave sees about 256 rows) take
-// rows w, w+W, ... with 8 non-temporal row loads in flight each, then combine their per-column sums through LDS, reduce across lanes
-// and write ONE partial per block.  A second one-block kernel adds the partials
-// in a fixed order, so the result does not depend on scheduling.
+// rows w, w+W, ... with 8 (bfloat16: 4) non-temporal row loads in flight each, then
+// combine their per-column sums through LDS, reduce across lanes and write ONE
+// partial per block.  A second one-block kernel adds the partials in a fixed
+// order, so the result does not depend on scheduling.
+//
+// What bounds it (MI355X).  Large states HBM: 1024 rows of 16 MiB at 6.8 TB/s.
+// Short rows the walk of a wave over its 256 rows: 1024 rows of 15,625 binary32,
+// 64 MB in 62 blocks, 67 us.  That walk took 146 us while every load stood behind
+// a branch of its own, which made the compiler wait for it before the next; rows
+// off the 16-byte boundaries, element by element in four times as many blocks, 71.
 #include <mutex>
 
 #include "moshpit_internal.h"
@@ -34,7 +41,6 @@ std::mutex g_scratch_mutex;
 double *g_scratch_ptr[kMaxDevices] = {};     // device address of `scratch`, per device
 
 constexpr int kMaxWaves = 16;      // waves per block: 1, 2, 4, 8 or 16
-constexpr int kRowsInFlight = 8;   // row loads issued before the first use
 
 template <int DT, int VE> struct Wide;
 
@@ -97,28 +103,32 @@ __global__ __launch_bounds__(kWaves * 64) void dist_partial_kernel(const char *_
     const int wave = threadIdx.x >> 6;
     const int64_t v = static_cast<int64_t>(blockIdx.x) * 64 + lane;
     constexpr int64_t kVec = sizeof(mem_t);
-    const bool valid = v * kVec < valid_bytes;
+    const bool valid = v * kVec < valid_bytes;            // (a lane past the row reads its last vector, for nothing)
     const int64_t at = v * kVec < valid_bytes - kVec ? v * kVec : valid_bytes - kVec;
     const int shared = static_cast<int>((v * kVec - at) / (kVec / NE));      // elements that belong to the neighbour
     const char *col = X + at;
 
+    constexpr int kRowsInFlight = NE == 8 ? 4 : 8;           // (16 sums of 8 values leave registers for 4)
     double x0[NE], s1[NE], s2[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) { x0[e] = 0.0; s1[e] = 0.0; s2[e] = 0.0; }
-    if (valid) V::widen(load_vec<false, mem_t>(col + first * row_bytes), x0);
-
-    for (int64_t i0 = wave; i0 < N; i0 += kWaves * kRowsInFlight) {
-        mem_t buf[kRowsInFlight];
-        bool have[kRowsInFlight];
+    V::widen(load_vec<false, mem_t>(col + first * row_bytes), x0);
+    // The wave looks at 64 of its rows at a time, then takes those that count, kRowsInFlight of them at once.
+    // Where fewer are left the others are row `first`, whose difference is 0: without a branch around
+    // them all the loads are issued before the first is used.
+    for (int64_t i0 = __builtin_amdgcn_readfirstlane(wave); i0 < N; i0 += kWaves * 64) {
+        const int64_t mine = i0 + static_cast<int64_t>(lane) * kWaves;
+        uint64_t rows = __ballot(mine < N && (present == nullptr || present[mine] != 0));
+        while (rows != 0) {
+            mem_t buf[kRowsInFlight];
 #pragma unroll
-        for (int u = 0; u < kRowsInFlight; ++u) {
-            const int64_t i = i0 + static_cast<int64_t>(u) * kWaves;
-            have[u] = valid && i < N && (present == nullptr || present[i] != 0);
-            if (have[u]) buf[u] = load_vec<true, mem_t>(col + i * row_bytes);
-        }
+            for (int u = 0; u < kRowsInFlight; ++u) {
+                const int64_t i = rows != 0 ? i0 + static_cast<int64_t>(__builtin_ctzll(rows)) * kWaves : first;
+                rows &= rows - 1;
+                buf[u] = load_vec<true, mem_t>(col + i * row_bytes);
+            }
 #pragma unroll
-        for (int u = 0; u < kRowsInFlight; ++u) {
-            if (have[u]) {
+            for (int u = 0; u < kRowsInFlight; ++u) {
                 double x[NE];
                 V::widen(buf[u], x);
 #pragma unroll
