@@ -347,12 +347,17 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // bfloat16: 4.3 -> 5.2, 4 x 4 x 4 x 9,000,001: 4.7 -> 5.6).
     const double touched = static_cast<double>(geom.N) * row_bytes * (geom.grad != nullptr ? 2 : 1);
     const bool whole_lines = reinterpret_cast<uintptr_t>(X) % 128 == 0 && row_bytes % 128 == 0;
-    // (off the cache lines the rule holds a little longer: 12 x 12 peers x 630,769 binary32, 347 MiB,
-    // 5.7 -> 6.1 TB/s)
+    // (off the cache lines that holds longer: 12 x 12 peers x 630,769 binary32, 347 MiB, 5.7 -> 6.1 TB/s)
     const bool cached = touched <= (whole_lines ? 256.0 : 448.0) * (1 << 20);
+    // binary32 rows off the cache lines, of a state too large for the last-level cache: such rounds in
+    // which (nearly) every peer takes part, in groups of the grid, have rules of their own below
+    const bool full = (alive == nullptr && geom.bits == nullptr) || geom.present >= 0.97f;
+    const bool large_odd = !whole_lines && dtype == 0 && touched > 800.0 * (1 << 20);
+    const bool all_odd = large_odd && full && geom.index == nullptr && geom.grad == nullptr;
     // (the SGD step on groups of up to 8 rows streams so few rows at once that non-temporal accesses
-    // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms)
-    const bool lines_meet = !whole_lines && (geom.grad == nullptr || geom.M > 8);
+    // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms; so does a round of
+    // groups of 7 or 8 binary32 rows with everybody present: 8 x 8 x 7,812,501 731 against 769 us)
+    const bool lines_meet = !whole_lines && (geom.grad == nullptr || geom.M > 8) && !(all_odd && geom.M > 6 && geom.M <= 8);
     const bool nt = tune.nt >= 0 ? tune.nt != 0 : (cached ? whole_lines && touched <= 24.0 * (1 << 20) : !lines_meet);
     const int block = (tune.block == 64 || tune.block == 128 || tune.block == 256) ? tune.block : 64;
     // Block order (measured on MI355X over row sizes of 128 KiB .. 32 MiB, groups of 16 and of
@@ -365,10 +370,30 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     int order = tune.order;
     if (order < 0) {
         order = 0;
-        if (cached) {
-            order = geom.M > 8 ? 1 : 0;
+        // A list with room for part-filled groups, as chunk-index rounds give, ends in empty ones: dealt to the
+        // dies in eighths it would leave half of them idle (16 x 16 x 390,625 binary32 149 us, 224 in eighths).
+        const bool holes = geom.index != nullptr && geom.n_index > geom.N;
+        if (holes) {
+            order = 0;
+        } else if (cached) {
+            // In eighths from groups of more than 8 rows (16 x 16 x 62,501 binary32, 64 MB: 25.9 us in the plain
+            // order, 22.7 in eighths), except for states of up to 24 MiB, whose few work items would leave some
+            // dies waiting: 16 MB of 16 x 16 peers 11.3 and 15.2, of 32 x 32 8.3 and 15.4 (on whole cache
+            // lines 7.5 and 11.6); 32 MB of 16 x 16 15.4 and 13.9.  With gradients or a peer list that ends sooner;
+            // 6 to 10 MiB in groups of up to 16 rows off the cache lines are ahead in eighths (16 x 16 x 7,813 8.8 and 8.4).
+            const double state = static_cast<double>(geom.N) * row_bytes / (1 << 20);
+            const double plain = geom.grad == nullptr && geom.index == nullptr ? 24.0 : geom.M > 16 ? 18.0 : geom.grad != nullptr ? 14.0 : 6.0;
+            const bool ahead = geom.M <= 16 && !whole_lines && state > 6.0 && state <= 10.0;
+            order = geom.M > 8 && (state > plain || ahead) ? 1 : 0;
         } else if (!whole_lines) {
             order = geom.M > (geom.grad != nullptr ? 8 : 16) || (geom.M <= 4 && geom.bits != nullptr) ? 1 : 0;
+            // (2 rows with a host mask: 2^6 x 7,812,501 binary32 578 us in the plain order, 607 in eighths; up to
+            // 16 rows with gradients and a mask: 16 x 16 x 488,281 279 and 284, 12 x 12 x 1,736,111 531 and 549,
+            // but 16 x 16 x 976,563 with everybody 626 and 588, and twice that state is 6 % ahead in eighths)
+            const bool grads = geom.M <= 16 && geom.grad != nullptr && touched <= (full ? 1600.0 : 2200.0) * (1 << 20);
+            if (dtype == 0 && (geom.M == 2 || grads)) order = 0;
+            // (5 x 5 x 5 x 2,000,001 380 us in the plain order, 368 in eighths; 24 x 24 x 434,027 381 and 400)
+            if (all_odd && geom.M > 4) order = geom.M <= 6 ? 1 : 0;
         } else if (geom.index == nullptr) {
             const int64_t member_stride = geom.S * row_bytes;
             const int64_t MiB = 1 << 20;
@@ -395,7 +420,6 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         // (nearly) every peer takes part each wave has more loads in flight and fewer waves do
         // better (16 MiB rows in groups of 32: 3 waves 6.2 TB/s, 4 waves 5.8).
         if (wpc < 4) wpc = 4;
-        const bool full = (alive == nullptr && geom.bits == nullptr) || geom.present >= 0.97f;
         if (full && geom.grad == nullptr && geom.index == nullptr) wpc -= 1;
         if (rows == 16 && cols == 1 && geom.M <= 16) {
             if (geom.grad != nullptr) wpc = 5;
@@ -409,9 +433,15 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         if (cached) wpc = geom.M > 8 ? 12 : 16;
         else if (lines_meet && rows * cols <= 4) wpc = 16;
         else if (!whole_lines && dtype == 1 && geom.M > 8 && geom.M <= 16) wpc = 128 / rows;
+        else if (large_odd && geom.grad != nullptr && geom.M > 8 && geom.M <= 16) wpc = 5;
+        // (8 x 8 x 3,906,251 371 us with 3 waves; 16 x 16 x 976,563 5 waves 405, 3 waves 384; 5 x 5 x 5 x
+        // 2,000,001 8 waves in eighths 368, 12 waves 376)
+        else if (all_odd && geom.M > 4) wpc = geom.M <= 6 ? 8 : 3;
         // a wave whose mask came with its arguments starts loading sooner: fewer do (8 x 8 peers x
         // 12,000,007 binary32: 3 waves 5.3 TB/s, 4 waves 5.0; 16 x 16 x 2,000,001: 5.3 and 4.9)
         else if (!whole_lines && dtype == 0 && geom.bits != nullptr && geom.M > 4 && geom.M <= 16) wpc = 52 / kib_per_wave;
+        // (a mask in device memory: 16 x 16 x 16 x 61,035 5 waves 344, 7 waves 358 us)
+        else if (large_odd && geom.grad == nullptr && geom.index == nullptr && geom.M > 8) wpc = 5;
         if (wpc > 32) wpc = 32;
     }
 
