@@ -891,9 +891,11 @@ int moshpit_dist_to_mean_static(const void *state_dev, int64_t N, int64_t P, int
         return fail(nullptr, MOSHPIT_EINVAL, "state pointer is not aligned to the element size");
     if (reinterpret_cast<uintptr_t>(out_dev) % sizeof(double) != 0)
         return fail(nullptr, MOSHPIT_EINVAL, "output pointer is not aligned to 8 bytes");
-    // (one partial sum per 64 elements is reserved where rows are not 16-byte aligned)
+    // (the limit is the contract, not what the kernel takes today: a partial sum per 64 vectors of a row
+    // and one for the elements after them, or one per 64 elements where rows are not 16-byte aligned)
     const bool aligned = reinterpret_cast<uintptr_t>(state_dev) % 16 == 0 && (row_stride_elems * esize) % 16 == 0;
-    const int64_t need = aligned ? dist_partials_count(dtype, P) : (P + 63) / 64;
+    const int64_t vec = 16 / esize;
+    const int64_t need = aligned ? (P / vec + 63) / 64 + (P % vec != 0 ? 1 : 0) : (P + 63) / 64;
     if (need > kStaticPartials)
         return fail(nullptr, MOSHPIT_EINVAL,
                     "rows of %lld elements need %lld partial sums, the static scratch holds %lld "

@@ -49,6 +49,20 @@ def test_create_rejects_bad_shapes_without_a_gpu():
         binding.Moshpit(15, 8, 4, 2, 0)
 
 
+@pytest.mark.parametrize("dtype,esize", [(0, 4), (1, 2)])
+def test_static_distortion_refuses_what_its_scratch_is_not_made_for(dtype, esize):
+    """2^17 partial sums: one per 64 vectors and one for what is left of an aligned row, one per 64
+    elements of any other."""
+    lib = binding.load_library()
+    most = 2 ** 17 * 64
+    vec = 16 // esize
+    whole = most * vec
+    for P, stride, start in ((whole - 1, whole, 4096), (whole - 63 * vec + 1, whole, 4096), (whole + vec, whole + vec, 4096),
+                             (most + 1, most + 1, 4096), (most + vec, most + vec, 4096 + esize)):
+        rc = lib.moshpit_dist_to_mean_static(start, 4, P, stride, dtype, None, 8192)
+        assert rc == -1 and b"static scratch" in lib.moshpit_last_error(None), (P, stride, start)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The benchmark measures one GPU's share; asking for more ends with a message, not a run."""
     import subprocess
