@@ -1,6 +1,8 @@
 """The one-launch random orders (up to 4096 peers) against the oracle: permutations, chunk-index
 keys over many rounds with failures (keys with more than M and with no members), and rounds in
 random groups with a mask."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -39,3 +41,47 @@ def test_permutation_and_keys(M, d):
         m.sync()
     # 9 rounds of at most 7 additions in a row (trees of 16, four of them) and a division, each within 2^-24
     assert_state_close(X.cpu().double().numpy(), ref, 9 * 8 * 2.0 ** -24, f"small order {M}^{d}")
+
+
+@pytest.mark.parametrize("M,d", [(16, 2), (8, 3), (64, 2)])
+def test_keys_that_have_come_together(M, d):
+    """Rounds in which every peer is alone in its group leave it chunk 0, until all peers share one key:
+    the next order ranks them all in one bucket, at about the price of any other."""
+    N, P, seed = M ** d, 4, 40 + M
+    print(f"keys together M={M} d={d}", flush=True)
+    r = np.random.default_rng(M)
+    X = torch.rand(N, P, device=DEV) + 1.0
+    ref = X.cpu().double().numpy().copy()
+    keys = orc.dynamic_init(N, M, d)
+    took = []
+    with binding.Moshpit(N, P, M, d, binding.F32) as m:
+        m.bind_state(X)
+
+        def one_round(t, alive):
+            m.sync()
+            start = time.perf_counter()
+            m.dynamic_round(t, seed, alive)
+            m.sync()
+            took.append(time.perf_counter() - start)
+            orc.dynamic_round(ref, M, d, keys, seed, t, alive)
+            assert np.array_equal(m.dynamic_keys(), np.asarray(keys).reshape(N, -1)), t
+
+        t = 0
+        while np.any(keys):
+            flat = np.asarray(keys).reshape(N, -1) @ (M ** np.arange(d - 1))
+            alive = np.zeros(N, dtype=np.uint8)
+            alive[[r.choice(np.flatnonzero(flat == k)) for k in np.unique(flat[flat != 0])]] = 1
+            one_round(t, alive)
+            t += 1
+        half = (r.random(N) < 0.5).astype(np.uint8)
+        one_round(t, half)                                          # half of one bucket, then the other half
+        one_round(t + 1, 1 - half)
+        crowded = min(took[-2:])
+        for k in (2, 3):
+            one_round(t + k, None)
+        apart = min(took[-2:])
+    print(f"  {1e6 * crowded:.0f} us a round, {1e6 * apart:.0f} with keys apart", flush=True)
+    # counting one bucket of 2048 took 240 us more
+    assert crowded <= apart + 100e-6
+    # at most 7 additions in a row and a division in the four rounds that average anything, each within 2^-24
+    assert_state_close(X.cpu().double().numpy(), ref, 4 * 8 * 2.0 ** -24, f"keys together {M}^{d}")
