@@ -719,6 +719,9 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
                 p.grad = static_cast<const char *>(grad);
                 p.grad_row_bytes = grad_row_stride * (h->dtype == MOSHPIT_F32 ? 4 : 2);
                 p.gamma = gamma;
+                // A single round adds a group's rows to +0, also the one row of a peer that is alone in its
+                // group, which turns -0 into +0; a documented pass leaves that row as its step made it.
+                p.step_zero = documented_pass(0, &fp) ? -0.f : 0.f;
             }
             if (dist_out_host) {
                 p.dist_before = r == 0 && grad == nullptr;

@@ -331,8 +331,12 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
                 const int32_t idx = t_ + (b0 + b) * T;
-                if (slot_valid(cur, idx) && (flags[idx >> full_shift] & 2))
+                if (slot_valid(cur, idx) && (flags[idx >> full_shift] & 2)) {
                     pre[b0 + b] = local_step<DT>(pre[b0 + b], g[b], p.gamma);
+                    if constexpr (DT == 0)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) pre[b0 + b][e] = __float_as_uint(__uint_as_float(pre[b0 + b][e]) + p.step_zero);
+                }
             }
         }
     }

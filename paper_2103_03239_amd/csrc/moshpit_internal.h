@@ -221,6 +221,7 @@ struct GridPlan {
     int32_t rounds;
     int32_t dist_before, refresh_first;   // distortion before the first round; refresh before it
     float gamma;
+    float step_zero;                 // added to the result of a binary32 step: +0 or -0
     const uint32_t *bitmaps;         // [rounds][groups], device; nullptr = everybody takes part
     const uint8_t *flags;            // [N], device: bit 0 written back, bit 1 takes the local step; nullptr = 3
     const uint32_t *copies;          // [rounds][N] pairs donor << 16 | returning peer; nullptr = no refresh

@@ -133,6 +133,35 @@ def test_sgd_pass_equals_step_and_rounds(M, d, P, pad, gpad):
     assert np.isfinite(dist if dist is not None else 0.0).all() and ref >= 0.0
 
 
+@pytest.mark.parametrize("P,flags,sign", [(1_000, 0, 0), (999, binding.RUN_FUSED, 0), (1_000, binding.RUN_FUSED, -2 ** 31)])
+def test_sgd_pass_zero_of_a_peer_alone_in_its_group(P, flags, sign):
+    """Peers whose row and gradient are zero end their step at -0.  A round adds the rows of a group to
+    +0, also a single one; a fused pass (16-byte-aligned rows) leaves a peer that is alone as it is."""
+    M, d, rounds = 4, 3, 3
+    N = M ** d
+    print(f"sgd pass, zero of a lone peer P={P} flags={flags}", flush=True)
+    masks = np.ones((rounds, N), dtype=np.uint8)
+    masks[0, [9, 10, 11]] = 0                             # peer 8 is alone in round 0, and absent then
+    masks[1:, 8] = 0
+    X = torch.randn(N, P, device=DEV)
+    X[[8, 20]] = -0.0                                     # (peer 20 has company)
+    G = torch.randn(N, P, device=DEV)
+    G[[8, 20]] = 0.0
+    A, B = X.clone(), X.clone()
+    with binding.Moshpit(N, P, M, d, 0) as m:
+        m.bind_state(A)
+        m.sgd_round(0, G, 0.05, masks[0])
+        for r in range(1, rounds):
+            m.round(r, masks[r])
+        m.bind_state(B)
+        m.sgd_run(0, rounds, G, 0.05, binding.Schedule(kind=binding.SCHED_EXPLICIT, explicit_masks=masks), flags=flags)
+        m.sync()
+    A, B = A.view(torch.int32), B.view(torch.int32)
+    assert bool((A[8] == 0).all()) and bool((B[8] == sign).all())
+    A[8] = B[8]
+    assert torch.equal(A, B)
+
+
 @pytest.mark.parametrize("dtype", [0, 1])
 def test_distortion_of_a_converged_state_with_an_outlier_first_row(dtype):
     """Row 0 (which the sums are shifted by) far from everybody else, rounds that nobody takes part in."""
