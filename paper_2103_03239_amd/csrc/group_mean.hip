@@ -66,20 +66,16 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
     const int lane = threadIdx.x & 63;
     const int kBlock = blockDim.x;
     constexpr int64_t kVec = sizeof(mem_t);
-    const int64_t nvec = (valid_bytes + kVec - 1) / kVec;
-    // the ragged last vector would be a work item of its own
-    const bool lone_last = valid_bytes % kVec != 0 && tiles > 1 && nvec == (tiles - 1) * kBlock * COLS + 1;
-
     // order 1: blocks b, b + 8, b + 16, ... (they run on the same one of the 8 dies) take
     // consecutive work items: each die streams through an eighth of the list.  The eighths are
-    // rounded up, so there are 8 * per places and the last ones may hold no item.
-    const int64_t per = (work_items + 7) >> 3;
-    const int64_t places = order == 1 ? 8 * per : work_items;
-    for (int64_t w0 = blockIdx.x; w0 < places; w0 += gridDim.x) {
+    // rounded up, so there are 8 * per places, a block for each, and the last ones may hold no item.
+    int64_t w0 = blockIdx.x;
+    do {
         int64_t w = w0;
         if (order == 1) {
+            const int64_t per = (work_items + 7) >> 3;
             w = (w0 & 7) * per + (w0 >> 3);
-            if (w >= work_items) continue;
+            if (w >= work_items) break;
         }
         const int64_t g = w / tiles;
         const int64_t tile = w - g * tiles;
@@ -106,8 +102,13 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
         const int cnt = __popcll(live);
         if (cnt < (SGD ? 1 : 2)) continue;           // nothing to do: rows stay as they are
 
+        // (only now: a work item of an empty group ends as soon as its mask is known)
+        int64_t bytes = valid_bytes;
+        asm volatile("" : "+s"(bytes));
+        const int64_t nvec = (bytes + kVec - 1) / kVec;
         int64_t v0 = tile * (static_cast<int64_t>(kBlock) * COLS) + threadIdx.x, v_end = nvec;
-        if (lone_last) {
+        // the ragged last vector would be a work item of its own
+        if (bytes % kVec != 0 && tiles > 1 && nvec == (tiles - 1) * kBlock * COLS + 1) {
             if (tile == tiles - 1) v0 -= 1;
             else if (tile == tiles - 2) v_end -= 2;
         }
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
             for (int c = 0; c < COLS; ++c)
                 if (in_row[c]) store_vec<NT, mem_t>(dst + at[c], mean[c]);
         }
-    }
+    } while ((w0 += gridDim.x) < work_items);
 }
 
 // The kernel uses no LDS.  The dynamic-LDS size of the launch is only a
