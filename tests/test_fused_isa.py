@@ -17,8 +17,10 @@ library's flags and checks every instantiation:
 The expected counts follow from the kernel's constant kPrefetch, read from the
 source.  A toolchain change that breaks any of this fails here (also when hipcc is
 missing: the check must not be skipped silently); behind it, the GPU tests that
-compare fused passes with single rounds bit for bit are the gate for any compiler
-change.
+compare this kernel's passes with single rounds bit for bit are the gate for any
+compiler change: test_sub_grid_passes_equal_single_rounds,
+test_whole_grid_in_a_persistent_pass and the grids of more than 4096 peers of
+test_fused_division_edge_values and test_many_peers_single_and_fused.
 """
 import os
 import re

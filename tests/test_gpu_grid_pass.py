@@ -218,6 +218,66 @@ def test_zero_rounds_with_both_outputs_on_a_fresh_handle(flags):
     assert abs(dist[0] - want) <= 4 * N * N * 2.0 ** -53 * want
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("M,d,P,rounds", [(16, 3, 24, 30), (2, 11, 8, 15), (8, 4, 16, 25), (4, 2, 504, 130), (32, 2, 40, 131)])
+def test_run_of_several_passes(M, d, P, rounds, dtype):
+    """More rounds than one pass takes (11 to 64), and not a multiple of the axes: plain, with refresh,
+    group-skip and both, and as an iteration of Moshpit SGD, each against its rounds one at a time; and
+    the curve.  Few peers take part, and in long runs only next to the rounds where a pass can end, so that
+    the state differs from peer to peer to the end."""
+    N, t0, seed = M ** d, 1, 33
+    print(f"several passes M={M} d={d} P={P} rounds={rounds} dtype={dtype}", flush=True)
+    rng = np.random.default_rng(rounds)
+    masks = (rng.random((rounds, N)) < 0.12).astype(np.uint8)
+    for r in range(rounds):
+        if rounds > 64 and (r + 2) % 64 > 3:
+            masks[r] = 0
+        if r not in (0, 14, 64):
+            continue
+        S = M ** ((t0 + r) % d)                            # a whole group, for group-skip
+        g = int(rng.integers(N // M))
+        masks[r, (g // S) * S * M + g % S + S * np.arange(M)] = 1
+    _, X = state(N, P, P, 0, dtype, 6, 3.0)
+    _, G = state(N, P, P, 0, dtype, 7)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        for kind in ("plain", "refresh", "skip", "refresh skip", "sgd", "sgd refresh"):
+            refresh, skip = "refresh" in kind, "skip" in kind
+            live = [orc.skip_filter(N, M, d, t0 + r, masks[r]) if skip else masks[r] for r in range(rounds)]
+            A, B = X.clone(), X.clone()
+            m.bind_state(A)
+            want = [m.dist_to_mean()]
+            for r in range(rounds):
+                if refresh and r > 0:
+                    m.refresh(t0 + r, seed, masks[r - 1], masks[r])
+                if "sgd" in kind and r == 0 and (dtype == 0 or refresh):
+                    m.sgd_round(t0, G, 0.05, live[0])
+                else:
+                    if "sgd" in kind and r == 0:           # a fused bfloat16 pass rounds the step
+                        m.local_step(G, 0.05, live[0])
+                    m.round(t0 + r, live[r])
+                want.append(m.dist_to_mean())
+            sched = binding.Schedule(kind=binding.SCHED_EXPLICIT, seed=seed, refresh=refresh, group_skip=skip, explicit_masks=masks)
+            flags = binding.RUN_FUSED if kind == "sgd" else 0
+            m.bind_state(B)
+            dist = None
+            if "sgd" in kind:
+                dist, _ = m.sgd_run(t0, rounds, G, 0.05, sched, want_dist=True, flags=flags)
+            else:
+                dist, _ = m.run(t0, rounds, sched, want_dist=True)
+            assert torch.equal(A, B), kind
+            have = ~np.isnan(dist)
+            assert have[0] and have[-1] and (flags != 0 or have.all())
+            # binary64 sums in another order: a few ulp per value added, times how much of s2 cancels
+            assert np.abs(dist - np.array(want))[have].max() <= 1e-11 * max(want), kind
+            if "sgd" not in kind:
+                B.copy_(X)
+                m.run(t0, rounds, sched)                   # and without the distortion
+                m.sync()
+                assert torch.equal(A, B), kind
+            if not refresh:                                # (a refresh makes rows equal)
+                assert A.float().unique(dim=0).shape[0] > N // 4, kind
+
+
 @pytest.mark.parametrize("M,d,P,dtype,rounds,refresh", [(16, 3, 24, 1, 962, True), (2, 11, 8, 0, 4_104, False)])
 def test_run_longer_than_its_tables(M, d, P, dtype, rounds, refresh):
     """More rounds than the tables of a pass are built for at once.  Nobody is present until shortly

@@ -368,6 +368,12 @@ def test_bf16_rounding_of_the_kernels_is_round_to_nearest_even_everywhere():
 # fused multi-round passes
 # --------------------------------------------------------------------------
 
+def one_by_one(m, t0, rounds, masks):
+    """The rounds of a run through moshpit_round (masks: [rounds, N] or None)."""
+    for r in range(rounds):
+        m.round(t0 + r, None if masks is None else masks[r])
+
+
 FUSED = [
     # M, d, P, dtype, p, t0, rounds
     (4, 2, 65_536, 0, 0.0, 0, 2),        # workload 1: whole 4x4 grid in one tile
@@ -404,12 +410,17 @@ def test_fused_equals_single_rounds_and_oracle(M, d, P, dtype, p, t0, rounds):
     ref = to_f64(A).copy()
     masks = orc.schedule_masks(w.kind, w.p, w.mask_seed, w.down, N, t0, rounds)
     dist_ref = orc.run(ref, M, d, t0, rounds, masks, want_dist=True)
+    C = A.clone()
     with binding.Moshpit(N, P, M, d, dtype) as m:
         m.bind_state(A)
         dist_a, _ = m.run(t0, rounds, sched_of(w), want_dist=True)
         m.bind_state(B)
         dist_b, ms = m.run(t0, rounds, sched_of(w), want_dist=True, want_times=True, flags=binding.RUN_FUSED)
-    assert torch.equal(A, B), "fused pass differs from single rounds"
+        m.bind_state(C)
+        one_by_one(m, t0, rounds, masks)
+        m.sync()
+    assert torch.equal(A, C), "run differs from single rounds"
+    assert torch.equal(B, C), "fused run differs from single rounds"
     assert_state_close(to_f64(B), ref, TOL[dtype], w.name)
     have = ~np.isnan(dist_b)
     assert have[0] and have[-1]
@@ -420,11 +431,14 @@ def test_fused_equals_single_rounds_and_oracle(M, d, P, dtype, p, t0, rounds):
         assert (~have).any(), "expected at least one fused pass"
 
 
-@pytest.mark.parametrize("M,d,dtype", [(6, 2, 0), (12, 2, 0), (20, 2, 0), (10, 2, 1)])
+@pytest.mark.parametrize("M,d,dtype", [(6, 2, 0), (12, 2, 0), (20, 2, 0), (10, 2, 1), (3, 3, 0), (2, 7, 1),
+                                       (6, 5, 0), (12, 4, 0), (20, 3, 1), (10, 4, 1), (3, 8, 0)])
 def test_fused_division_edge_values(M, d, dtype):
-    """Sums that are tiny (quotient subnormal), zero, huge or infinite: the fused kernel
-    must give the bits of the single-round kernel, NaN for NaN."""
-    N, P, rounds = M ** d, 2_048, 4
+    """Sums that are tiny (quotient subnormal), zero, huge or infinite: runs in passes over the whole
+    grid (up to 4096 peers, M <= 32) and over sub-grids give the bits of the single-round kernel, NaN
+    for NaN."""
+    N, rounds = M ** d, 4
+    P = 2_048 if N <= 4_096 else 320
     say(f"fused division edge values M={M} d={d} dtype={dtype}")
     g = torch.Generator(device="cpu").manual_seed(4242 + M)
     kind = torch.randint(0, 6, (1, P), generator=g).expand(N, P)       # one kind of value per column
@@ -438,15 +452,20 @@ def test_fused_division_edge_values(M, d, dtype):
     x[(kind == 4) & (torch.rand(N, P, generator=g) < 0.01)] = float("inf")
     A = x.to(torch.bfloat16 if dtype else torch.float32).to(DEV).contiguous()
     B = A.clone()
+    C = A.clone()
     sched = binding.Schedule(kind=inputs.KIND_IID, p=0.2, seed=77 + M)
     with binding.Moshpit(N, P, M, d, dtype) as m:
         m.bind_state(A)
-        m.run(0, rounds, sched)
+        one_by_one(m, 0, rounds, orc.schedule_masks(inputs.KIND_IID, 0.2, 77 + M, 0, N, 0, rounds))
         m.bind_state(B)
-        m.run(0, rounds, sched, flags=binding.RUN_FUSED)      # whole grid in one tile: one fused pass
+        m.run(0, rounds, sched, flags=binding.RUN_FUSED)
+        m.bind_state(C)
+        m.run(0, rounds, sched)
+        m.sync()
     bits = torch.int16 if dtype else torch.int32
-    same = (A.view(bits) == B.view(bits)) | (torch.isnan(A) & torch.isnan(B))
-    assert bool(same.all()), f"{int((~same).sum())} elements differ in bits"
+    for X in (B, C):
+        same = (A.view(bits) == X.view(bits)) | (torch.isnan(A) & torch.isnan(X))
+        assert bool(same.all()), f"{int((~same).sum())} elements differ in bits"
     tiny = (A != 0) & (A.abs().float() < 2.0 ** -126)
     assert bool(tiny.any()) and bool(torch.isinf(A).any() | torch.isnan(A).any())
 
@@ -499,7 +518,7 @@ def test_fused_with_explicit_masks_and_dead_rounds():
     sched = binding.Schedule(kind=binding.SCHED_EXPLICIT, explicit_masks=masks)
     with binding.Moshpit(N, P, M, d, 0) as m:
         m.bind_state(A)
-        m.run(0, rounds, sched)
+        one_by_one(m, 0, rounds, masks)
         m.bind_state(B)
         dist, _ = m.run(0, rounds, sched, want_dist=True, flags=binding.RUN_FUSED)
     assert np.isnan(dist[1:-1]).all(), "expected one fused pass"
@@ -551,7 +570,14 @@ def test_random_shapes_single_and_fused(M, d, P, dtype, pad, p, t0, rounds, seed
         dist_a, _ = m.run(t0, rounds, sched_of(w), want_dist=True)
         m.bind_state(B)
         dist_b, _ = m.run(t0, rounds, sched_of(w), want_dist=True, flags=binding.RUN_FUSED)
-    assert torch.equal(bufA, bufB), "fused run differs from single rounds (or padding was touched)"
+        bufC = torch.full_like(bufA, 512.0)
+        C = bufC[: N * stride].view(N, stride)[:, :P]
+        C.copy_(inputs.make_state(w, DEV))
+        m.bind_state(C)
+        one_by_one(m, t0, rounds, masks if p > 0 else None)
+        m.sync()
+    assert torch.equal(bufA, bufC), "run differs from single rounds (or padding was touched)"
+    assert torch.equal(bufB, bufC), "fused run differs from single rounds (or padding was touched)"
     assert_state_close(to_f64(A), ref, TOL[dtype], w.name)
     have = ~np.isnan(dist_b)
     assert np.array_equal(dist_b[have], dist_a[have])
@@ -606,6 +632,80 @@ def test_many_peers_single_and_fused(M, d, P, dtype, p, t0, rounds):
         m.sync()
     assert torch.equal(A, B), "fused run differs from single rounds"
     assert_state_close(to_f64(A), ref, TOL[dtype], w.name)
+
+
+# Grids of more than 4096 peers, whose passes take planes of them
+PLANES = [(3, 8, 136), (6, 5, 72), (8, 5, 24), (12, 4, 40), (20, 3, 72), (17, 3, 24), (22, 3, 40), (2, 13, 72), (4, 7, 40), (16, 4, 8)]
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("M,d,P", PLANES)
+def test_sub_grid_passes_equal_single_rounds(M, d, P, dtype):
+    """Fused passes over planes, start on a later axis, with and without failures, and the local step
+    riding on the first: bit for bit the single rounds, and moshpit_local_step before them in bfloat16."""
+    N, rounds, t0 = M ** d, d + 3, d - 1
+    say(f"sub-grid passes M={M} d={d} P={P} dtype={dtype}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(P + M)
+    td = torch.bfloat16 if dtype else torch.float32
+    X = torch.randn(N, P, generator=gen, device=DEV).to(td)
+    G = torch.randn(N, P, generator=gen, device=DEV).to(td)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        for p in (0.0, 0.3):
+            masks = orc.schedule_masks(1, p, 5, 0, N, t0, rounds) if p > 0 else None
+            sched = binding.Schedule(kind=binding.SCHED_IID, p=p, seed=5) if p > 0 else None
+            for sgd in (False, True):
+                A, B = X.clone(), X.clone()
+                m.bind_state(A)
+                if sgd and dtype == 1:
+                    m.local_step(G, 0.05, None if masks is None else masks[0])
+                if sgd and dtype == 0:
+                    m.sgd_round(t0, G, 0.05, None if masks is None else masks[0])
+                    one_by_one(m, t0 + 1, rounds - 1, None if masks is None else masks[1:])
+                else:
+                    one_by_one(m, t0, rounds, masks)
+                m.bind_state(B)
+                if sgd:
+                    dist, _ = m.sgd_run(t0, rounds, G, 0.05, sched, want_dist=True, flags=binding.RUN_FUSED)
+                else:
+                    dist, _ = m.run(t0, rounds, sched, want_dist=True, flags=binding.RUN_FUSED)
+                assert np.isnan(dist[1]), "expected a fused pass"
+                assert torch.equal(A, B), (p, sgd)
+
+
+@pytest.mark.parametrize("M,d,P,dtype,p,rounds", [(24, 2, 262_144, 1, 0.2, 7), (16, 2, 1_048_576, 0, 0.9, 2)])
+def test_whole_grid_in_a_persistent_pass(M, d, P, dtype, p, rounds):
+    """Fused runs on a whole grid that go through the persistent kernel: 24 x 24 bfloat16 peers of more
+    than 256 MiB, and a run in which hardly anybody is averaged (where it is the cheaper pass)."""
+    N = M ** d
+    say(f"persistent pass M={M} d={d} P={P} dtype={dtype}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(P)
+    td = torch.bfloat16 if dtype else torch.float32
+    X = torch.randn(N, P, generator=gen, device=DEV).to(td)
+    G = torch.randn(N, P, generator=gen, device=DEV).to(td)
+    masks = orc.schedule_masks(1, p, 9, 0, N, 0, rounds)
+    sched = binding.Schedule(kind=binding.SCHED_IID, p=p, seed=9)
+    A, B = torch.empty_like(X), torch.empty_like(X)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        for sgd in (False, True):
+            A.copy_(X)
+            B.copy_(X)
+            m.bind_state(A)
+            if sgd and dtype == 1:
+                m.local_step(G, 0.05, masks[0])
+            if sgd and dtype == 0:
+                m.sgd_round(0, G, 0.05, masks[0])
+                one_by_one(m, 1, rounds - 1, masks[1:])
+            else:
+                one_by_one(m, 0, rounds, masks)
+            m.bind_state(B)
+            if sgd:
+                m.sgd_run(0, rounds, G, 0.05, sched, flags=binding.RUN_FUSED)
+            else:
+                m.run(0, rounds, sched, flags=binding.RUN_FUSED)
+            m.sync()
+            assert torch.equal(A, B), sgd
 
 
 # --------------------------------------------------------------------------
