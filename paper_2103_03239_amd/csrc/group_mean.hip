@@ -348,12 +348,16 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // bfloat16: 4.3 -> 5.2, 4 x 4 x 4 x 9,000,001: 4.7 -> 5.6).
     const double touched = static_cast<double>(geom.N) * row_bytes * (geom.grad != nullptr ? 2 : 1);
     const bool whole_lines = reinterpret_cast<uintptr_t>(X) % 128 == 0 && row_bytes % 128 == 0;
-    // (off the cache lines that holds longer: 12 x 12 peers x 630,769 binary32, 347 MiB, 5.7 -> 6.1 TB/s)
+    // (off the cache lines that holds longer: 12 x 12 peers x 630,769 binary32, 347 MiB, 5.7 -> 6.1 TB/s;
+    // at 381 MiB, everybody present, groups of 7 to 32 rows are within 3 % of what larger states take, 5 rows
+    // would gain 9 % from their rules)
     const bool cached = touched <= (whole_lines ? 256.0 : 448.0) * (1 << 20);
     // binary32 rows off the cache lines, of a state too large for the last-level cache: such rounds in
     // which (nearly) every peer takes part, in groups of the grid, have rules of their own below
     const bool full = (alive == nullptr && geom.bits == nullptr) || geom.present >= 0.97f;
-    const bool large_odd = !whole_lines && dtype == 0 && touched > 800.0 * (1 << 20);
+    // (more than 16 rows as soon as it is too large, 24 x 24 x 303,819, 668 MiB, everybody present 284 -> 266 us,
+    // 10 % absent 256 -> 247; fewer from 800 MiB on: 12 x 12 x 1,215,277, 668 MiB, 258 us by the general rules, 273)
+    const bool large_odd = !whole_lines && dtype == 0 && !cached && (geom.M > 16 || touched > 800.0 * (1 << 20));
     const bool all_odd = large_odd && full && geom.index == nullptr && geom.grad == nullptr;
     // (the SGD step on groups of up to 8 rows streams so few rows at once that non-temporal accesses
     // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms; so does a round of
@@ -387,14 +391,23 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
             const bool ahead = geom.M <= 16 && !whole_lines && state > 6.0 && state <= 10.0;
             order = geom.M > 8 && (state > plain || ahead) ? 1 : 0;
         } else if (!whole_lines) {
-            order = geom.M > (geom.grad != nullptr ? 8 : 16) || (geom.M <= 4 && geom.bits != nullptr) ? 1 : 0;
-            // (2 rows with a host mask: 2^6 x 7,812,501 binary32 578 us in the plain order, 607 in eighths; up to
-            // 16 rows with gradients and a mask: 16 x 16 x 488,281 279 and 284, 12 x 12 x 1,736,111 531 and 549,
-            // but 16 x 16 x 976,563 with everybody 626 and 588, and twice that state is 6 % ahead in eighths)
-            const bool grads = geom.M <= 16 && geom.grad != nullptr && touched <= (full ? 1600.0 : 2200.0) * (1 << 20);
-            if (dtype == 0 && (geom.M == 2 || grads)) order = 0;
-            // (5 x 5 x 5 x 2,000,001 380 us in the plain order, 368 in eighths; 24 x 24 x 434,027 381 and 400)
-            if (all_odd && geom.M > 4) order = geom.M <= 6 ? 1 : 0;
+            // With gradients from 9 rows on (16 x 16 x 976,563 binary32, everybody present: 626 us in the plain order,
+            // 588 in eighths), but up to 24 binary32 rows of less state, up to 16 with a mask until a little later, in
+            // the plain one (16 x 16 x 488,281 with a mask 279 and 284, 12 x 12 x 1,736,111 531 and 549, 24 x 24 x
+            // 303,819 385 and 398; twice that state is 6 % ahead in eighths).  Without gradients more than 16 binary32 rows (32 x 32 x 488,281 with a mask in device memory
+            // 758 us in the plain order, 720 in eighths; as bits 772 and 717; bfloat16 24 x 24 x 868,055 343 and 362)
+            // and 3 or 4 of them with a mask as bits (4 x 4 x 4 x 7,812,501 657 and 636; 2^6 x 7,812,501 578 and 607;
+            // bfloat16 4 x 4 x 4 x 7,812,501 333 and 352).
+            if (geom.grad != nullptr)
+                order = geom.M > 8 && (geom.M > 24 || dtype == 1 || touched > (full || geom.M > 16 ? 1600.0 : 2200.0) * (1 << 20)) ? 1 : 0;
+            else
+                order = dtype == 0 && (geom.M > 16 || (geom.M > 2 && geom.M <= 4 && geom.bits != nullptr)) ? 1 : 0;
+            // Everybody present: 5 x 5 x 5 x 2,000,001 380 us in the plain order, 368 in eighths; 17 and 18 rows (a
+            // chunk of 16 and a short one) 17 x 17 x 2,595,156 1244 and 1189; 24 x 24 x 1,302,084 1161 and 1217;
+            // 32 x 32 x 732,422 1323 and 1228, 64 x 64 x 91,553 662 and 610.  A mask in device memory: 20 x 20 x
+            // 937,501 528 and 575, 24 x 24 x 651,042 531 and 553, 28 x 28 x 478,317 567 and 553.
+            if (all_odd && geom.M > 4) order = geom.M <= 6 || geom.M == 17 || geom.M == 18 || geom.M > 28 ? 1 : 0;
+            else if (large_odd && geom.M > 16 && geom.M <= 24 && geom.grad == nullptr && geom.index == nullptr && geom.bits == nullptr) order = 0;
         } else if (geom.index == nullptr) {
             const int64_t member_stride = geom.S * row_bytes;
             const int64_t MiB = 1 << 20;
@@ -437,12 +450,12 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         else if (large_odd && geom.grad != nullptr && geom.M > 8 && geom.M <= 16) wpc = 5;
         // (8 x 8 x 3,906,251 371 us with 3 waves; 16 x 16 x 976,563 5 waves 405, 3 waves 384; 5 x 5 x 5 x
         // 2,000,001 8 waves in eighths 368, 12 waves 376)
-        else if (all_odd && geom.M > 4) wpc = geom.M <= 6 ? 8 : 3;
+        else if (all_odd && geom.M > 4 && geom.M <= 28) wpc = order == 0 ? 3 : 8;
         // a wave whose mask came with its arguments starts loading sooner: fewer do (8 x 8 peers x
         // 12,000,007 binary32: 3 waves 5.3 TB/s, 4 waves 5.0; 16 x 16 x 2,000,001: 5.3 and 4.9)
         else if (!whole_lines && dtype == 0 && geom.bits != nullptr && geom.M > 4 && geom.M <= 16) wpc = 52 / kib_per_wave;
         // (a mask in device memory: 16 x 16 x 16 x 61,035 5 waves 344, 7 waves 358 us)
-        else if (large_odd && geom.grad == nullptr && geom.index == nullptr && geom.M > 8) wpc = 5;
+        else if (large_odd && !all_odd && geom.grad == nullptr && geom.index == nullptr && geom.M > 8) wpc = 5;
         if (wpc > 32) wpc = 32;
     }
 
