@@ -622,7 +622,7 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
             by_rounds += distortions * distortion_us(size);
             if (grad != nullptr) by_passes += distortion_us(size);
         }
-        if (by_rounds < by_passes) return MOSHPIT_OK;
+        if (by_rounds < kRoundsAhead * by_passes) return MOSHPIT_OK;
     }
 
     int rc = MOSHPIT_OK;

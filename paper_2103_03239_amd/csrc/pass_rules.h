@@ -158,6 +158,12 @@ inline double fused_pass_us(const RunSize &z, const Participation &w, int32_t ro
     return 6.9 + 3.1 * rounds + z.megabytes() * cached * per_mb;
 }
 
+// Rounds one by one are taken if they are priced below this part of the passes.  Over 22,000 runs on 11
+// grids, 256 KiB to 3 GB, they were slower than the passes in 1 of 1,400 runs then (45 % at most); with
+// any price below that of the passes in 1 of 40 (up to twice).  It leaves 5 % of the runs more than 5 %
+// slower than the better way.
+constexpr double kRoundsAhead = 0.8;
+
 // A distortion on its own: the chain over the rows that a wave walks (8 rows at a time in binary32, 4
 // in bfloat16, up to 256 rows to a wave), or one read of the state where that takes longer.
 // Within a curve, 1,089 binary32 rows of 1, 64, 256 and 2,000 MB take 46, 37, 47 and 312 us, 4,096
@@ -187,7 +193,8 @@ inline double grid_passes_us(const RunSize &z, const Participation &w, const Gri
     const double item_us = z.M > 16 ? 0.73 : z.M > 8 ? (f32 ? 0.69 : 1.2) : z.M > 4 ? (f32 ? 0.76 : 0.87) : z.M > 2 ? 0.48 : 0.22;
     const int64_t items = z.N / z.M * (t.row_bytes / t.parts / (4 * z.element_bytes)) * split;
     const double per_thread = static_cast<double>((items + t.threads - 1) / t.threads);
-    int64_t per_cu = 16 / (t.threads / 64);                                  // (16 waves: 128 registers each)
+    const int32_t waves = t.threads / 64;
+    int64_t per_cu = waves > 8 && waves <= 12 ? 2 : 16 / waves;              // (75 to 81 registers each in one part)
     if (per_cu > 160 * 1024 / t.lds_bytes) per_cu = 160 * 1024 / t.lds_bytes;
     if (per_cu < 1) per_cu = 1;
     const double turns = static_cast<double>(t.tiles) / (256.0 * static_cast<double>(per_cu));

@@ -130,7 +130,7 @@ int main()
         t.tiles = (z.valid_bytes + row - 1) / row;
         if (curve) other += distortions * distortion_us(z);
         const double pass = grid_passes_us(z, w, t, rounds, curve ? distortions : 0);
-        if ((pass < other) != (pass_us < other_us)) {
+        if ((kRoundsAhead * pass <= other) != (pass_us < other_us)) {
             std::printf("%d^%d x %lld, %d rounds, %.2f absent: other way %.0f (measured %.0f), pass %.0f (%.0f)\n", M, d, P, rounds,
                         absent, other, other_us, pass, pass_us);
             ++bad;
