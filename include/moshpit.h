@@ -99,15 +99,18 @@ typedef struct {
  * F times on chip (any number of times when F = d) and stored once.  The state
  * after a pass is bit-identical to the state after the same rounds run one by
  * one.  On grids of up to 4096 peers with M <= 32 and rows of at least 16 bytes
- * a pass covers the whole grid, with the distortion after every round and the
- * refresh of returning peers computed on the way, whatever the flags; only a
- * run that asks for the time of every single round (round_ms_out_host without
- * MOSHPIT_RUN_FUSED) goes round by round there.
- * MOSHPIT_RUN_FUSED allows passes on larger grids too (rows 16-byte aligned, no
+ * a pass can cover the whole grid, whatever the flags, with the distortions that
+ * the run returns and the refresh of returning peers computed on the way (not
+ * 2^12 peers, and not 24 x 24 bfloat16 peers of more than 256 MiB).  It is taken
+ * where it is estimated to cost less than the rounds one by one, which depends
+ * on the participation too; a run that asks for the time of every single round
+ * (round_ms_out_host without MOSHPIT_RUN_FUSED), or for whose scratch there is no
+ * memory, goes round by round.
+ * MOSHPIT_RUN_FUSED allows passes on planes of any grid (rows 16-byte aligned, no
  * refresh, a sub-grid that fits on-chip memory, at least two rounds; three
  * where its rows get only 128 bytes on chip), shares the time of a pass out
  * evenly over its rounds, and leaves the distortion between the rounds of such
- * a pass NaN. */
+ * a pass NaN, also where a pass over the whole grid takes its place. */
 enum {
     MOSHPIT_RUN_DEFAULT = 0,
     MOSHPIT_RUN_FUSED   = 1
@@ -150,8 +153,8 @@ int moshpit_round_dev(moshpit_ctx *h, int64_t t, const uint8_t *alive_dev);
  * (NULL = nobody fails).  Masks are generated on the device.
  * dist_out_host: NULL, or host array of rounds+1 doubles that receives the
  *   average distortion (see moshpit_dist_to_mean) before the first round and
- *   after every round.  With MOSHPIT_RUN_FUSED the state between the rounds of
- *   one pass never exists in memory; those entries are NaN.
+ *   after every round.  With MOSHPIT_RUN_FUSED the entries between the rounds of
+ *   one pass over a sub-grid are NaN (see above).
  * round_ms_out_host: NULL, or host array of `rounds` floats that receives the
  *   GPU time of each round's averaging kernel in milliseconds (a fused pass's
  *   time is split evenly over its rounds).

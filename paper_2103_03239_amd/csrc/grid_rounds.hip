@@ -11,13 +11,15 @@
 // state after a pass has the bits of the same rounds run one by one.
 //
 // Tiles.  Wb is a power of two: as wide as 32 KiB of tile allow (1 KiB at most), 256 bytes up to
-// 64 KiB, 128 bytes for up to 1024 peers and 32 bytes above.  A block holds its tile 16 bytes at a
+// 64 KiB, 128 bytes for up to 1024 peers, 64 for up to 2048 and 32 above.  A block holds its tile 16 bytes at a
 // time in the registers of its threads and works on it in LDS, at most 64 KiB at once, so that two
 // blocks or more share a compute unit: one block's loads and stores overlap another's rounds.  (A
 // wave that issues vector memory instructions faster than its compute unit's share of HBM delivers
 // is held at the issue; with one block of 128 KiB per compute unit that prefetched its next tile
 // the memory time and the time of the rounds added up.)  Tiles of 128 KiB wait in the registers
-// and pass through LDS in two column parts, so that HBM still sees the full width.
+// and pass through LDS in two column parts, so that HBM still sees the full width.  Next to 16 slots
+// few of the 128 registers of a thread are free: the two-part kernels with the distortion keep 20 to 36
+// bytes a lane in scratch (14 of the 80 kernels; the others none).
 //
 // What bounds it (MI355X).  Up to about 6 rounds the memory side: 64 rows of 102 MB in tiles of
 // 512 bytes 5.1 TB/s, 256 rows of 4 MiB in tiles of 256 bytes 5.4 TB/s (a copy in that pattern
@@ -622,7 +624,8 @@ bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t ro
     // the width of its accesses: 256 bytes at most (250 MiB, 4 x 4 x 4 peers: 103 against 109 us at
     // 512), one part in LDS for up to 1024 peers (32 x 32, 4 rounds: 8 MiB 22 -> 14 us, 250 MiB
     // 115 -> 97) and, above, while that gives a compute unit no second tile to run (16 x 16 x 16,
-    // 6 rounds: 16 MiB 46 -> 29 us, but 128 MiB 96 -> 127) ...
+    // 6 rounds: 16 MiB 46 -> 29 us, but 128 MiB 96 -> 127; rows of whole vectors only, since a
+    // last tile of less than 16 bytes takes 16 from its neighbour, which must have more) ...
     const double state_bytes = static_cast<double>(N) * p.row_bytes;
     const bool cached = state_bytes <= 256.0 * (1 << 20);
     if (cached && wb > 256) wb = 256;
@@ -666,7 +669,7 @@ bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t ro
     const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + waves) * 8 - kRcpBytes - 64;
     const int64_t most = room / (static_cast<int64_t>(p.groups) * bitmap_bytes(M));
     p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
-    if (p.max_rounds < 4) return false;
+    if (p.max_rounds < 4) return false;      // (2^12 peers; 24 x 24 in tiles of 128 bytes with 8 columns to a vector)
     *out = p;
     return true;
 }
