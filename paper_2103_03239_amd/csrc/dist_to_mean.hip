@@ -16,7 +16,7 @@
 // partial per block.  A second one-block kernel adds the partials in a fixed
 // order, so the result does not depend on scheduling.
 //
-// What bounds it (MI355X).  Large states HBM: 1024 rows of 16 MiB at 6.8 TB/s.
+// What bounds it (MI355X).  Large states HBM: 1024 rows of 16 MiB at 6.9 TB/s.
 // Short rows the walk of a wave over its 256 rows: 1024 rows of 15,625 binary32,
 // 64 MB in 62 blocks, 67 us.  That walk took 146 us while every load stood behind
 // a branch of its own, which made the compiler wait for it before the next; rows

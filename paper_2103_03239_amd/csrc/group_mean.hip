@@ -394,14 +394,15 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
             // With gradients from 9 rows on (16 x 16 x 976,563 binary32, everybody present: 626 us in the plain order,
             // 588 in eighths), but up to 24 binary32 rows of less state, up to 16 with a mask until a little later, in
             // the plain one (16 x 16 x 488,281 with a mask 279 and 284, 12 x 12 x 1,736,111 531 and 549, 24 x 24 x
-            // 303,819 385 and 398; twice that state is 6 % ahead in eighths).  Without gradients more than 16 binary32 rows (32 x 32 x 488,281 with a mask in device memory
-            // 758 us in the plain order, 720 in eighths; as bits 772 and 717; bfloat16 24 x 24 x 868,055 343 and 362)
-            // and 3 or 4 of them with a mask as bits (4 x 4 x 4 x 7,812,501 657 and 636; 2^6 x 7,812,501 578 and 607;
-            // bfloat16 4 x 4 x 4 x 7,812,501 333 and 352).
+            // 303,819 385 and 398; twice that state is 6 % ahead in eighths).  Without gradients more than 16 binary32
+            // rows (32 x 32 x 488,281 with a mask in device memory 758 us in the plain order, 720 in eighths; as bits
+            // 772 and 717), more than 28 bfloat16 rows (24 x 24 x 868,055 343 and 362, but 32 x 32 x 1,445,344 1245
+            // and 1147), and 3 or 4 binary32 rows with a mask as bits (4 x 4 x 4 x 7,812,501 657 and 636; not 2^6 x
+            // 7,812,501 578 and 607; not bfloat16 4 x 4 x 4 x 7,812,501 333 and 352).
             if (geom.grad != nullptr)
                 order = geom.M > 8 && (geom.M > 24 || dtype == 1 || touched > (full || geom.M > 16 ? 1600.0 : 2200.0) * (1 << 20)) ? 1 : 0;
             else
-                order = dtype == 0 && (geom.M > 16 || (geom.M > 2 && geom.M <= 4 && geom.bits != nullptr)) ? 1 : 0;
+                order = geom.M > 28 || (dtype == 0 && (geom.M > 16 || (geom.M > 2 && geom.M <= 4 && geom.bits != nullptr))) ? 1 : 0;
             // Everybody present: 5 x 5 x 5 x 2,000,001 380 us in the plain order, 368 in eighths; 17 and 18 rows (a
             // chunk of 16 and a short one) 17 x 17 x 2,595,156 1244 and 1189; 24 x 24 x 1,302,084 1161 and 1217;
             // 32 x 32 x 732,422 1323 and 1228, 64 x 64 x 91,553 662 and 610.  A mask in device memory: 20 x 20 x
