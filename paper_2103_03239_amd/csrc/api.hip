@@ -365,6 +365,25 @@ int grow_if_fits(moshpit_ctx *h, void **buffer, int64_t *cap, int64_t need, bool
     return MOSHPIT_OK;
 }
 
+// Rounds t0+r0 .. t0+r0+rounds-1 of a run that starts at round t0 under schedule s, as the kernels that fill
+// tables take them.
+GridSchedule grid_schedule(const moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32_t r0, int32_t rounds)
+{
+    GridSchedule g{};
+    g.N = static_cast<int32_t>(h->N);
+    g.M = h->M;
+    g.d = h->d;
+    g.rounds = rounds;
+    g.group_skip = s->group_skip != 0;
+    g.refresh = s->refresh != 0;
+    g.continued = r0 > 0;
+    g.threshold = schedule_threshold(s);
+    g.seed = s->seed;
+    g.t0 = t0 + r0;
+    if (s->kind != MOSHPIT_SCHED_IID) g.masks = h->d_masks + static_cast<int64_t>(r0) * h->N;
+    return g;
+}
+
 // Queue the tables for rounds t0+r0 .. t0+r0+rounds-1 of a run that starts at round t0 under
 // schedule s (which has failures):
 // [bitmaps rounds x N/M][with refresh: copies rounds x N, copy counts rounds][flags N].
@@ -381,19 +400,37 @@ int queue_grid_plan(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32
         end = reinterpret_cast<uint32_t *>(o.copy_counts + rounds);
     }
     o.flags = reinterpret_cast<uint8_t *>(end);
-    GridSchedule g{};
-    g.N = static_cast<int32_t>(h->N);
-    g.M = h->M;
-    g.d = h->d;
-    g.rounds = rounds;
-    g.group_skip = s->group_skip != 0;
-    g.refresh = refresh;
-    g.continued = r0 > 0;
-    g.threshold = schedule_threshold(s);
-    g.seed = s->seed;
-    g.t0 = t0 + r0;
-    if (s->kind != MOSHPIT_SCHED_IID) g.masks = h->d_masks + static_cast<int64_t>(r0) * h->N;
-    HIP_TRY(h, launch_grid_plan(g, o, h->stream));
+    HIP_TRY(h, launch_grid_plan(grid_schedule(h, s, t0, r0, rounds), o, h->stream));
+    *tables = o;
+    return MOSHPIT_OK;
+}
+
+// The same for the kernel that keeps one mean per group: [entries][final places of each pass][moves][terms, where distortions are
+// wanted][move counts][term counts][bitmaps under group-skip].
+int64_t mean_plan_bytes(const GridPlan &plan, int64_t rounds, int64_t pass_rounds)
+{
+    return rounds * mean_table_round_bytes(plan.N, plan.M, plan.split) +
+           2 * mean_place_stride(plan) * ((rounds + pass_rounds - 1) / pass_rounds);
+}
+int queue_mean_plan(moshpit_ctx *h, const moshpit_schedule *s, const GridPlan &plan, int64_t t0, int32_t r0, int32_t rounds,
+                    int32_t pass_rounds, bool want_terms, MeanTables *tables)
+{
+    const GridSchedule g = grid_schedule(h, s, t0, r0, rounds);
+    const int64_t R = rounds, groups = plan.groups, N = plan.N;
+    MeanTables o{};
+    o.pass_rounds = pass_rounds;
+    o.place_stride = mean_place_stride(plan);
+    uint32_t *at = static_cast<uint32_t *>(h->d_grid);
+    const auto take = [&](int64_t words) { uint32_t *mine = at; at += words; return mine; };
+    // (16-byte pieces first: they are read as such)
+    o.entries = take(R * groups * plan.split * 4);
+    o.places = reinterpret_cast<uint16_t *>(take((R + pass_rounds - 1) / pass_rounds * o.place_stride / 2));
+    o.moves = take(R * N);
+    if (want_terms) o.terms = take(R * (N + groups));
+    o.move_counts = reinterpret_cast<int32_t *>(take(R));
+    o.term_counts = reinterpret_cast<int32_t *>(take(R));
+    if (g.group_skip) o.bitmaps = take(R * groups);
+    HIP_TRY(h, launch_mean_plan(g, plan, o, h->stream));
     *tables = o;
     return MOSHPIT_OK;
 }
@@ -576,7 +613,12 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
     if (rounds == 0) round_ms_out_host = nullptr;        // (one launch for the distortion alone, no round to time)
     if (rounds < 2 && !dist_out_host) return MOSHPIT_OK;
     GridPlan plan;
-    if (!plan_grid(h->dtype, h->N, h->M, h->d, h->P, h->row_stride, h->X, t0, &plan)) return MOSHPIT_OK;
+    GridAsk ask;
+    ask.absent = failures;
+    ask.local_step = grad != nullptr;
+    ask.distortions = dist_out_host != nullptr;
+    ask.rounds = rounds;
+    if (!plan_grid(h->dtype, h->N, h->M, h->d, h->P, h->row_stride, h->X, t0, ask, &plan)) return MOSHPIT_OK;
     const bool refresh = failures && s->refresh != 0;
 
     // A bfloat16 local step is rounded before the first round only where a fused pass is documented
@@ -616,6 +658,10 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
         tiles.lds_bytes = plan.tile_bytes + plan.N;
         tiles.max_rounds = plan.max_rounds;
         tiles.tiles = plan.tiles;
+        if (plan.means) {
+            tiles.round_share = failures ? 0.65 : 0.53;
+            tiles.distortion_share = failures ? 0.65 : 0.4;
+        }
         double by_passes = step_first ? single : 0.0;
         by_passes += grid_passes_us(size, who, tiles, step_first ? rounds - 1 : rounds, dist_out_host ? distortions : 0);
         if (dist_out_host) {
@@ -627,16 +673,20 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
 
     int rc = MOSHPIT_OK;
     GridTables tables{};
+    MeanTables mean_tables{};
     int32_t tables_first = 0, tables_end = 0;                       // the rounds they hold now
     const int64_t entry_tiles = plan.tiles * plan.phases;           // partial sums of one distortion
     const int32_t pass_most = grid_pass_rounds(plan.max_rounds, dist_out_host ? entry_tiles : 0);
-    const int64_t tables_most = grid_table_rounds(h->N, h->M, refresh, pass_most);
+    const int64_t tables_most = plan.means ? table_rounds(mean_table_round_bytes(h->N, h->M, plan.split), pass_most)
+                                           : grid_table_rounds(h->N, h->M, refresh, pass_most);
     const uint8_t *first_mask = nullptr;
     {
         bool fits = true;
+        const int64_t most = rounds < tables_most ? rounds : tables_most;
         if (failures && rounds > 0)
             rc = grow_if_fits(h, &h->d_grid, &h->grid_cap,
-                              (rounds < tables_most ? rounds : tables_most) * grid_table_round_bytes(h->N, h->M, refresh) + h->N,
+                              plan.means ? mean_plan_bytes(plan, most, pass_most)
+                                         : most * grid_table_round_bytes(h->N, h->M, refresh) + h->N,
                               &fits);
         if (rc == MOSHPIT_OK && fits && dist_out_host)
             rc = grow_if_fits(h, &h->d_grid_partials, &h->grid_partials_cap,
@@ -701,15 +751,27 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
                 if (r >= tables_end) {
                     tables_first = r;
                     tables_end = rounds - r < tables_most ? rounds : r + static_cast<int32_t>(tables_most);
-                    rc = queue_grid_plan(h, s, t0, tables_first, tables_end - tables_first, &tables);
+                    rc = plan.means ? queue_mean_plan(h, s, plan, t0, tables_first, tables_end - tables_first, pass_most,
+                                                      dist_out_host != nullptr, &mean_tables)
+                                    : queue_grid_plan(h, s, t0, tables_first, tables_end - tables_first, &tables);
                     if (rc != MOSHPIT_OK) return rc;
                 }
                 if (now > tables_end - r) now = tables_end - r;
                 p.rounds = now;
                 const int64_t at = r - tables_first;
-                p.bitmaps = tables.bitmaps + at * (h->N / h->M);
-                p.flags = tables.flags;
-                if (refresh) {
+                if (plan.means) {
+                    const MeanTables &o = mean_tables;
+                    p.entries = o.entries + at * p.groups * p.split * 4;
+                    p.moves = o.moves + at * p.N;
+                    if (o.terms != nullptr) p.terms = o.terms + at * (p.N + p.groups);
+                    p.move_counts = o.move_counts + at;
+                    p.term_counts = o.term_counts + at;
+                    p.places = o.places + at / pass_most * o.place_stride;
+                } else {
+                    p.bitmaps = tables.bitmaps + at * (h->N / h->M);
+                    p.flags = tables.flags;
+                }
+                if (refresh && !plan.means) {
                     p.copies = tables.copies + at * h->N;
                     p.copy_counts = tables.copy_counts + at;
                     p.refresh_first = r > 0;
@@ -728,7 +790,7 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
                 for (int32_t k = 0; k < now; ++k) p.dist_after |= static_cast<uint64_t>(wanted[r + k + 1]) << k;
                 if (p.dist_before || p.dist_after != 0) p.partials = partials;
             }
-            HIP_TRY(h, launch_grid_rounds(h->X, h->dtype, p, h->stream));
+            HIP_TRY(h, p.means ? launch_mean_rounds(h->X, h->dtype, p, h->stream) : launch_grid_rounds(h->X, h->dtype, p, h->stream));
             // (summed before the next pass writes its own)
             if (p.partials != nullptr) HIP_TRY(h, launch_grid_dist(p, h->d_dist + r, h->stream));
         }

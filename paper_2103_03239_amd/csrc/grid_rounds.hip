@@ -29,7 +29,8 @@
 // Measured against the persistent kernel of fused_rounds.hip, which serves the larger grids:
 // 4 x 4 x 4 peers x 25,557,032 binary32, 6 rounds 2.92 -> 2.56 ms; 32 x 32 x 4,194,304, 8 rounds
 // 10.6 -> 9.3 ms; 16 x 16 x 16 x 262,144 bfloat16, 12 rounds 5.15 -> 2.08 ms (one pass instead
-// of six over planes of 256 rows; 32-byte rows move at 3.7 TB/s, see tile_of).
+// of six over planes of 256 rows; 32-byte rows move at 3.7 TB/s, see tile_of).  Longer runs of groups of more than 4
+// are taken over by the kernel of mean_rounds.hip (choose_means).
 //
 // Row ends and alignment.  Rows need no alignment beyond the element's: the loads and stores are
 // 128-bit accesses at element-aligned addresses.  Where a row does not end on a 16-byte boundary
@@ -37,73 +38,11 @@
 // neighbour are averaged twice, with the same bits.
 #include <type_traits>
 
-#include "mix64.h"
-#include "moshpit_internal.h"
+#include "grid_tile.h"
 #include "tile_math.h"
 
 namespace moshpit {
 namespace {
-
-constexpr int kPhaseSlots = 8;               // 16-byte slots of the tile in LDS per thread
-constexpr int kLdsPerBlock = 80 * 1024;      // two blocks share a compute unit
-constexpr int64_t kGridMaxPeers = 4096;
-
-template <int DT> __device__ __forceinline__ void widen16(const u32x4 &m, float (&f)[DT == 0 ? 4 : 8])
-{
-    if constexpr (DT == 0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(m[e]);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            f[2 * e] = __uint_as_float(m[e] << 16);
-            f[2 * e + 1] = __uint_as_float(m[e] & 0xffff0000u);
-        }
-    }
-}
-
-// n / d for n < 2^16 and magic = ceil(2^32 / d), d >= 2
-__device__ __forceinline__ int32_t quotient(int32_t n, uint32_t magic)
-{
-    return static_cast<int32_t>(__umulhi(static_cast<uint32_t>(n), magic));
-}
-
-struct TileSpan {
-    int64_t col0;          // first byte of the tile within a row
-    int32_t seg;           // bytes of every row in it (>= 16)
-};
-
-// Tile w covers bytes [w * Wb, (w + 1) * Wb) of every row.  A last tile of fewer than 16 bytes
-// takes the last vector of its neighbour as well.
-__device__ __forceinline__ TileSpan tile_span(const GridPlan &p, int64_t w)
-{
-    TileSpan t;
-    const int64_t left = p.valid_bytes - w * p.Wb;
-    t.col0 = w * p.Wb;
-    t.seg = static_cast<int32_t>(left < p.Wb ? left : p.Wb);
-    if (t.seg < 16) {
-        t.col0 -= 16;
-        t.seg += 16;
-    } else if (left > p.Wb && left < p.Wb + 16) {
-        t.seg -= 16;
-    }
-    return t;
-}
-
-// Position i of the work list -> tile.  Blocks b, b + 8, b + 16, ... run on the same one of the 8
-// dies; each die takes `run` consecutive tiles of every 8 * run, so that tiles that share cache
-// lines or DRAM pages meet in one die's L2.  A copy of 4096 rows x 32 bytes moves 1.4 TB/s dealt in
-// order, 3.7 TB/s in runs of 32 (ordinary loads and stores: they have to stay in L2; 1.3 TB/s with
-// non-temporal ones).
-__device__ __forceinline__ int64_t tile_of(const GridPlan &p, int64_t i)
-{
-    if (p.die_run <= 1) return i;
-    const int64_t span = 8 * static_cast<int64_t>(p.die_run);
-    const int64_t q = i / span;
-    if ((q + 1) * span > p.tiles) return i;
-    const int64_t r = i - q * span;
-    return q * span + (r & 7) * p.die_run + (r >> 3);
-}
 
 // TREE, SPLIT, PER as chosen from M: TREE = summation block (power of two >= M, at most 16);
 // SPLIT lanes of a wave share the positions of a group, PER positions each (SPLIT = 1: one lane
@@ -444,15 +383,6 @@ __global__ __launch_bounds__(256) void grid_dist_kernel(const double *__restrict
 
 // ---- what a pass needs to know about the peers: one launch per run ----------------------------
 
-constexpr int kPlanThreads = 1024;
-constexpr int kPerThread = kGridMaxPeers / kPlanThreads;
-
-__device__ __forceinline__ bool failure_event(uint64_t seed, int64_t s, int64_t i, uint32_t threshold)
-{
-    const uint64_t round_key = mix64(seed + 0x9E3779B97F4A7C15ull * static_cast<uint64_t>(s + 1));
-    return static_cast<uint32_t>(mix64(round_key ^ static_cast<uint64_t>(i)) >> 40) < threshold;
-}
-
 // Stable compaction step of one block: number of set flags of the threads before this one; *total the block's.
 __device__ __forceinline__ int32_t block_rank(bool flag, int32_t *wave_sums, int32_t *total)
 {
@@ -469,20 +399,6 @@ __device__ __forceinline__ int32_t block_rank(bool flag, int32_t *wave_sums, int
     __syncthreads();
     *total = all;
     return base + __popcll(ballot & ((1ull << lane) - 1ull));
-}
-
-// Is peer i present in round t0 + r (and in the round before it, if that belongs to the run)?
-__device__ __forceinline__ void presence(const GridSchedule &s, int32_t i, int64_t r, bool &before, bool &now)
-{
-    before = true;
-    const bool earlier = r > 0 || s.continued;
-    if (s.masks != nullptr) {
-        now = s.masks[r * s.N + i] != 0;
-        if (earlier) before = s.masks[(r - 1) * s.N + i] != 0;
-    } else {
-        now = !failure_event(s.seed, s.t0 + r, i, s.threshold);
-        if (s.refresh && earlier) before = !failure_event(s.seed, s.t0 + r - 1, i, s.threshold);
-    }
 }
 
 // Blocks 0 .. rounds-1: round r = blockIdx.x: bitmaps[r][g] (bit j: position j of group g takes
@@ -597,8 +513,53 @@ hipError_t launch_grid_plan(const GridSchedule &s, const GridTables &tables, hip
     return hipGetLastError();
 }
 
+namespace {
+// One mean per group (mean_rounds.hip) or M copies of it (the kernel above)?  MI355X, the former
+// against the latter, us:
+//   nobody ever absent: ahead from 4 rounds on (16 x 16, 200 MB binary32, 6 rounds 70 : 80; 24 x 24, 1.5 GB bfloat16
+//     887 : 1,234; 32 x 32, 16 GB, 16 rounds 10,450 : 14,200), behind by up to 11 % for 2 or 3 (8 x 8 x 8, 1.5 GB
+//     bfloat16 715 : 643) and for small states of 8 x 8 peers in bfloat16 (8 MB, 8 rounds 12.8 : 12.5);
+//     with distortions ahead everywhere (16 x 16, 1 GB binary32, 5 rounds 602 : 860).  Groups of 2 to 4 save little.
+//   with failures, whose tables cost a launch and a wait: ahead from 5 rounds (4 on more than 1024 peers) of
+//     states beyond 32 MB on (32 x 32, 16 GB, 8 rounds 8,110 : 9,320, 4 rounds of 200 MB 85 : 83; 16 x 16 x 16, 1.5 GB
+//     bfloat16, 4 rounds 927 : 1,228; 8 MB, 8 rounds 31 : 28), and not for 8 x 8 peers, whose passes
+//     wait for memory (1.5 GB binary32, 8 rounds 652 : 631).  Places are 8 to a lane: groups of 8, 16 or 32.  The
+//     distortion of bfloat16 rows of 64 bytes and more spills (16 x 16, 1 GB, 5 rounds 1,616 : 1,341).
+// A local step would take its registers: not with one.
+bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
+{
+    const int64_t state = p->N * p->row_bytes;
+    const bool large = state >= 32000000;
+    if (p->M <= 4 || ask.local_step) return false;
+    if (ask.absent) {
+        if (!large || p->N < 256 || ask.rounds < (p->N > 1024 ? 4 : 5)) return false;
+    } else if (!ask.distortions) {
+        if (ask.rounds < 4 || (p->M <= 8 && p->N <= 64 && esize == 2 && !large)) return false;
+    }
+    const bool cached = static_cast<double>(p->N) * p->row_bytes <= 256.0 * (1 << 20);
+    for (int32_t wb = p->Wb, phases = p->phases; phases <= 2 && wb / phases >= 16;) {
+        GridPlan q = *p;
+        const int32_t part = wb / phases;
+        q.Wb = wb;
+        q.phases = phases;
+        const int64_t threads = (q.N * part / (16 * kPhaseSlots) + 63) / 64 * 64, waves = threads / 64 < 1 ? 1 : threads / 64;
+        const int64_t bytes = lay_out_means(&q, part, ask.absent, ask.distortions);
+        if (ask.absent && (q.M != 8 * q.split || (phases == 2 && part == 32) || (ask.distortions && esize == 2 && part >= 64))) return false;
+        if (bytes + (ask.distortions ? (waves * (part / esize) + 5 * waves) * 8 : 0) <= kLdsPerBlock) {
+            q.red_offset = static_cast<int32_t>(bytes);
+            *p = q;
+            return true;
+        }
+        // (a state in the last-level cache: narrower tiles, see below; 8 x 8 x 8 peers, 8 MiB, 3 rounds: two parts 13.2 us)
+        if (cached && phases == 1 && wb > 32) wb >>= 1;
+        else ++phases;
+    }
+    return false;
+}
+}  // namespace
+
 bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
-               GridPlan *out)
+               const GridAsk &ask, GridPlan *out)
 {
     const int64_t esize = dtype == 0 ? 4 : 2;
     GridPlan p{};
@@ -637,21 +598,26 @@ bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t ro
     while (wb > least && N * wb > 4096 && (p.valid_bytes + wb - 1) / wb < 2048) wb >>= 1;
     while (wb > 32 && wb / 2 >= p.valid_bytes) wb >>= 1;
     p.Wb = wb;
+    p.phases = N * wb > 72 * 1024 ? 2 : 1;
+    p.means = choose_means(&p, esize, ask) ? 1 : 0;
+    wb = p.Wb;
     p.wv_shift = 0;
     while ((16 << p.wv_shift) < wb) ++p.wv_shift;
-    p.phases = N * wb > 72 * 1024 ? 2 : 1;
     const int32_t part = wb / p.phases;              // bytes of a row in LDS
     p.threads = static_cast<int32_t>((N * part / (16 * kPhaseSlots) + 63) / 64 * 64);
     if (p.threads < 64) p.threads = 64;
     if (p.threads > (p.phases == 1 ? 1024 : 512)) return false;
-    p.pad = part < 256 && M >= 8 && (M * part) % 256 == 0 ? part : 0;
+    if (!p.means) {
+        p.pad = part < 256 && M >= 8 && (M * part) % 256 == 0 ? part : 0;
+        p.tile_bytes = static_cast<int32_t>(N * part + p.groups * p.pad);
+    }
+    S = 1;
     for (int32_t a = 0; a < d; ++a) {
         p.S[a] = S;
         p.magic_s[a] = S > 1 ? magic(S) : 0;
         p.pad_step[a] = a == 0 ? 0 : S / M * p.pad;
         S *= M;
     }
-    p.tile_bytes = static_cast<int32_t>(N * part + p.groups * p.pad);
     p.tiles = (p.valid_bytes + wb - 1) / wb;
     // Tiles of whole cache lines are not seen again: non-temporal (256 rows of 4 MiB: 5.5 TB/s
     // against 5.1 with ordinary accesses).  Others share lines with their neighbours in the row.
@@ -666,6 +632,13 @@ bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t ro
     if (p.tiles < 8 * p.die_run) p.die_run = p.tiles >= 16 ? static_cast<int32_t>(p.tiles / 8) : 1;
     // rounds of one pass: as many bitmaps as fit next to the tile
     const int64_t waves = p.threads / 64, columns = part / esize;
+    if (p.means) {
+        // (a sum per wave for every distortion)
+        const int64_t sums = (kLdsPerBlock - p.red_offset - waves * columns * 8) / (8 * waves) - 1;
+        p.max_rounds = static_cast<int32_t>(ask.distortions && sums < 64 ? sums : 64);
+        *out = p;
+        return p.max_rounds >= 4;
+    }
     const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + waves) * 8 - kRcpBytes - 64;
     const int64_t most = room / (static_cast<int64_t>(p.groups) * bitmap_bytes(M));
     p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);

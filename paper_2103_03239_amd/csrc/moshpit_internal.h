@@ -217,6 +217,13 @@ struct GridPlan {
     int32_t S[kGridMaxAxes], pad_step[kGridMaxAxes];
     uint32_t magic_s[kGridMaxAxes];
     int64_t row_bytes, valid_bytes, tiles;
+    // means != 0: the kernel of mean_rounds.hip, and where its LDS holds what
+    int32_t means;
+    int32_t split;                   // lanes that share a group
+    int32_t part;                    // bytes of a row in LDS
+    int32_t means_at, means_bytes, zero_at, rcp_at, words_at;
+    int32_t words_shift;             // log2 of N / 2: 32-bit words that a round's places take
+    int32_t mean_step[kGridMaxAxes];      // bytes between the means that the rows of a group were given by the round before
     // filled in by the caller
     int32_t rounds;
     int32_t dist_before, refresh_first;   // distortion before the first round; refresh before it
@@ -230,9 +237,20 @@ struct GridPlan {
     int64_t grad_row_bytes;
     double *partials;                // [rounds + 1][tiles * phases], of this pass, or nullptr (no distortion wanted)
     uint64_t dist_after;             // bit r: the distortion after round r of the pass is wanted
+    // means != 0, with failures: this pass's part of the tables below
+    const uint32_t *entries, *moves, *terms;
+    const int32_t *move_counts, *term_counts;
+    const uint16_t *places;
+};
+// What a run asks of its passes.
+struct GridAsk {
+    bool absent = false;             // somebody may be (a failure schedule)
+    bool local_step = false;         // it starts with one
+    bool distortions = false;        // they are wanted
+    int32_t rounds = 0;
 };
 bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
-               GridPlan *out);
+               const GridAsk &ask, GridPlan *out);
 hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStream_t stream);
 // The pass's distortions that were wanted, out[0] = before it .. out[rounds] = after its last round.
 hipError_t launch_grid_dist(const GridPlan &plan, double *out, hipStream_t stream);
@@ -252,6 +270,22 @@ struct GridTables {
     int32_t *copy_counts;
 };
 hipError_t launch_grid_plan(const GridSchedule &s, const GridTables &tables, hipStream_t stream);
+
+// The same for the kernel of mean_rounds.hip.  Places are LDS addresses in units of 16 bytes.
+struct MeanTables {
+    uint32_t *entries;               // [rounds][groups][split][4]: places of a group's positions, 13 bits of 16 each, and its count
+    uint32_t *moves;                 // [rounds][N]: from | to << 16
+    uint32_t *terms;                 // [rounds][N + groups]: place | weight << 16; nullptr = no distortion wanted
+    int32_t *move_counts, *term_counts;      // [rounds]
+    uint16_t *places;                // [passes][place_stride]: where a row's value ends, 0xffff = not stored
+    uint32_t *bitmaps;               // [rounds][groups] participants, group-skip schedules only; else nullptr
+    int64_t place_stride;
+    int32_t pass_rounds;             // round r of the tables is round r mod pass_rounds of its pass
+};
+int64_t lay_out_means(GridPlan *p, int32_t part, bool tables, bool distortions);
+int64_t mean_place_stride(const GridPlan &p);
+hipError_t launch_mean_plan(const GridSchedule &s, const GridPlan &plan, const MeanTables &tables, hipStream_t stream);
+hipError_t launch_mean_rounds(void *X, int dtype, const GridPlan &plan, hipStream_t stream);
 
 // Queue a plain 128-bit copy of nbytes (multiple of 16) from src to dst.
 hipError_t launch_copy_probe(void *dst, const void *src, int64_t nbytes, hipStream_t stream);

@@ -18,13 +18,25 @@ inline int64_t grid_table_round_bytes(int64_t N, int32_t M, bool refresh)
     return 4 * (N / M) + (refresh ? 4 * N + 4 : 0);
 }
 
-// Rounds the tables are built for at once: whole passes of max_rounds rounds, at least one.
-inline int64_t grid_table_rounds(int64_t N, int32_t M, bool refresh, int64_t max_rounds)
+// Of the kernel that keeps one mean per group: 16 bytes of places per lane of a group, 4 bytes per peer that moves, 4 per term of the distortion, two counts; a bitmap per group for
+// group-skip schedules.
+inline int64_t mean_table_round_bytes(int64_t N, int32_t M, int32_t split)
 {
-    int64_t n = kGridTableBytes / grid_table_round_bytes(N, M, refresh);
+    const int64_t groups = N / M;
+    return groups * 16 * split + 4 * N + 4 * (N + groups) + 8 + 4 * groups;
+}
+
+// Rounds the tables are built for at once: whole passes of max_rounds rounds, at least one.
+inline int64_t table_rounds(int64_t round_bytes, int64_t max_rounds)
+{
+    int64_t n = kGridTableBytes / round_bytes;
     if (n > kGridTableRounds) n = kGridTableRounds;
     n = n / max_rounds * max_rounds;
     return n < max_rounds ? max_rounds : n;
+}
+inline int64_t grid_table_rounds(int64_t N, int32_t M, bool refresh, int64_t max_rounds)
+{
+    return table_rounds(grid_table_round_bytes(N, M, refresh), max_rounds);
 }
 
 // A pass leaves one partial sum per tile for every distortion it computes; they are summed before
@@ -185,6 +197,7 @@ inline double refresh_us(const RunSize &z) { return 6.5 + 0.14 * z.megabytes(); 
 struct GridTiles {
     int32_t row_bytes = 0, parts = 1, threads = 0, lds_bytes = 0, max_rounds = 1;
     int64_t tiles = 0;
+    double round_share = 1.0, distortion_share = 1.0;      // of what the kernel with M copies of a mean takes
 };
 inline double grid_passes_us(const RunSize &z, const Participation &w, const GridTiles &t, int32_t rounds, int32_t distortions)
 {
@@ -198,7 +211,7 @@ inline double grid_passes_us(const RunSize &z, const Participation &w, const Gri
     if (per_cu > 160 * 1024 / t.lds_bytes) per_cu = 160 * 1024 / t.lds_bytes;
     if (per_cu < 1) per_cu = 1;
     const double turns = static_cast<double>(t.tiles) / (256.0 * static_cast<double>(per_cu));
-    const double round_us = (turns > 1.0 ? turns : 1.0) * per_thread * item_us * (0.63 + 0.37 * w.groups) * t.parts;
+    const double round_us = (turns > 1.0 ? turns : 1.0) * per_thread * item_us * (0.63 + 0.37 * w.groups) * t.parts * t.round_share;
     const bool narrow = t.row_bytes <= 64;
     const double read = t.row_bytes <= 32 ? 0.47 : narrow ? 0.36 : t.row_bytes <= 128 ? 0.25 : 0.17;
     const double masked = t.row_bytes <= 32 ? 0.34 : narrow ? 0.25 : t.row_bytes <= 128 ? 0.12 : 0.13;
@@ -209,7 +222,7 @@ inline double grid_passes_us(const RunSize &z, const Participation &w, const Gri
         const int32_t n = left < t.max_rounds ? left : t.max_rounds;
         us += 4.2 + 8.2 * static_cast<double>(z.N) / 4096.0 + memory * (read + (w.failures ? masked * w.ever(n) : whole)) + n * round_us;
     }
-    return us + distortions * (6.3 + z.megabytes() * (t.parts == 1 ? 0.065 : 0.14) * (f32 ? 1.0 : 2.3));
+    return us + distortions * (6.3 + z.megabytes() * (t.parts == 1 ? 0.065 : 0.14) * (f32 ? 1.0 : 2.3) * t.distortion_share);
 }
 
 }  // namespace moshpit
