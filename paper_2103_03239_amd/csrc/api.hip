@@ -423,7 +423,11 @@ int queue_mean_plan(moshpit_ctx *h, const moshpit_schedule *s, const GridPlan &p
     uint32_t *at = static_cast<uint32_t *>(h->d_grid);
     const auto take = [&](int64_t words) { uint32_t *mine = at; at += words; return mine; };
     // (16-byte pieces first: they are read as such)
-    o.entries = take(R * groups * plan.split * 4);
+    o.entries = take(plan.bits ? R * groups : R * groups * plan.split * 4);
+    if (plan.bits) {
+        o.move_rows = take((R + 15) / 16 * 8 * plan.threads);
+        o.move_bytes = take((R + 15) / 16 * 4 * plan.threads);
+    }
     o.places = reinterpret_cast<uint16_t *>(take((R + pass_rounds - 1) / pass_rounds * o.place_stride / 2));
     o.moves = take(R * N);
     if (want_terms) o.terms = take(R * (N + groups));
@@ -616,6 +620,7 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
     GridAsk ask;
     ask.absent = failures;
     ask.local_step = grad != nullptr;
+    ask.refresh = failures && s->refresh != 0;
     ask.distortions = dist_out_host != nullptr;
     ask.rounds = rounds;
     if (!plan_grid(h->dtype, h->N, h->M, h->d, h->P, h->row_stride, h->X, t0, ask, &plan)) return MOSHPIT_OK;
@@ -761,7 +766,11 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
                 const int64_t at = r - tables_first;
                 if (plan.means) {
                     const MeanTables &o = mean_tables;
-                    p.entries = o.entries + at * p.groups * p.split * 4;
+                    p.entries = o.entries + at * p.groups * (p.bits ? 1 : p.split * 4);
+                    if (p.bits) {                                // (passes are whole multiples of 16 rounds, but for a run's last)
+                        p.move_rows = o.move_rows + at / 2 * p.threads;
+                        p.move_bytes = o.move_bytes + at / 4 * p.threads;
+                    }
                     p.moves = o.moves + at * p.N;
                     if (o.terms != nullptr) p.terms = o.terms + at * (p.N + p.groups);
                     p.move_counts = o.move_counts + at;

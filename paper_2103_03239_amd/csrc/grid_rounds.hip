@@ -522,7 +522,7 @@ namespace {
 //     with distortions ahead everywhere (16 x 16, 1 GB binary32, 5 rounds 602 : 860).  Groups of 2 to 4 save little.
 //   with failures, whose tables cost a launch and a wait: ahead from 5 rounds (4 on more than 1024 peers) of
 //     states beyond 32 MB on (32 x 32, 16 GB, 8 rounds 8,110 : 9,320, 4 rounds of 200 MB 85 : 83; 16 x 16 x 16, 1.5 GB
-//     bfloat16, 4 rounds 927 : 1,228; 8 MB, 8 rounds 31 : 28), and not for 8 x 8 peers, whose passes
+//     bfloat16, 4 rounds 911 : 1,222, 16 rounds 1,570 : 2,640; 8 MB, 8 rounds 31 : 28), and not for 8 x 8 peers, whose passes
 //     wait for memory (1.5 GB binary32, 8 rounds 652 : 631).  Places are 8 to a lane: groups of 8, 16 or 32.  The
 //     distortion of bfloat16 rows of 64 bytes and more spills (16 x 16, 1 GB, 5 rounds 1,616 : 1,341).
 // A local step would take its registers: not with one.
@@ -543,6 +543,7 @@ bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
         q.Wb = wb;
         q.phases = phases;
         const int64_t threads = (q.N * part / (16 * kPhaseSlots) + 63) / 64 * 64, waves = threads / 64 < 1 ? 1 : threads / 64;
+        q.bits = ask.absent && !ask.refresh && !ask.distortions && part == 16 && q.M == 16 && 2 * q.groups == threads ? 1 : 0;
         const int64_t bytes = lay_out_means(&q, part, ask.absent, ask.distortions);
         if (ask.absent && (q.M != 8 * q.split || (phases == 2 && part == 32) || (ask.distortions && esize == 2 && part >= 64))) return false;
         if (bytes + (ask.distortions ? (waves * (part / esize) + 5 * waves) * 8 : 0) <= kLdsPerBlock) {

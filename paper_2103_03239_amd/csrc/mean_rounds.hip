@@ -34,9 +34,10 @@
 //   16 x 16 x 1,048,576 binary32, 10 rounds, 11 distortions      1.54 -> 1.06 ms
 //   16 x 16 x 16 x 131,072 bfloat16, 6 rounds with refresh       1.12 -> 0.87 ms
 //   16 x 16 x 16 x 262,144 bfloat16, 12 rounds, nobody absent    1.98 -> 1.48 ms
-// With failures the last takes 2.09 as before: its places are 8 KiB a round and part, read from memory in the rounds,
-// and a compute unit returns loads in order, so they wait behind the tile that its other block is
-// loading (without those loads, with wrong results, it takes 1.5 ms).  See the tables in the kernel.
+//   the same with 10 % absent                                    2.09 -> 1.90
+// A round's vector instructions count as much as its LDS traffic, and a load from memory in a round costs
+// more than either: a compute unit returns loads in order, so it waits behind the tile that its other
+// block is loading (see the tables in the kernel).
 #include <type_traits>
 
 #include "grid_tile.h"
@@ -47,7 +48,7 @@ namespace {
 
 constexpr int kPositions = 8;                // of a group, per lane
 constexpr int kMaxGroup = 32;
-constexpr int kClosed = 0, kLds = 1, kAheadOnly = 2;
+constexpr int kClosed = 0, kLds = 1, kAheadOnly = 2, kBits = 3;
 constexpr int32_t kLeastLdsPart = 64;        // bytes of a row in LDS from which on a round's tables take one register or less
 constexpr int kRegisters = 8;                // of a thread for a table
 constexpr int kAhead = 3;                    // rounds that the tables are read ahead
@@ -172,7 +173,7 @@ __device__ __forceinline__ double lanes_sum(double v, int32_t from)
 
 // SPLIT: lanes (16 or 32 apart) that share a group, 8 positions each.  HALF: 0 where the whole tile is in LDS; else
 // its two column parts take turns, and HALF is the lanes between them in a wave that loads it.  NT: non-temporal loads and stores.  DIST: distortions are
-// wanted.  TAB: where the places come from: kClosed (nobody is ever absent), kLds or kAheadOnly (see below).
+// wanted.  TAB: where the places come from: kClosed (nobody is ever absent), kLds, kBits or kAheadOnly (see below).
 template <int DT, int SPLIT, int HALF, bool NT, bool DIST, int TAB>
 __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(char *X, GridPlan p)
 {
@@ -221,8 +222,10 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
     // TAB == kLds 4 bytes of a round's places, moves and terms per thread and register (1024 peers and more than 64
     // bytes of a row fill the threads once or less), `per_register` rounds in each of kRegisters.  Every round the threads that
     // hold them write those of the round after next to LDS, and the lanes read the next one's from there.  Where a row is
-    // shorter a round's places would fill many registers: they are loaded kAhead rounds ahead, which costs less
-    // than copies of the means do.
+    // shorter a round's places would fill many registers.  There they come from two bits a position (kBits: does it
+    // take part, was it averaged in the round before; 16 x 16 x 16 x 262,144 bfloat16, 12
+    // rounds: 2.09 -> 1.90 ms; as 16-bit places read in the rounds 2.10, and with quotients by multiplication in place of the shifts 2.09), or, for
+    // what bits cannot say (the donor of a returning peer) and with distortions, are loaded kAhead rounds ahead.
     const int32_t words_shift = p.words_shift, words = 1 << words_shift;      // of a round's places, two in each
     const int32_t per_register = T >> words_shift;
     const int32_t move_words_max = words >> 1;                // of a round's moves; more are read from memory
@@ -248,6 +251,40 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
             if constexpr (DIST)
                 term[i] = table_get<uint32_t>(p.terms + r * (p.N + p.groups), static_cast<uint32_t>(tid < last ? tid >> wv_shift : 0) * 4u);
         }
+    };
+    // kBits: a group's bits in one word, a round's in T / groups threads; rows that move two to a thread and round, in
+    // 24 bits (12 of the first and 4 of the second in row_words, two rounds to a word; 8 in row_bytes_4, four).
+    constexpr int kRowRounds = 2 * kRegisters;
+    [[maybe_unused]] u32x8 bit_words, row_words;
+    [[maybe_unused]] u32x4 row_bytes_4;
+    [[maybe_unused]] uint32_t group_bits = 0;
+    const int32_t bit_threads = p.groups, bit_rounds = TAB == kBits ? T / bit_threads : 1;
+    const int32_t bit_round = TAB == kBits ? tid / bit_threads : 0, bit_group = tid - bit_round * bit_threads;
+    auto fetch_bits = [&](int32_t first) {
+        if constexpr (TAB == kBits)
+#pragma unroll
+            for (int q = 0; q < kRegisters; ++q) {
+                const int32_t r = first + q * bit_rounds + bit_round;
+                bit_words[q] = table_get<uint32_t>(p.entries, static_cast<uint32_t>((r < p.rounds ? r : 0) * bit_threads + bit_group) * 4u);
+            }
+    };
+    auto fetch_rows = [&](int32_t first) {                    // (the tables hold whole multiples of kRowRounds)
+        if constexpr (TAB == kBits) {
+#pragma unroll
+            for (int q = 0; q < kRegisters; ++q) row_words[q] = table_get<uint32_t>(p.move_rows, static_cast<uint32_t>((first / 2 + q) * T + tid) * 4u);
+#pragma unroll
+            for (int q = 0; q < kRegisters / 2; ++q) row_bytes_4[q] = table_get<uint32_t>(p.move_bytes, static_cast<uint32_t>((first / 4 + q) * T + tid) * 4u);
+        }
+    };
+    auto write_bits = [&](int32_t r) {
+        if constexpr (TAB == kBits) {
+            const int32_t in = r % (kRegisters * bit_rounds), q = in / bit_rounds;
+            if (r > 0 && in == 0) fetch_bits(r);
+            if (bit_round == in - q * bit_rounds) lds_put(base + p.words_at + (r & 1) * 4 * bit_threads + bit_group * 4, static_cast<uint32_t>(bit_words[q]));
+        }
+    };
+    auto read_bits = [&](int32_t r) {
+        if constexpr (TAB == kBits) group_bits = lds_get<uint32_t>(base + p.words_at + (r & 1) * 4 * bit_threads + (item0 < items ? item0 >> wv_shift : 0) * 4);
     };
     // kLds: rounds first .. first + kRegisters * per_register - 1 into the registers
     auto fetch_words = [&](int32_t first) {
@@ -315,6 +352,8 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
             for (int i = 0; i < kAhead; ++i) fetch_round(i, i);
         fetch_words(0);
         fetch_terms(0);
+        fetch_bits(0);
+        fetch_rows(0);
         places = table_get<u32x4>(p.places, static_cast<uint32_t>(((tid >> 6) * rows_per_slot + row_in_slot) * PHASES + (upper ? 1 : 0)) * 16u);
         moves = p.move_counts[r];
         if constexpr (DIST) {
@@ -418,7 +457,51 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
 
     // Round r of the pass on axis `axis`, of the part in LDS (seg bytes wide); its tables are in entry[i], move[i].
     auto round = [&](int i, int32_t seg, int32_t r, int32_t axis) {
-        if constexpr (TAB != kClosed) {
+        if constexpr (TAB == kBits) {
+            const uint32_t bits = group_bits;
+            if (r > 0 && r % kRowRounds == 0) fetch_rows(r);
+            const uint32_t row_word = row_words[r % kRowRounds / 2] >> (r % 2 * 16), row_byte = row_bytes_4[r % kRowRounds / 4] >> (r % 4 * 8);
+            if (r + 1 < p.rounds) read_bits(r + 1);
+            if (r + 2 < p.rounds) write_bits(r + 2);
+            // (groups of 16 and 16 bytes of a row: every quotient is a shift)
+            const int32_t here = 4 * axis, there = 4 * (axis == 0 ? p.d - 1 : axis - 1);
+            const uint32_t means_before = base + p.means_at + ((r + 1) & 1) * p.means_bytes;
+            const auto at_row = [&](uint32_t row) -> uint32_t { return row * 16 + (row >> 4) * p.pad; };
+            const auto before = [&](uint32_t row) -> uint32_t {           // place of the mean that the last round gave a row
+                return means_before + at_row((row >> (there + 4)) << there | (row & ((1u << there) - 1u)));
+            };
+            const uint32_t count = __popc(bits & 0xffffu);
+            if (count != 0 && (item0 & wv_mask) * 16 < seg) {
+                const uint32_t g = item0, first = sub * kPositions;
+                const uint32_t row0 = (g >> here) << (here + 4) | (g & ((1u << here) - 1u));
+                const int32_t own_step = axis == 0 ? 16 : p.S[axis] * 16 + p.pad_step[axis], mean_step = p.mean_step[axis];
+                uint32_t own = base + at_row(row0) + __umul24(first, own_step);
+                uint32_t mean = before(row0) + __umul24(first, mean_step);
+                const int32_t live = static_cast<int32_t>(bits >> first), was = static_cast<int32_t>(bits >> (16 + first));
+                const uint32_t zero = base + p.zero_at;
+                uint32_t at[kPositions];
+#pragma unroll
+                for (int u = 0; u < kPositions; ++u) {
+                    const uint32_t averaged_before = static_cast<uint32_t>(__builtin_amdgcn_sbfe(was, u, 1));
+                    const uint32_t on = static_cast<uint32_t>(__builtin_amdgcn_sbfe(live, u, 1));
+                    const uint32_t from = (averaged_before & mean) | (~averaged_before & own);
+                    at[u] = (on & from) | (~on & zero);
+                    own += own_step;
+                    mean += mean_step;
+                }
+                const float y = lds_get<float>(base + p.rcp_at + count * 4);
+                average(at, base + p.means_at + (r & 1) * p.means_bytes + at_row(g) + out_at, static_cast<float>(count), y);
+            }
+            const int32_t n = __builtin_amdgcn_readlane(moves, r);
+            auto one_move = [&](uint32_t row) { lds_put(base + at_row(row), lds_get<u32x4>(before(row))); };
+            if (tid < n) one_move(row_word & 0xfffu);
+            if (tid + T < n) one_move(((row_word >> 12) & 0xfu) | (row_byte & 0xffu) << 4);
+#pragma unroll 1
+            for (int32_t it = tid + 2 * T; it < n; it += T) {
+                const uint32_t pair = table_get<uint32_t>(p.moves + static_cast<int64_t>(r) * p.N, static_cast<uint32_t>(it) * 4u);
+                lds_put(place<1>(pair, base), lds_get<u32x4>(place<0>(pair, base)));
+            }
+        } else if constexpr (TAB != kClosed) {
             const u32x4 ent = entry[i];
             const uint32_t mv[2] = {move[i][0], move[i][1]};
             const int32_t move_items = __builtin_amdgcn_readlane(moves, r) << wv_shift;
@@ -615,6 +698,12 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                 if constexpr (DIST) term[kLast] = t;
             }
         }
+        if (TAB == kBits && p.rounds > 0) {
+            if (phase == 1 && p.rounds > kRegisters * bit_rounds) fetch_bits(0);
+            if (phase == 1 && p.rounds > kRowRounds) fetch_rows(0);
+            write_bits(0);
+            if (p.rounds > 1) write_bits(1);
+        }
         if (TAB == kLds && p.rounds > 0) {
             // (the words of the first part's rounds have been read; they are still in the registers in a short run)
             if (phase == 1 && p.rounds > kRegisters * per_register) {
@@ -632,7 +721,10 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
             if (mine && row < p.N) lds_put(base + own_at(p, row) + (vec & wv_mask) * 16, kept[phase][k]);
         }
         lds_barrier();
-        if (p.rounds > 0) read_words(0);
+        if (p.rounds > 0) {
+            read_words(0);
+            read_bits(0);
+        }
 
         if constexpr (DIST)
             if (p.dist_before) distortion(0, seg, -1);
@@ -764,12 +856,13 @@ __device__ __forceinline__ void write_place(const GridSchedule &s, const GridPla
 }
 
 // Blocks 0 .. rounds-1: round r = blockIdx.x of the tables (entries, moves, terms).  Blocks
-// after that, one for each pass: the final places, and for the first pass the flags of the local step; under group-skip schedules those come from mean_places_kernel.
+// after that, one for each pass: the final places; under group-skip schedules those come from mean_places_kernel.
 __global__ __launch_bounds__(kPlanThreads) void mean_plan_kernel(GridSchedule s, GridPlan p, MeanTables o)
 {
     __shared__ uint16_t source[kGridMaxPeers];                // where a peer's value is, in 16 bytes of LDS
     __shared__ uint16_t candidates[kGridMaxPeers];
     __shared__ uint32_t bits_now[kGridMaxPeers / 2], bits_before[kGridMaxPeers / 2];
+    __shared__ uint32_t o_rows[kPlanThreads];                 // plan.bits: the two rows that a thread moves, 12 bits each
     __shared__ int32_t sums[64];
     const int32_t N = s.N, M = s.M, groups = N / M, tid = threadIdx.x;
     if (static_cast<int32_t>(blockIdx.x) >= s.rounds) {
@@ -802,6 +895,7 @@ __global__ __launch_bounds__(kPlanThreads) void mean_plan_kernel(GridSchedule s,
     const bool follows = within > 0;                          // the pass has a round before this one
     bool was[kPerThread], is[kPerThread];
     for (int32_t g = tid; g < groups; g += kPlanThreads) bits_now[g] = bits_before[g] = 0;
+    o_rows[tid] = 0;
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
         const int32_t i = tid + k * kPlanThreads;
@@ -854,7 +948,17 @@ __global__ __launch_bounds__(kPlanThreads) void mean_plan_kernel(GridSchedule s,
     __syncthreads();
     const int32_t width = kPositions * p.split;
     uint16_t *entries = reinterpret_cast<uint16_t *>(o.entries) + static_cast<int64_t>(r) * groups * width;
-    for (int32_t q = tid; q < groups * width; q += kPlanThreads) {
+    if (p.bits)
+        for (int32_t g = tid; g < groups; g += kPlanThreads) {
+            // (who was averaged in the round before, by this round's groups)
+            uint32_t was_bits = 0;
+            for (int32_t j = 0; j < M; ++j) {
+                const int32_t i = g / p.S[axis] * p.S[axis] * M + g % p.S[axis] + j * p.S[axis];
+                was_bits |= static_cast<uint32_t>(source[i] != static_cast<uint16_t>(own_at(p, i) >> 4)) << j;
+            }
+            o.entries[static_cast<int64_t>(r) * groups + g] = bits_now[g] | was_bits << 16;
+        }
+    for (int32_t q = tid; !p.bits && q < groups * width; q += kPlanThreads) {
         const int32_t g = q / width, j = q % width, S = p.S[axis];
         const bool on = (bits_now[g] >> j) & 1u;              // (positions past the group are never set)
         const uint32_t at = on ? source[g / S * S * M + g % S + j * S] : static_cast<uint32_t>(p.zero_at) >> 4;
@@ -876,7 +980,16 @@ __global__ __launch_bounds__(kPlanThreads) void mean_plan_kernel(GridSchedule s,
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
         const int32_t i = tid + k * kPlanThreads;
-        if (moves[k]) o.moves[static_cast<int64_t>(r) * N + rank[k]] = source[i] | static_cast<uint32_t>(own_at(p, i) >> 4) << 16;
+        if (!moves[k]) continue;
+        o.moves[static_cast<int64_t>(r) * N + rank[k]] = source[i] | static_cast<uint32_t>(own_at(p, i) >> 4) << 16;
+        if (p.bits && rank[k] < 2 * p.threads) atomicOr(&o_rows[rank[k] % p.threads], static_cast<uint32_t>(i) << (rank[k] / p.threads * 12));
+    }
+    if (p.bits) {
+        __syncthreads();
+        for (int32_t t = tid; t < p.threads; t += kPlanThreads) {
+            reinterpret_cast<uint16_t *>(o.move_rows)[2 * (static_cast<int64_t>(r / 2) * p.threads + t) + r % 2] = static_cast<uint16_t>(o_rows[t] & 0xffffu);
+            reinterpret_cast<uint8_t *>(o.move_bytes)[4 * (static_cast<int64_t>(r / 4) * p.threads + t) + r % 4] = static_cast<uint8_t>(o_rows[t] >> 16);
+        }
     }
     if (o.terms == nullptr) return;
     uint32_t *terms = o.terms + static_cast<int64_t>(r) * (N + groups);
@@ -932,6 +1045,7 @@ namespace {
 // two rounds' places and moves, and the terms of a distortion
 int64_t mean_words_bytes(const GridPlan &p, bool tables, bool distortions)
 {
+    if (p.bits) return 8 * p.groups;                         // (two rounds' bits)
     return tables && p.part >= kLeastLdsPart ? (distortions ? 16ll : 12ll) << p.words_shift : 0;
 }
 }  // namespace
@@ -969,7 +1083,9 @@ typedef void (*mean_kernel_t)(char *, GridPlan);
 
 template <int DT, int SPLIT, int HALF, int TAB> mean_kernel_t pick_mode(bool nt, bool dist)
 {
-    if constexpr (DT == 1 && TAB == kLds) return nt ? mean_rounds_kernel<DT, SPLIT, HALF, true, false, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, false, false, TAB>;
+    // (rows of less than a cache line are never streamed)
+    if constexpr (TAB == kAheadOnly) return dist ? mean_rounds_kernel<DT, SPLIT, HALF, false, true, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, false, false, TAB>;
+    else if constexpr (DT == 1 && TAB == kLds) return nt ? mean_rounds_kernel<DT, SPLIT, HALF, true, false, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, false, false, TAB>;
     else
     return nt ? (dist ? mean_rounds_kernel<DT, SPLIT, HALF, true, true, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, true, false, TAB>)
               : (dist ? mean_rounds_kernel<DT, SPLIT, HALF, false, true, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, false, false, TAB>);
@@ -979,6 +1095,9 @@ template <int DT, int SPLIT> mean_kernel_t pick_tables(const GridPlan &p, bool d
 {
     const bool nt = p.streaming != 0, wide = p.part >= kLeastLdsPart;
     if (p.entries != nullptr) {
+        if constexpr (SPLIT == 2)
+            if (p.bits) return dist ? nullptr : p.phases == 1 ? mean_rounds_kernel<DT, 2, 0, false, false, kBits> : mean_rounds_kernel<DT, 2, 1, false, false, kBits>;
+        if (p.bits) return nullptr;
         if (wide && DT == 1 && dist) return nullptr;         // (choose_means: too few registers)
         if (p.phases == 1) return wide ? pick_mode<DT, SPLIT, 0, kLds>(nt, dist) : pick_mode<DT, SPLIT, 0, kAheadOnly>(nt, dist);
         return wide ? pick_mode<DT, SPLIT, 32, kLds>(nt, dist) : p.part == 16 ? pick_mode<DT, SPLIT, 1, kAheadOnly>(nt, dist) : nullptr;

@@ -220,6 +220,7 @@ struct GridPlan {
     // means != 0: the kernel of mean_rounds.hip, and where its LDS holds what
     int32_t means;
     int32_t split;                   // lanes that share a group
+    int32_t bits;                    // 1 = who takes part comes as bits instead of places
     int32_t part;                    // bytes of a row in LDS
     int32_t means_at, means_bytes, zero_at, rcp_at, words_at;
     int32_t words_shift;             // log2 of N / 2: 32-bit words that a round's places take
@@ -238,7 +239,7 @@ struct GridPlan {
     double *partials;                // [rounds + 1][tiles * phases], of this pass, or nullptr (no distortion wanted)
     uint64_t dist_after;             // bit r: the distortion after round r of the pass is wanted
     // means != 0, with failures: this pass's part of the tables below
-    const uint32_t *entries, *moves, *terms;
+    const uint32_t *entries, *moves, *move_rows, *move_bytes, *terms;
     const int32_t *move_counts, *term_counts;
     const uint16_t *places;
 };
@@ -246,6 +247,7 @@ struct GridPlan {
 struct GridAsk {
     bool absent = false;             // somebody may be (a failure schedule)
     bool local_step = false;         // it starts with one
+    bool refresh = false;            // returning peers copy another one
     bool distortions = false;        // they are wanted
     int32_t rounds = 0;
 };
@@ -273,8 +275,12 @@ hipError_t launch_grid_plan(const GridSchedule &s, const GridTables &tables, hip
 
 // The same for the kernel of mean_rounds.hip.  Places are LDS addresses in units of 16 bytes.
 struct MeanTables {
-    uint32_t *entries;               // [rounds][groups][split][4]: places of a group's positions, 13 bits of 16 each, and its count
+    uint32_t *entries;               // [rounds][groups][split][4]: places of a group's positions, 13 bits of 16 each, and its count;
+                                     // plan.bits: [rounds][groups]: who takes part | who was averaged in the round before << 16
     uint32_t *moves;                 // [rounds][N]: from | to << 16
+    // plan.bits, [rounds / 16 up][8 or 4][threads]: the rows of moves t and t + threads, 12 bits each, the lower 16 bits
+    // of two rounds to a word and the upper 8 of four
+    uint32_t *move_rows, *move_bytes;
     uint32_t *terms;                 // [rounds][N + groups]: place | weight << 16; nullptr = no distortion wanted
     int32_t *move_counts, *term_counts;      // [rounds]
     uint16_t *places;                // [passes][place_stride]: where a row's value ends, 0xffff = not stored
