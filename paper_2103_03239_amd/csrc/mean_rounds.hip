@@ -724,6 +724,8 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
         if (p.rounds > 0) {
             read_words(0);
             read_bits(0);
+            // (the first round writes the third's over what is read here; later ones read a barrier before they are written over)
+            if constexpr (TAB == kLds || TAB == kBits) lds_barrier();
         }
 
         if constexpr (DIST)

@@ -51,6 +51,12 @@ FAILURES = [
     (16, 3, 17, 1, 0.7, 4, False, False, True),          # more than two moves a thread
     (16, 3, 40, 1, 0.2, 6, True, False, False),
     (16, 3, 9, 0, 0.01, 5, True, True, False),
+    # many tiles: blocks of a compute unit out of step, their waves too
+    (16, 2, 40_000, 0, 0.1, 6, False, False, True),
+    (16, 2, 80_001, 1, 0.1, 7, False, False, False),
+    (32, 2, 12_000, 0, 0.1, 6, False, False, False),
+    (8, 3, 24_000, 1, 0.1, 6, False, False, False),
+    (16, 3, 8_192, 0, 0.1, 5, False, False, False),
 ]
 
 
