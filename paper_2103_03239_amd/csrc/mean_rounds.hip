@@ -35,6 +35,8 @@
 //   16 x 16 x 16 x 131,072 bfloat16, 6 rounds with refresh       1.12 -> 0.87 ms
 //   16 x 16 x 16 x 262,144 bfloat16, 12 rounds, nobody absent    1.98 -> 1.48 ms
 //   the same with 10 % absent                                    2.09 -> 1.90
+// Next to a second part of the tile few of the 128 registers are free: the two-part kernels with the distortion keep
+// 32 to 190 bytes a lane in scratch (and are still ahead), the others none.
 // A round's vector instructions count as much as its LDS traffic, and a load from memory in a round costs
 // more than either: a compute unit returns loads in order, so it waits behind the tile that its other
 // block is loading (see the tables in the kernel).
