@@ -30,7 +30,7 @@
 // 4 x 4 x 4 peers x 25,557,032 binary32, 6 rounds 2.92 -> 2.56 ms; 32 x 32 x 4,194,304, 8 rounds
 // 10.6 -> 9.3 ms; 16 x 16 x 16 x 262,144 bfloat16, 12 rounds 5.15 -> 2.08 ms (one pass instead
 // of six over planes of 256 rows; 32-byte rows move at 3.7 TB/s, see tile_of).  Longer runs of groups of more than 4
-// are taken over by the kernel of mean_rounds.hip (choose_means).
+// are taken over by the kernel of mean_rounds.hip (choose_means in grid_plan.h).
 //
 // Row ends and alignment.  Rows need no alignment beyond the element's: the loads and stores are
 // 128-bit accesses at element-aligned addresses.  Where a row does not end on a 16-byte boundary
@@ -499,10 +499,6 @@ __global__ __launch_bounds__(256) void grid_skip_flags_kernel(GridSchedule s, Gr
 
 }  // namespace
 
-namespace {
-int64_t bitmap_bytes(int32_t M) { return M <= 16 ? 2 : 4; }
-}  // namespace
-
 hipError_t launch_grid_plan(const GridSchedule &s, const GridTables &tables, hipStream_t stream)
 {
     if (s.rounds <= 0) return hipSuccess;
@@ -511,141 +507,6 @@ hipError_t launch_grid_plan(const GridSchedule &s, const GridTables &tables, hip
     if (s.group_skip)
         grid_skip_flags_kernel<<<dim3((s.N + 255) / 256), dim3(256), 0, stream>>>(s, tables);
     return hipGetLastError();
-}
-
-namespace {
-// One mean per group (mean_rounds.hip) or M copies of it (the kernel above)?  MI355X, the former
-// against the latter, us:
-//   nobody ever absent: ahead from 4 rounds on (16 x 16, 200 MB binary32, 6 rounds 70 : 80; 24 x 24, 1.5 GB bfloat16
-//     887 : 1,234; 32 x 32, 16 GB, 16 rounds 10,450 : 14,200), behind by up to 11 % for 2 or 3 (8 x 8 x 8, 1.5 GB
-//     bfloat16 715 : 643) and for small states of 8 x 8 peers in bfloat16 (8 MB, 8 rounds 12.8 : 12.5);
-//     with distortions ahead everywhere (16 x 16, 1 GB binary32, 5 rounds 602 : 860).  Groups of 2 to 4 save little.
-//   with failures, whose tables cost a launch and a wait: ahead from 5 rounds (4 on more than 1024 peers) of
-//     states beyond 32 MB on (32 x 32, 16 GB, 8 rounds 8,110 : 9,320, 4 rounds of 200 MB 85 : 83; 16 x 16 x 16, 1.5 GB
-//     bfloat16, 4 rounds 911 : 1,222, 16 rounds 1,570 : 2,640; 8 MB, 8 rounds 31 : 28), and not for 8 x 8 peers, whose passes
-//     wait for memory (1.5 GB binary32, 8 rounds 652 : 631).  Places are 8 to a lane: groups of 8, 16 or 32.  The
-//     distortion of bfloat16 rows of 64 bytes and more spills (16 x 16, 1 GB, 5 rounds 1,616 : 1,341).
-// A local step would take its registers: not with one.
-bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
-{
-    const int64_t state = p->N * p->row_bytes;
-    const bool large = state >= 32000000;
-    if (p->M <= 4 || ask.local_step) return false;
-    if (ask.absent) {
-        if (!large || p->N < 256 || ask.rounds < (p->N > 1024 ? 4 : 5)) return false;
-    } else if (!ask.distortions) {
-        if (ask.rounds < 4 || (p->M <= 8 && p->N <= 64 && esize == 2 && !large)) return false;
-    }
-    const bool cached = static_cast<double>(p->N) * p->row_bytes <= 256.0 * (1 << 20);
-    for (int32_t wb = p->Wb, phases = p->phases; phases <= 2 && wb / phases >= 16;) {
-        GridPlan q = *p;
-        const int32_t part = wb / phases;
-        q.Wb = wb;
-        q.phases = phases;
-        const int64_t threads = (q.N * part / (16 * kPhaseSlots) + 63) / 64 * 64, waves = threads / 64 < 1 ? 1 : threads / 64;
-        q.bits = ask.absent && !ask.refresh && !ask.distortions && part == 16 && q.M == 16 && 2 * q.groups == threads ? 1 : 0;
-        const int64_t bytes = lay_out_means(&q, part, ask.absent, ask.distortions);
-        if (ask.absent && (q.M != 8 * q.split || (phases == 2 && part == 32) || (ask.distortions && esize == 2 && part >= 64))) return false;
-        if (bytes + (ask.distortions ? (waves * (part / esize) + 5 * waves) * 8 : 0) <= kLdsPerBlock) {
-            q.red_offset = static_cast<int32_t>(bytes);
-            *p = q;
-            return true;
-        }
-        // (a state in the last-level cache: narrower tiles, see below; 8 x 8 x 8 peers, 8 MiB, 3 rounds: two parts 13.2 us)
-        if (cached && phases == 1 && wb > 32) wb >>= 1;
-        else ++phases;
-    }
-    return false;
-}
-}  // namespace
-
-bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
-               const GridAsk &ask, GridPlan *out)
-{
-    const int64_t esize = dtype == 0 ? 4 : 2;
-    GridPlan p{};
-    p.valid_bytes = P * esize;
-    p.row_bytes = row_stride * esize;
-    if (N > kGridMaxPeers || M > 32 || p.valid_bytes < 16) return false;
-    p.N = static_cast<int32_t>(N);
-    p.M = M;
-    p.d = d;
-    p.groups = static_cast<int32_t>(N / M);
-    p.full_bitmap = M == 32 ? ~0u : (1u << M) - 1u;
-    p.axis0 = static_cast<int32_t>(t0 % d);
-    int32_t S = 1;
-    const auto magic = [](int64_t n) { return static_cast<uint32_t>(((int64_t(1) << 32) + n - 1) / n); };
-    p.magic_m = magic(M);
-    // Widest tile: rows of 512 bytes beat 1 KiB on 64 rows (2.55 against 2.73 ms), 256 bytes beat
-    // 128 on 256 rows (0.40 against 0.46 ms for 3 rounds).
-    int32_t wb = 1024;
-    while (wb > 256 && N * wb > 32 * 1024) wb >>= 1;
-    while (wb > 128 && N * wb > 64 * 1024) wb >>= 1;
-    while (wb > 32 && N * wb > 128 * 1024) wb >>= 1;
-    // A state of up to 256 MiB stays in the last-level cache and is bound by latency more than by
-    // the width of its accesses: 256 bytes at most (250 MiB, 4 x 4 x 4 peers: 103 against 109 us at
-    // 512), one part in LDS for up to 1024 peers (32 x 32, 4 rounds: 8 MiB 22 -> 14 us, 250 MiB
-    // 115 -> 97) and, above, while that gives a compute unit no second tile to run (16 x 16 x 16,
-    // 6 rounds: 16 MiB 46 -> 29 us, but 128 MiB 96 -> 127; rows of whole vectors only, since a
-    // last tile of less than 16 bytes takes 16 from its neighbour, which must have more) ...
-    const double state_bytes = static_cast<double>(N) * p.row_bytes;
-    const bool cached = state_bytes <= 256.0 * (1 << 20);
-    if (cached && wb > 256) wb = 256;
-    if (cached && N * wb > 64 * 1024 && (N <= 1024 || (p.valid_bytes % 16 == 0 && p.valid_bytes <= 256 * wb))) wb >>= 1;
-    // ... and narrow tiles, so that every compute unit gets several blocks (8 MiB, 4 x 4 x 4 peers,
-    // 6 rounds: 15.3 -> 13.3 us; 5 x 5 x 5, 32 MiB: 31.9 -> 25.1), but not below 4 KiB or one
-    // cache line of 256 rows and more.
-    const int32_t least = N >= 256 ? 128 : 64;
-    while (wb > least && N * wb > 4096 && (p.valid_bytes + wb - 1) / wb < 2048) wb >>= 1;
-    while (wb > 32 && wb / 2 >= p.valid_bytes) wb >>= 1;
-    p.Wb = wb;
-    p.phases = N * wb > 72 * 1024 ? 2 : 1;
-    p.means = choose_means(&p, esize, ask) ? 1 : 0;
-    wb = p.Wb;
-    p.wv_shift = 0;
-    while ((16 << p.wv_shift) < wb) ++p.wv_shift;
-    const int32_t part = wb / p.phases;              // bytes of a row in LDS
-    p.threads = static_cast<int32_t>((N * part / (16 * kPhaseSlots) + 63) / 64 * 64);
-    if (p.threads < 64) p.threads = 64;
-    if (p.threads > (p.phases == 1 ? 1024 : 512)) return false;
-    if (!p.means) {
-        p.pad = part < 256 && M >= 8 && (M * part) % 256 == 0 ? part : 0;
-        p.tile_bytes = static_cast<int32_t>(N * part + p.groups * p.pad);
-    }
-    S = 1;
-    for (int32_t a = 0; a < d; ++a) {
-        p.S[a] = S;
-        p.magic_s[a] = S > 1 ? magic(S) : 0;
-        p.pad_step[a] = a == 0 ? 0 : S / M * p.pad;
-        S *= M;
-    }
-    p.tiles = (p.valid_bytes + wb - 1) / wb;
-    // Tiles of whole cache lines are not seen again: non-temporal (256 rows of 4 MiB: 5.5 TB/s
-    // against 5.1 with ordinary accesses).  Others share lines with their neighbours in the row.
-    // Runs per die: where tiles share lines, and for rows of one line (1024 rows of 16 MiB, 8
-    // rounds: 9.43 -> 9.33 ms, 4 rounds: 10.2 -> 8.3 ms); wider ones lose 1 % to them.
-    const bool whole_lines = wb >= 128 && reinterpret_cast<uintptr_t>(X) % 128 == 0 && p.row_bytes % 128 == 0;
-    // States in the last-level cache stay there with ordinary accesses (16 x 16 peers, 4 rounds:
-    // 128 MiB 58.6 -> 52.8 us, 250 MiB 113 -> 89); below the L2s' 32 MiB the non-temporal ones are
-    // ahead again (16 MiB: 12.5 against 13.8), they leave no dirty lines to be written back at the end.
-    p.streaming = whole_lines && (!cached || state_bytes <= 24.0 * (1 << 20)) ? 1 : 0;
-    p.die_run = whole_lines && wb > 128 ? 1 : 32;
-    if (p.tiles < 8 * p.die_run) p.die_run = p.tiles >= 16 ? static_cast<int32_t>(p.tiles / 8) : 1;
-    // rounds of one pass: as many bitmaps as fit next to the tile
-    const int64_t waves = p.threads / 64, columns = part / esize;
-    if (p.means) {
-        // (a sum per wave for every distortion)
-        const int64_t sums = (kLdsPerBlock - p.red_offset - waves * columns * 8) / (8 * waves) - 1;
-        p.max_rounds = static_cast<int32_t>(ask.distortions && sums < 64 ? sums : 64);
-        *out = p;
-        return p.max_rounds >= 4;
-    }
-    const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + waves) * 8 - kRcpBytes - 64;
-    const int64_t most = room / (static_cast<int64_t>(p.groups) * bitmap_bytes(M));
-    p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
-    if (p.max_rounds < 4) return false;      // (2^12 peers; 24 x 24 in tiles of 128 bytes with 8 columns to a vector)
-    *out = p;
-    return true;
 }
 
 namespace {

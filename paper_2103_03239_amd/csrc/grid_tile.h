@@ -12,10 +12,6 @@
 
 namespace moshpit {
 
-constexpr int kPhaseSlots = 8;               // 16-byte slots of the tile in LDS per thread
-constexpr int kLdsPerBlock = 80 * 1024;      // two blocks share a compute unit
-constexpr int64_t kGridMaxPeers = 4096;
-
 template <int DT> __device__ __forceinline__ void widen16(const u32x4 &m, float (&f)[DT == 0 ? 4 : 8])
 {
     if constexpr (DT == 0) {

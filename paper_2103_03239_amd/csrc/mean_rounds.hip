@@ -49,9 +49,7 @@ namespace moshpit {
 namespace {
 
 constexpr int kPositions = 8;                // of a group, per lane
-constexpr int kMaxGroup = 32;
 constexpr int kClosed = 0, kLds = 1, kAheadOnly = 2, kBits = 3;
-constexpr int32_t kLeastLdsPart = 64;        // bytes of a row in LDS from which on a round's tables take one register or less
 constexpr int kRegisters = 8;                // of a thread for a table
 constexpr int kAhead = 3;                    // rounds that the tables are read ahead
 constexpr uint32_t kPlaceMask = 0x1fff1fffu; // a place has 13 bits; the other 3 of a lane's first two hold the group's count
@@ -1032,8 +1030,6 @@ __global__ __launch_bounds__(256) void mean_places_kernel(GridSchedule s, GridPl
 
 }  // namespace
 
-int64_t mean_place_stride(const GridPlan &p) { return static_cast<int64_t>(p.threads) * kPhaseSlots * p.phases; }
-
 hipError_t launch_mean_plan(const GridSchedule &s, const GridPlan &plan, const MeanTables &tables, hipStream_t stream)
 {
     if (s.rounds <= 0) return hipSuccess;
@@ -1043,42 +1039,6 @@ hipError_t launch_mean_plan(const GridSchedule &s, const GridPlan &plan, const M
     if (s.group_skip)
         mean_places_kernel<<<dim3(static_cast<uint32_t>(passes * ((s.N + 255) / 256))), dim3(256), 0, stream>>>(s, plan, tables);
     return hipGetLastError();
-}
-
-namespace {
-// two rounds' places and moves, and the terms of a distortion
-int64_t mean_words_bytes(const GridPlan &p, bool tables, bool distortions)
-{
-    if (p.bits) return 8 * p.groups;                         // (two rounds' bits)
-    return tables && p.part >= kLeastLdsPart ? (distortions ? 16ll : 12ll) << p.words_shift : 0;
-}
-}  // namespace
-
-// The LDS of a tile of p.N rows x `part` bytes with its two arrays of means; p.part, p.pad, p.split and the
-// places in LDS are set.  tables: somebody may be absent; distortions: they are wanted.  Returns the bytes before the distortion's sums.
-int64_t lay_out_means(GridPlan *p, int32_t part, bool tables, bool distortions)
-{
-    p->part = part;
-    p->split = p->M <= 8 ? 1 : p->M <= 16 ? 2 : 4;
-    p->pad = part < 256 && p->M >= 8 && (p->M * part) % 256 == 0 ? part : 0;
-    const auto padded_bytes = [&](int64_t rows) { return rows * part + (rows + p->M - 1) / p->M * p->pad; };
-    p->tile_bytes = static_cast<int32_t>(padded_bytes(p->N));
-    p->means_at = p->tile_bytes;
-    p->means_bytes = static_cast<int32_t>(padded_bytes(p->groups));
-    p->zero_at = p->means_at + 2 * p->means_bytes;
-    const int64_t pad = p->pad;
-    int64_t S = 1;
-    for (int32_t a = 0; a < p->d; ++a) {
-        // groups of the round before that hold the rows of a group of this axis: step from row to row
-        const int64_t groups_step = a > 0 ? S / p->M : p->d > 1 ? 1 : 0;
-        p->mean_step[a] = static_cast<int32_t>(groups_step * part + groups_step / p->M * pad);
-        S *= p->M;
-    }
-    p->rcp_at = p->zero_at + part;
-    p->words_at = p->rcp_at + 4 * (kMaxGroup + 4);
-    p->words_shift = 0;
-    while (2 << p->words_shift < p->N) ++p->words_shift;
-    return p->words_at + mean_words_bytes(*p, tables, distortions);
 }
 
 namespace {

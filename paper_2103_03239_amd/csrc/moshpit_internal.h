@@ -7,6 +7,8 @@
 #include <type_traits>
 #include <stdint.h>
 
+#include "grid_plan.h"
+
 namespace moshpit {
 
 // Per-device launch facts, looked up once per device and kept in a table guarded by a
@@ -200,59 +202,7 @@ bool plan_fused(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t r
 hipError_t launch_fused_rounds(void *X, int dtype, const FusedPlan &plan, const uint8_t *masks,
                                hipStream_t stream);
 
-// Several rounds on a whole grid of up to 4096 peers in one pass over HBM (grid_rounds.hip).
-// plan_grid: does the shape qualify, and how is it cut into tiles (a pure function of its
-// arguments; depends on t0 through the first axis only).  The caller fills in the rest.
-constexpr int kGridMaxAxes = 12;
-struct GridPlan {
-    int32_t N, M, d, groups;
-    int32_t Wb, wv_shift;            // bytes of a row per tile; log2 of its 16-byte vectors
-    int32_t threads, tile_bytes, lds_bytes, red_offset;
-    int32_t pad;                     // LDS bytes added after every M rows (bank conflicts of axis 0)
-    int32_t die_run;                 // consecutive tiles per die (1 = tiles dealt in order)
-    int32_t streaming;               // 1 = non-temporal loads and stores
-    int32_t phases, max_rounds;      // column parts of a tile (1 or 2); most rounds of one pass
-    int32_t axis0;                   // axis of the pass's first round
-    uint32_t full_bitmap, magic_m;
-    int32_t S[kGridMaxAxes], pad_step[kGridMaxAxes];
-    uint32_t magic_s[kGridMaxAxes];
-    int64_t row_bytes, valid_bytes, tiles;
-    // means != 0: the kernel of mean_rounds.hip, and where its LDS holds what
-    int32_t means;
-    int32_t split;                   // lanes that share a group
-    int32_t bits;                    // 1 = who takes part comes as bits instead of places
-    int32_t part;                    // bytes of a row in LDS
-    int32_t means_at, means_bytes, zero_at, rcp_at, words_at;
-    int32_t words_shift;             // log2 of N / 2: 32-bit words that a round's places take
-    int32_t mean_step[kGridMaxAxes];      // bytes between the means that the rows of a group were given by the round before
-    // filled in by the caller
-    int32_t rounds;
-    int32_t dist_before, refresh_first;   // distortion before the first round; refresh before it
-    float gamma;
-    float step_zero;                 // added to the result of a binary32 step: +0 or -0
-    const uint32_t *bitmaps;         // [rounds][groups], device; nullptr = everybody takes part
-    const uint8_t *flags;            // [N], device: bit 0 written back, bit 1 takes the local step; nullptr = 3
-    const uint32_t *copies;          // [rounds][N] pairs donor << 16 | returning peer; nullptr = no refresh
-    const int32_t *copy_counts;      // [rounds]
-    const char *grad;                // gradients (SGD) or nullptr
-    int64_t grad_row_bytes;
-    double *partials;                // [rounds + 1][tiles * phases], of this pass, or nullptr (no distortion wanted)
-    uint64_t dist_after;             // bit r: the distortion after round r of the pass is wanted
-    // means != 0, with failures: this pass's part of the tables below
-    const uint32_t *entries, *moves, *move_rows, *move_bytes, *terms;
-    const int32_t *move_counts, *term_counts;
-    const uint16_t *places;
-};
-// What a run asks of its passes.
-struct GridAsk {
-    bool absent = false;             // somebody may be (a failure schedule)
-    bool local_step = false;         // it starts with one
-    bool refresh = false;            // returning peers copy another one
-    bool distortions = false;        // they are wanted
-    int32_t rounds = 0;
-};
-bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
-               const GridAsk &ask, GridPlan *out);
+// Queue one pass of a plan of plan_grid (grid_plan.h).
 hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStream_t stream);
 // The pass's distortions that were wanted, out[0] = before it .. out[rounds] = after its last round.
 hipError_t launch_grid_dist(const GridPlan &plan, double *out, hipStream_t stream);
@@ -288,8 +238,6 @@ struct MeanTables {
     int64_t place_stride;
     int32_t pass_rounds;             // round r of the tables is round r mod pass_rounds of its pass
 };
-int64_t lay_out_means(GridPlan *p, int32_t part, bool tables, bool distortions);
-int64_t mean_place_stride(const GridPlan &p);
 hipError_t launch_mean_plan(const GridSchedule &s, const GridPlan &plan, const MeanTables &tables, hipStream_t stream);
 hipError_t launch_mean_rounds(void *X, int dtype, const GridPlan &plan, hipStream_t stream);
 

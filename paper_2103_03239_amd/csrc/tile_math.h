@@ -7,13 +7,13 @@
 #include <stdint.h>
 
 #include "bf16_round.h"
+#include "grid_plan.h"
 #include "row_vec.h"
 
 namespace moshpit {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kRcpBytes = 272;       // 65 reciprocals, padded to a multiple of 16 bytes
 constexpr int kNormalOrZero = 0x168;  // v_cmp_class mask: -normal, -0, +0, +normal
 
 // Block barrier that orders LDS traffic only.  __syncthreads() also waits for
