@@ -38,6 +38,7 @@ struct GridPlan {
     int32_t part;                    // bytes of a row in LDS
     int32_t means_at, means_bytes, zero_at, rcp_at, words_at;
     int32_t words_shift;             // log2 of N / 2: 32-bit words that a round's places take
+    int32_t dist_window;             // distortions of a part of the tile whose sums LDS holds at a time
     int32_t mean_step[kGridMaxAxes];      // bytes between the means that the rows of a group were given by the round before
     // filled in by the caller
     int32_t rounds;
@@ -65,6 +66,13 @@ struct GridAsk {
     bool distortions = false;        // they are wanted
     int32_t rounds = 0;
 };
+
+// Do the sums of a pass's distortions leave LDS in between, when no more of them have room, so that a pass takes 64
+// rounds whatever fits?  On 32 x 32 binary32 peers with failures LDS holds the sums of 9 rounds, and a pass of no more lost to
+// the kernel with M copies of a mean (10 % absent, 1 GB: 10 rounds 2.37 : 1.95 ms, 40 rounds 7.45 : 6.43; so 1.81 and
+// 4.78 ms).  Elsewhere the test in every round costs more (2 to 6 %) than it gives: 16 x 16 binary32 takes 24 rounds a pass
+// with failures (3 GB, 40 rounds 10.8 : 14.7 ms), 6 x 6 x 6 bfloat16 10 with nobody absent (1 GB, 40 rounds 8.6 : 11.0).
+constexpr bool sums_leave_in_between(int dtype, int32_t split, bool tables_in_lds) { return dtype == 0 && split == 4 && tables_in_lds; }
 
 // ---- LDS of the kernel that keeps one mean per group ---------------------------------------------
 
@@ -228,8 +236,9 @@ inline bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int
     const int64_t waves = p.threads / 64, columns = part / esize;
     if (p.means) {
         // (a sum per wave for every distortion)
-        const int64_t sums = (kLdsPerBlock - p.red_offset - waves * columns * 8) / (8 * waves) - 1;
-        p.max_rounds = static_cast<int32_t>(ask.distortions && sums < 64 ? sums : 64);
+        const int64_t sums = (kLdsPerBlock - p.red_offset - waves * columns * 8) / (8 * waves);
+        p.dist_window = static_cast<int32_t>(sums < 65 ? sums : 65);
+        p.max_rounds = ask.distortions && !sums_leave_in_between(dtype, p.split, ask.absent && part >= kLeastLdsPart) ? p.dist_window - 1 : 64;
         *out = p;
         return p.max_rounds >= 4;
     }

@@ -560,7 +560,10 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
     // its columns of s2 - s1^2 / N, s1 and s2 the sums of the differences from one peer's row and of their
     // squares in binary64 (the differences are exact).  Thread (k, vector c) takes every
     // (T >> wv_shift)-th term.  Column sums of the waves meet in `red`; what a wave adds to
-    // the total waits in `tot` for the end of the tile's rounds.
+    // the total waits in `tot` for the end of the tile's rounds, or, kWindow, until LDS has no room for more: entries
+    // held .. held + dist_window - 1 then (entry 0: before the first round).
+    constexpr bool kWindow = DIST && sums_leave_in_between(DT, SPLIT, TAB == kLds);
+    [[maybe_unused]] int32_t held = 0;
     double *red = reinterpret_cast<double *>(lds + p.red_offset);
     [[maybe_unused]] auto distortion = [&](int i, int32_t seg, int32_t r) {
         if constexpr (DIST) {
@@ -649,7 +652,22 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                 s2 -= t1 * t1 / static_cast<double>(p.N);          // (columns outside the tile hold 0)
             }
             s2 = lanes_sum(s2, 0);
-            if (lane == 0) red[waves * columns + (r + 1) * waves + wave] = s2;
+            if (lane == 0) red[waves * columns + (r + 1 - held) * waves + wave] = s2;
+        }
+    };
+    // Entries held .. end - 1 of the part (its tile and number: part_at) leave LDS.
+    [[maybe_unused]] auto write_distortions = [&](int32_t end, int64_t part_at) {
+        if constexpr (DIST) {
+            const int32_t waves = T >> 6;
+            const double *tot = red + waves * (NE << wv_shift);
+            lds_barrier();
+            for (int32_t e = held + tid; e < end; e += T)
+                if (e == 0 ? p.dist_before != 0 : ((p.dist_after >> (e - 1)) & 1u) != 0) {
+                    double sum = 0.0;
+                    for (int32_t k = 0; k < waves; ++k) sum += tot[(e - held) * waves + k];
+                    p.partials[e * p.tiles * PHASES + part_at] = sum;
+                }
+            if constexpr (kWindow) held = end;
         }
     };
 
@@ -728,6 +746,7 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
             if constexpr (TAB == kLds || TAB == kBits) lds_barrier();
         }
 
+        if constexpr (kWindow) held = 0;
         if constexpr (DIST)
             if (p.dist_before) distortion(0, seg, -1);
         int32_t axis = p.axis0;
@@ -743,20 +762,12 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                 if constexpr (DIST) {
                     if ((p.dist_after >> r) & 1u) distortion(i, seg, r);
                     fetch_round(i, r + kAhead);
+                    if constexpr (kWindow)
+                        if (r + 2 - held == p.dist_window) write_distortions(r + 2, w * PHASES + phase);
                 }
                 axis = axis + 1 == p.d ? 0 : axis + 1;
             }
-        if constexpr (DIST) {
-            const int32_t waves = T >> 6;
-            const double *tot = red + waves * (NE << wv_shift);
-            lds_barrier();
-            for (int32_t e = tid; e <= p.rounds; e += T)
-                if (e == 0 ? p.dist_before != 0 : ((p.dist_after >> (e - 1)) & 1u) != 0) {
-                    double sum = 0.0;
-                    for (int32_t k = 0; k < waves; ++k) sum += tot[e * waves + k];
-                    p.partials[e * tiles + w * PHASES + phase] = sum;
-                }
-        }
+        write_distortions(p.rounds + 1, w * PHASES + phase);
         // back into the registers; the next part enters LDS when everybody is done with this one
         // (always read, whoever is stored, so that the registers need not keep what they held before)
         row_ = lds_row;
@@ -1085,7 +1096,7 @@ hipError_t launch_mean_rounds(void *X, int dtype, const GridPlan &plan, hipStrea
     p.red_offset = static_cast<int32_t>(at);
     if (dist) {
         const int64_t waves = p.threads / 64, columns = p.part / (dtype == 0 ? 4 : 2);
-        at += (waves * columns + (p.rounds + 1) * waves) * 8;
+        at += (waves * columns + (p.rounds + 1 < p.dist_window ? p.rounds + 1 : p.dist_window) * waves) * 8;
     }
     p.lds_bytes = static_cast<int32_t>(at);
     if (p.lds_bytes > kLdsPerBlock || p.tiles > 0x7fffffffLL || p.grad != nullptr) return hipErrorInvalidValue;

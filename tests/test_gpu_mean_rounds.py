@@ -13,9 +13,18 @@ from test_gpu_grid_pass import state
 pytestmark = pytest.mark.gpu
 
 
-def wide_stride(N, P, dtype):
-    """Row stride that makes the state 34 MB, so that a failure schedule takes these passes."""
-    return max(P + 3, 34_000_000 // (N * (4 if dtype == 0 else 2)) + 5)
+# Bytes of the whole matrix, rows a multiple of 128 bytes or not (then the matrix starts off them as well):
+# from 32 MB on a failure schedule takes these passes, beyond 256 MiB (no longer in the last-level cache) tiles are wider.
+LAYOUTS = {"odd": (0, False), "lines": (0, True), "34 MB": (34_000_000, False), "300 MB": (300_000_000, False),
+           "300 MB lines": (300_000_000, True)}
+
+
+def layout(N, P, dtype, name):
+    """Row stride and offset, in elements."""
+    least, lines = LAYOUTS[name]
+    es = 4 if dtype == 0 else 2
+    stride = max(P + 3, least // (N * es) + 5)
+    return ((stride * es + 127) // 128 * 128 // es, 0) if lines else (stride | 1, 1)
 
 
 def one_by_one(m, sched, presence, t0, rounds, N, M, d, curve):
@@ -66,9 +75,9 @@ def test_with_failures(M, d, P, dtype, p, rounds, refresh, skip, curve):
     print(f"mean rounds M={M} d={d} P={P} dtype={dtype} p={p} rounds={rounds} refresh={refresh} skip={skip}", flush=True)
     presence = orc.schedule_masks(2, p, seed, 2, N, t0, rounds)
     sched = binding.Schedule(kind=binding.SCHED_REJOIN, p=p, seed=seed, down_rounds=2, group_skip=skip, refresh=refresh)
-    stride = wide_stride(N, P, dtype)
-    bufA, A = state(N, P, stride, 1, dtype, seed)
-    bufB, B = state(N, P, stride, 1, dtype, seed)
+    stride, offset = layout(N, P, dtype, "34 MB")
+    bufA, A = state(N, P, stride, offset, dtype, seed)
+    bufB, B = state(N, P, stride, offset, dtype, seed)
     with binding.Moshpit(N, P, M, d, dtype) as m:
         m.bind_state(A)
         want = one_by_one(m, sched, presence, t0, rounds, N, M, d, curve)
@@ -109,7 +118,7 @@ def test_absent_peers_keep_their_nan_and_infinity_to_themselves(M, d, P, dtype):
     masks[:4, [3, N - 2]] = 0
     sched = binding.Schedule(kind=binding.SCHED_EXPLICIT, explicit_masks=masks)
     print(f"mean rounds, NaN M={M} d={d} P={P} dtype={dtype}", flush=True)
-    stride = wide_stride(N, P, dtype)
+    stride, _ = layout(N, P, dtype, "34 MB")
     _, A = state(N, P, stride, 0, dtype, 5)
     _, B = state(N, P, stride, 0, dtype, 5)
     for X in (A, B):
@@ -132,3 +141,28 @@ def test_absent_peers_keep_their_nan_and_infinity_to_themselves(M, d, P, dtype):
         m.sync()
     # (which of several NaN a sum hands on is not laid down)
     assert torch.equal(A.isnan(), B.isnan()) and torch.equal(A.nan_to_num(7.0, 8.0, 9.0), B.nan_to_num(7.0, 8.0, 9.0))
+
+
+@pytest.mark.parametrize("M,d,P,dtype,where,p,rounds,refresh", [
+    (32, 2, 45, 0, "34 MB", 0.1, 23, False),             # LDS holds 10 of the sums at a time
+    (32, 2, 70, 0, "300 MB lines", 0.1, 23, False),      # in two column parts
+    (32, 2, 70, 0, "300 MB", 0.2, 68, True),             # and two passes
+    (6, 3, 300, 1, "300 MB", 0.0, 25, False),            # 9
+    (16, 2, 259, 0, "300 MB", 0.3, 30, False),           # 24 rounds a pass
+])
+def test_curves_of_more_rounds_than_lds_holds_sums(M, d, P, dtype, where, p, rounds, refresh):
+    N, t0, seed = M ** d, 1, 5
+    print(f"mean rounds, long curve M={M} d={d} P={P} dtype={dtype} {where} p={p} rounds={rounds}", flush=True)
+    presence = orc.schedule_masks(1, p, seed, 0, N, t0, rounds) if p else None
+    sched = binding.Schedule(kind=binding.SCHED_IID, p=p, seed=seed, refresh=refresh) if p else None
+    stride, offset = layout(N, P, dtype, where)
+    bufA, A = state(N, P, stride, offset, dtype, seed)
+    bufB, B = state(N, P, stride, offset, dtype, seed)
+    with binding.Moshpit(N, P, M, d, dtype) as m:
+        m.bind_state(A)
+        want = one_by_one(m, sched, presence, t0, rounds, N, M, d, True)
+        m.bind_state(B)
+        got, _ = m.run(t0, rounds, sched, want_dist=True)
+        m.sync()
+    assert torch.equal(bufA, bufB)
+    assert np.abs(got - want).max() <= 1e-11 * max(want)

@@ -87,7 +87,7 @@ static void check(const GridPlan &p, int dtype, const GridAsk &a)
     if (!p.means) return;
     if (a.local_step) say("local step", p, dtype, a);
     // LDS of a pass of max_rounds rounds with distortions
-    const int64_t waves = p.threads / 64, sums = a.distortions ? (waves * (part / es) + (p.max_rounds + 1) * waves) * 8 : 0;
+    const int64_t waves = p.threads / 64, sums = a.distortions ? (waves * (part / es) + p.dist_window * waves) * 8 : 0;
     if (p.red_offset + sums > kLdsPerBlock || p.red_offset % 8 != 0 || p.zero_at + part > kLdsPerBlock) say("LDS", p, dtype, a);
     if (!a.absent) return;
     // tables: a place has 13 bits, a lane one item of 8 positions, a register a round's words
@@ -101,4 +101,26 @@ static void check(const GridPlan &p, int dtype, const GridAsk &a)
 def test_every_plan_fits_its_kernel(tmp_path):
     """Threads, LDS and tables of every plan are what the kernels assume."""
     out = run_host(tmp_path, FITS)
+    assert out.returncode == 0, out.stdout
+
+
+ROUNDS = SWEEP + r"""
+static void check(const GridPlan &p, int dtype, const GridAsk &a)
+{
+    if (!p.means) return;
+    GridAsk other = a;
+    other.local_step = true;                 // (takes the kernel with M copies of a mean)
+    GridPlan q;
+    const int64_t es = dtype == 0 ? 4 : 2;
+    if (!plan_grid(dtype, p.N, p.M, p.d, p.valid_bytes / es, p.row_bytes / es, reinterpret_cast<void *>(4096), 1, other, &q)) return;
+    // (measured ahead all the same: see sums_leave_in_between)
+    if (p.max_rounds < q.max_rounds && p.max_rounds < (p.M == 6 && p.N == 216 ? 10 : 24)) say("fewer rounds a pass", p, dtype, a);
+}
+"""
+
+
+def test_one_mean_per_group_takes_no_more_passes(tmp_path):
+    """A run does not read and write the state more often because the kernel with one mean per group takes it,
+    but for runs of more than 24 rounds (6 x 6 x 6: 10)."""
+    out = run_host(tmp_path, ROUNDS)
     assert out.returncode == 0, out.stdout
