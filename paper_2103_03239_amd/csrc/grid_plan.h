@@ -11,7 +11,6 @@ constexpr int kPhaseSlots = 8;               // 16-byte slots of the tile in LDS
 constexpr int kLdsPerBlock = 80 * 1024;      // two blocks share a compute unit
 constexpr int64_t kGridMaxPeers = 4096;
 constexpr int kRcpBytes = 272;       // 65 reciprocals, padded to a multiple of 16 bytes
-constexpr int kMaxGroup = 32;
 constexpr int32_t kLeastLdsPart = 64;        // bytes of a row in LDS from which on a round's tables take one register or less
 
 // Several rounds on a whole grid of up to 4096 peers in one pass over HBM (grid_rounds.hip).
@@ -106,15 +105,43 @@ inline int64_t lay_out_means(GridPlan *p, int32_t part, bool tables, bool distor
         S *= p->M;
     }
     p->rcp_at = p->zero_at + part;
-    p->words_at = p->rcp_at + 4 * (kMaxGroup + 4);
+    p->words_at = p->rcp_at + 4 * (32 + 4);
     p->words_shift = 0;
     while (2 << p->words_shift < p->N) ++p->words_shift;
     return p->words_at + mean_words_bytes(*p, tables, distortions);
 }
 
-// ---- which kernel, which tiles ---------------------------------------------------------------------
+// LDS of a pass of `rounds` rounds; tables: p.entries will be set; sums_at: where the distortion's begin.
+inline int64_t means_lds_bytes(const GridPlan &p, bool tables, int32_t rounds, bool dist, int64_t esize, int32_t *sums_at)
+{
+    int64_t at = p.words_at + mean_words_bytes(p, tables, dist);
+    *sums_at = static_cast<int32_t>(at);
+    const int64_t waves = p.threads / 64;
+    if (dist) at += (waves * (p.part / esize) + (rounds + 1 < p.dist_window ? rounds + 1 : p.dist_window) * waves) * 8;
+    return at;
+}
+
+// ---- LDS of the kernel with M copies of a mean ---------------------------------------------------
 
 inline int64_t bitmap_bytes(int32_t M) { return M <= 16 ? 2 : 4; }
+
+inline int64_t copies_lds_bytes(const GridPlan &p, int32_t rounds, bool dist, int64_t esize, int32_t *sums_at)
+{
+    int64_t at = p.tile_bytes + static_cast<int64_t>(rounds) * p.groups * bitmap_bytes(p.M) + p.N;
+    at = (at + 15) / 16 * 16;
+    *sums_at = static_cast<int32_t>(at);
+    if (dist) {
+        const int64_t waves = p.threads / 64, columns = p.Wb / p.phases / esize;
+        at += (waves * columns + waves) * 8;
+        at = (at + 15) / 16 * 16;
+    }
+    return at + kRcpBytes + 32;
+}
+
+// Blocks with so much LDS that share a compute unit: 160 KiB are handed out in 128 pieces.
+inline int64_t blocks_by_lds(int64_t bytes) { return 128 / ((bytes + 1279) / 1280); }
+
+// ---- which kernel, which tiles ---------------------------------------------------------------------
 
 // One mean per group (mean_rounds.hip) or M copies of it (grid_rounds.hip)?  MI355X, the former
 // against the latter, us:
@@ -150,6 +177,7 @@ inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
         if (ask.absent && (q.M != 8 * q.split || (phases == 2 && part == 32) || (ask.distortions && esize == 2 && part >= 64))) return false;
         if (bytes + (ask.distortions ? (waves * (part / esize) + 5 * waves) * 8 : 0) <= kLdsPerBlock) {
             q.red_offset = static_cast<int32_t>(bytes);
+            q.means = 1;
             *p = q;
             return true;
         }
@@ -158,6 +186,101 @@ inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
         else ++phases;
     }
     return false;
+}
+
+// The rest of a plan whose tiles and kernel are chosen.
+inline bool fill_in(GridPlan *plan, const void *X, int64_t esize, const GridAsk &ask)
+{
+    GridPlan &p = *plan;
+    const int32_t wb = p.Wb, M = p.M;
+    const int64_t N = p.N;
+    p.wv_shift = 0;
+    while ((16 << p.wv_shift) < wb) ++p.wv_shift;
+    const int32_t part = wb / p.phases;              // bytes of a row in LDS
+    p.threads = static_cast<int32_t>((N * part / (16 * kPhaseSlots) + 63) / 64 * 64);
+    if (p.threads < 64) p.threads = 64;
+    if (p.threads > (p.phases == 1 ? 1024 : 512)) return false;
+    if (!p.means) {
+        p.pad = part < 256 && M >= 8 && (M * part) % 256 == 0 ? part : 0;
+        p.tile_bytes = static_cast<int32_t>(N * part + p.groups * p.pad);
+    }
+    const auto magic = [](int64_t n) { return static_cast<uint32_t>(((int64_t(1) << 32) + n - 1) / n); };
+    p.magic_m = magic(M);
+    int32_t S = 1;
+    for (int32_t a = 0; a < p.d; ++a) {
+        p.S[a] = S;
+        p.magic_s[a] = S > 1 ? magic(S) : 0;
+        p.pad_step[a] = a == 0 ? 0 : S / M * p.pad;
+        S *= M;
+    }
+    p.tiles = (p.valid_bytes + wb - 1) / wb;
+    // Tiles of whole cache lines are not seen again: non-temporal (256 rows of 4 MiB: 5.5 TB/s
+    // against 5.1 with ordinary accesses).  Others share lines with their neighbours in the row.
+    // Runs per die: where tiles share lines, and for rows of one line (1024 rows of 16 MiB, 8
+    // rounds: 9.43 -> 9.33 ms, 4 rounds: 10.2 -> 8.3 ms); wider ones lose 1 % to them.
+    const bool whole_lines = wb >= 128 && reinterpret_cast<uintptr_t>(X) % 128 == 0 && p.row_bytes % 128 == 0;
+    const double state_bytes = static_cast<double>(N) * p.row_bytes;
+    const bool cached = state_bytes <= 256.0 * (1 << 20);
+    // States in the last-level cache stay there with ordinary accesses (16 x 16 peers, 4 rounds:
+    // 128 MiB 58.6 -> 52.8 us, 250 MiB 113 -> 89); below the L2s' 32 MiB the non-temporal ones are
+    // ahead again (16 MiB: 12.5 against 13.8), they leave no dirty lines to be written back at the end.
+    p.streaming = whole_lines && (!cached || state_bytes <= 24.0 * (1 << 20)) ? 1 : 0;
+    p.die_run = whole_lines && wb > 128 ? 1 : 32;
+    if (p.tiles < 8 * p.die_run) p.die_run = p.tiles >= 16 ? static_cast<int32_t>(p.tiles / 8) : 1;
+    // rounds of one pass: as many bitmaps as fit next to the tile
+    const int64_t waves = p.threads / 64, columns = part / esize;
+    if (p.means) {
+        // (a sum per wave for every distortion)
+        const int64_t sums = (kLdsPerBlock - p.red_offset - waves * columns * 8) / (8 * waves);
+        p.dist_window = static_cast<int32_t>(sums < 65 ? sums : 65);
+        p.max_rounds = ask.distortions && !sums_leave_in_between(esize == 4 ? 0 : 1, p.split, ask.absent && part >= kLeastLdsPart) ? p.dist_window - 1 : 64;
+        return p.max_rounds >= 4;
+    }
+    const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + waves) * 8 - kRcpBytes - 64;
+    const int64_t most = room / (static_cast<int64_t>(p.groups) * bitmap_bytes(M));
+    p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
+    if (p.max_rounds < 4) return false;      // (2^12 peers; 24 x 24 in tiles of 128 bytes with 8 columns to a vector)
+    return true;
+}
+
+// Of two plans for a state, is the one with M copies of a mean the faster?  MI355X, one mean against M copies, us, binary32
+// unless stated.
+inline bool copies_ahead(const GridPlan &copies, const GridPlan &means, int64_t esize, const GridAsk &ask)
+{
+    const int32_t M = copies.M, rounds = ask.rounds;
+    const bool f32 = esize == 4;
+    // With failures a short run of a small state does not make up for its larger tables, which take the launch that fills
+    // them longer (40 MB: 16 x 16 x 16, 5 rounds 50.0 : 47.8, 12 rounds 70.0 : 69.9, bfloat16 53.8 : 52.0; 32 x 32, 5
+    // rounds 32.5 : 31.6, 48 MB, 8 rounds 41.8 : 43.9; 16 x 16 25.7 : 26.6).
+    if (ask.absent && !ask.refresh && !ask.distortions && copies.N * copies.row_bytes < 48000000 &&
+        rounds < (copies.N > 1024 ? 10 : f32 && M > 16 ? 8 : 0)) return true;
+    // The means cost a second column part that M copies do without.  8 x 8 x 8 peers of 1 GB: 5 rounds 440 : 421, 8 rounds 425 :
+    // 502; with failures 5 rounds 457 : 433, 8 rounds 446 : 515 (and refresh: 5 rounds 458 : 554); with failures and curve, where few
+    // registers are left, 5 rounds 1,311 : 985, 40 rounds 5,560 : 5,470, 64 rounds 8,410 : 8,760.  Curves with nobody absent: 13 x 13 x 13
+    // of 1 GB 5 rounds 1,494 : 1,420, 3 GB, 8 rounds 5,690 : 6,070; 24 x 24 of 1 GB 5 rounds 1,290 : 1,180, 12 rounds 2,307 : 2,320.
+    // (In bfloat16 M copies take longer: 8 x 8 x 8, 5 rounds with failures 460 : 542.)
+    if (f32 && copies.phases == 1 && means.phases == 2) {
+        if (ask.distortions) {
+            if (rounds < (ask.absent ? 40 : M > 16 ? 10 : M > 8 ? 8 : 0)) return true;
+        } else if (M <= 8 && !ask.refresh && rounds < 6) {
+            return true;
+        }
+    }
+    // A block with the means takes more LDS.  Where the chip has room for all blocks with M copies at once, but not for all of the
+    // others, those come in two turns.  28 MB, nobody absent: 7 x 7 x 7 (2 blocks a compute unit : 3; 640 tiles) 4
+    // rounds 22.4 : 19.1, 64 rounds 138 : 127, bfloat16 27.9 : 25.2 (20 MB, one turn of each: 13.7 : 15.8); 8 x 8, 4 rounds 18.6 :
+    // 15.9, 10 rounds 24.4 : 22.9, 32 rounds 49.0 : 48.8; 8 x 8 x 8, 4 rounds 18.3 : 15.7, 10 rounds 25.1 : 24.3, 16 rounds 32.0 : 32.7; 24 x 24 of 30 MB, 4 rounds 22.8 : 20.7, 16
+    // rounds 45.0 : 43.5; with failures 8 x 8 x 8 of 33 MB, 5 rounds 40.9 : 38.4, 20 rounds 50.3 : 48.8.  Other groups of 9 to 16, other bfloat16 rows and distortions are worth more than a turn (9 x 9 of 33 MB, 4 rounds
+    // 20.2 : 24.2; 8 x 8 x 8 bfloat16, 4 rounds 23.2 : 25.2; curve of 8 x 8 x 8, 1 round 44.5 : 40.5, 2 rounds 47.9 : 45.9, 5 rounds
+    // 57.7 : 60.6).
+    const int32_t most = ask.absent ? (f32 && M <= 8 && !ask.refresh && !ask.distortions ? 20 : 0)
+                         : ask.distortions ? (f32 && M <= 8 ? 1 : 0) : M == 7 ? 64 : !f32 ? 0 : M > 16 ? 64 : M > 8 ? 0 : copies.N <= 64 ? 10 : 6;
+    if (rounds > most) return false;
+    int32_t at = 0;
+    const auto pass = [&](const GridPlan &p) { return rounds < p.max_rounds ? rounds : p.max_rounds; };
+    const int64_t room_copies = 256 * blocks_by_lds(copies_lds_bytes(copies, pass(copies), ask.distortions, esize, &at));
+    const int64_t room_means = 256 * blocks_by_lds(means_lds_bytes(means, ask.absent, pass(means), ask.distortions, esize, &at));
+    return copies.tiles <= room_copies && means.tiles > room_means;
 }
 
 inline bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int64_t row_stride, const void *X, int64_t t0,
@@ -174,9 +297,6 @@ inline bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int
     p.groups = static_cast<int32_t>(N / M);
     p.full_bitmap = M == 32 ? ~0u : (1u << M) - 1u;
     p.axis0 = static_cast<int32_t>(t0 % d);
-    int32_t S = 1;
-    const auto magic = [](int64_t n) { return static_cast<uint32_t>(((int64_t(1) << 32) + n - 1) / n); };
-    p.magic_m = magic(M);
     // Widest tile: rows of 512 bytes beat 1 KiB on 64 rows (2.55 against 2.73 ms), 256 bytes beat
     // 128 on 256 rows (0.40 against 0.46 ms for 3 rounds).
     int32_t wb = 1024;
@@ -201,52 +321,10 @@ inline bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int
     while (wb > 32 && wb / 2 >= p.valid_bytes) wb >>= 1;
     p.Wb = wb;
     p.phases = N * wb > 72 * 1024 ? 2 : 1;
-    p.means = choose_means(&p, esize, ask) ? 1 : 0;
-    wb = p.Wb;
-    p.wv_shift = 0;
-    while ((16 << p.wv_shift) < wb) ++p.wv_shift;
-    const int32_t part = wb / p.phases;              // bytes of a row in LDS
-    p.threads = static_cast<int32_t>((N * part / (16 * kPhaseSlots) + 63) / 64 * 64);
-    if (p.threads < 64) p.threads = 64;
-    if (p.threads > (p.phases == 1 ? 1024 : 512)) return false;
-    if (!p.means) {
-        p.pad = part < 256 && M >= 8 && (M * part) % 256 == 0 ? part : 0;
-        p.tile_bytes = static_cast<int32_t>(N * part + p.groups * p.pad);
-    }
-    S = 1;
-    for (int32_t a = 0; a < d; ++a) {
-        p.S[a] = S;
-        p.magic_s[a] = S > 1 ? magic(S) : 0;
-        p.pad_step[a] = a == 0 ? 0 : S / M * p.pad;
-        S *= M;
-    }
-    p.tiles = (p.valid_bytes + wb - 1) / wb;
-    // Tiles of whole cache lines are not seen again: non-temporal (256 rows of 4 MiB: 5.5 TB/s
-    // against 5.1 with ordinary accesses).  Others share lines with their neighbours in the row.
-    // Runs per die: where tiles share lines, and for rows of one line (1024 rows of 16 MiB, 8
-    // rounds: 9.43 -> 9.33 ms, 4 rounds: 10.2 -> 8.3 ms); wider ones lose 1 % to them.
-    const bool whole_lines = wb >= 128 && reinterpret_cast<uintptr_t>(X) % 128 == 0 && p.row_bytes % 128 == 0;
-    // States in the last-level cache stay there with ordinary accesses (16 x 16 peers, 4 rounds:
-    // 128 MiB 58.6 -> 52.8 us, 250 MiB 113 -> 89); below the L2s' 32 MiB the non-temporal ones are
-    // ahead again (16 MiB: 12.5 against 13.8), they leave no dirty lines to be written back at the end.
-    p.streaming = whole_lines && (!cached || state_bytes <= 24.0 * (1 << 20)) ? 1 : 0;
-    p.die_run = whole_lines && wb > 128 ? 1 : 32;
-    if (p.tiles < 8 * p.die_run) p.die_run = p.tiles >= 16 ? static_cast<int32_t>(p.tiles / 8) : 1;
-    // rounds of one pass: as many bitmaps as fit next to the tile
-    const int64_t waves = p.threads / 64, columns = part / esize;
-    if (p.means) {
-        // (a sum per wave for every distortion)
-        const int64_t sums = (kLdsPerBlock - p.red_offset - waves * columns * 8) / (8 * waves);
-        p.dist_window = static_cast<int32_t>(sums < 65 ? sums : 65);
-        p.max_rounds = ask.distortions && !sums_leave_in_between(dtype, p.split, ask.absent && part >= kLeastLdsPart) ? p.dist_window - 1 : 64;
-        *out = p;
-        return p.max_rounds >= 4;
-    }
-    const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + waves) * 8 - kRcpBytes - 64;
-    const int64_t most = room / (static_cast<int64_t>(p.groups) * bitmap_bytes(M));
-    p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
-    if (p.max_rounds < 4) return false;      // (2^12 peers; 24 x 24 in tiles of 128 bytes with 8 columns to a vector)
-    *out = p;
+    GridPlan one = p;
+    const bool copies = fill_in(&p, X, esize, ask), means = choose_means(&one, esize, ask) && fill_in(&one, X, esize, ask);
+    if (!copies && !means) return false;
+    *out = means && !(copies && copies_ahead(p, one, esize, ask)) ? one : p;
     return true;
 }
 

@@ -544,15 +544,7 @@ hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStrea
 {
     GridPlan p = plan;
     const bool dist = p.partials != nullptr;
-    int64_t at = p.tile_bytes + static_cast<int64_t>(p.rounds) * p.groups * bitmap_bytes(p.M) + p.N;
-    at = (at + 15) / 16 * 16;
-    p.red_offset = static_cast<int32_t>(at);
-    if (dist) {
-        const int64_t waves = p.threads / 64, columns = p.Wb / p.phases / (dtype == 0 ? 4 : 2);
-        at += (waves * columns + waves) * 8;
-        at = (at + 15) / 16 * 16;
-    }
-    p.lds_bytes = static_cast<int32_t>(at + kRcpBytes + 32);
+    p.lds_bytes = static_cast<int32_t>(copies_lds_bytes(p, p.rounds, dist, dtype == 0 ? 4 : 2, &p.red_offset));
     if (p.lds_bytes > kLdsPerBlock || p.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     const grid_kernel_t kernel = pick_kernel(dtype, p, dist);
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsPerBlock);

@@ -378,7 +378,7 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
         if constexpr (PHASES == 2) exchange_parts<HALF>(kept[0], kept[1]);
     }
     if constexpr (TAB != kClosed)
-        for (int32_t q = tid; q <= kMaxGroup; q += T) lds_put(base + p.rcp_at + q * 4, q == 0 ? 0.f : 1.f / static_cast<float>(q));
+        for (int32_t q = tid; q <= 32; q += T) lds_put(base + p.rcp_at + q * 4, q == 0 ? 0.f : 1.f / static_cast<float>(q));
     if (tid <= wv_mask) lds_put(base + p.zero_at + tid * 16, u32x4{0u, 0u, 0u, 0u});
 
     // Mean of one group over 16 bytes (vector v): places of the 8 positions -> mean, written to dst.
@@ -1091,14 +1091,7 @@ hipError_t launch_mean_rounds(void *X, int dtype, const GridPlan &plan, hipStrea
 {
     GridPlan p = plan;
     const bool dist = p.partials != nullptr;
-    int64_t at = p.words_at;
-    at += mean_words_bytes(p, p.entries != nullptr, dist);
-    p.red_offset = static_cast<int32_t>(at);
-    if (dist) {
-        const int64_t waves = p.threads / 64, columns = p.part / (dtype == 0 ? 4 : 2);
-        at += (waves * columns + (p.rounds + 1 < p.dist_window ? p.rounds + 1 : p.dist_window) * waves) * 8;
-    }
-    p.lds_bytes = static_cast<int32_t>(at);
+    p.lds_bytes = static_cast<int32_t>(means_lds_bytes(p, p.entries != nullptr, p.rounds, dist, dtype == 0 ? 4 : 2, &p.red_offset));
     if (p.lds_bytes > kLdsPerBlock || p.tiles > 0x7fffffffLL || p.grad != nullptr) return hipErrorInvalidValue;
     const mean_kernel_t kernel = dtype == 0 ? pick_kernel<0>(p, dist) : pick_kernel<1>(p, dist);
     if (kernel == nullptr) return hipErrorInvalidValue;

@@ -84,11 +84,13 @@ static void check(const GridPlan &p, int dtype, const GridAsk &a)
     if (p.threads % 64 != 0 || p.threads > (p.phases == 1 ? 1024 : 512) || p.max_rounds < 1 || p.max_rounds > 64) say("threads or rounds", p, dtype, a);
     // a thread's slots hold the tile, and every column is in some tile
     if (static_cast<int64_t>(p.threads) * 16 * kPhaseSlots < p.N * part || p.tiles * p.Wb < p.valid_bytes) say("tile", p, dtype, a);
+    // LDS of a pass
+    int32_t sums_at = 0;
+    const int64_t lds = p.means ? means_lds_bytes(p, a.absent, p.max_rounds, a.distortions, es, &sums_at)
+                                : copies_lds_bytes(p, p.max_rounds, a.distortions, es, &sums_at);
+    if (lds > kLdsPerBlock || sums_at % 8 != 0 || (p.means && (sums_at != p.red_offset || p.zero_at + part > p.rcp_at))) say("LDS", p, dtype, a);
     if (!p.means) return;
     if (a.local_step) say("local step", p, dtype, a);
-    // LDS of a pass of max_rounds rounds with distortions
-    const int64_t waves = p.threads / 64, sums = a.distortions ? (waves * (part / es) + p.dist_window * waves) * 8 : 0;
-    if (p.red_offset + sums > kLdsPerBlock || p.red_offset % 8 != 0 || p.zero_at + part > kLdsPerBlock) say("LDS", p, dtype, a);
     if (!a.absent) return;
     // tables: a place has 13 bits, a lane one item of 8 positions, a register a round's words
     if (p.zero_at / 16 >= 1 << 13 || p.M != 8 * p.split || static_cast<int64_t>(p.groups) * (part / 16) * p.split > p.threads) say("places", p, dtype, a);
@@ -124,3 +126,60 @@ def test_one_mean_per_group_takes_no_more_passes(tmp_path):
     but for runs of more than 24 rounds (6 x 6 x 6: 10)."""
     out = run_host(tmp_path, ROUNDS)
     assert out.returncode == 0, out.stdout
+
+
+CHOICE = r"""
+#include <cstdio>
+#include "grid_plan.h"
+using namespace moshpit;
+int main()
+{
+    int M, d, dtype, rounds, absent, curve, refresh;
+    double mb;
+    while (std::scanf("%d %d %d %lf %d %d %d %d", &M, &d, &dtype, &mb, &rounds, &absent, &curve, &refresh) == 8) {
+        const int64_t es = dtype == 0 ? 4 : 2;
+        int64_t N = 1;
+        for (int q = 0; q < d; ++q) N *= M;
+        const int64_t P = static_cast<int64_t>(mb * 1e6) / (N * es) / 8 * 8;
+        GridAsk a;
+        a.absent = absent != 0;
+        a.distortions = curve != 0;
+        a.refresh = refresh != 0;
+        a.rounds = rounds;
+        GridPlan p;
+        std::printf("%d\n", plan_grid(dtype, N, M, d, P, P, reinterpret_cast<void *>(4096), 0, a, &p) ? p.means : -1);
+    }
+}
+"""
+
+# Measured on MI355X: grid, type, MB, rounds, failures (10 % absent), curve, refresh; microseconds with M copies of a
+# mean and with one mean per group.
+MEASURED = [
+    # as many blocks as tiles at once, or two turns
+    (7, 3, 0, 20, 4, 0, 0, 0, 15.8, 13.7), (7, 3, 0, 28, 4, 0, 0, 0, 19.1, 22.4), (7, 3, 0, 28, 20, 0, 0, 0, 47.9, 53.0),
+    (7, 3, 1, 28, 20, 0, 0, 0, 63.3, 69.6), (7, 3, 0, 36, 10, 0, 0, 0, 41.6, 36.6), (8, 2, 0, 24, 4, 0, 0, 0, 13.7, 12.2),
+    (8, 2, 0, 33, 4, 0, 0, 0, 16.4, 19.1), (8, 2, 0, 33, 64, 0, 0, 0, 120.6, 85.4), (8, 2, 0, 40, 6, 0, 0, 0, 23.6, 22.0),
+    (24, 2, 0, 30, 10, 0, 0, 0, 32.1, 33.9), (24, 2, 0, 30, 32, 0, 0, 0, 94.9, 75.9), (5, 3, 0, 36, 4, 0, 0, 0, 20.2, 21.8),
+    (5, 3, 0, 28, 4, 0, 0, 0, 18.5, 15.0), (8, 3, 0, 28, 6, 0, 0, 0, 18.6, 20.9), (9, 2, 0, 33, 4, 0, 0, 0, 24.2, 20.2),
+    (8, 3, 0, 28, 1, 0, 1, 0, 40.5, 44.5), (8, 3, 0, 28, 5, 0, 1, 0, 60.6, 57.7), (8, 3, 1, 28, 4, 0, 0, 0, 25.2, 23.2),
+    (24, 2, 1, 33, 8, 0, 0, 0, 39.7, 36.5), (9, 2, 1, 30, 2, 0, 1, 0, 74.1, 62.0), (8, 3, 1, 32, 32, 0, 0, 0, 112.4, 82.5),
+    # small states with failures
+    (16, 3, 0, 33, 5, 1, 0, 0, 55.3, 60.2), (16, 3, 1, 40, 8, 1, 0, 0, 63.4, 66.5), (32, 2, 0, 36, 5, 1, 0, 0, 28.1, 30.8),
+    (8, 3, 0, 33, 5, 1, 0, 0, 38.4, 40.9), (8, 3, 0, 44, 8, 1, 0, 0, 40.1, 35.9), (16, 2, 0, 36, 5, 1, 0, 0, 25.1, 23.7),
+    (8, 3, 0, 200, 5, 1, 0, 1, 108.9, 86.5), (32, 2, 0, 40, 10, 1, 1, 0, 124.3, 106.7), (16, 3, 0, 200, 5, 1, 1, 0, 320.7, 226.0),
+    # two column parts in place of one
+    (8, 3, 0, 1000, 4, 0, 0, 0, 420, 443), (8, 3, 0, 1000, 8, 0, 0, 0, 502, 425), (8, 3, 0, 1000, 5, 1, 0, 0, 433, 457),
+    (8, 3, 0, 1000, 8, 1, 0, 0, 515, 446), (8, 3, 0, 1000, 5, 1, 1, 0, 987, 1311), (8, 3, 0, 3000, 20, 1, 1, 0, 8605, 9338), (8, 3, 0, 3000, 64, 1, 1, 0, 26047, 24796),
+    (8, 3, 0, 1000, 5, 1, 0, 1, 554, 458), (8, 3, 0, 200, 5, 1, 1, 0, 222.8, 196.6), (8, 3, 0, 1000, 5, 0, 1, 0, 961, 787),
+    (13, 3, 0, 1000, 5, 0, 1, 0, 1420, 1494), (13, 3, 0, 1000, 12, 0, 1, 0, 2670, 2548), (13, 3, 0, 1000, 4, 0, 0, 0, 776, 600),
+    (13, 3, 1, 1000, 2, 0, 1, 0, 1778, 1370), (24, 2, 0, 1000, 5, 0, 1, 0, 1180, 1290), (24, 2, 0, 1000, 40, 0, 1, 0, 7329, 6360), (24, 2, 0, 3000, 12, 0, 1, 0, 7185, 6663),
+    (24, 2, 0, 1000, 4, 0, 0, 0, 532, 497), (24, 2, 1, 1000, 8, 0, 0, 0, 3055, 828),
+]
+
+
+def test_the_faster_kernel_of_measured_runs_is_taken(tmp_path):
+    text = "".join(" ".join(map(str, row[:8])) + "\n" for row in MEASURED)
+    out = run_host(tmp_path, CHOICE, text)
+    assert out.returncode == 0
+    wrong = [(row, means) for row, means in zip(MEASURED, out.stdout.split(), strict=True) if int(means) != (row[9] < row[8])]
+    assert not wrong, wrong
