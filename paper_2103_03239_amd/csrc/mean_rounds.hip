@@ -378,7 +378,7 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
         if constexpr (PHASES == 2) exchange_parts<HALF>(kept[0], kept[1]);
     }
     if constexpr (TAB != kClosed)
-        for (int32_t q = tid; q <= 32; q += T) lds_put(base + p.rcp_at + q * 4, q == 0 ? 0.f : 1.f / static_cast<float>(q));
+        for (int32_t q = tid; q <= kPositions * SPLIT; q += T) lds_put(base + p.rcp_at + q * 4, q == 0 ? 0.f : 1.f / static_cast<float>(q));
     if (tid <= wv_mask) lds_put(base + p.zero_at + tid * 16, u32x4{0u, 0u, 0u, 0u});
 
     // Mean of one group over 16 bytes (vector v): places of the 8 positions -> mean, written to dst.

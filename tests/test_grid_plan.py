@@ -147,7 +147,11 @@ int main()
         a.refresh = refresh != 0;
         a.rounds = rounds;
         GridPlan p;
-        std::printf("%d\n", plan_grid(dtype, N, M, d, P, P, reinterpret_cast<void *>(4096), 0, a, &p) ? p.means : -1);
+        // (means, blocks of a pass that share a compute unit)
+        int32_t at = 0;
+        const bool planned = plan_grid(dtype, N, M, d, P, P, reinterpret_cast<void *>(4096), 0, a, &p);
+        const int64_t lds = p.means ? means_lds_bytes(p, a.absent, rounds, a.distortions, es, &at) : copies_lds_bytes(p, rounds, a.distortions, es, &at);
+        std::printf("%d %d\n", planned ? p.means : -1, static_cast<int>(blocks_by_lds(lds)));
     }
 }
 """
@@ -177,9 +181,19 @@ MEASURED = [
 ]
 
 
-def test_the_faster_kernel_of_measured_runs_is_taken(tmp_path):
-    text = "".join(" ".join(map(str, row[:8])) + "\n" for row in MEASURED)
-    out = run_host(tmp_path, CHOICE, text)
+def plans(tmp_path, rows):
+    """(one mean per group, blocks per compute unit) of each."""
+    out = run_host(tmp_path, CHOICE, "".join(" ".join(map(str, row)) + "\n" for row in rows))
     assert out.returncode == 0
-    wrong = [(row, means) for row, means in zip(MEASURED, out.stdout.split(), strict=True) if int(means) != (row[9] < row[8])]
+    return [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
+
+
+def test_the_faster_kernel_of_measured_runs_is_taken(tmp_path):
+    got = plans(tmp_path, [row[:8] for row in MEASURED])
+    wrong = [(row, means) for row, (means, _) in zip(MEASURED, got, strict=True) if means != (row[9] < row[8])]
     assert not wrong, wrong
+
+
+def test_256_peers_with_failures_fit_a_compute_unit_four_times(tmp_path):
+    """In tiles of 128 bytes, as with M copies of a mean."""
+    assert plans(tmp_path, [(16, 2, dtype, mb, 16, 1, 0, 0) for dtype in (0, 1) for mb in (33, 100)]) == [(1, 4)] * 4
