@@ -623,6 +623,10 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
     ask.refresh = failures && s->refresh != 0;
     ask.distortions = dist_out_host != nullptr;
     ask.rounds = rounds;
+    Participation who;
+    if (rounds > 0 && h->N <= kGridMaxPeers) who = participation(s, h->N, h->M, h->d, t0, rounds);
+    ask.averaged = who.averaged;
+    ask.live = who.groups;
     if (!plan_grid(h->dtype, h->N, h->M, h->d, h->P, h->row_stride, h->X, t0, ask, &plan)) return MOSHPIT_OK;
     const bool refresh = failures && s->refresh != 0;
 
@@ -646,7 +650,6 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
         size.element_bytes = h->dtype == MOSHPIT_F32 ? 4 : 2;
         size.valid_bytes = plan.valid_bytes;
         size.row_bytes = plan.row_bytes;
-        const Participation who = participation(s, h->N, h->M, h->d, t0, rounds);
         const double single = single_round_us(size, who);
         double by_rounds = 0.0;                                     // (masks and gradients cost either way the same)
         int32_t distortions = 1;                                    // of the other way, and (fused) of a pass too

@@ -64,6 +64,7 @@ struct GridAsk {
     bool refresh = false;            // returning peers copy another one
     bool distortions = false;        // they are wanted
     int32_t rounds = 0;
+    double averaged = 1.0, live = 1.0;       // of the peers, those averaged in a round; of the groups, those with an average
 };
 
 // Do the sums of a pass's distortions leave LDS in between, when no more of them have room, so that a pass takes 64
@@ -149,7 +150,7 @@ inline int64_t blocks_by_lds(int64_t bytes) { return 128 / ((bytes + 1279) / 128
 // against the latter, us:
 //   nobody ever absent: ahead from 4 rounds on (16 x 16, 200 MB binary32, 6 rounds 70 : 80; 24 x 24, 1.5 GB bfloat16
 //     887 : 1,234; 32 x 32, 16 GB, 16 rounds 10,450 : 14,200), behind by up to 11 % for 2 or 3 (8 x 8 x 8, 1.5 GB
-//     bfloat16 715 : 643) and for small states of 8 x 8 peers in bfloat16 (8 MB, 8 rounds 12.8 : 12.5);
+//     bfloat16 715 : 643), by 3 to 9 % for 4 of 32 x 32 in binary32 (250 MB 108 : 99) and for small states of 8 x 8 peers in bfloat16 (8 MB, 8 rounds 12.8 : 12.5);
 //     with distortions ahead everywhere (16 x 16, 1 GB binary32, 5 rounds 602 : 860).  Groups of 2 to 4 save little.
 //   with failures, whose tables cost a launch and a wait: ahead from 5 rounds (4 on more than 1024 peers) of
 //     states beyond 32 MB on (32 x 32, 16 GB, 8 rounds 8,110 : 9,320, 4 rounds of 200 MB 85 : 83; 16 x 16 x 16, 1.5 GB
@@ -165,7 +166,8 @@ inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
     if (ask.absent) {
         if (!large || p->N < 256 || ask.rounds < (p->N > 1024 ? 4 : 5)) return false;
     } else if (!ask.distortions) {
-        if (ask.rounds < 4 || (p->M <= 8 && p->N <= 64 && esize == 2 && !large)) return false;
+        if (ask.rounds < (esize == 4 && p->N >= 1024 && p->M > 16 && state > 100000000 ? 5 : 4)) return false;
+        if (p->M <= 8 && p->N <= 64 && esize == 2 && !large) return false;
     }
     const bool cached = static_cast<double>(p->N) * p->row_bytes <= 256.0 * (1 << 20);
     for (int32_t wb = p->Wb, phases = p->phases; phases <= 2 && wb / phases >= 16;) {
@@ -251,11 +253,44 @@ inline bool copies_ahead(const GridPlan &copies, const GridPlan &means, int64_t 
 {
     const int32_t M = copies.M, rounds = ask.rounds;
     const bool f32 = esize == 4;
+    // Bitmaps of all groups next to the tile leave M copies fewer rounds to a pass (16 x 16 x 16 peers 14, 8 x 8 x 8 24 to 40): a pass more
+    // is never worth it (16 x 16 x 16 of 0.98 GB, group-skip with 5 % absent, 16 rounds 1,240 : 1,920).
+    const auto passes = [&](const GridPlan &p) { return (rounds + p.max_rounds - 1) / p.max_rounds; };
+    if (passes(copies) > passes(means)) return false;
     // With failures a short run of a small state does not make up for its larger tables, which take the launch that fills
     // them longer (40 MB: 16 x 16 x 16, 5 rounds 50.0 : 47.8, 12 rounds 70.0 : 69.9, bfloat16 53.8 : 52.0; 32 x 32, 5
     // rounds 32.5 : 31.6, 48 MB, 8 rounds 41.8 : 43.9; 16 x 16 25.7 : 26.6).
-    if (ask.absent && !ask.refresh && !ask.distortions && copies.N * copies.row_bytes < 48000000 &&
+    const int64_t state = copies.N * copies.row_bytes;
+    if (ask.absent && !ask.refresh && !ask.distortions && state < 48000000 &&
         rounds < (copies.N > 1024 ? 10 : f32 && M > 16 ? 8 : 0)) return true;
+    // Who is absent costs M copies nothing.  Next to the means an absent peer's value moves to its own row (most often where
+    // half are away), a group without an average is read through its table all the same, and a distortion takes a term of every
+    // absent peer.  Time with one mean per group over that with M copies, 60 to 1,500 MB:
+    const bool short_of_time = rounds >= 8 || state < 100000000;
+    const double moves = ask.averaged * (1.0 - ask.averaged);
+    if (ask.absent && copies.N <= 1024) {
+        if (ask.distortions) {
+            // (12 rounds, 1,024 peers: 70 % absent 0.98 to 1.05, 80 % 1.06 to 1.12; 256: 70 % 1.02 to 1.11, 50 % 0.95 to 0.96, of
+            // 60 MB 1.07; 512, 60 MB: 30 % 0.98, 50 % 1.11, 90 % 1.34)
+            if (ask.averaged < (M <= 8 ? 0.6 : M > 16 ? (state < 1000000000 ? 0.35 : 0.25) : state < 100000000 ? 0.55 : 0.4)) return true;
+        } else if (ask.refresh) {
+            // (512 peers, 12 rounds: 6 % of the groups live 0.92 to 1.07, 2 % 1.02 to 1.18, 6 rounds of 300 MB and more 0.86 to 0.98)
+            if (M <= 8 && ask.live < 0.03 && short_of_time) return true;
+        } else {
+            // (12 rounds, 512 peers in bfloat16: 50 % of the groups live 0.94 to 0.95, 19 % 1.07 to 1.14, 6 % 1.39, in binary32 50 %
+            // 1.00 to 1.04, 43 % of them whole 1.02 to 1.07, 19 % 1.09 to 1.14; 256: 19 % 0.85 to 0.97, none 1.16 to 1.24; 1,024: 46 % 0.83 to
+            // 0.90, 3 % 1.06 to 1.10; in binary32, 512 peers, half of them absent 1.04 to 1.12, 30 or 70 % 0.95 to 1.01, 256
+            // beyond 256 MiB, 6 rounds 1.04 to 1.07, 12 rounds 0.93 to 0.98)
+            if (ask.live < (M > 8 ? 0.1 : f32 ? 0.45 : 0.3) && short_of_time) return true;
+            if (f32 && M <= 8 && moves > 0.215) return true;
+            if (f32 && M > 8 && M <= 16 && moves > 0.22 && rounds <= 8 && state > 268435456) return true;
+        }
+    } else if (ask.absent && !ask.refresh && !ask.distortions) {
+        // (4,096 peers of 60 MB: 30 % absent 0.98 to 1.00, 50 to 95 % 0.98 to 1.12; with two moves a thread at hand half of the peers
+        // are too many for longer runs: bfloat16, 300 MB and more, 6 rounds 0.89, 12 rounds 1.14 to 1.16, at 30 and 70 % 0.98 to 1.01)
+        if (ask.averaged < 0.6 && state < 100000000) return true;
+        if (means.bits && !f32 && rounds > 8 && moves * copies.N > 1.9 * means.threads) return true;
+    }
     // The means cost a second column part that M copies do without.  8 x 8 x 8 peers of 1 GB: 5 rounds 440 : 421, 8 rounds 425 :
     // 502; with failures 5 rounds 457 : 433, 8 rounds 446 : 515 (and refresh: 5 rounds 458 : 554); with failures and curve, where few
     // registers are left, 5 rounds 1,311 : 985, 40 rounds 5,560 : 5,470, 64 rounds 8,410 : 8,760.  Curves with nobody absent: 13 x 13 x 13
