@@ -659,24 +659,14 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
             r += sub_grid ? fp.rounds : 1;
             if (refresh && r < rounds) by_rounds += refresh_us(size);
         }
-        GridTiles tiles;
-        tiles.row_bytes = plan.Wb;
-        tiles.parts = plan.phases;
-        tiles.threads = plan.threads;
-        tiles.lds_bytes = plan.tile_bytes + plan.N;
-        tiles.max_rounds = plan.max_rounds;
-        tiles.tiles = plan.tiles;
-        if (plan.means) {
-            tiles.round_share = failures ? 0.65 : 0.53;
-            tiles.distortion_share = failures ? 0.65 : 0.4;
-        }
+        const GridTiles tiles = grid_tiles(plan, ask, size.element_bytes);
         double by_passes = step_first ? single : 0.0;
         by_passes += grid_passes_us(size, who, tiles, step_first ? rounds - 1 : rounds, dist_out_host ? distortions : 0);
         if (dist_out_host) {
             by_rounds += distortions * distortion_us(size);
             if (grad != nullptr) by_passes += distortion_us(size);
         }
-        if (by_rounds < kRoundsAhead * by_passes) return MOSHPIT_OK;
+        if (rounds_ahead(by_rounds, by_passes, tiles)) return MOSHPIT_OK;
     }
 
     int rc = MOSHPIT_OK;

@@ -4,6 +4,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "grid_plan.h"
+
 namespace moshpit {
 
 // Tables of whole-grid passes (who takes part in which round, who copies whom) are built for a
@@ -170,11 +172,13 @@ inline double fused_pass_us(const RunSize &z, const Participation &w, int32_t ro
     return 6.9 + 3.1 * rounds + z.megabytes() * cached * per_mb;
 }
 
-// Rounds one by one are taken if they are priced below this part of the passes.  Over 22,000 runs on 11
+// Rounds one by one are taken if they are priced below this part of the passes with M copies of a mean.  Over 22,000 runs on 11
 // grids, 256 KiB to 3 GB, they were slower than the passes in 1 of 1,400 runs then (45 % at most); with
 // any price below that of the passes in 1 of 40 (up to twice).  It leaves 5 % of the runs more than 5 %
 // slower than the better way.
-constexpr double kRoundsAhead = 0.8;
+// Passes with one mean per group are taken unless rounds are priced below them: over 801 runs under failures the way taken is
+// more than 5 % slower than the better one in 3.0 % and more than 15 % in 1.6 % then, 5.9 and 3.8 % at four fifths.
+constexpr double kRoundsAhead = 0.8, kRoundsAheadOfMeans = 1.0;
 
 // A distortion on its own: the chain over the rows that a wave walks (8 rows at a time in binary32, 4
 // in bfloat16, up to 256 rows to a wave), or one read of the state where that takes longer.
@@ -197,8 +201,26 @@ inline double refresh_us(const RunSize &z) { return 6.5 + 0.14 * z.megabytes(); 
 struct GridTiles {
     int32_t row_bytes = 0, parts = 1, threads = 0, lds_bytes = 0, max_rounds = 1;
     int64_t tiles = 0;
-    double round_share = 1.0, distortion_share = 1.0;      // of what the kernel with M copies of a mean takes
+    bool means = false;                  // the kernel that keeps one mean per group; else M copies of it
 };
+inline GridTiles grid_tiles(const GridPlan &p, const GridAsk &ask, int64_t esize)
+{
+    GridTiles t;
+    t.row_bytes = p.Wb;
+    t.parts = p.phases;
+    t.threads = p.threads;
+    t.max_rounds = p.max_rounds;
+    t.tiles = p.tiles;
+    t.means = p.means != 0;
+    int32_t sums_at = 0;
+    t.lds_bytes = p.tile_bytes + p.N;
+    if (t.means) t.lds_bytes = static_cast<int32_t>(means_lds_bytes(p, ask.absent, ask.rounds < p.max_rounds ? ask.rounds : p.max_rounds, ask.distortions, esize, &sums_at));
+    return t;
+}
+inline bool rounds_ahead(double by_rounds, double by_passes, const GridTiles &t)
+{
+    return by_rounds < (t.means ? kRoundsAheadOfMeans : kRoundsAhead) * by_passes;
+}
 inline double grid_passes_us(const RunSize &z, const Participation &w, const GridTiles &t, int32_t rounds, int32_t distortions)
 {
     const bool f32 = z.element_bytes == 4;
@@ -211,18 +233,27 @@ inline double grid_passes_us(const RunSize &z, const Participation &w, const Gri
     if (per_cu > 160 * 1024 / t.lds_bytes) per_cu = 160 * 1024 / t.lds_bytes;
     if (per_cu < 1) per_cu = 1;
     const double turns = static_cast<double>(t.tiles) / (256.0 * static_cast<double>(per_cu));
-    const double round_us = (turns > 1.0 ? turns : 1.0) * per_thread * item_us * (0.63 + 0.37 * w.groups) * t.parts * t.round_share;
+    // One mean per group, fitted to 1,333 runs (half of the prices lie within 7 % of the times, 90 % within 30): the rounds
+    // are a share of what M copies take, and hide half of the memory's time under failures, whose tables take a while to fill.
+    const int32_t kind = z.M <= 8 ? 0 : z.M <= 16 ? 1 : 2;
+    constexpr double kEverybody[3] = {0.68, 0.62, 0.54}, kLive[3] = {0.19, 0.45, 0.55};
+    constexpr double kSome32[3] = {1.19, 1.26, 1.07}, kSome16[3] = {0.74, 0.95, 0.75};
+    const bool tables = t.means && w.failures;
+    const double share = !t.means ? 0.63 + 0.37 * w.groups : tables ? (f32 ? kSome32 : kSome16)[kind] + kLive[kind] * w.groups : kEverybody[kind];
+    const double fixed = tables ? 11.3 + 32.0 * static_cast<double>(z.N) / 4096.0 : 4.2 + 8.2 * static_cast<double>(z.N) / 4096.0;
+    const double distortion_share = !t.means ? 1.0 : tables ? (f32 ? 0.83 : 0.57) : (f32 ? 0.7 : 0.56);
+    const double round_us = (turns > 1.0 ? turns : 1.0) * per_thread * item_us * share * t.parts;
     const bool narrow = t.row_bytes <= 64;
     const double read = t.row_bytes <= 32 ? 0.47 : narrow ? 0.36 : t.row_bytes <= 128 ? 0.25 : 0.17;
     const double masked = t.row_bytes <= 32 ? 0.34 : narrow ? 0.25 : t.row_bytes <= 128 ? 0.12 : 0.13;
     const double whole = t.row_bytes <= 32 ? 0.19 : narrow ? 0.17 : t.row_bytes <= 128 ? 0.13 : 0.11;
-    const double memory = z.megabytes() * (z.cached() ? (narrow ? 0.66 : 0.9) : 1.0);
+    const double memory = z.megabytes() * (z.cached() ? (narrow ? 0.66 : 0.9) : 1.0) * (tables ? 0.49 : 1.0);
     double us = 0.0;
     for (int32_t left = rounds; left > 0; left -= t.max_rounds) {
         const int32_t n = left < t.max_rounds ? left : t.max_rounds;
-        us += 4.2 + 8.2 * static_cast<double>(z.N) / 4096.0 + memory * (read + (w.failures ? masked * w.ever(n) : whole)) + n * round_us;
+        us += fixed + memory * (read + (w.failures ? masked * w.ever(n) : whole)) + n * round_us;
     }
-    return us + distortions * (6.3 + z.megabytes() * (t.parts == 1 ? 0.065 : 0.14) * (f32 ? 1.0 : 2.3) * t.distortion_share);
+    return us + distortions * (6.3 + z.megabytes() * (t.parts == 1 ? 0.065 : 0.14) * (f32 ? 1.0 : 2.3) * distortion_share);
 }
 
 }  // namespace moshpit

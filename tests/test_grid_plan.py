@@ -130,7 +130,6 @@ def test_one_mean_per_group_takes_no_more_passes(tmp_path):
 
 CHOICE = r"""
 #include <cstdio>
-#include "grid_plan.h"
 #include "pass_rules.h"
 using namespace moshpit;
 int main()
@@ -157,7 +156,16 @@ int main()
         int32_t at = 0;
         const bool planned = plan_grid(dtype, N, M, d, P, P, reinterpret_cast<void *>(4096), 0, a, &p);
         const int64_t lds = p.means ? means_lds_bytes(p, a.absent, rounds, a.distortions, es, &at) : copies_lds_bytes(p, rounds, a.distortions, es, &at);
-        std::printf("%d %d\n", planned ? p.means : -1, static_cast<int>(blocks_by_lds(lds)));
+        // (and are passes cheaper than rounds one by one?)
+        RunSize z;
+        z.N = N;
+        z.M = M;
+        z.element_bytes = static_cast<int32_t>(es);
+        z.valid_bytes = z.row_bytes = P * es;
+        const GridTiles t = grid_tiles(p, a, es);
+        const double by_rounds = rounds * single_round_us(z, who) + (refresh ? (rounds - 1) * refresh_us(z) : 0.0) + (curve ? (rounds + 1) * distortion_us(z) : 0.0);
+        const bool passes = planned && !rounds_ahead(by_rounds, grid_passes_us(z, who, t, rounds, curve ? rounds + 1 : 0), t);
+        std::printf("%d %d %d %d\n", planned ? p.means : -1, static_cast<int>(blocks_by_lds(lds)), passes, p.means ? t.lds_bytes == lds : 1);
     }
 }
 """
@@ -183,7 +191,7 @@ MEASURED = [
     (8, 3, 0, 1000, 5, 10, 0, 0, 1, 554, 458), (8, 3, 0, 200, 5, 10, 0, 1, 0, 222.8, 196.6), (8, 3, 0, 1000, 5, 0, 0, 1, 0, 961, 787),
     (13, 3, 0, 1000, 5, 0, 0, 1, 0, 1420, 1494), (13, 3, 0, 1000, 12, 0, 0, 1, 0, 2670, 2548), (13, 3, 0, 1000, 4, 0, 0, 0, 0, 776, 600),
     (13, 3, 1, 1000, 2, 0, 0, 1, 0, 1778, 1370), (24, 2, 0, 1000, 5, 0, 0, 1, 0, 1180, 1290), (24, 2, 0, 1000, 40, 0, 0, 1, 0, 7329, 6360), (24, 2, 0, 3000, 12, 0, 0, 1, 0, 7185, 6663),
-    (24, 2, 0, 1000, 4, 0, 0, 0, 0, 532, 497), (24, 2, 1, 1000, 8, 0, 0, 0, 0, 3055, 828),
+    (24, 2, 0, 1000, 4, 0, 0, 0, 0, 532, 497), (32, 2, 0, 250, 4, 0, 0, 0, 0, 99, 108), (24, 2, 1, 1000, 8, 0, 0, 0, 0, 3055, 828),
     # who is absent (60 MB and more, 12 rounds unless stated): curves, refresh, groups without an average, half of the peers
     (16, 2, 0, 300, 12, 30, 0, 1, 0, 542, 466), (16, 2, 0, 300, 12, 80, 0, 1, 0, 537, 602), (32, 2, 0, 1500, 12, 90, 0, 1, 0, 3209, 3519),
     (8, 3, 0, 60, 12, 70, 0, 1, 0, 163, 192), (16, 3, 0, 300, 12, 90, 0, 1, 0, 817, 705),
@@ -196,7 +204,7 @@ MEASURED = [
 
 
 def plans(tmp_path, rows):
-    """(one mean per group, blocks per compute unit) of each."""
+    """(one mean per group, blocks per compute unit, passes instead of rounds, LDS as priced) of each."""
     out = run_host(tmp_path, CHOICE, "".join(" ".join(map(str, row)) + "\n" for row in rows))
     assert out.returncode == 0
     return [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
@@ -210,5 +218,21 @@ def test_the_faster_kernel_of_measured_runs_is_taken(tmp_path):
 
 def test_256_peers_with_failures_fit_a_compute_unit_four_times(tmp_path):
     """In tiles of 128 bytes, as with M copies of a mean."""
-    assert plans(tmp_path, [(16, 2, dtype, mb, 16, 10, 0, 0, 0) for dtype in (0, 1) for mb in (33, 100)]) == [(1, 4)] * 4
+    assert plans(tmp_path, [(16, 2, dtype, mb, 16, 10, 0, 0, 0) for dtype in (0, 1) for mb in (33, 100)]) == [(1, 4, 1, 1)] * 4
 
+
+# The same columns; microseconds round by round and in passes with one mean per group.
+WAYS = [
+    (16, 2, 1, 1646, 6, 95, 0, 0, 0, 322, 522), (16, 2, 1, 494, 6, 95, 0, 0, 0, 110, 173), (16, 2, 1, 513, 8, 95, 0, 0, 0, 156, 214),
+    (16, 3, 1, 370, 8, 90, 0, 0, 0, 212, 293), (16, 3, 1, 487, 16, 95, 0, 0, 0, 387, 595), (16, 3, 0, 804, 5, 90, 0, 0, 0, 296, 424),
+    (32, 2, 1, 304, 6, 95, 0, 0, 0, 110, 149), (16, 2, 0, 735, 12, 95, 0, 0, 0, 412, 304), (16, 2, 1, 307, 6, 90, 0, 0, 0, 177, 133),
+    (32, 2, 0, 105, 16, 90, 0, 0, 0, 148, 95), (32, 2, 1, 835, 10, 95, 0, 0, 0, 730, 561), (16, 3, 1, 1327, 12, 80, 0, 0, 0, 1947, 1334),
+    (16, 3, 0, 2151, 10, 70, 0, 0, 0, 2772, 1584), (16, 2, 1, 191, 7, 90, 0, 0, 0, 143, 95), (16, 2, 0, 39, 10, 80, 0, 0, 0, 70, 32),
+]
+
+
+def test_the_cheaper_way_of_measured_runs_is_taken(tmp_path):
+    """Passes with one mean per group or rounds one by one, priced with the LDS that the launch takes."""
+    got = plans(tmp_path, [row[:9] for row in WAYS])
+    wrong = [(row, g) for row, g in zip(WAYS, got, strict=True) if g[2] != (row[10] < row[9]) or not g[3]]
+    assert not wrong, wrong
