@@ -124,6 +124,35 @@ inline int64_t means_lds_bytes(const GridPlan &p, bool tables, int32_t rounds, b
     return at;
 }
 
+// Which instance of the kernel takes a pass.  half: lanes between the two column parts of a tile, 0 = one part; tab: where the
+// places come from (mean_rounds.hip).
+constexpr int kClosed = 0, kLds = 1, kAheadOnly = 2, kBits = 3;
+struct MeanKernel {
+    int split, half, tab;
+    bool nt, dist;
+};
+inline MeanKernel mean_kernel(const GridPlan &p, bool tables, bool dist)
+{
+    const bool wide = p.part >= kLeastLdsPart;
+    MeanKernel k;
+    k.split = p.split;
+    k.half = p.phases == 1 ? 0 : wide ? 32 : p.part == 32 ? 2 : 1;
+    k.tab = !tables ? kClosed : p.bits ? kBits : wide ? kLds : kAheadOnly;
+    k.nt = p.streaming != 0;
+    k.dist = dist;
+    return k;
+}
+// Those that some plan asks for: rows of less than a cache line are never streamed; grids with tables have 8^d, 16^d or 32^d
+// peers, of which 256 fit one part, and 4096 two parts of 16 bytes or one; groups of more than 16 mean at most 1024 peers; distortions of
+// wide bfloat16 rows under failures go to the kernel with M copies of a mean.
+constexpr bool mean_kernel_built(int dtype, int split, int half, bool nt, bool dist, int tab)
+{
+    if (tab == kBits) return split == 2 && half <= 1 && !nt && !dist;
+    if (tab == kAheadOnly) return !nt && (half == 0 || (split == 2 && half == 1));
+    if (tab == kLds) return !(dtype == 1 && dist) && (half == 0 ? split == 2 || !nt : half == 32 && split != 2);
+    return half == 0 || half == 32 || (split != 4 && !nt);
+}
+
 // ---- LDS of the kernel with M copies of a mean ---------------------------------------------------
 
 inline int64_t bitmap_bytes(int32_t M) { return M <= 16 ? 2 : 4; }

@@ -49,7 +49,6 @@ namespace moshpit {
 namespace {
 
 constexpr int kPositions = 8;                // of a group, per lane
-constexpr int kClosed = 0, kLds = 1, kAheadOnly = 2, kBits = 3;
 constexpr int kRegisters = 8;                // of a thread for a table
 constexpr int kAhead = 3;                    // rounds that the tables are read ahead
 constexpr uint32_t kPlaceMask = 0x1fff1fffu; // a place has 13 bits; the other 3 of a lane's first two hold the group's count
@@ -1056,33 +1055,29 @@ namespace {
 
 typedef void (*mean_kernel_t)(char *, GridPlan);
 
-template <int DT, int SPLIT, int HALF, int TAB> mean_kernel_t pick_mode(bool nt, bool dist)
+template <int DT, int SPLIT, int HALF, int TAB, bool NT, bool DIST> mean_kernel_t built()
 {
-    // (rows of less than a cache line are never streamed)
-    if constexpr (TAB == kAheadOnly) return dist ? mean_rounds_kernel<DT, SPLIT, HALF, false, true, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, false, false, TAB>;
-    else if constexpr (DT == 1 && TAB == kLds) return nt ? mean_rounds_kernel<DT, SPLIT, HALF, true, false, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, false, false, TAB>;
-    else
-    return nt ? (dist ? mean_rounds_kernel<DT, SPLIT, HALF, true, true, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, true, false, TAB>)
-              : (dist ? mean_rounds_kernel<DT, SPLIT, HALF, false, true, TAB> : mean_rounds_kernel<DT, SPLIT, HALF, false, false, TAB>);
+    if constexpr (mean_kernel_built(DT, SPLIT, HALF, NT, DIST, TAB)) return mean_rounds_kernel<DT, SPLIT, HALF, NT, DIST, TAB>;
+    else return nullptr;
 }
-// (grids with tables have 8^d, 16^d or 32^d peers: two parts of 64 bytes or of 16)
-template <int DT, int SPLIT> mean_kernel_t pick_tables(const GridPlan &p, bool dist)
+template <int DT, int SPLIT, int HALF, int TAB> mean_kernel_t pick_mode(const MeanKernel &k)
 {
-    const bool nt = p.streaming != 0, wide = p.part >= kLeastLdsPart;
-    if (p.entries != nullptr) {
-        if constexpr (SPLIT == 2)
-            if (p.bits) return dist ? nullptr : p.phases == 1 ? mean_rounds_kernel<DT, 2, 0, false, false, kBits> : mean_rounds_kernel<DT, 2, 1, false, false, kBits>;
-        if (p.bits) return nullptr;
-        if (wide && DT == 1 && dist) return nullptr;         // (choose_means: too few registers)
-        if (p.phases == 1) return wide ? pick_mode<DT, SPLIT, 0, kLds>(nt, dist) : pick_mode<DT, SPLIT, 0, kAheadOnly>(nt, dist);
-        return wide ? pick_mode<DT, SPLIT, 32, kLds>(nt, dist) : p.part == 16 ? pick_mode<DT, SPLIT, 1, kAheadOnly>(nt, dist) : nullptr;
-    }
-    if (p.phases == 1) return pick_mode<DT, SPLIT, 0, kClosed>(nt, dist);
-    return wide ? pick_mode<DT, SPLIT, 32, kClosed>(nt, dist) : p.part == 32 ? pick_mode<DT, SPLIT, 2, kClosed>(nt, dist) : pick_mode<DT, SPLIT, 1, kClosed>(nt, dist);
+    return k.nt ? (k.dist ? built<DT, SPLIT, HALF, TAB, true, true>() : built<DT, SPLIT, HALF, TAB, true, false>())
+                : (k.dist ? built<DT, SPLIT, HALF, TAB, false, true>() : built<DT, SPLIT, HALF, TAB, false, false>());
 }
-template <int DT> mean_kernel_t pick_kernel(const GridPlan &p, bool dist)
+template <int DT, int SPLIT, int HALF> mean_kernel_t pick_tables(const MeanKernel &k)
 {
-    return p.split == 1 ? pick_tables<DT, 1>(p, dist) : p.split == 2 ? pick_tables<DT, 2>(p, dist) : pick_tables<DT, 4>(p, dist);
+    return k.tab == kClosed ? pick_mode<DT, SPLIT, HALF, kClosed>(k) : k.tab == kLds ? pick_mode<DT, SPLIT, HALF, kLds>(k)
+         : k.tab == kAheadOnly ? pick_mode<DT, SPLIT, HALF, kAheadOnly>(k) : pick_mode<DT, SPLIT, HALF, kBits>(k);
+}
+template <int DT, int SPLIT> mean_kernel_t pick_parts(const MeanKernel &k)
+{
+    return k.half == 0 ? pick_tables<DT, SPLIT, 0>(k) : k.half == 1 ? pick_tables<DT, SPLIT, 1>(k)
+         : k.half == 2 ? pick_tables<DT, SPLIT, 2>(k) : pick_tables<DT, SPLIT, 32>(k);
+}
+template <int DT> mean_kernel_t pick_kernel(const MeanKernel &k)
+{
+    return k.split == 1 ? pick_parts<DT, 1>(k) : k.split == 2 ? pick_parts<DT, 2>(k) : pick_parts<DT, 4>(k);
 }
 
 }  // namespace
@@ -1093,7 +1088,8 @@ hipError_t launch_mean_rounds(void *X, int dtype, const GridPlan &plan, hipStrea
     const bool dist = p.partials != nullptr;
     p.lds_bytes = static_cast<int32_t>(means_lds_bytes(p, p.entries != nullptr, p.rounds, dist, dtype == 0 ? 4 : 2, &p.red_offset));
     if (p.lds_bytes > kLdsPerBlock || p.tiles > 0x7fffffffLL || p.grad != nullptr) return hipErrorInvalidValue;
-    const mean_kernel_t kernel = dtype == 0 ? pick_kernel<0>(p, dist) : pick_kernel<1>(p, dist);
+    const MeanKernel which = mean_kernel(p, p.entries != nullptr, dist);
+    const mean_kernel_t kernel = dtype == 0 ? pick_kernel<0>(which) : pick_kernel<1>(which);
     if (kernel == nullptr) return hipErrorInvalidValue;
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsPerBlock);
     if (e != hipSuccess) return e;

@@ -128,6 +128,45 @@ def test_one_mean_per_group_takes_no_more_passes(tmp_path):
     assert out.returncode == 0, out.stdout
 
 
+KERNELS = SWEEP.replace("return bad != 0", "built(); return bad != 0").replace("int main()", "static void built();\nint main()") + r"""
+#include <set>
+#include <tuple>
+static std::set<std::tuple<int, int, int, int, int, int>> asked;
+static void check(const GridPlan &p, int dtype, const GridAsk &a)
+{
+    if (!p.means) return;
+    for (int dist = 0; dist <= (a.distortions ? 1 : 0); ++dist) {       // (a pass none of whose distortions is returned does without)
+        const MeanKernel k = mean_kernel(p, a.absent, dist != 0);
+        if (!mean_kernel_built(dtype, k.split, k.half, k.nt, k.dist, k.tab)) say("no such kernel", p, dtype, a);
+        asked.insert({dtype, k.split, k.half, k.nt, k.dist, k.tab});
+    }
+}
+static void built()
+{
+    int n = 0;
+    for (int dtype : {0, 1})
+        for (int split : {1, 2, 4})
+            for (int half : {0, 1, 2, 32})
+                for (int nt : {0, 1})
+                    for (int dist : {0, 1})
+                        for (int tab : {kClosed, kLds, kAheadOnly, kBits}) {
+                            if (!mean_kernel_built(dtype, split, half, nt != 0, dist != 0, tab)) continue;
+                            ++n;
+                            if (asked.count({dtype, split, half, nt, dist, tab}) == 0) {
+                                std::printf("never asked for: dtype %d split %d half %d nt %d dist %d tab %d\n", dtype, split, half, nt, dist, tab);
+                                ++bad;
+                            }
+                        }
+    std::printf("%d kernels\n", n);
+}
+"""
+
+
+def test_the_kernels_that_are_built_are_those_that_plans_ask_for(tmp_path):
+    out = run_host(tmp_path, KERNELS)
+    assert out.returncode == 0, out.stdout
+
+
 CHOICE = r"""
 #include <cstdio>
 #include "pass_rules.h"
