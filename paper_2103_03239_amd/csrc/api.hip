@@ -405,35 +405,27 @@ int queue_grid_plan(moshpit_ctx *h, const moshpit_schedule *s, int64_t t0, int32
     return MOSHPIT_OK;
 }
 
-// The same for the kernel that keeps one mean per group: [entries][final places of each pass][moves][terms, where distortions are
-// wanted][move counts][term counts][bitmaps under group-skip].
-int64_t mean_plan_bytes(const GridPlan &plan, int64_t rounds, int64_t pass_rounds)
-{
-    return rounds * mean_table_round_bytes(plan.N, plan.M, plan.split) +
-           2 * mean_place_stride(plan) * ((rounds + pass_rounds - 1) / pass_rounds);
-}
+// The same for the kernel that keeps one mean per group (mean_table_words).
 int queue_mean_plan(moshpit_ctx *h, const moshpit_schedule *s, const GridPlan &plan, int64_t t0, int32_t r0, int32_t rounds,
                     int32_t pass_rounds, bool want_terms, MeanTables *tables)
 {
     const GridSchedule g = grid_schedule(h, s, t0, r0, rounds);
-    const int64_t R = rounds, groups = plan.groups, N = plan.N;
+    const MeanTableWords w = mean_table_words(plan, rounds, pass_rounds, want_terms, g.group_skip != 0);
+    uint32_t *words = static_cast<uint32_t *>(h->d_grid);
     MeanTables o{};
     o.pass_rounds = pass_rounds;
     o.place_stride = mean_place_stride(plan);
-    uint32_t *at = static_cast<uint32_t *>(h->d_grid);
-    const auto take = [&](int64_t words) { uint32_t *mine = at; at += words; return mine; };
-    // (16-byte pieces first: they are read as such)
-    o.entries = take(plan.bits ? R * groups : R * groups * plan.split * 4);
+    o.entries = words + w.entries;
     if (plan.bits) {
-        o.move_rows = take((R + 15) / 16 * 8 * plan.threads);
-        o.move_bytes = take((R + 15) / 16 * 4 * plan.threads);
+        o.move_rows = words + w.move_rows;
+        o.move_bytes = words + w.move_bytes;
     }
-    o.places = reinterpret_cast<uint16_t *>(take((R + pass_rounds - 1) / pass_rounds * o.place_stride / 2));
-    o.moves = take(R * N);
-    if (want_terms) o.terms = take(R * (N + groups));
-    o.move_counts = reinterpret_cast<int32_t *>(take(R));
-    o.term_counts = reinterpret_cast<int32_t *>(take(R));
-    if (g.group_skip) o.bitmaps = take(R * groups);
+    o.places = reinterpret_cast<uint16_t *>(words + w.places);
+    o.moves = words + w.moves;
+    if (want_terms) o.terms = words + w.terms;
+    o.move_counts = reinterpret_cast<int32_t *>(words + w.move_counts);
+    o.term_counts = reinterpret_cast<int32_t *>(words + w.term_counts);
+    if (g.group_skip) o.bitmaps = words + w.bitmaps;
     HIP_TRY(h, launch_mean_plan(g, plan, o, h->stream));
     *tables = o;
     return MOSHPIT_OK;
@@ -683,7 +675,7 @@ int run_on_grid(moshpit_ctx *h, int64_t t0, int32_t rounds, const moshpit_schedu
         const int64_t most = rounds < tables_most ? rounds : tables_most;
         if (failures && rounds > 0)
             rc = grow_if_fits(h, &h->d_grid, &h->grid_cap,
-                              plan.means ? mean_plan_bytes(plan, most, pass_most)
+                              plan.means ? 4 * mean_table_words(plan, most, pass_most, dist_out_host != nullptr, s->group_skip != 0).total
                                          : most * grid_table_round_bytes(h->N, h->M, refresh) + h->N,
                               &fits);
         if (rc == MOSHPIT_OK && fits && dist_out_host)

@@ -124,6 +124,30 @@ inline int64_t means_lds_bytes(const GridPlan &p, bool tables, int32_t rounds, b
     return at;
 }
 
+// Its tables for `rounds` rounds in passes of pass_rounds, in 32-bit words from the start of a buffer: [entries][with bits: rows that
+// move][final places of each pass][moves][terms, where distortions are wanted][move counts][term counts][bitmaps under
+// group-skip].  Pieces that are read 16 bytes at a time come first.
+struct MeanTableWords {
+    int64_t entries, move_rows, move_bytes, places, moves, terms, move_counts, term_counts, bitmaps, total;
+};
+inline MeanTableWords mean_table_words(const GridPlan &p, int64_t rounds, int64_t pass_rounds, bool terms, bool group_skip)
+{
+    MeanTableWords w{};
+    int64_t at = 0;
+    const auto take = [&](int64_t words) { const int64_t mine = at; at += words; return mine; };
+    w.entries = take(p.bits ? rounds * p.groups : rounds * p.groups * p.split * 4);
+    w.move_rows = take(p.bits ? (rounds + 15) / 16 * 8 * p.threads : 0);
+    w.move_bytes = take(p.bits ? (rounds + 15) / 16 * 4 * p.threads : 0);
+    w.places = take((rounds + pass_rounds - 1) / pass_rounds * mean_place_stride(p) / 2);
+    w.moves = take(rounds * p.N);
+    w.terms = take(terms ? rounds * (p.N + p.groups) : 0);
+    w.move_counts = take(rounds);
+    w.term_counts = take(rounds);
+    w.bitmaps = take(group_skip ? rounds * p.groups : 0);
+    w.total = at;
+    return w;
+}
+
 // Which instance of the kernel takes a pass.  half: lanes between the two column parts of a tile, 0 = one part; tab: where the
 // places come from (mean_rounds.hip).
 constexpr int kClosed = 0, kLds = 1, kAheadOnly = 2, kBits = 3;

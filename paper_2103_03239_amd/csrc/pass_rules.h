@@ -10,7 +10,8 @@ namespace moshpit {
 
 // Tables of whole-grid passes (who takes part in which round, who copies whom) are built for a
 // bounded number of rounds at a time, so that their memory and the launch that fills them do not
-// grow with the length of a run: 16 MiB hold 16,000 rounds of 16 x 16 x 16 peers, 900 with refresh.
+// grow with the length of a run.  16 MiB hold, of 16 x 16 x 16 peers, 16,000 rounds of the kernel with M copies of a mean (with
+// refresh 960) and 390 of the kernel that keeps one mean per group, in both cases cut to whole passes.
 constexpr int64_t kGridTableBytes = int64_t(16) << 20;
 constexpr int64_t kGridTableRounds = 65536;            // (the launch has one block per round)
 
@@ -20,8 +21,8 @@ inline int64_t grid_table_round_bytes(int64_t N, int32_t M, bool refresh)
     return 4 * (N / M) + (refresh ? 4 * N + 4 : 0);
 }
 
-// Of the kernel that keeps one mean per group: 16 bytes of places per lane of a group, 4 bytes per peer that moves, 4 per term of the distortion, two counts; a bitmap per group for
-// group-skip schedules.
+// Of the kernel that keeps one mean per group, at most (mean_table_words): 16 bytes of places per lane of a group, 4 per peer that
+// moves, 4 per term of the distortion, two counts, a bitmap per group.
 inline int64_t mean_table_round_bytes(int64_t N, int32_t M, int32_t split)
 {
     const int64_t groups = N / M;

@@ -167,6 +167,43 @@ def test_the_kernels_that_are_built_are_those_that_plans_ask_for(tmp_path):
     assert out.returncode == 0, out.stdout
 
 
+TABLES = SWEEP.replace('#include "grid_plan.h"', '#include "pass_rules.h"') + r"""
+static void check(const GridPlan &p, int dtype, const GridAsk &a)
+{
+    if (!p.means || !a.absent) return;
+    const int64_t pass_most = grid_pass_rounds(p.max_rounds, a.distortions ? p.tiles * p.phases : 0);
+    const int64_t most = table_rounds(mean_table_round_bytes(p.N, p.M, p.split), pass_most);
+    if (most < pass_most || most % pass_most != 0 || (p.bits && pass_most % 16 != 0)) say("passes", p, dtype, a);
+    for (int skip = 0; skip <= 1; ++skip) {
+        const MeanTableWords full = mean_table_words(p, most, pass_most, a.distortions, skip != 0);
+        // (final places: 2 bytes for every slot of a pass)
+        const int64_t places = 2 * mean_place_stride(p) * (most / pass_most);
+        if (4 * full.total > kGridTableBytes + places && most > pass_most) say("bound", p, dtype, a);
+        for (int64_t rounds : {int64_t(1), int64_t(5), int64_t(17), pass_most, pass_most + 1, most - 1, most}) {
+            if (rounds < 1 || rounds > most) continue;
+            const MeanTableWords w = mean_table_words(p, rounds, pass_most, a.distortions, skip != 0);
+            if (w.total > full.total || w.total >= (int64_t(1) << 31)) say("size", p, dtype, a);
+            if (w.entries % 4 != 0 || w.move_rows % 4 != 0 || w.move_bytes % 4 != 0 || w.places % 4 != 0) say("alignment", p, dtype, a);
+            // what the kernels index: the last word of each piece lies before the next
+            const int64_t width = p.bits ? 1 : 4 * p.split, last = rounds - 1;
+            if ((last * p.groups + p.groups - 1) * width + width > w.move_rows - w.entries) say("entries", p, dtype, a);
+            if (p.bits && (last / 2 * p.threads + p.threads - 1 >= w.move_bytes - w.move_rows ||
+                           last / 4 * p.threads + p.threads - 1 >= w.places - w.move_bytes)) say("rows", p, dtype, a);
+            if (p.bits && (last / 16 * 8 + 8) * p.threads > w.move_bytes - w.move_rows) say("rows read ahead", p, dtype, a);
+            if (2 * (w.moves - w.places) < (last / pass_most + 1) * mean_place_stride(p)) say("places", p, dtype, a);
+            if (w.terms - w.moves < rounds * p.N || w.move_counts - w.terms < (a.distortions ? rounds * (p.N + p.groups) : 0)) say("moves", p, dtype, a);
+            if (w.term_counts - w.move_counts < rounds || w.bitmaps - w.term_counts < rounds || w.total - w.bitmaps < skip * rounds * p.groups) say("counts", p, dtype, a);
+        }
+    }
+}
+"""
+
+
+def test_tables_of_one_mean_per_group_are_bounded_and_do_not_overlap(tmp_path):
+    out = run_host(tmp_path, TABLES)
+    assert out.returncode == 0, out.stdout
+
+
 CHOICE = r"""
 #include <cstdio>
 #include "pass_rules.h"
