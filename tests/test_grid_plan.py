@@ -312,3 +312,74 @@ def test_the_cheaper_way_of_measured_runs_is_taken(tmp_path):
     got = plans(tmp_path, [row[:9] for row in WAYS])
     wrong = [(row, g) for row, g in zip(WAYS, got, strict=True) if g[2] != (row[10] < row[9]) or not g[3]]
     assert not wrong, wrong
+
+
+INSTANCE = r"""
+#include <cstdio>
+#include "pass_rules.h"
+using namespace moshpit;
+int main()
+{
+    int M, d, dtype, rounds, down, skip, curve, refresh;
+    long long P, stride, offset;
+    double p;
+    while (std::scanf("%d %d %d %lld %lld %lld %d %lf %d %d %d %d", &M, &d, &dtype, &P, &stride, &offset, &rounds, &p, &down, &skip, &curve, &refresh) == 12) {
+        int64_t N = 1;
+        for (int q = 0; q < d; ++q) N *= M;
+        GridAsk a;
+        a.absent = p > 0.0;
+        a.distortions = curve != 0;
+        a.refresh = refresh != 0;
+        a.rounds = rounds;
+        const Participation who = a.absent ? independent_presence((1.0 - p) / (1.0 + p * (down - 1)), M, skip != 0) : Participation{};
+        a.averaged = who.averaged;
+        a.live = who.groups;
+        GridPlan g;
+        const void *at = reinterpret_cast<void *>(4096 + offset * (dtype == 0 ? 4 : 2));
+        if (!plan_grid(dtype, N, M, d, P, stride, at, 0, a, &g) || !g.means) {
+            std::printf("none\n");
+            continue;
+        }
+        const MeanKernel k = mean_kernel(g, a.absent, a.distortions);
+        std::printf("%s %d x %d|%d %d %d %d %d %d\n", k.tab == kClosed ? "closed" : k.tab == kLds ? "lds" : k.tab == kAheadOnly ? "ahead" : "bits", g.phases,
+                    g.part, dtype, k.split, k.half, k.nt, k.dist, k.tab);
+    }
+}
+"""
+
+BUILT = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "grid_plan.h"
+using namespace moshpit;
+int main()
+{
+    for (int dtype : {0, 1})
+        for (int split : {1, 2, 4})
+            for (int half : {0, 1, 2, 32})
+                for (int nt : {0, 1})
+                    for (int dist : {0, 1})
+                        for (int tab : {kClosed, kLds, kAheadOnly, kBits})
+                            if (mean_kernel_built(dtype, split, half, nt != 0, dist != 0, tab))
+                                std::printf("%d %d %d %d %d %d\n", dtype, split, half, nt, dist, tab);
+}
+"""
+
+
+def test_the_gpu_tests_take_every_kernel(tmp_path):
+    """The runs that test_gpu_mean_rounds.py compares with single rounds go where they say, and together through every instance."""
+    import test_gpu_mean_rounds as gpu
+    runs = [(M, d, dtype, P, *gpu.layout(M ** d, P, dtype, where), rounds, p, 2, skip, curve, refresh, kernel)
+            for M, d, P, dtype, where, p, rounds, refresh, skip, curve, kernel in gpu.FAILURES]
+    runs += [(M, d, dtype, P, *gpu.layout(M ** d, P, dtype, where), rounds, 0.0, 1, 0, curve, 0, "closed " + parts if parts and not dtype else None)
+             for M, d, P, where, rounds, parts in gpu.EVERYBODY for dtype in (0, 1) for curve in (0, 1)]
+    runs += [(M, d, dtype, P, *gpu.layout(M ** d, P, dtype, where), rounds, p, 1, 0, 1, refresh, None)
+             for M, d, P, dtype, where, p, rounds, refresh in gpu.LONG_CURVES]
+    text = "".join(" ".join(str(int(v) if isinstance(v, bool) else v) for v in run[:-1]) + "\n" for run in runs)
+    out = run_host(tmp_path, INSTANCE, text).stdout.splitlines()
+    assert len(out) == len(runs)
+    wrong = [(run, got) for run, got in zip(runs, out) if got == "none" or (run[-1] is not None and got.split("|")[0] != run[-1])]
+    assert not wrong, "\n".join(map(str, wrong))
+    built = set(run_host(tmp_path, BUILT).stdout.splitlines())
+    taken = {got.split("|")[1] for got in out}
+    assert taken == built, sorted(built - taken)
