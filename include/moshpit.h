@@ -101,8 +101,9 @@ typedef struct {
  * one.  On grids of up to 4096 peers with M <= 32 and rows of at least 16 bytes
  * a pass can cover the whole grid, whatever the flags, with the distortions that
  * the run returns and the refresh of returning peers computed on the way (not
- * 2^12 peers, and not 24 x 24 bfloat16 peers of more than 256 MiB).  It is taken
- * where it is estimated to cost less than the rounds one by one, which depends
+ * 2^12 peers, and 24 x 24 bfloat16 peers of more than 256 MiB only with nobody
+ * absent and more than 3 rounds or a distortion).  It is taken where
+ * it is estimated to cost less than the rounds one by one, which depends
  * on the participation too; a run that asks for the time of every single round
  * (round_ms_out_host without MOSHPIT_RUN_FUSED), or for whose scratch there is no
  * memory, goes round by round.

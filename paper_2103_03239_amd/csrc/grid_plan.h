@@ -207,10 +207,11 @@ inline int64_t blocks_by_lds(int64_t bytes) { return 128 / ((bytes + 1279) / 128
 //     with distortions ahead everywhere (16 x 16, 1 GB binary32, 5 rounds 602 : 860).  Groups of 2 to 4 save little.
 //   with failures, whose tables cost a launch and a wait: ahead from 5 rounds (4 on more than 1024 peers) of
 //     states beyond 32 MB on (32 x 32, 16 GB, 8 rounds 8,110 : 9,320, 4 rounds of 200 MB 85 : 83; 16 x 16 x 16, 1.5 GB
-//     bfloat16, 4 rounds 911 : 1,222, 16 rounds 1,570 : 2,640; 8 MB, 8 rounds 31 : 28), and not for 8 x 8 peers, whose passes
+//     bfloat16, 4 rounds 911 : 1,222, 16 rounds 1,570 : 2,640; 8 MB, 8 rounds 31 : 28; not taken although ahead: longer runs
+//     of small states, 8 MB, 16 rounds 38 : 54), and not for 8 x 8 peers, whose passes
 //     wait for memory (1.5 GB binary32, 8 rounds 652 : 631).  Places are 8 to a lane: groups of 8, 16 or 32.  The
 //     distortion of bfloat16 rows of 64 bytes and more spills (16 x 16, 1 GB, 5 rounds 1,616 : 1,341).
-// A local step would take its registers: not with one.
+// A local step would take its registers: not with one.  Where both have a plan copies_ahead looks closer.
 inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
 {
     const int64_t state = p->N * p->row_bytes;

@@ -66,7 +66,8 @@ def test_tables_of_a_long_run_are_bounded_and_hold_whole_passes(tmp_path):
 
 # Measured on MI355X: grid, rounds, fraction of the peers absent, group-skip, fused passes of the other way
 # (rounds, whole grid, blocks per compute unit), tile of the whole-grid pass (bytes of a row, parts, threads,
-# LDS bytes, rounds), curve; microseconds of the other way and of the pass.
+# LDS bytes, rounds), curve; microseconds of the other way and of the pass with M copies of a mean (some of the longer runs
+# take the kernel with one mean per group by now: test_grid_plan.py has measured runs of that one).
 MEASURED = [
     (16, 2, 4, 1_048_576, 2, 0.0, 0, [], (256, 1, 512, 65_800, 64), 0, 733, 408),
     (16, 2, 4, 1_048_576, 2, 0.2, 0, [], (256, 1, 512, 65_800, 64), 0, 597, 402),
