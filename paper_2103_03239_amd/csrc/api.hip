@@ -541,7 +541,7 @@ int moshpit_bind_state(moshpit_ctx *h, void *state_dev, int64_t row_stride_elems
         return fail(h, MOSHPIT_EINVAL, "state pointer is not device memory");
     }
     if (h->X) HIP_TRY(h, hipStreamSynchronize(h->stream));
-    const int64_t need = dist_partials_count(h->dtype, h->P);
+    const int64_t need = dist_partials_count(h->dtype, h->N, h->P);
     if (need > h->partials_cap) {
         if (h->d_partials) HIP_TRY(h, hipFree(h->d_partials));
         h->d_partials = nullptr;

@@ -1,0 +1,57 @@
+// Tiles of the distortion's pass over a state (dist_to_mean.hip): host arithmetic on plain numbers, without GPU types.
+#pragma once
+
+#include <stdint.h>
+
+namespace moshpit {
+
+struct DistTiles {
+    int32_t lanes, waves;        // 16-byte vectors of a row in a tile; waves of a block, which share its rows
+    int64_t blocks;
+    bool streaming;              // non-temporal loads
+};
+
+// Tiles for N rows of P elements; whole_lines: rows start on cache lines.  false: rows of less than a vector, or too many of
+// them for 32-bit row numbers.  From sweeps on MI355X (8 to 64 lanes, 1 to 8 waves, both kinds of loads; 9 to 4096 rows, 0.4 MB
+// to 1.6 GB, on and off the cache lines), us:
+//   Tiles as wide as leaves 160 of them, whose 8 waves a block then make 1,300 on the chip: 4096 rows, 400 MB, 32 lanes x 8
+//   waves 60, 8 x 1 64; 1024 rows, 25 MB, 8 x 8 8.2, 16 x 8 9.6; 512 rows, 100 MB, 64 x 8 18.0, 16 x 1 19.1.  A block of several
+//   waves ends with barriers for every element of a vector, so bfloat16 states of few rows take narrow tiles of one wave:
+//   144 rows, 25 MB, 16 x 1 10.3, 32 x 4 12.5.
+//   Waves until the chip has 1,000: 4096 rows, 2.1 GB bfloat16, 32 x 1 316, 16 x 8 344; 256 rows, 400 MB, 1 wave 64.5, 8 waves
+//   73.5; 1024 rows, 25 MB binary32, 8 waves 8.2, 4 waves 8.8.  Beyond 1 GB of binary32 few columns at a time are better for
+//   HBM: 256 rows, 1.6 GB, 8 waves 233, 1 wave 239; 64 rows 233 and 241.
+//   Fewer than 32 rows are a load or two of a wide tile: 16 rows, 6.4 MB bfloat16, 32 x 1 6.9, 8 x 4 9.4.
+//   Never more than 65,536 tiles where they can be wider (their sums take one block 10 us).
+//   Non-temporal loads beyond 64 MB (4096 rows, 1.6 GB 231 : 250; 1024 rows, 25 MB 9.4 : 8.2), but where neighbours share cache lines
+//   only in 1 KiB tiles of 32 rows and more (1024 rows, 1.6 GB, 32 lanes 281 : 262, 64 lanes 248 : 258; 144 rows 256 : 269; 9 rows, 100 MB
+//   22.5 : 20.8), which such states take as soon as there are enough.
+inline bool dist_tiles(int64_t esize, int64_t N, int64_t P, bool whole_lines, DistTiles *out)
+{
+    const int64_t row = P * esize;
+    if (row < 16 || N > (int64_t(1) << 30)) return false;
+    const int64_t vectors = (row + 15) / 16;
+    const double state = static_cast<double>(N) * static_cast<double>(row);
+    const bool f32 = esize == 4, large = state > 1e9, few = N < 32;
+    int32_t lanes = few ? (f32 || N <= 12 ? 64 : 32) : f32 && N < 1024 ? 64 : 32;
+    if (!whole_lines && !few && (f32 ? vectors >= 65536 : large && N < 512)) lanes = 64;
+    const int64_t least = f32 || N >= 512 ? 160 : 512;
+    while (!few && lanes > 8 && vectors < least * lanes) lanes /= 2;
+    while (lanes < 64 && vectors > 65536ll * lanes) lanes *= 2;
+    const int64_t blocks = (vectors + lanes - 1) / lanes;
+    if (blocks > 0x7fffffffll) return false;
+    int32_t waves = 1;
+    const auto twice = [&] { return waves < 8 && N >= 2 * waves * (64 / lanes); };           // (a row for every lane)
+    if (!few) {
+        while (twice() && blocks * waves < 1000) waves *= 2;
+        if (large && f32 && (N < 128 || (N >= 256 && N < 1024)))
+            while (twice()) waves *= 2;
+    }
+    out->lanes = lanes;
+    out->waves = waves;
+    out->blocks = blocks;
+    out->streaming = state > 64e6 && (whole_lines || (lanes == 64 && !few));
+    return true;
+}
+
+}  // namespace moshpit

@@ -9,22 +9,28 @@
 // are then tiny and exact in binary64.  With a `present` mask (a partly filled
 // grid) the same runs over the rows that hold a peer, shifted by the first one.
 //
-// Mapping.  A block owns a tile of 64 vectors (one 128-bit vector per lane,
-// 1 KiB per row); its W waves (W chosen so that a wave sees about 256 rows) take
-// rows w, w+W, ... with 8 (bfloat16: 4) non-temporal row loads in flight each, then
-// combine their per-column sums through LDS, reduce across lanes and write ONE
-// partial per block.  A second one-block kernel adds the partials in a fixed
-// order, so the result does not depend on scheduling.
+// Mapping (dist_rows_kernel).  A block owns a tile of `lanes` vectors of 16 bytes of every row; a
+// wave has 64 / lanes rows in one load, eight loads in flight and its block's waves take turns along the
+// rows.  Their per-column sums meet across lanes and in LDS, and the block writes ONE partial.  A second
+// one-block kernel adds the partials in a fixed order, so the result does not depend on scheduling.
 //
-// What bounds it (MI355X).  Large states HBM: 1024 rows of 16 MiB at 6.9 TB/s.
-// Short rows the walk of a wave over its 256 rows: 1024 rows of 15,625 binary32,
-// 64 MB in 62 blocks, 67 us.  That walk took 146 us while every load stood behind
-// a branch of its own, which made the compiler wait for it before the next; rows
-// off the 16-byte boundaries, element by element in four times as many blocks, 71.
+// What bounds it (MI355X): HBM where there are enough tiles (6.8 to 6.9 TB/s from 1.6 GB on); below, the
+// walk along the rows, so tiles get narrower until the chip has waves enough (dist_tiles.h).  A tile was
+// 64 vectors wide whatever the state's shape, with a wave for 256 rows of it.  us, both kernels, then and now:
+//   1024 rows, 25 MB            binary32 44.6 -> 8.2     bfloat16 75 -> 11.2
+//   256 rows, 6.4 MB            39.9 -> 7.4              69 -> 9.3
+//   4096 rows, 100 MB           82 -> 19.5               110 -> 22
+//   512 rows, 400 MB            64 -> 61                 93 -> 65
+//   4096 rows, 1.6 GB           253 -> 232               273 -> 236
+//   4096 rows, 2.1 GB                                    344 -> 314
+//   16 rows, 1.6 GB             321 -> 243               328 -> 272   (the sum of 97,657 partials: 60 us of it)
+// dist_partial_kernel takes a row mask, and rows of less than 16 bytes.
 #include <mutex>
 
+#include "dist_tiles.h"
 #include "moshpit_internal.h"
 #include "row_vec.h"
+#include "sum_partials.h"
 
 // Partial sums of the allocation-free entry point: one double per block of the
 // first kernel, kept in the code object so that no call ever allocates.  Every
@@ -163,45 +169,194 @@ __global__ __launch_bounds__(kWaves * 64) void dist_partial_kernel(const char *_
     }
 }
 
-__global__ __launch_bounds__(256) void dist_final_kernel(const double *__restrict__ partials, int64_t count,
-                                                         int64_t n, double *__restrict__ out)
+constexpr int kRowLoads = 8;       // of a lane in flight
+constexpr int kDieRun = 32;
+
+// The same where every row counts and has 16 bytes or more.  LANES lanes of a wave take a row's part of the tile, the
+// others the rows after it.  Dynamic LDS: rows_lds_bytes (sized by the block's waves: one-wave blocks take none, with
+// the 33 KB of 16 waves five of them shared a compute unit, and 16 rows of 100 MB took 425 us instead of 243).
+constexpr int rows_lds_bytes(int lanes, int waves) { return waves == 1 ? 0 : (4 * lanes + 1) * waves * 8; }
+
+template <int DT, int LANES, bool NT>
+__global__ __launch_bounds__(8 * 64, 4) void dist_rows_kernel(const char *__restrict__ X, int64_t row_bytes, int64_t valid_bytes,
+                                                           int32_t N, double *__restrict__ partials)
 {
-    __shared__ double sh[256];
-    double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < count; i += 256) acc += partials[i];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (static_cast<int>(threadIdx.x) < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
+    typedef Wide<DT, DT == 0 ? 4 : 8> V;
+    typedef typename V::mem_t mem_t;
+    constexpr int NE = V::NE, kRows = 64 / LANES;
+    extern __shared__ __align__(16) double lds[];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    const int c = lane & (LANES - 1), sub = lane / LANES;
+    // Blocks b, b + 8, b + 16, ... run on the same one of the 8 dies; each die takes kDieRun neighbouring tiles, so that
+    // the parts of a cache line that two of them share meet in its L2.
+    int64_t tile = blockIdx.x;
+    const int64_t span = tile / (8 * kDieRun) * (8 * kDieRun), in_span = tile - span;
+    if (span + 8 * kDieRun <= gridDim.x) tile = span + (in_span & 7) * kDieRun + (in_span >> 3);
+    const int64_t begin = (tile * LANES + c) * 16;
+    const bool valid = begin < valid_bytes;                 // (a lane past the row reads its last vector, for nothing)
+    const int64_t at = begin < valid_bytes - 16 ? begin : valid_bytes - 16;
+    const int shared = static_cast<int>((begin - at) / (16 / NE));           // elements that belong to the neighbour
+    const char *col = X + at;
+
+    double x0[NE], s1[NE], s2[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) { s1[e] = 0.0; s2[e] = 0.0; }
+    V::widen(load_vec<false, mem_t>(col), x0);
+    const auto add = [&](const mem_t &row) {
+        double x[NE];
+        V::widen(row, x);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const double dlt = x[e] - x0[e];
+            s1[e] += dlt;
+            s2[e] = fma(dlt, dlt, s2[e]);
+        }
+    };
+    // From the last row to the first: rounds and whoever fills a state end with the last rows, which the last-level cache
+    // then holds (4096 rows of a state just written, 2.1 GB bfloat16, 402 -> 380 us, 1024 rows of 4.3 GB binary32 794 -> 775).
+    const int32_t step = waves * kRows;
+    const int64_t step_bytes = step * row_bytes;
+    const char *from = col + (N - 1 - (wave * kRows + sub)) * row_bytes;
+    int32_t i = wave * kRows;                               // rows before the wave's next load
+    for (; i + (kRowLoads - 1) * step + kRows <= N; i += kRowLoads * step) {
+        mem_t buf[kRowLoads];
+#pragma unroll
+        for (int u = 0; u < kRowLoads; ++u) {
+            buf[u] = load_vec<NT, mem_t>(from);
+            from -= step_bytes;
+        }
+#pragma unroll
+        for (int u = 0; u < kRowLoads; ++u) add(buf[u]);
     }
-    if (threadIdx.x == 0) out[0] = sh[0] / static_cast<double>(n);
+    if (i < N) {
+        // (row 0, whose difference is 0, in the place of rows before the first)
+        mem_t buf[kRowLoads];
+#pragma unroll
+        for (int u = 0; u < kRowLoads; ++u) {
+            buf[u] = load_vec<NT, mem_t>(i + u * step + sub < N ? from : col);
+            from -= step_bytes;
+        }
+#pragma unroll
+        for (int u = 0; u < kRowLoads; ++u) add(buf[u]);
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int off = 32; off >= LANES; off >>= 1) {
+            s1[e] += __shfl_xor(s1[e], off, 64);
+            s2[e] += __shfl_xor(s2[e], off, 64);
+        }
+
+    double mine = 0.0;
+    if (waves == 1) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (valid && sub == 0 && e >= shared) mine += s2[e] - s1[e] * s1[e] / static_cast<double>(N);
+    } else {
+        // the waves' sums of element e of every vector meet in one of two buffers, and wave e % waves adds them
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            double *here = lds + (e & 1) * 2 * waves * LANES;
+            if (sub == 0) {
+                here[wave * LANES + c] = s1[e];
+                here[(waves + wave) * LANES + c] = s2[e];
+            }
+            __syncthreads();
+            if (wave == (e & (waves - 1)) && sub == 0) {
+                double t1 = 0.0, t2 = 0.0;
+                for (int w = 0; w < waves; ++w) { t1 += here[w * LANES + c]; t2 += here[(waves + w) * LANES + c]; }
+                if (valid && e >= shared) mine += t2 - t1 * t1 / static_cast<double>(N);
+            }
+        }
+    }
+#pragma unroll
+    for (int off = LANES / 2; off > 0; off >>= 1) mine += __shfl_down(mine, off, 64);
+    if (waves == 1) {
+        if (lane == 0) partials[blockIdx.x] = mine;
+        return;
+    }
+    double *total = lds + 4 * waves * LANES;
+    if (lane == 0) total[wave] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double sum = 0.0;
+        for (int w = 0; w < waves; ++w) sum += total[w];
+        partials[blockIdx.x] = sum;
+    }
 }
 
-int64_t row_blocks(int dtype, int64_t P)
+__global__ __launch_bounds__(kSumThreads) void dist_final_kernel(const double *__restrict__ partials, int64_t count,
+                                                                 int64_t n, double *__restrict__ out)
+{
+    const double sum = block_sum(partials, count);
+    if (threadIdx.x == 0) out[0] = sum / static_cast<double>(n);
+}
+
+// Blocks of dist_partial_kernel.
+int64_t general_blocks(int dtype, int64_t P)
 {
     const int64_t valid_bytes = P * (dtype == 0 ? 4 : 2);
     const int64_t nvec = valid_bytes < 16 ? P : (valid_bytes + 15) / 16;
     return (nvec + 63) / 64;
 }
 
+template <int DT, int LANES>
+hipError_t launch_rows(const char *X, int64_t row_bytes, int64_t valid_bytes, int64_t N, const DistTiles &t, double *partials,
+                       hipStream_t stream)
+{
+    const auto kernel = t.streaming ? dist_rows_kernel<DT, LANES, true> : dist_rows_kernel<DT, LANES, false>;
+    kernel<<<dim3(static_cast<uint32_t>(t.blocks)), dim3(t.waves * 64), rows_lds_bytes(LANES, t.waves), stream>>>(
+        X, row_bytes, valid_bytes, static_cast<int32_t>(N), partials);
+    return hipGetLastError();
+}
+template <int DT>
+hipError_t launch_rows_of(const char *X, int64_t row_bytes, int64_t valid_bytes, int64_t N, const DistTiles &t, double *partials,
+                          hipStream_t stream)
+{
+    switch (t.lanes) {
+    case 64: return launch_rows<DT, 64>(X, row_bytes, valid_bytes, N, t, partials, stream);
+    case 32: return launch_rows<DT, 32>(X, row_bytes, valid_bytes, N, t, partials, stream);
+    case 16: return launch_rows<DT, 16>(X, row_bytes, valid_bytes, N, t, partials, stream);
+    case 8: return launch_rows<DT, 8>(X, row_bytes, valid_bytes, N, t, partials, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
 }  // namespace
 
-int64_t dist_partials_count(int dtype, int64_t P) { return row_blocks(dtype, P); }
+int64_t dist_partials_count(int dtype, int64_t N, int64_t P)
+{
+    int64_t most = general_blocks(dtype, P);
+    for (int whole_lines = 0; whole_lines < 2; ++whole_lines) {
+        DistTiles t;
+        if (dist_tiles(dtype == 0 ? 4 : 2, N, P, whole_lines != 0, &t) && t.blocks > most) most = t.blocks;
+    }
+    return most;
+}
 
 hipError_t launch_dist_to_mean(const void *X, int dtype, int64_t N, int64_t P, int64_t row_stride,
                                double *partials, double *out, const uint8_t *present, int64_t first, int64_t n,
                                hipStream_t stream)
 {
-    const int64_t blocks = row_blocks(dtype, P);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int64_t esize = dtype == 0 ? 4 : 2;
     const int64_t row_bytes = row_stride * esize, valid_bytes = P * esize;
     const char *base = static_cast<const char *>(X);
-    // about 256 rows per wave (measured best on MI355X for 64 <= N <= 4096)
-    int waves = 1;
-    while (waves < kMaxWaves && N / (waves * 2) >= 256) waves *= 2;
-    const dim3 grid(static_cast<uint32_t>(blocks));
+    DistTiles tiles;
+    int64_t blocks = 0;
+    hipError_t e = hipSuccess;
+    const bool whole_lines = reinterpret_cast<uintptr_t>(X) % 128 == 0 && row_bytes % 128 == 0;
+    if (present == nullptr && dist_tiles(esize, N, P, whole_lines, &tiles)) {
+        blocks = tiles.blocks;
+        e = dtype == 0 ? launch_rows_of<0>(base, row_bytes, valid_bytes, N, tiles, partials, stream)
+                       : launch_rows_of<1>(base, row_bytes, valid_bytes, N, tiles, partials, stream);
+    } else {
+        blocks = general_blocks(dtype, P);
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+        // about 256 rows per wave
+        int waves = 1;
+        while (waves < kMaxWaves && N / (waves * 2) >= 256) waves *= 2;
+        const dim3 grid(static_cast<uint32_t>(blocks));
 #define MOSHPIT_DIST_CALL(DT, VE, W) \
     dist_partial_kernel<DT, VE, W><<<grid, dim3(W * 64), 0, stream>>>(base, row_bytes, valid_bytes, N, partials, present, first, n)
 #define MOSHPIT_DIST(W)                                                                                        \
@@ -214,18 +369,17 @@ hipError_t launch_dist_to_mean(const void *X, int dtype, int64_t N, int64_t P, i
             else MOSHPIT_DIST_CALL(1, 1, W);                                                                   \
         }                                                                                                      \
     }
-    MOSHPIT_DIST(1)
-    MOSHPIT_DIST(2)
-    MOSHPIT_DIST(4)
-    MOSHPIT_DIST(8)
-    MOSHPIT_DIST(16)
+        MOSHPIT_DIST(1)
+        MOSHPIT_DIST(2)
+        MOSHPIT_DIST(4)
+        MOSHPIT_DIST(8)
+        MOSHPIT_DIST(16)
 #undef MOSHPIT_DIST
 #undef MOSHPIT_DIST_CALL
-    {
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        e = hipGetLastError();
     }
-    dist_final_kernel<<<dim3(1), dim3(256), 0, stream>>>(partials, blocks, n, out);
+    if (e != hipSuccess) return e;
+    dist_final_kernel<<<dim3(1), dim3(sum_threads(blocks)), 0, stream>>>(partials, blocks, n, out);
     return hipGetLastError();
 }
 

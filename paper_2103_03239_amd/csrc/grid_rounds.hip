@@ -39,6 +39,7 @@
 #include <type_traits>
 
 #include "grid_tile.h"
+#include "sum_partials.h"
 #include "tile_math.h"
 
 namespace moshpit {
@@ -364,21 +365,12 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
 
 // out[e] = (sum of partials[e][0 .. tiles)) / n, entry e = blockIdx.x, in a fixed order, for the entries
 // that the pass computed
-__global__ __launch_bounds__(256) void grid_dist_kernel(const double *__restrict__ partials, int64_t tiles, double n,
-                                                        int32_t before, uint64_t after, double *__restrict__ out)
+__global__ __launch_bounds__(kSumThreads) void grid_dist_kernel(const double *__restrict__ partials, int64_t tiles, double n,
+                                                                int32_t before, uint64_t after, double *__restrict__ out)
 {
-    __shared__ double sh[256];
     if (blockIdx.x == 0 ? before == 0 : ((after >> (blockIdx.x - 1)) & 1u) == 0) return;
-    const double *mine = partials + blockIdx.x * tiles;
-    double acc = 0.0;
-    for (int64_t k = threadIdx.x; k < tiles; k += 256) acc += mine[k];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (static_cast<int>(threadIdx.x) < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[blockIdx.x] = sh[0] / n;
+    const double sum = block_sum(partials + blockIdx.x * tiles, tiles);
+    if (threadIdx.x == 0) out[blockIdx.x] = sum / n;
 }
 
 // ---- what a pass needs to know about the peers: one launch per run ----------------------------
@@ -555,8 +547,9 @@ hipError_t launch_grid_rounds(void *X, int dtype, const GridPlan &plan, hipStrea
 
 hipError_t launch_grid_dist(const GridPlan &p, double *out, hipStream_t stream)
 {
-    grid_dist_kernel<<<dim3(static_cast<uint32_t>(p.rounds + 1)), dim3(256), 0, stream>>>(
-        p.partials, p.tiles * p.phases, static_cast<double>(p.N), p.dist_before, p.dist_after, out);
+    const int64_t tiles = p.tiles * p.phases;
+    grid_dist_kernel<<<dim3(static_cast<uint32_t>(p.rounds + 1)), dim3(sum_threads(tiles)), 0, stream>>>(
+        p.partials, tiles, static_cast<double>(p.N), p.dist_before, p.dist_after, out);
     return hipGetLastError();
 }
 

@@ -99,7 +99,7 @@ hipError_t launch_local_step(void *X, int dtype, int64_t N, int64_t P, int64_t r
                              int64_t g_row_stride, const uint8_t *alive, float gamma, hipStream_t stream);
 
 // Number of partial sums launch_dist_partials writes for this shape.
-int64_t dist_partials_count(int dtype, int64_t P);
+int64_t dist_partials_count(int dtype, int64_t N, int64_t P);
 
 // Queue the distortion reduction: partials (device, dist_partials_count
 // doubles) then out[0] = (sum of partials) / n.  present: device, N bytes, or
