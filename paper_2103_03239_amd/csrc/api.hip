@@ -1135,7 +1135,7 @@ int moshpit_dynamic_round(moshpit_ctx *h, int64_t t, uint64_t seed, const uint8_
         PeerBits bits;
         if (alive_host) bits = pack_bits(alive_host, h->N);
         HIP_TRY(h, launch_small_grouping(h->N, h->M, h->d, seed, t, alive_host ? &bits : nullptr, L.keys, L.index, L.n_index,
-                                         h->stream));
+                                         L.count, h->stream));
     } else {
         const uint8_t *alive_dev = stage_mask(h, alive_host, &rc);
         if (rc != MOSHPIT_OK) return rc;
@@ -1143,6 +1143,7 @@ int moshpit_dynamic_round(moshpit_ctx *h, int64_t t, uint64_t seed, const uint8_
                                            L.index, L.n_index, h->d_sort, h->stream));
     }
     RoundGeom geom{h->N, h->M, 1, L.index, L.n_index};
+    if (h->N <= kSmallOrderPeers) geom.n_groups = L.count;
     HIP_TRY(h, launch_group_mean(h->X, h->dtype, h->P, h->row_stride, geom, nullptr, h->tune, h->stream));
     return MOSHPIT_OK;
 }
@@ -1154,6 +1155,14 @@ int moshpit_dynamic_keys(moshpit_ctx *h, int32_t *keys_host)
     int rc = dyn_ensure(h);
     if (rc != MOSHPIT_OK) return rc;
     const DynLayout L = dyn_layout(h);
+    if (L.kd > 0 && h->N <= kSmallOrderPeers) {
+        std::vector<int32_t> packed(static_cast<size_t>(h->N));
+        HIP_TRY(h, hipMemcpyAsync(packed.data(), L.keys, sizeof(int32_t) * packed.size(), hipMemcpyDeviceToHost, h->stream));
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        for (int32_t key : packed)
+            for (int64_t q = 0; q < L.kd; ++q, key /= h->M) *keys_host++ = key % h->M;
+        return MOSHPIT_OK;
+    }
     if (L.kd > 0)
         HIP_TRY(h, hipMemcpyAsync(keys_host, L.keys, sizeof(int32_t) * static_cast<size_t>(h->N * L.kd),
                                   hipMemcpyDeviceToHost, h->stream));

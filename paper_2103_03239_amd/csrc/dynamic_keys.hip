@@ -135,12 +135,20 @@ __global__ __launch_bounds__(256) void dyn_place_kernel(int64_t N, int32_t M, in
     }
 }
 
+// the same keys as base-M numbers, first coordinate lowest
+__global__ __launch_bounds__(256) void packed_init_kernel(int64_t N, int32_t M, int32_t *__restrict__ keys)
+{
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i < N) keys[i] = static_cast<int32_t>(i / M);
+}
+
 }  // namespace
 
 hipError_t launch_dynamic_init(int64_t N, int32_t M, int32_t d, int32_t *keys, hipStream_t stream)
 {
     const uint32_t blocks = static_cast<uint32_t>((N + 255) / 256);
-    dyn_init_kernel<<<dim3(blocks), dim3(256), 0, stream>>>(N, M, d - 1, keys);
+    if (N <= kSmallOrderPeers) packed_init_kernel<<<dim3(blocks), dim3(256), 0, stream>>>(N, M, keys);
+    else dyn_init_kernel<<<dim3(blocks), dim3(256), 0, stream>>>(N, M, d - 1, keys);
     return hipGetLastError();
 }
 

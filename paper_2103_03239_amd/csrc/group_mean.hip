@@ -50,15 +50,21 @@ constexpr int kLdsPerCu = 160 * 1024;   // gfx950: LDS bytes per compute unit
 //              (rows g_row_bytes apart); a peer that is alone in its group still
 //              takes its local step
 struct NoBits {};
+// BITS: 0 none, 1 up to kFewPeers peers, 2 up to kSmallOrderPeers
+template <int BITS> struct BitsOf;
+template <> struct BitsOf<0> { typedef NoBits type; };
+template <> struct BitsOf<1> { typedef FewPeerBits type; };
+template <> struct BitsOf<2> { typedef PeerBits type; };
 
-template <int DT, int VE, int COLS, int U, bool NT, bool IDX, bool SGD, bool BITS>
+template <int DT, int VE, int COLS, int U, bool NT, bool IDX, bool SGD, int BITS>
 __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t row_bytes, int64_t valid_bytes,
                                                             const uint8_t *__restrict__ alive, int32_t M,
                                                             int64_t S, int64_t tiles, int64_t work_items,
                                                             const int32_t *__restrict__ index, int64_t n_index,
+                                                            const int32_t *__restrict__ n_groups,
                                                             const char *__restrict__ G, int64_t g_row_bytes,
                                                             float gamma, int order,
-                                                            typename std::conditional<BITS, PeerBits, NoBits>::type bits)
+                                                            typename BitsOf<BITS>::type bits)
 {
     typedef Vec<DT, VE> V;
     typedef typename V::mem_t mem_t;
@@ -88,13 +94,14 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
             takes_part = my_row >= 0 && ((alive == nullptr) || (alive[my_row] != 0));
         } else {
             base = (g / S) * S * M + (g % S);
-            if (!BITS && lane < M) takes_part = (alive == nullptr) || (alive[base + static_cast<int64_t>(lane) * S] != 0);
+            if (BITS == 0 && lane < M) takes_part = (alive == nullptr) || (alive[base + static_cast<int64_t>(lane) * S] != 0);
         }
         uint64_t live = __ballot(takes_part);
-        if constexpr (BITS) {
+        if constexpr (BITS != 0) {
             // (g is uniform: two or three words of the argument block through the scalar cache)
             const uint32_t first = static_cast<uint32_t>(g) * static_cast<uint32_t>(M), at = first >> 5, shift = first & 31;
-            const auto word = [&](uint32_t k) -> uint64_t { return k < kSmallOrderPeers / 32 ? bits.word[k] : 0u; };
+            constexpr uint32_t kWords = sizeof(bits) / 4;
+            const auto word = [&](uint32_t k) -> uint64_t { return k < kWords ? bits.word[k] : 0u; };
             live = (word(at) | word(at + 1) << 32) >> shift;
             if (shift != 0 && M > 32) live |= word(at + 2) << (64 - shift);
             if (M < 64) live &= (1ull << M) - 1ull;
@@ -208,13 +215,13 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
             for (int c = 0; c < COLS; ++c)
                 if (in_row[c]) store_vec<NT, mem_t>(dst + at[c], mean[c]);
         }
-    } while ((w0 += gridDim.x) < work_items);
+    } while ((w0 += gridDim.x) < work_items && (!IDX || n_groups == nullptr || w0 < *n_groups * tiles));
 }
 
 // The kernel uses no LDS.  The dynamic-LDS size of the launch is only a
 // throttle: a block that reserves lds bytes lets floor(160 KiB / lds) blocks
 // share a compute unit, which bounds the number of row loads in flight.
-template <int DT, int VE, int COLS, int U, bool NT, bool IDX = false, bool SGD = false, bool BITS = false>
+template <int DT, int VE, int COLS, int U, bool NT, bool IDX = false, bool SGD = false, int BITS = 0>
 hipError_t launch_one(char *X, int64_t row_bytes, int64_t valid_bytes, const uint8_t *alive, const RoundGeom &geom,
                       int block, int waves_per_cu, int order, hipStream_t stream)
 {
@@ -228,13 +235,20 @@ hipError_t launch_one(char *X, int64_t row_bytes, int64_t valid_bytes, const uin
     const int64_t work = groups * tiles;
     if (work <= 0) return hipSuccess;
     int64_t grid = work < 0x7fffffffLL ? work : 0x7fffffffLL;
+    // A list with room for part-filled groups, as chunk-index rounds give, is half empty.  Where its work items come in many
+    // turns, blocks for those that fill it when everybody takes part do; a block goes on to another if there is one
+    // (16 x 16 x 16 x 6,824 binary32 56 us a round with a block for every place, 45 so; but 8 x 8 x 8 x 3,712 bfloat16, 512
+    // work items, 11.7 and 12.5).
+    const int64_t full = geom.N / geom.M * tiles;
+    if (IDX && geom.n_groups != nullptr && full >= 8192 && full < grid) grid = full;
     if (order == 1) {
         grid = ((work + 7) >> 3) << 3;
         if (grid > 0x7fffffffLL) { grid = 0x7fffffffLL; order = 0; }    // (more work items than blocks: plain order)
     }
     auto kernel = group_mean_kernel<DT, VE, COLS, U, NT, IDX, SGD, BITS>;
-    typename std::conditional<BITS, PeerBits, NoBits>::type bits{};
-    if constexpr (BITS) bits = *geom.bits;
+    typename BitsOf<BITS>::type bits{};
+    if constexpr (BITS == 1) bits = few_bits(*geom.bits);
+    else if constexpr (BITS == 2) bits = *geom.bits;
     size_t lds = 0;
     if (waves_per_cu > 0 && waves_per_cu < 32) {
         int blocks_per_cu = waves_per_cu / (block / 64);
@@ -245,7 +259,7 @@ hipError_t launch_one(char *X, int64_t row_bytes, int64_t valid_bytes, const uin
     }
     kernel<<<dim3(static_cast<uint32_t>(grid)), dim3(block), lds, stream>>>(X, row_bytes, valid_bytes, alive, geom.M,
                                                                             geom.S, tiles, work, geom.index,
-                                                                            geom.n_index, geom.grad, geom.grad_row_bytes,
+                                                                            geom.n_index, geom.n_groups, geom.grad, geom.grad_row_bytes,
                                                                             geom.gamma, order, bits);
     return hipGetLastError();
 }
@@ -256,15 +270,21 @@ hipError_t launch_shape(int cols, int unroll, bool nt, char *X, int64_t row_byte
 {
     if (geom.bits != nullptr) {
         // a host mask of up to 4096 peers: the default shapes only
+        const bool few = geom.N <= kFewPeers;
+#define MOSHPIT_BITS_OF(C, UU, B)                                                                                       \
+            return nt ? launch_one<DT, VE, C, UU, true, false, false, B>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream) \
+                      : launch_one<DT, VE, C, UU, false, false, false, B>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
 #define MOSHPIT_BITS(C, UU)                                                                                             \
-        if (cols == C && unroll == UU)                                                                                 \
-            return nt ? launch_one<DT, VE, C, UU, true, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream) \
-                      : launch_one<DT, VE, C, UU, false, false, false, true>(X, row_bytes, valid_bytes, alive, geom, block, wpc, order, stream);
+        if (cols == C && unroll == UU) {                                                                               \
+            if (few) MOSHPIT_BITS_OF(C, UU, 1)                                                                          \
+            MOSHPIT_BITS_OF(C, UU, 2)                                                                                   \
+        }
         MOSHPIT_BITS(1, 16)
         MOSHPIT_BITS(2, 8)
         MOSHPIT_BITS(1, 4)
         MOSHPIT_BITS(4, 2)
 #undef MOSHPIT_BITS
+#undef MOSHPIT_BITS_OF
         return hipErrorInvalidValue;
     }
     if (geom.index != nullptr) {
@@ -472,8 +492,8 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         return dtype == 0 ? launch_one<0, 1, 1, 16, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
                           : launch_one<1, 1, 1, 16, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
     if (geom.bits != nullptr)
-        return dtype == 0 ? launch_one<0, 1, 1, 16, false, false, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
-                          : launch_one<1, 1, 1, 16, false, false, false, true>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
+        return dtype == 0 ? launch_one<0, 1, 1, 16, false, false, false, 2>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
+                          : launch_one<1, 1, 1, 16, false, false, false, 2>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
     return dtype == 0 ? launch_one<0, 1, 1, 16, false>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream)
                       : launch_one<1, 1, 1, 16, false>(base, row_bytes, valid_bytes, alive, geom, 64, 32, 0, stream);
 }

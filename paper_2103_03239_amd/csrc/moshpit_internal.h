@@ -65,6 +65,18 @@ constexpr int64_t kSmallOrderPeers = 4096;
 struct PeerBits {
     uint32_t word[kSmallOrderPeers / 32];
 };
+// The same for up to 1024 peers: the host writes a kernel's arguments to device memory, 512 bytes of them in 1.1 us,
+// as long again as a third of a launch.
+constexpr int64_t kFewPeers = 1024;
+struct FewPeerBits {
+    uint32_t word[kFewPeers / 32];
+};
+inline FewPeerBits few_bits(const PeerBits &all)
+{
+    FewPeerBits b;
+    for (int64_t k = 0; k < kFewPeers / 32; ++k) b.word[k] = all.word[k];
+    return b;
+}
 
 // Geometry of one round: group g (0 <= g < N/M) owns rows base(g) + j*S,
 // j = 0..M-1, with S = M^(t mod d) and base(g) = (g / S) * S * M + g % S.
@@ -76,6 +88,8 @@ struct RoundGeom {
     int64_t S;
     const int32_t *index = nullptr;
     int64_t n_index = 0;
+    // How many of the list's groups are not empty (device; the first ones), or nullptr
+    const int32_t *n_groups = nullptr;
     // Moshpit SGD step: average theta - gamma * g, g from `grad` (device, laid out like X)
     const char *grad = nullptr;
     int64_t grad_row_bytes = 0;
@@ -124,7 +138,8 @@ hipError_t launch_schedule(int kind, uint32_t threshold, uint64_t seed, int down
                            int rounds, uint8_t *masks, int64_t s_begin, const int32_t *away_in, int32_t *away_out,
                            hipStream_t stream);
 
-// Alg. 1 with chunk-index keys.  keys: device, N x (d-1) int32.  init writes the initial
+// Alg. 1 with chunk-index keys.  keys: device, N x (d-1) int32, or (up to kSmallOrderPeers peers) N int32, a
+// key as a base-M number, first index lowest.  init writes the initial
 // keys; grouping turns (keys, alive, seed, t) into the padded peer list index[0..n_index)
 // (group g = entries [g*M, (g+1)*M), unused entries -1; n_index >= (N/M + M^(d-1)) * M) and
 // shifts each participant's chunk index into its key.  packed: N int32, count/first:
@@ -152,11 +167,12 @@ hipError_t launch_refresh_copy(void *X, int dtype, int64_t N, int64_t P, int64_t
 
 // The two below for up to 4096 peers, in one launch, without scratch.  bits: host, who takes part
 // (nullptr: everybody); peers that do not are left out of the groups (chunk-index rounds) or get
-// an entry of -1 in place of their index (permutation).
+// an entry of -1 in place of their index (permutation).  The groups fill the list from its start, *n_groups (device) of
+// them; what is left is -1.
 hipError_t launch_small_permutation(uint64_t seed, int64_t t, int64_t N, const PeerBits *bits, int32_t *perm,
                                     hipStream_t stream);
 hipError_t launch_small_grouping(int64_t N, int32_t M, int32_t d, uint64_t seed, int64_t t, const PeerBits *bits,
-                                 int32_t *keys, int32_t *index, int64_t n_index, hipStream_t stream);
+                                 int32_t *keys, int32_t *index, int64_t n_index, int32_t *n_groups, hipStream_t stream);
 
 // Queue the random-permutation kernels: perm[r] = peer of rank r when the peers
 // are ordered by their 64-bit key of (seed, t), ties by index (device, N int32).

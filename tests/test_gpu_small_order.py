@@ -85,3 +85,24 @@ def test_keys_that_have_come_together(M, d):
     assert crowded <= apart + 100e-6
     # at most 7 additions in a row and a division in the four rounds that average anything, each within 2^-24
     assert_state_close(X.cpu().double().numpy(), ref, 4 * 8 * 2.0 ** -24, f"keys together {M}^{d}")
+
+
+@pytest.mark.parametrize("M,d,P", [(2, 3, 2_100_003), (3, 2, 2_800_000), (16, 2, 131_072)])
+def test_chunk_index_rounds_of_many_work_items(M, d, P):
+    """A state with so many column tiles that the launch has no blocks for the groups which fill the list's spare
+    places (the blocks go on to them) against the same rounds on some of its columns, bit for bit; the masks leave
+    some keys with more than M members, some with none."""
+    N, seed, some = M ** d, 71 + M, 1_000
+    print(f"many work items M={M} d={d}", flush=True)
+    r = np.random.default_rng(M)
+    X = torch.randn(N, P, device=DEV)
+    parts = [X[:, :some].clone(), X[:, P // 2:P // 2 + some].clone(), X[:, P - some:].clone()]
+    masks = [None] + [(r.random(N) < q).astype(np.uint8) for q in (0.6, 0.5, 0.7, 0.9, 1.0)]
+    for state in [X] + parts:
+        with binding.Moshpit(N, state.shape[1], M, d, binding.F32) as m:
+            m.bind_state(state)
+            for t, alive in enumerate(masks):
+                m.dynamic_round(t, seed, alive)
+            m.sync()
+    for part, first in zip(parts, (0, P // 2, P - some)):
+        assert torch.equal(X[:, first:first + some], part), first
