@@ -372,6 +372,10 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // at 381 MiB, everybody present, groups of 7 to 32 rows are within 3 % of what larger states take, 5 rows
     // would gain 9 % from their rules)
     const bool cached = touched <= (whole_lines ? 256.0 : 448.0) * (1 << 20);
+    // Peer lists, whose rows lie apart and come back in other groups, hold on to it longer: with ordinary accesses and
+    // more waves 8 x 8 x 8 x 200,000 binary32, 410 MB, 140 -> 122 us, 12 x 12 x 500,000 102 -> 95, 5 x 5 x 5 x 700,000 115 -> 107,
+    // 16 x 16 x 16 x 65,536 bfloat16, 537 MB, 184 -> 175; 8 x 8 x 5,000,000, 640 MB, 213 : 215.
+    const bool cached_list = geom.index != nullptr && whole_lines && !cached && touched <= 544.0 * (1 << 20);
     // binary32 rows off the cache lines, of a state too large for the last-level cache: such rounds in
     // which (nearly) every peer takes part, in groups of the grid, have rules of their own below
     const bool full = (alive == nullptr && geom.bits == nullptr) || geom.present >= 0.97f;
@@ -383,7 +387,7 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms; so does a round of
     // groups of 7 or 8 binary32 rows with everybody present: 8 x 8 x 7,812,501 731 against 769 us)
     const bool lines_meet = !whole_lines && (geom.grad == nullptr || geom.M > 8) && !(all_odd && geom.M > 6 && geom.M <= 8);
-    const bool nt = tune.nt >= 0 ? tune.nt != 0 : (cached ? whole_lines && touched <= 24.0 * (1 << 20) : !lines_meet);
+    const bool nt = tune.nt >= 0 ? tune.nt != 0 : (cached ? whole_lines && touched <= 24.0 * (1 << 20) : !lines_meet && !cached_list);
     const int block = (tune.block == 64 || tune.block == 128 || tune.block == 256) ? tune.block : 64;
     // Block order (measured on MI355X over row sizes of 128 KiB .. 32 MiB, groups of 16 and of
     // 32 rows).  Work items go to the blocks tile-fastest, so the waves in flight stream a
@@ -449,16 +453,16 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         const int kib_per_wave = rows * cols * (block / 64) * (geom.grad != nullptr ? 2 : 1);
         wpc = (dtype == 0 ? 64 : 80) / kib_per_wave * (block / 64);
         // groups of up to 16 rows (16 KiB in flight per wave): 5 waves; 7 when the rows are
-        // shorter than 1 MiB, for groups given as a peer list and when every die streams its
-        // own part of the list; 5 for the Moshpit SGD step (which also streams the gradients)
+        // shorter than 1 MiB and when every die streams its own part of the list; 5 for groups given as a
+        // peer list (16 x 16 x 1,048,576 binary32 344 us, 7 waves 354; 16 x 16 x 16 x 65,536 380 and 394) and for
+        // the Moshpit SGD step (which also streams the gradients)
         // The figures above and below were measured with 5 - 20 % of the peers absent.  When
         // (nearly) every peer takes part each wave has more loads in flight and fewer waves do
         // better (16 MiB rows in groups of 32: 3 waves 6.2 TB/s, 4 waves 5.8).
         if (wpc < 4) wpc = 4;
         if (full && geom.grad == nullptr && geom.index == nullptr) wpc -= 1;
         if (rows == 16 && cols == 1 && geom.M <= 16) {
-            if (geom.grad != nullptr) wpc = 5;
-            else if (geom.index != nullptr) wpc = 7;
+            if (geom.grad != nullptr || geom.index != nullptr) wpc = 5;
             else if (full) wpc = order == 1 ? 6 : 5;
             else wpc = (order == 1 || row_bytes < (1 << 20)) ? 7 : 5;
         }
@@ -466,6 +470,7 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         if (rows * cols <= 4) wpc = full ? 14 : 21;
         // ordinary accesses (see above): more in flight, 8 for bfloat16 rows off the cache lines
         if (cached) wpc = geom.M > 8 ? 12 : 16;
+        else if (cached_list) wpc = geom.M > 8 ? 8 : 10;
         else if (lines_meet && rows * cols <= 4) wpc = 16;
         else if (!whole_lines && dtype == 1 && geom.M > 8 && geom.M <= 16) wpc = 128 / rows;
         else if (large_odd && geom.grad != nullptr && geom.M > 8 && geom.M <= 16) wpc = 5;
