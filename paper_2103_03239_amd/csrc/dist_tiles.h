@@ -20,7 +20,9 @@ struct DistTiles {
 //   144 rows, 25 MB, 16 x 1 10.3, 32 x 4 12.5.
 //   Waves until the chip has 1,000: 4096 rows, 2.1 GB bfloat16, 32 x 1 316, 16 x 8 344; 256 rows, 400 MB, 1 wave 64.5, 8 waves
 //   73.5; 1024 rows, 25 MB binary32, 8 waves 8.2, 4 waves 8.8.  Beyond 1 GB of binary32 few columns at a time are better for
-//   HBM: 256 rows, 1.6 GB, 8 waves 233, 1 wave 239; 64 rows 233 and 241.
+//   HBM: 256 rows, 1.6 GB, 8 waves 233, 1 wave 239; 64 rows 233 and 241; beyond 1.8 GB of bfloat16, if the chip still has 600 tiles
+//   of 64 lanes: 576 rows, 2.9 GB, 64 x 8 426, 32 x 1 455; 1024 rows of 2.6 GB off the cache lines 405 and 436; 125 rows, 2.5 GB,
+//   64 x 4 365, 32 x 1 379.
 //   Fewer than 32 rows are a load or two of a wide tile: 16 rows, 6.4 MB bfloat16, 32 x 1 6.9, 8 x 4 9.4.
 //   Never more than 65,536 tiles where they can be wider (their sums take one block 10 us).
 //   Non-temporal loads beyond 64 MB (4096 rows, 1.6 GB 231 : 250; 1024 rows, 25 MB 9.4 : 8.2), but where neighbours share cache lines
@@ -35,6 +37,8 @@ inline bool dist_tiles(int64_t esize, int64_t N, int64_t P, bool whole_lines, Di
     const bool f32 = esize == 4, large = state > 1e9, few = N < 32;
     int32_t lanes = few ? (f32 || N <= 12 ? 64 : 32) : f32 && N < 1024 ? 64 : 32;
     if (!whole_lines && !few && (f32 ? vectors >= 65536 : large && N < 512)) lanes = 64;
+    const bool very_large = !f32 && !few && state > 1.8e9 && vectors >= 64 * 600;
+    if (very_large) lanes = 64;
     const int64_t least = f32 || N >= 512 ? 160 : 512;
     while (!few && lanes > 8 && vectors < least * lanes) lanes /= 2;
     while (lanes < 64 && vectors > 65536ll * lanes) lanes *= 2;
@@ -44,8 +48,8 @@ inline bool dist_tiles(int64_t esize, int64_t N, int64_t P, bool whole_lines, Di
     const auto twice = [&] { return waves < 8 && N >= 2 * waves * (64 / lanes); };           // (a row for every lane)
     if (!few) {
         while (twice() && blocks * waves < 1000) waves *= 2;
-        if (large && f32 && (N < 128 || (N >= 256 && N < 1024)))
-            while (twice()) waves *= 2;
+        if (f32 ? large && (N < 128 || (N >= 256 && N < 1024)) : very_large && N >= 96)
+            while (twice() && (f32 || N >= 256 || waves < 4)) waves *= 2;
     }
     out->lanes = lanes;
     out->waves = waves;
