@@ -30,6 +30,7 @@ struct GridPlan {
     int32_t S[kGridMaxAxes], pad_step[kGridMaxAxes];
     uint32_t magic_s[kGridMaxAxes];
     int64_t row_bytes, valid_bytes, tiles;
+    double inv_n;                    // 1 / N
     // means != 0: the kernel of mean_rounds.hip, and where its LDS holds what
     int32_t means;
     int32_t split;                   // lanes that share a group
@@ -37,7 +38,7 @@ struct GridPlan {
     int32_t part;                    // bytes of a row in LDS
     int32_t means_at, means_bytes, zero_at, rcp_at, words_at;
     int32_t words_shift;             // log2 of N / 2: 32-bit words that a round's places take
-    int32_t dist_window;             // distortions of a part of the tile whose sums LDS holds at a time
+    int32_t dist_barrier;            // a barrier behind every distortion (a refresh, or LDS has room for one round's terms only)
     int32_t mean_step[kGridMaxAxes];      // bytes between the means that the rows of a group were given by the round before
     // filled in by the caller
     int32_t rounds;
@@ -67,22 +68,27 @@ struct GridAsk {
     double averaged = 1.0, live = 1.0;       // of the peers, those averaged in a round; of the groups, those with an average
 };
 
-// Do the sums of a pass's distortions leave LDS in between, when no more of them have room, so that a pass takes 64
-// rounds whatever fits?  On 32 x 32 binary32 peers with failures LDS holds the sums of 9 rounds, and a pass of no more lost to
-// the kernel with M copies of a mean (10 % absent, 1 GB: 10 rounds 2.37 : 1.95 ms, 40 rounds 7.45 : 6.43; so 1.81 and
-// 4.78 ms).  Elsewhere the test in every round costs more (2 to 6 %) than it gives: 16 x 16 binary32 takes 24 rounds a pass
-// with failures (3 GB, 40 rounds 10.8 : 14.7 ms), 6 x 6 x 6 bfloat16 10 with nobody absent (1 GB, 40 rounds 8.6 : 11.0).
-constexpr bool sums_leave_in_between(int dtype, int32_t split, bool tables_in_lds) { return dtype == 0 && split == 4 && tables_in_lds; }
-
 // ---- LDS of the kernel that keeps one mean per group ---------------------------------------------
 
 inline int64_t mean_place_stride(const GridPlan &p) { return static_cast<int64_t>(p.threads) * kPhaseSlots * p.phases; }
 
-// two rounds' places and moves, and the terms of a distortion
+// Waves of a block that share a distortion: half of them, the halves in turn, or all.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int32_t dist_sharers(int32_t waves) { return waves % 2 == 0 ? waves / 2 : waves; }
+
+// The distortions' LDS: two rounds' sums of the sharing waves, a column each and one of squares, and the totals of a pass.
+inline int64_t dist_sums_bytes(int64_t waves, int64_t columns, int64_t rounds)
+{
+    return 2 * dist_sharers(static_cast<int32_t>(waves)) * (columns + 1) * 8 + (rounds + 1) * 8;
+}
+
+// two rounds' places and moves, and the terms of one or two distortions
 inline int64_t mean_words_bytes(const GridPlan &p, bool tables, bool distortions)
 {
     if (p.bits) return 8 * p.groups;                         // (two rounds' bits)
-    return tables && p.part >= kLeastLdsPart ? (distortions ? 16ll : 12ll) << p.words_shift : 0;
+    return tables && p.part >= kLeastLdsPart ? (!distortions ? 12ll : p.dist_barrier ? 16ll : 20ll) << p.words_shift : 0;
 }
 
 // The LDS of a tile of p.N rows x `part` bytes with its two arrays of means; p.part, p.pad, p.split and the
@@ -120,7 +126,7 @@ inline int64_t means_lds_bytes(const GridPlan &p, bool tables, int32_t rounds, b
     int64_t at = p.words_at + mean_words_bytes(p, tables, dist);
     *sums_at = static_cast<int32_t>(at);
     const int64_t waves = p.threads / 64;
-    if (dist) at += (waves * (p.part / esize) + (rounds + 1 < p.dist_window ? rounds + 1 : p.dist_window) * waves) * 8;
+    if (dist) at += dist_sums_bytes(waves, p.part / esize, rounds);
     return at;
 }
 
@@ -181,16 +187,34 @@ constexpr bool mean_kernel_built(int dtype, int split, int half, bool nt, bool d
 
 inline int64_t bitmap_bytes(int32_t M) { return M <= 16 ? 2 : 4; }
 
+// Sums of a distortion: rows of 256 bytes and more in one part are taken 4 bytes a thread, in `parts` parts of the rows that add
+// their columns up in LDS; of others every wave has all columns.  (A tile of few rows and 1 KiB of each left 3 blocks of 5 on a
+// compute unit room next to sums by waves.)
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int32_t dist_parts(int32_t threads, int32_t row_bytes) { return threads >= row_bytes / 4 ? threads / (row_bytes / 4) : 1; }
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int32_t dist_sum_rows(int32_t threads, int32_t row_bytes, int32_t phases)
+{
+    if (phases > 1 || row_bytes < 256) return threads / 64;
+    const int32_t parts = dist_parts(threads, row_bytes);
+    return parts > 1 ? parts : 0;
+}
+inline int64_t copies_sums_bytes(const GridPlan &p, int64_t esize)
+{
+    const int32_t part = p.Wb / p.phases;
+    return (dist_sum_rows(p.threads, part, p.phases) * (part / esize) + p.threads / 64) * 8;
+}
+
 inline int64_t copies_lds_bytes(const GridPlan &p, int32_t rounds, bool dist, int64_t esize, int32_t *sums_at)
 {
     int64_t at = p.tile_bytes + static_cast<int64_t>(rounds) * p.groups * bitmap_bytes(p.M) + p.N;
     at = (at + 15) / 16 * 16;
     *sums_at = static_cast<int32_t>(at);
-    if (dist) {
-        const int64_t waves = p.threads / 64, columns = p.Wb / p.phases / esize;
-        at += (waves * columns + waves) * 8;
-        at = (at + 15) / 16 * 16;
-    }
+    if (dist) at = (at + copies_sums_bytes(p, esize) + 15) / 16 * 16;
     return at + kRcpBytes + 32;
 }
 
@@ -231,10 +255,15 @@ inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
         q.phases = phases;
         const int64_t threads = (q.N * part / (16 * kPhaseSlots) + 63) / 64 * 64, waves = threads / 64 < 1 ? 1 : threads / 64;
         q.bits = ask.absent && !ask.refresh && !ask.distortions && part == 16 && q.M == 16 && 2 * q.groups == threads ? 1 : 0;
-        const int64_t bytes = lay_out_means(&q, part, ask.absent, ask.distortions);
-        if (ask.absent && (q.M != 8 * q.split || (phases == 2 && part == 32) || (ask.distortions && esize == 2 && part >= 64))) return false;
-        if (bytes + (ask.distortions ? (waves * (part / esize) + 5 * waves) * 8 : 0) <= kLdsPerBlock) {
+        const auto fits = [&](bool barrier) {
+            q.dist_barrier = barrier ? 1 : 0;
+            const int64_t bytes = lay_out_means(&q, part, ask.absent, ask.distortions);
             q.red_offset = static_cast<int32_t>(bytes);
+            return bytes + (ask.distortions ? dist_sums_bytes(waves, part / esize, 4) : 0) <= kLdsPerBlock;
+        };
+        const bool room = (!(ask.distortions && ask.refresh) && fits(false)) || fits(ask.distortions);
+        if (ask.absent && (q.M != 8 * q.split || (phases == 2 && part == 32) || (ask.distortions && esize == 2 && part >= 64))) return false;
+        if (room) {
             q.means = 1;
             *p = q;
             return true;
@@ -288,13 +317,11 @@ inline bool fill_in(GridPlan *plan, const void *X, int64_t esize, const GridAsk 
     // rounds of one pass: as many bitmaps as fit next to the tile
     const int64_t waves = p.threads / 64, columns = part / esize;
     if (p.means) {
-        // (a sum per wave for every distortion)
-        const int64_t sums = (kLdsPerBlock - p.red_offset - waves * columns * 8) / (8 * waves);
-        p.dist_window = static_cast<int32_t>(sums < 65 ? sums : 65);
-        p.max_rounds = ask.distortions && !sums_leave_in_between(esize == 4 ? 0 : 1, p.split, ask.absent && part >= kLeastLdsPart) ? p.dist_window - 1 : 64;
+        const int64_t most = ask.distortions ? (kLdsPerBlock - p.red_offset - dist_sums_bytes(waves, columns, -1)) / 8 - 1 : 64;
+        p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
         return p.max_rounds >= 4;
     }
-    const int64_t room = kLdsPerBlock - p.tile_bytes - N - (waves * columns + waves) * 8 - kRcpBytes - 64;
+    const int64_t room = kLdsPerBlock - p.tile_bytes - N - copies_sums_bytes(p, esize) - kRcpBytes - 64;
     const int64_t most = room / (static_cast<int64_t>(p.groups) * bitmap_bytes(M));
     p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
     if (p.max_rounds < 4) return false;      // (2^12 peers; 24 x 24 in tiles of 128 bytes with 8 columns to a vector)
@@ -386,6 +413,7 @@ inline bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int
     p.M = M;
     p.d = d;
     p.groups = static_cast<int32_t>(N / M);
+    p.inv_n = 1.0 / static_cast<double>(N);
     p.full_bitmap = M == 32 ? ~0u : (1u << M) - 1u;
     p.axis0 = static_cast<int32_t>(t0 % d);
     // Widest tile: rows of 512 bytes beat 1 KiB on 64 rows (2.55 against 2.73 ms), 256 bytes beat

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
     char *tile = lds;
     bits_t *bitmaps = reinterpret_cast<bits_t *>(lds + p.tile_bytes);
     uint8_t *flags = reinterpret_cast<uint8_t *>(bitmaps + p.rounds * p.groups);
-    double *red = reinterpret_cast<double *>(lds + p.red_offset);      // DIST: [waves][columns], then [waves]
+    double *red = reinterpret_cast<double *>(lds + p.red_offset);      // DIST: [dist_sum_rows][columns], then [waves]
     float *rcp_tab = reinterpret_cast<float *>(lds + p.lds_bytes - 32 - kRcpBytes);
     elem_t *zeros = reinterpret_cast<elem_t *>(lds + p.lds_bytes - 32);
     elem_t *trash = reinterpret_cast<elem_t *>(lds + p.lds_bytes - 16);
@@ -181,79 +181,117 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
     };
 
     // Distortion of the tile: sum over its columns of s2 - s1^2 / N, s1 and s2 the sums of the
-    // differences from row 0 and of their squares in binary64 (the differences are exact).
-    // Thread (part, vector c) takes every parts-th row; the lanes and waves that share a column
-    // are added in a fixed order.  Latency bounds it (a chain of lane exchanges and two barriers per
-    // tile and round): with four rows requested at once and one chain of exchanges for both sums
-    // the curve of 16 x 16 peers x 1,048,576 binary32 over 10 rounds went from 1.80 to 1.54 ms.
-    [[maybe_unused]] auto distortion = [&](int32_t seg, int64_t out_at) {
+    // differences from row 0 and of their squares in binary64 (the differences are exact).  The lanes and waves that share a column
+    // are added in a fixed order; what they left is put together by one wave behind the barrier that every distortion needs (the
+    // next round writes over the rows), while the others go on.
+    // Rows of 256 bytes and more: a thread takes 4 bytes of every parts-th row, so that a wave shares its columns with the waves of
+    // other parts only, in wide tiles of few rows with nobody.  Shorter rows: 16 bytes, and the lanes that share a column are summed
+    // by exchanges (column_sums).  Vector instructions bound it: 3 x 3 x 3 x 7,875,648 bfloat16, 9 distortions 1.26 -> 0.81 ms,
+    // 4 x 4 x 6,643,636 binary32, 11 distortions 708 -> 577 us against 16 bytes everywhere with all lanes' sums through LDS.
+    [[maybe_unused]] auto distortion = [&](int32_t seg, int32_t entry, int64_t out_at) {
         if constexpr (DIST) {
-            const int32_t waves = T >> 6, lane = tid & 63, wave = tid >> 6;
-            const int32_t c = tid & wv_mask, parts = T >> wv_shift;
-            const int32_t columns = NE << wv_shift;
-            const bool in = c * 16 < seg;
-            const int32_t early = c * 16 - (seg - 16);             // > 0: the row's last vector, first `early` bytes not its own
-            const int32_t dup = early > 0 ? early / kEs : 0;
-            constexpr int kChains = PHASES == 1 ? NE : 1;
-            double s1[NE], sq[kChains], s2 = 0.0;
-            float x0[NE];
-            widen16<DT>(*lds_vec(0, c), x0);
+            const int32_t waves = T >> 6, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+            int32_t columns = NE << wv_shift, parts = waves;
+            double *squares = red + dist_sum_rows(T, Wb, PHASES) * columns;
+            if (PHASES == 1 && wv_shift >= 4) {
+                constexpr int kIn = 4 / kEs;
+                const int32_t words = Wb >> 2;
+                parts = dist_parts(T, Wb);
+                const int32_t part = T >= words ? tid / words : 0;
+                double v = 0.0;
+                if (part < parts)
+                    for (int32_t q = tid - part * words; q < words; q += T) {
+                        const int32_t early = (q & ~3) * 4 - (seg - 16);     // > 0: the row's last vector, first `early` bytes not its own
+                        const char *at = tile + q * 4;
+                        const auto widen = [&](uint32_t raw, double (&x)[kIn]) {
+                            if constexpr (kIn == 1) {
+                                x[0] = __uint_as_float(raw);
+                            } else {
+                                x[0] = __uint_as_float(raw << 16);
+                                x[1] = __uint_as_float(raw & 0xffff0000u);
+                            }
+                        };
+                        double x0[kIn], s1[kIn], sq[kIn];
+                        widen(*reinterpret_cast<const uint32_t *>(at), x0);
 #pragma unroll
-            for (int e = 0; e < NE; ++e) s1[e] = 0.0;
+                        for (int e = 0; e < kIn; ++e) s1[e] = sq[e] = 0.0;
+                        constexpr int kRows = 8;                             // requested before the first is used
+                        for (int32_t row0 = part; row0 < p.N; row0 += kRows * parts) {
+                            uint32_t raw[kRows];
 #pragma unroll
-            for (int e = 0; e < kChains; ++e) sq[e] = 0.0;
-            if (in) {
-                // (four rows are requested before the first is used: LDS latency is what a lone read waits for)
-                constexpr int kRows = PHASES == 1 ? 4 : 1;       // (few registers are free next to 16 slots)
-                for (int32_t row0 = tid >> wv_shift; row0 < p.N; row0 += kRows * parts) {
-                    u32x4 raw[kRows];
+                            for (int u = 0; u < kRows; ++u) {
+                                const int32_t row = row0 + u * parts;
+                                raw[u] = *reinterpret_cast<const uint32_t *>(at + (row < p.N ? row : 0) * Wb);       // (row 0 adds zeros)
+                            }
 #pragma unroll
-                    for (int u = 0; u < kRows; ++u) {
-                        const int32_t row = row0 + u * parts;
-                        raw[u] = *lds_vec(row < p.N ? row : 0, c);       // (row 0 adds zeros)
+                            for (int u = 0; u < kRows; ++u) {
+                                double x[kIn];
+                                widen(raw[u], x);
+#pragma unroll
+                                for (int e = 0; e < kIn; ++e) {
+                                    const double dlt = x[e] - x0[e];
+                                    s1[e] += dlt;
+                                    sq[e] = fma(dlt, dlt, sq[e]);
+                                }
+                            }
+                        }
+#pragma unroll
+                        for (int e = 0; e < kIn; ++e) {
+                            if ((q & ~3) * 4 >= seg || (q & 3) * 4 + e * kEs < early) s1[e] = sq[e] = 0.0;
+                            v += parts == 1 ? sq[e] - s1[e] * s1[e] * p.inv_n : sq[e];
+                            if (parts > 1) red[part * columns + q * kIn + e] = s1[e];
+                        }
                     }
+                v = wave_sum(v);
+                if (lane == 0) squares[wave] = v;
+                if (parts == 1) columns = 0;
+            } else {
+                const int32_t c = tid & wv_mask, sharers = T >> wv_shift;
+                const int32_t early = c * 16 - (seg - 16);
+                const int32_t dup = early > 0 ? early / kEs : 0;
+                constexpr int kChains = PHASES == 1 ? NE : 1;
+                double s1[NE], sq[kChains], s2 = 0.0;
+                float x0[NE];
+                widen16<DT>(*lds_vec(0, c), x0);
 #pragma unroll
-                    for (int u = 0; u < kRows; ++u) {
-                        float x[NE];
-                        widen16<DT>(raw[u], x);
+                for (int e = 0; e < NE; ++e) s1[e] = 0.0;
 #pragma unroll
-                        for (int e = 0; e < NE; ++e) {
-                            double dlt = static_cast<double>(x[e]) - static_cast<double>(x0[e]);
-                            if (PHASES > 1 && e < dup) dlt = 0.0;
-                            s1[e] += dlt;
-                            sq[e % kChains] = fma(dlt, dlt, sq[e % kChains]);
+                for (int e = 0; e < kChains; ++e) sq[e] = 0.0;
+                if (c * 16 < seg) {
+                    // (four rows are requested before the first is used: LDS latency is what a lone read waits for)
+                    constexpr int kRows = PHASES == 1 ? 4 : 1;       // (few registers are free next to 16 slots)
+                    for (int32_t row0 = tid >> wv_shift; row0 < p.N; row0 += kRows * sharers) {
+                        u32x4 raw[kRows];
+#pragma unroll
+                        for (int u = 0; u < kRows; ++u) {
+                            const int32_t row = row0 + u * sharers;
+                            raw[u] = *lds_vec(row < p.N ? row : 0, c);       // (row 0 adds zeros)
+                        }
+#pragma unroll
+                        for (int u = 0; u < kRows; ++u) {
+                            float x[NE];
+                            widen16<DT>(raw[u], x);
+#pragma unroll
+                            for (int e = 0; e < NE; ++e) {
+                                double dlt = static_cast<double>(x[e]) - static_cast<double>(x0[e]);
+                                if (PHASES > 1 && e < dup) dlt = 0.0;
+                                s1[e] += dlt;
+                                sq[e % kChains] = fma(dlt, dlt, sq[e % kChains]);
+                            }
                         }
                     }
                 }
+#pragma unroll
+                for (int e = 0; e < kChains; ++e) {
+                    if (PHASES == 1 && e < dup) { s1[e] = 0.0; sq[e] = 0.0; }
+                    s2 += sq[e];
+                }
+                column_sums<NE>(s1, s2, wv_shift, red + wave * columns, squares + wave);
             }
-#pragma unroll
-            for (int e = 0; e < kChains; ++e) {
-                if (PHASES == 1 && e < dup) { s1[e] = 0.0; sq[e] = 0.0; }
-                s2 += sq[e];
-            }
-            for (int32_t off = 1 << wv_shift; off < 64; off <<= 1)
-#pragma unroll
-                for (int e = 0; e < NE; ++e) s1[e] += __shfl_xor(s1[e], off, 64);
-            if (lane <= wv_mask)
-#pragma unroll
-                for (int e = 0; e < NE; ++e) red[wave * columns + c * NE + e] = s1[e];
-            double *tot = red + waves * columns;
             lds_barrier();
-            double part = s2;
-            for (int32_t col = tid; col < columns; col += T) {
-                double t1 = 0.0;
-#pragma unroll 4
-                for (int32_t k = 0; k < waves; ++k) t1 += red[k * columns + col];
-                part -= t1 * t1 / static_cast<double>(p.N);          // (columns outside the tile hold 0)
-            }
-#pragma unroll
-            for (int32_t off = 1; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
-            if (lane == 0) tot[wave] = part;
-            lds_barrier();
-            if (tid == 0) {
-                double sum = 0.0;
-                for (int32_t k = 0; k < waves; ++k) sum += tot[k];
-                p.partials[out_at] = sum;
+            if (wave == entry % waves) {
+                const double sum = finish_columns(red, parts, columns, squares, waves, p.inv_n);
+                if (lane == 0) p.partials[out_at] = sum;
             }
         }
     };
@@ -306,7 +344,7 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
         lds_barrier();
 
         if constexpr (DIST)
-            if (p.dist_before) distortion(seg, w * PHASES + phase);
+            if (p.dist_before) distortion(seg, 0, w * PHASES + phase);
         int32_t axis = p.axis0;
         for (int32_t r = 0; r < p.rounds; ++r) {
             if (p.copies != nullptr && (r > 0 || p.refresh_first)) {
@@ -323,7 +361,7 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
             round(seg, axis, bitmaps + r * p.groups);
             lds_barrier();
             if constexpr (DIST)
-                if ((p.dist_after >> r) & 1u) distortion(seg, (r + 1) * tiles + w * PHASES + phase);
+                if ((p.dist_after >> r) & 1u) distortion(seg, r + 1, (r + 1) * tiles + w * PHASES + phase);
             axis = axis + 1 == p.d ? 0 : axis + 1;
         }
         if constexpr (PHASES == 2) {

@@ -22,23 +22,22 @@
 // bytes it costs one address (one multiply-add), one 128-bit LDS read and the additions.
 //
 // The distortion after a round needs one term per group (weight: the count) and one per peer that
-// was not averaged, instead of one per peer; lanes are summed by rotations and row exchanges instead of
-// trips through LDS, and the sums over waves are kept back until the tile's rounds are done, one
-// barrier less per round.
+// was not averaged, instead of one per peer.  Half of a block's waves take it, the halves in turn, while the others are at the next
+// round; lanes are summed by exchanges that halve the columns each keeps, waves by one of them behind the next round's barrier.
 //
 // What bounds it (MI355X; before: the kernel of grid_rounds.hip).  A round takes 21 us per GiB of
 // binary32 where nobody is absent (before 39), 0.42 ms on 32 x 32 peers x 4,194,304 (0.63); on 16 x 16 x 16
 // bfloat16 it is the widening and adding, 31 us of 2 GiB (75).  Short runs wait for memory as before:
 //   32 x 32 x 4,194,304 binary32, 8 rounds, 20 % absent          9.35 -> 8.11 ms (4.2 TB/s; a copy in tiles of 128
 //                                                                bytes 4.7), 16 rounds, nobody 14.2 -> 10.5
-//   16 x 16 x 1,048,576 binary32, 10 rounds, 11 distortions      1.54 -> 1.06 ms
+//   16 x 16 x 1,048,576 binary32, 10 rounds, 11 distortions      1.54 -> 0.82 ms
 //   16 x 16 x 16 x 131,072 bfloat16, 6 rounds with refresh       1.12 -> 0.87 ms
 //   16 x 16 x 16 x 262,144 bfloat16, 12 rounds, nobody absent    1.98 -> 1.48 ms
 //   the same with 10 % absent                                    2.09 -> 1.90
 // What a compute unit's time goes into (counters): vector instructions take 89 % of the issue slots on 16 x 16 x 16 bfloat16,
-// 71 % under the curve of 16 x 16 binary32 (binary64 sums), 56 % on 32 x 32, where memory moves 4.2 TB/s.
-// Next to a second part of the tile few of the 128 registers are free: of the kernels with tables and the distortion those with
-// two parts keep 32 to 196 bytes a lane in scratch, the others and all without either none.
+// 61 % under the curve of 16 x 16 binary32 (binary64 sums), 56 % on 32 x 32, where memory moves 4.2 TB/s.
+// Next to a second part of the tile few of the 128 registers are free: six of the kernels with the distortion keep 28 to 188
+// bytes a lane in scratch, the others none.
 // A round's vector instructions count as much as its LDS traffic, and a load from memory in a round costs
 // more than either: a compute unit returns loads in order, so it waits behind the tile that its other
 // block is loading (see the tables in the kernel).
@@ -145,33 +144,6 @@ template <int DISTANCE> __device__ __forceinline__ void exchange_parts(u32x4 (&a
     }
 }
 
-// Sum over the lanes that differ by multiples of 1 << from (every lane gets it), without a trip through LDS:
-// rotations of 16 lanes, then exchanges of rows of 16.
-template <int CTRL> __device__ __forceinline__ double rotated(double v)
-{
-    const uint64_t bits = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(bits), CTRL, 0xf, 0xf, true);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(bits >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
-}
-__device__ __forceinline__ double lanes_sum(double v, int32_t from)
-{
-    if (from <= 3) v += rotated<0x128>(v);
-    if (from <= 2) v += rotated<0x124>(v);
-    if (from <= 1) v += rotated<0x122>(v);
-    if (from <= 0) v += rotated<0x121>(v);
-    const auto halves = [](double x, bool far) {
-        const uint64_t bits = __builtin_bit_cast(uint64_t, x);
-        const uint32_t lo = static_cast<uint32_t>(bits), hi = static_cast<uint32_t>(bits >> 32);
-        const auto l = far ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false) : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto h = far ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false) : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        return __builtin_bit_cast(double, static_cast<uint64_t>(h[0]) << 32 | l[0]) + __builtin_bit_cast(double, static_cast<uint64_t>(h[1]) << 32 | l[1]);
-    };
-    if (from <= 4) v = halves(v, false);
-    if (from <= 5) v = halves(v, true);
-    return v;
-}
-
 // SPLIT: lanes (16 or 32 apart) that share a group, 8 positions each.  HALF: 0 where the whole tile is in LDS; else
 // its two column parts take turns, and HALF is the lanes between them in a wave that loads it.  NT: non-temporal loads and stores.  DIST: distortions are
 // wanted.  TAB: where the places come from: kClosed (nobody is ever absent), kLds, kBits or kAheadOnly (see below).
@@ -218,6 +190,11 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
     const int32_t items = p.groups << wv_shift;
     const uint32_t out_at = SPLIT == 1 ? 0 : SPLIT == 2 ? sub * 8 : ((sub & 1) * 2 + (sub >> 1)) * 4;
 
+    // waves that take a distortion (see there), and the thread's first term of one
+    const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = T >> 6;
+    const int32_t sharers = dist_sharers(waves), halves = waves / sharers;
+    [[maybe_unused]] const int32_t first_term = (tid - (wave >= sharers ? sharers * 64 : 0)) >> wv_shift;
+
     // Tables.  Loads in the rounds would wait for the tile that the compute unit's other block is loading (a compute
     // unit returns loads in order), so the block takes what it can into registers along with its tile: with
     // TAB == kLds 4 bytes of a round's places, moves and terms per thread and register (1024 peers and more than 64
@@ -228,7 +205,8 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
     // rounds: 2.09 -> 1.90 ms; as 16-bit places read in the rounds 2.10, and with quotients by multiplication in place of the shifts 2.09), or, for
     // what bits cannot say (the donor of a returning peer) and with distortions, are loaded kAhead rounds ahead.
     const int32_t words_shift = p.words_shift, words = 1 << words_shift;      // of a round's places, two in each
-    const int32_t per_register = T >> words_shift;
+    const int32_t per_register = T >> words_shift;           // (both are powers of two where there are tables)
+    [[maybe_unused]] const int32_t per_shift = 31 - __builtin_clz(per_register > 0 ? per_register : 1);
     const int32_t move_words_max = words >> 1;                // of a round's moves; more are read from memory
     [[maybe_unused]] u32x8 entry_words, term_words;
     [[maybe_unused]] u32x4 move_words;
@@ -250,7 +228,7 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
             for (int k = 0; k < 2; ++k)
                 move[i][k] = table_get<uint32_t>(p.moves + r * p.N, static_cast<uint32_t>((tid + k * T < last ? tid + k * T : 0) >> wv_shift) * 4u);
             if constexpr (DIST)
-                term[i] = table_get<uint32_t>(p.terms + r * (p.N + p.groups), static_cast<uint32_t>(tid < last ? tid >> wv_shift : 0) * 4u);
+                term[i] = table_get<uint32_t>(p.terms + r * (p.N + p.groups), static_cast<uint32_t>(first_term < p.N ? first_term : 0) * 4u);
         }
     };
     // kBits: a group's bits in one word, a round's in T / groups threads; rows that move two to a thread and round, in
@@ -315,7 +293,10 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
     // kLds: those of round r from the registers to LDS
     auto write_words = [&](int32_t r) {
         if constexpr (TAB == kLds) {
-            const int32_t in = r % (kRegisters * per_register), q = in / per_register;
+            // (Where no distortion is wanted the quotients are left as they are: with shifts the two blocks of a compute unit fall
+            // into step, 32 x 32 x 4,194,304, 8 rounds, 8,870 us on every one of four states, 8,150 with the divisions)
+            const int32_t in = DIST ? r & (kRegisters * per_register - 1) : r % (kRegisters * per_register);
+            const int32_t q = DIST ? in >> per_shift : in / per_register;
             if (r > 0 && in == 0) fetch_words(r);
             if (tid >> words_shift == in - q * per_register) {
                 lds_put(base + p.words_at + (r & 1) * 4 * words + (tid & (words - 1)) * 4, static_cast<uint32_t>(entry_words[q]));
@@ -324,13 +305,15 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                 lds_put(base + p.words_at + 8 * words + (r & 1) * 2 * words + (tid & (move_words_max - 1)) * 4, static_cast<uint32_t>(move_words[q / 2]));
         }
     };
-    // (of round r itself: they are read behind its barrier, and the next round's are written behind that of the distortion)
+    // (of round r itself: they are read behind its barrier; where LDS has room for one round's only (p.dist_barrier), the next
+    // round's are written behind a barrier of the distortion)
+    const uint32_t terms_at = base + p.words_at + 12 * words, terms_step = p.dist_barrier ? 0 : 4 * words;
     [[maybe_unused]] auto write_terms = [&](int32_t r) {
         if constexpr (TAB == kLds && DIST) {
-            const int32_t in = r % (kRegisters * per_register), q = in / per_register;
+            const int32_t in = r & (kRegisters * per_register - 1), q = in >> per_shift;
             if (r > 0 && in == 0) fetch_terms(r);
-            if (tid >> words_shift == in - q * per_register)
-                lds_put(base + p.words_at + 12 * words + (tid & (words - 1)) * 4, static_cast<uint32_t>(term_words[q]));
+            if (tid >> words_shift == (in & (per_register - 1)))
+                lds_put(terms_at + (r & 1) * terms_step + (tid & (words - 1)) * 4, static_cast<uint32_t>(term_words[q]));
         }
     };
     // kLds: the lane's own of round r from LDS
@@ -559,20 +542,24 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
 
     // Distortion of the part in LDS after round r of the pass (r = -1: before the first): sum over
     // its columns of s2 - s1^2 / N, s1 and s2 the sums of the differences from one peer's row and of their
-    // squares in binary64 (the differences are exact).  Thread (k, vector c) takes every
-    // (T >> wv_shift)-th term.  Column sums of the waves meet in `red`; what a wave adds to
-    // the total waits in `tot` for the end of the tile's rounds, or, kWindow, until LDS has no room for more: entries
-    // held .. held + dist_window - 1 then (entry 0: before the first round).
-    constexpr bool kWindow = DIST && sums_leave_in_between(DT, SPLIT, TAB == kLds);
-    [[maybe_unused]] int32_t held = 0;
-    double *red = reinterpret_cast<double *>(lds + p.red_offset);
+    // squares in binary64 (the differences are exact).  There are far fewer terms than threads, so where the block has an even
+    // number of waves its halves take the rounds in turn (sharers of them a round): thread (k, vector c) of the half takes every
+    // parts-th term.  What the waves of a half leave in LDS is put together by its first wave after the next round's barrier, when the
+    // other half is busy with that round's.
+    const int32_t columns = NE << wv_shift;
+    double *red = reinterpret_cast<double *>(lds + p.red_offset), *totals = red + 2 * sharers * (columns + 1);
+    [[maybe_unused]] auto sums_of = [&](int32_t r) -> double * { return red + ((r + 1) & 1) * sharers * (columns + 1); };
+    [[maybe_unused]] auto first_wave = [&](int32_t r) -> int32_t { return halves == 2 ? ((r + 1) & 1) * sharers : 0; };
     [[maybe_unused]] auto distortion = [&](int i, int32_t seg, int32_t r) {
         if constexpr (DIST) {
-            const int32_t waves = T >> 6, wave = tid >> 6;
-            const int32_t c = tid & wv_mask, parts = T >> wv_shift, first = tid >> wv_shift;
-            const int32_t columns = NE << wv_shift;
+            const int32_t w0 = first_wave(r);
+            if (wave < w0 || wave >= w0 + sharers) return;
+            const int32_t c = tid & wv_mask, first = first_term, parts = sharers * 64 >> wv_shift;
             const int32_t early = c * 16 - (seg - 16);             // > 0: the row's last vector, first `early` bytes not its own
-            const int32_t dup = early > 0 ? early / kEs : 0;
+            // (their bits are cleared in every term, and in the row that is subtracted)
+            u32x4 own;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) own[k] = early >= 4 * k + 4 ? 0u : early > 4 * k ? 0xffff0000u : ~0u;
             const uint32_t col = base + c * 16;
             const int32_t n = r < 0 ? p.N : TAB != kClosed ? __builtin_amdgcn_readlane(terms, r) : p.groups;
             const uint32_t *list = p.terms + static_cast<int64_t>(r < 0 ? 0 : r) * (p.N + p.groups);
@@ -581,23 +568,20 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                 if (r < 0) return col + own_at(p, k);
                 if constexpr (TAB != kClosed) {
                     uint32_t t;
-                    if (TAB == kLds && k < words) t = lds_get<uint32_t>(base + p.words_at + 12 * words + k * 4);
+                    if (TAB == kLds && k < words) t = lds_get<uint32_t>(terms_at + (r & 1) * terms_step + k * 4);
                     else if (TAB == kAheadOnly && k == first) t = term[i];
                     else t = table_get<uint32_t>(list, static_cast<uint32_t>(k) * 4u);
                     weight = static_cast<float>(t >> 16);
                     return place<0>(t, col);
                 } else {
-                    weight = full_count;
-                    return col + mean_at(p, r, k);
+                    return col + mean_at(p, r, k);               // (all terms count the same: below)
                 }
             };
             float x0[NE];
-            {
-                uint32_t at0 = col + (r < 0 ? own_at(p, 0) : mean_at(p, r, 0));
-                if constexpr (TAB != kClosed)
-                    if (r >= 0) at0 = place<0>(__builtin_amdgcn_readlane(term0, r), col);
-                widen16<DT>(lds_get<u32x4>(at0), x0);
-            }
+            uint32_t at0 = col + (r < 0 ? own_at(p, 0) : mean_at(p, r, 0));
+            if constexpr (TAB != kClosed)
+                if (r >= 0) at0 = place<0>(__builtin_amdgcn_readlane(term0, r), col);
+            widen16<DT>(lds_get<u32x4>(at0) & own, x0);
             double s1[NE], s2 = 0.0;
 #pragma unroll
             for (int e = 0; e < NE; ++e) s1[e] = 0.0;
@@ -610,23 +594,23 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                     for (int u = 0; u < kRows; ++u) {
                         const int32_t k = k0 + u * parts;
                         at[u] = term_at(k < n ? k : first, weight[u]);
-                        if (k >= n) weight[u] = 0.f;
+                        if (k >= n) at[u] = at0;                  // (its difference is 0)
                     }
 #pragma unroll
                     for (int u = 0; u < kRows; ++u) raw[u] = lds_get<u32x4>(at[u]);
 #pragma unroll
                     for (int u = 0; u < kRows; ++u) {
                         float x[NE];
-                        widen16<DT>(raw[u], x);
-                        const double wt = static_cast<double>(weight[u]);
+                        widen16<DT>(raw[u] & own, x);
+                        [[maybe_unused]] const double wt = static_cast<double>(weight[u]);
+                        double sq = TAB == kClosed ? s2 : 0.0;
 #pragma unroll
                         for (int e = 0; e < NE; ++e) {
-                            double dlt = static_cast<double>(x[e]) - static_cast<double>(x0[e]);
-                            if (e < dup) dlt = 0.0;
-                            const double weighted = wt * dlt;
-                            s1[e] += weighted;
-                            s2 = fma(weighted, dlt, s2);
+                            const double dlt = static_cast<double>(x[e]) - static_cast<double>(x0[e]);
+                            s1[e] = TAB == kClosed ? s1[e] + dlt : fma(wt, dlt, s1[e]);
+                            sq = fma(dlt, dlt, sq);
                         }
+                        s2 = TAB == kClosed ? sq : fma(wt, sq, s2);
                     }
             };
             if (c * 16 < seg && first < n) {
@@ -640,35 +624,32 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                     for (int32_t k0 = first; k0 < n; k0 += 2 * parts) add_terms(std::integral_constant<int, 2>(), k0);
                 }
             }
+            if (TAB == kClosed && r >= 0) {
+                const double wt = static_cast<double>(full_count);
 #pragma unroll
-            for (int e = 0; e < NE; ++e) s1[e] = lanes_sum(s1[e], wv_shift);
-            if (lane <= wv_mask)
-#pragma unroll
-                for (int e = 0; e < NE; ++e) red[wave * columns + c * NE + e] = s1[e];
-            lds_barrier();
-            for (int32_t q = tid; q < columns; q += T) {
-                double t1 = 0.0;
-#pragma unroll 8
-                for (int32_t k = 0; k < waves; ++k) t1 += red[k * columns + q];
-                s2 -= t1 * t1 / static_cast<double>(p.N);          // (columns outside the tile hold 0)
+                for (int e = 0; e < NE; ++e) s1[e] *= wt;
+                s2 *= wt;
             }
-            s2 = lanes_sum(s2, 0);
-            if (lane == 0) red[waves * columns + (r + 1 - held) * waves + wave] = s2;
+            double *sums = sums_of(r);
+            column_sums<NE>(s1, s2, wv_shift, sums + (wave - w0) * columns, sums + sharers * columns + (wave - w0));
         }
     };
-    // Entries held .. end - 1 of the part (its tile and number: part_at) leave LDS.
-    [[maybe_unused]] auto write_distortions = [&](int32_t end, int64_t part_at) {
+    // Behind the next barrier: the total of the distortion after round r.
+    [[maybe_unused]] auto finish = [&](int32_t r) {
         if constexpr (DIST) {
-            const int32_t waves = T >> 6;
-            const double *tot = red + waves * (NE << wv_shift);
+            if (wave != first_wave(r) || !(r < 0 ? p.dist_before != 0 : ((p.dist_after >> r) & 1u) != 0)) return;
+            const double sum = finish_columns(sums_of(r), sharers, columns, sums_of(r) + sharers * columns, sharers, p.inv_n);
+            if (lane == 0) totals[r + 1] = sum;
+        }
+    };
+    // All totals of a part (its tile and number: part_at) leave LDS.
+    [[maybe_unused]] auto write_distortions = [&](int64_t part_at) {
+        if constexpr (DIST) {
             lds_barrier();
-            for (int32_t e = held + tid; e < end; e += T)
-                if (e == 0 ? p.dist_before != 0 : ((p.dist_after >> (e - 1)) & 1u) != 0) {
-                    double sum = 0.0;
-                    for (int32_t k = 0; k < waves; ++k) sum += tot[(e - held) * waves + k];
-                    p.partials[e * p.tiles * PHASES + part_at] = sum;
-                }
-            if constexpr (kWindow) held = end;
+            finish(p.rounds - 1);
+            lds_barrier();
+            for (int32_t e = tid; e <= p.rounds; e += T)
+                if (e == 0 ? p.dist_before != 0 : ((p.dist_after >> (e - 1)) & 1u) != 0) p.partials[e * p.tiles * PHASES + part_at] = totals[e];
         }
     };
 
@@ -747,9 +728,11 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
             if constexpr (TAB == kLds || TAB == kBits) lds_barrier();
         }
 
-        if constexpr (kWindow) held = 0;
         if constexpr (DIST)
-            if (p.dist_before) distortion(0, seg, -1);
+            if (p.dist_before) {
+                distortion(0, seg, -1);
+                if (p.dist_barrier) lds_barrier();
+            }
         int32_t axis = p.axis0;
         constexpr int kUnroll = TAB == kAheadOnly ? kAhead : 1;            // (registers have no index)
 #pragma unroll 1
@@ -761,14 +744,15 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
                 round(i, seg, r, axis);
                 lds_barrier();
                 if constexpr (DIST) {
+                    finish(r - 1);
                     if ((p.dist_after >> r) & 1u) distortion(i, seg, r);
                     fetch_round(i, r + kAhead);
-                    if constexpr (kWindow)
-                        if (r + 2 - held == p.dist_window) write_distortions(r + 2, w * PHASES + phase);
+                    // (a returning peer may copy its donor to its own row, which the distortion has read)
+                    if (p.dist_barrier) lds_barrier();
                 }
                 axis = axis + 1 == p.d ? 0 : axis + 1;
             }
-        write_distortions(p.rounds + 1, w * PHASES + phase);
+        write_distortions(w * PHASES + phase);
         // back into the registers; the next part enters LDS when everybody is done with this one
         // (always read, whoever is stored, so that the registers need not keep what they held before)
         row_ = lds_row;

@@ -181,14 +181,11 @@ inline double fused_pass_us(const RunSize &z, const Participation &w, int32_t ro
 // more than 5 % slower than the better one in 3.0 % and more than 15 % in 1.6 % then, 5.9 and 3.8 % at four fifths.
 constexpr double kRoundsAhead = 0.8, kRoundsAheadOfMeans = 1.0;
 
-// A distortion on its own: the chain over the rows that a wave walks (8 rows at a time in binary32, 4
-// in bfloat16, up to 256 rows to a wave), or one read of the state where that takes longer.
-// Within a curve, 1,089 binary32 rows of 1, 64, 256 and 2,000 MB take 46, 37, 47 and 312 us, 4,096
-// bfloat16 rows 99, 100, 106 and 374.
+// A distortion on its own: two launches and the chain over the rows that a wave walks, or one read of the state where that takes
+// longer.  1,024 binary32 rows of 1.6, 25, 100 and 1,600 MB take 7.5, 8.2, 20 and 235 us, 4,096 bfloat16 rows 17, 19, 22 and 236.
 inline double distortion_us(const RunSize &z)
 {
-    const double first = static_cast<double>(z.N < 1024 ? z.N : 1024), more = static_cast<double>(z.N) - first;
-    const double chain = 6.0 + first * (z.element_bytes == 2 ? 0.07 : 0.036) + 0.006 * more, read = 4.0 + 0.165 * z.megabytes();
+    const double chain = 6.5 + static_cast<double>(z.N) * (z.element_bytes == 2 ? 0.0027 : 0.0015), read = 4.0 + 0.165 * z.megabytes();
     return chain > read ? chain : read;
 }
 

@@ -44,6 +44,96 @@ __device__ __forceinline__ LanePair swap32(float a, float b)
     return LanePair{__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
 
+// The same of binary64 values.
+struct DoublePair { double first, second; };
+template <bool FAR> __device__ __forceinline__ DoublePair swap_halves(double a, double b)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const uint32_t xl = static_cast<uint32_t>(x), xh = static_cast<uint32_t>(x >> 32), yl = static_cast<uint32_t>(y), yh = static_cast<uint32_t>(y >> 32);
+    const auto l = FAR ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false) : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto h = FAR ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false) : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    return DoublePair{__builtin_bit_cast(double, static_cast<uint64_t>(h[0]) << 32 | l[0]), __builtin_bit_cast(double, static_cast<uint64_t>(h[1]) << 32 | l[1])};
+}
+template <int CTRL> __device__ __forceinline__ double rotated(double v)
+{
+    const uint64_t bits = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(bits), CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(bits >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
+}
+// Sum over the lanes of a row of 16 that differ by multiples of 1 << from (every lane gets it), by rotations.
+__device__ __forceinline__ double row_sum(double v, int32_t from)
+{
+    if (from <= 3) v += rotated<0x128>(v);
+    if (from <= 2) v += rotated<0x124>(v);
+    if (from <= 1) v += rotated<0x122>(v);
+    if (from <= 0) v += rotated<0x121>(v);
+    return v;
+}
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v = row_sum(v, 0);
+    DoublePair p = swap_halves<false>(v, v);
+    v = p.first + p.second;
+    p = swap_halves<true>(v, v);
+    return p.first + p.second;
+}
+
+// Distortion of a tile in LDS: sum over its columns of s2 - s1^2 / N, s1 and s2 the sums of the differences from one row
+// and of their squares.  A lane holds s1 of the NE columns of its vector (lane & (vectors - 1)) and s2 of all of them
+// together.  column_sums: those of a wave, to LDS: cols[NE << wv_shift], *squares.  The lanes that share a column are added by
+// exchanges that halve the columns of a lane (a sum of four columns over four lanes takes 3 additions and 6
+// exchanges instead of 8 and 16).
+template <int NE> __device__ __forceinline__ void column_sums(const double (&s1)[NE], double s2, int32_t wv_shift, double *cols, double *squares)
+{
+    asm volatile("" : "+s"(wv_shift));           // (what is asked of it below is not kept in registers from round to round)
+    const int32_t lane = threadIdx.x & 63;
+    const double all = wave_sum(s2);
+    if (lane == 0) *squares = all;
+    double *mine = cols + (lane & ((1 << wv_shift) - 1)) * NE;
+    if (wv_shift >= 6) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) mine[e] = s1[e];
+        return;
+    }
+    double half[NE / 2];
+#pragma unroll
+    for (int e = 0; e < NE / 2; ++e) {
+        const DoublePair p = swap_halves<true>(s1[e], s1[e + NE / 2]);      // lower half of the wave: column e
+        half[e] = p.first + p.second;
+    }
+    mine += (lane >> 5) * (NE / 2);
+    if (wv_shift == 5) {
+#pragma unroll
+        for (int e = 0; e < NE / 2; ++e) mine[e] = half[e];
+        return;
+    }
+    double quarter[NE / 4];
+#pragma unroll
+    for (int e = 0; e < NE / 4; ++e) {
+        const DoublePair p = swap_halves<false>(half[e], half[e + NE / 4]);  // rows 0 and 2: column e
+        quarter[e] = row_sum(p.first + p.second, wv_shift);
+    }
+    mine += ((lane >> 4) & 1) * (NE / 4);
+    if ((lane & 15) >> wv_shift == 0)
+#pragma unroll
+        for (int e = 0; e < NE / 4; ++e) mine[e] = quarter[e];
+}
+// One wave: the sum over the columns, from what `parts` parts of the rows left in cols and `waves` waves in squares; inv = 1 / N.
+// (columns outside the tile hold 0)
+__device__ __forceinline__ double finish_columns(const double *cols, int32_t parts, int32_t columns, const double *squares, int32_t waves, double inv)
+{
+    const int32_t lane = threadIdx.x & 63;
+    double sum = lane < waves ? squares[lane] : 0.0;
+    for (int32_t q = lane; q < columns; q += 64) {
+        double t1 = 0.0;
+#pragma unroll 4
+        for (int32_t k = 0; k < parts; ++k) t1 += cols[k * columns + q];
+        sum -= t1 * t1 * inv;
+    }
+    return wave_sum(sum);
+}
+
 // CV consecutive columns of one row in LDS, widened to binary32.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 template <int DT, int CV> struct Cols;
