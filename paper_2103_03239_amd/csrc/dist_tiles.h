@@ -14,15 +14,17 @@ struct DistTiles {
 // Tiles for N rows of P elements; whole_lines: rows start on cache lines.  false: rows of less than a vector, or too many of
 // them for 32-bit row numbers.  From sweeps on MI355X (8 to 64 lanes, 1 to 8 waves, both kinds of loads; 9 to 4096 rows, 0.4 MB
 // to 1.6 GB, on and off the cache lines), us:
-//   Tiles as wide as leaves 160 of them, whose 8 waves a block then make 1,300 on the chip: 4096 rows, 400 MB, 32 lanes x 8
+//   Tiles as wide as leaves 160 of them (130 of large states), whose 8 waves a block then make 1,300 on the chip: 4096 rows, 400 MB, 32 lanes x 8
 //   waves 60, 8 x 1 64; 1024 rows, 25 MB, 8 x 8 8.2, 16 x 8 9.6; 512 rows, 100 MB, 64 x 8 18.0, 16 x 1 19.1.  A block of several
 //   waves ends with barriers for every element of a vector, so bfloat16 states of few rows take narrow tiles of one wave:
 //   144 rows, 25 MB, 16 x 1 10.3, 32 x 4 12.5.
-//   Waves until the chip has 1,000: 4096 rows, 2.1 GB bfloat16, 32 x 1 316, 16 x 8 344; 256 rows, 400 MB, 1 wave 64.5, 8 waves
-//   73.5; 1024 rows, 25 MB binary32, 8 waves 8.2, 4 waves 8.8.  Beyond 1 GB of binary32 few columns at a time are better for
-//   HBM: 256 rows, 1.6 GB, 8 waves 233, 1 wave 239; 64 rows 233 and 241; beyond 1.8 GB of bfloat16, if the chip still has 600 tiles
-//   of 64 lanes: 576 rows, 2.9 GB, 64 x 8 426, 32 x 1 455; 1024 rows of 2.6 GB off the cache lines 405 and 436; 125 rows, 2.5 GB,
-//   64 x 4 365, 32 x 1 379.
+//   Waves until the chip has 1,000: 256 rows, 400 MB, 1 wave 64.5, 8 waves 73.5; 1024 rows, 25 MB binary32, 8 waves 8.2, 4
+//   waves 8.8.  From 550 MB on 64 lanes and waves until the chip has 1,100: the last-level cache is full of what wrote the state, and
+//   the lines that a pass pushes out of it cost most with more than 2,050 waves in flight (the pass that follows the write : the next
+//   one; 4096 rows of 2.1 GB bfloat16 1,002 waves 387 : 395, 2,004 313 : 308, 4,008 340 : 316; 576 rows of 2.1 GB binary32 64 x 8 423 :
+//   311, 64 x 1 340 : 313; 1024 rows of 4.2 GB bfloat16 64 x 8 748 : 616, 64 x 1 644 : 621).  Where that would be two waves, whole
+//   lines of bfloat16 take tiles of half the width (2048 rows of 1.4 GB 64 x 2 270 : 214, 32 x 1 219 : 216; 4096 rows of 3 GB 549 : 452 and 460 : 453).
+//   Beyond 1 GB under 128 rows of binary32 8 waves, if a wave then still has a load of 8 rows (64 rows, 2.1 GB, 1 wave 404 : 311, 8 waves 383 : 306).
 //   Fewer than 32 rows are a load or two of a wide tile: 16 rows, 6.4 MB bfloat16, 32 x 1 6.9, 8 x 4 9.4.
 //   Never more than 65,536 tiles where they can be wider (their sums take one block 10 us).
 //   Non-temporal loads beyond 64 MB (4096 rows, 1.6 GB 231 : 250; 1024 rows, 25 MB 9.4 : 8.2), but where neighbours share cache lines
@@ -34,23 +36,18 @@ inline bool dist_tiles(int64_t esize, int64_t N, int64_t P, bool whole_lines, Di
     if (row < 16 || N > (int64_t(1) << 30)) return false;
     const int64_t vectors = (row + 15) / 16;
     const double state = static_cast<double>(N) * static_cast<double>(row);
-    const bool f32 = esize == 4, large = state > 1e9, few = N < 32;
+    const bool f32 = esize == 4, few = N < 32, large = !few && state > 5.5e8;
     int32_t lanes = few ? (f32 || N <= 12 ? 64 : 32) : f32 && N < 1024 ? 64 : 32;
-    if (!whole_lines && !few && (f32 ? vectors >= 65536 : large && N < 512)) lanes = 64;
-    const bool very_large = !f32 && !few && state > 1.8e9 && vectors >= 64 * 600;
-    if (very_large) lanes = 64;
-    const int64_t least = f32 || N >= 512 ? 160 : 512;
+    if (large || (!whole_lines && !few && f32 && vectors >= 65536)) lanes = 64;
+    if (large && !f32 && whole_lines && vectors > 64 * 550 && vectors <= 64 * 1000) lanes = 32;
+    const int64_t least = large ? 130 : f32 || N >= 512 ? 160 : 512;
     while (!few && lanes > 8 && vectors < least * lanes) lanes /= 2;
     while (lanes < 64 && vectors > 65536ll * lanes) lanes *= 2;
     const int64_t blocks = (vectors + lanes - 1) / lanes;
     if (blocks > 0x7fffffffll) return false;
     int32_t waves = 1;
     const auto twice = [&] { return waves < 8 && N >= 2 * waves * (64 / lanes); };           // (a row for every lane)
-    if (!few) {
-        while (twice() && blocks * waves < 1000) waves *= 2;
-        if (f32 ? large && (N < 128 || (N >= 256 && N < 1024)) : very_large && N >= 96)
-            while (twice() && (f32 || N >= 256 || waves < 4)) waves *= 2;
-    }
+    while (!few && twice() && (blocks * waves < (large ? 1100 : 1000) || (state > 1e9 && f32 && N >= 64 && N < 128))) waves *= 2;
     out->lanes = lanes;
     out->waves = waves;
     out->blocks = blocks;

@@ -18,7 +18,8 @@ DEV = "cuda:0"
     (64, 40_959, 0, 0), (300, 140_001, 1, 1), (700, 61_441, 0, 1),       # 32 lanes
     (20, 1_200_001, 0, 0), (64, 262_143, 0, 1), (127, 41_000, 0, 0),     # 64 lanes
     (300, 900_003, 0, 0), (700, 720_005, 1, 1), (300, 900_032, 0, 0),    # beyond 1 GB
-    (2_900, 320_001, 1, 1), (100, 9_100_001, 1, 0),                      # beyond 1.8 GB
+    (2_900, 320_001, 1, 1), (700, 412_000, 1, 0), (700, 394_240, 1, 0),  # more than half a GB: 2 waves of 64 lanes or 1 of 32
+    (90, 2_900_001, 0, 1), (40, 7_100_001, 1, 0), (4_096, 33_281, 0, 0),
     (3, 8_300_003, 0, 1),                                                # tiles widened so that there are not too many
 ])
 def test_against_binary64(N, P, dtype, odd):
