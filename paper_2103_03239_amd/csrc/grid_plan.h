@@ -22,7 +22,7 @@ struct GridPlan {
     int32_t Wb, wv_shift;            // bytes of a row per tile; log2 of its 16-byte vectors
     int32_t threads, tile_bytes, lds_bytes, red_offset;
     int32_t pad;                     // LDS bytes added after every M rows (bank conflicts of axis 0)
-    int32_t die_run;                 // consecutive tiles per die (1 = tiles dealt in order)
+    int32_t die_run;                 // consecutive tiles per die (1: tiles dealt in order)
     int32_t streaming;               // 1 = non-temporal loads and stores
     int32_t phases, max_rounds;      // column parts of a tile (1 or 2); most rounds of one pass
     int32_t axis0;                   // axis of the pass's first round
@@ -275,6 +275,20 @@ inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
     return false;
 }
 
+// Consecutive tiles per die, about as many as asked for.  Tiles that whole runs of all dies leave at the end are dealt in order, which costs
+// most where tiles share cache lines: of 4096 rows of 100 MB 250 of 762 tiles, 6 rounds 99 us, in runs of 31 (18 left) 74; 1024 rows of
+// 60 MB 33.9 -> 30.1.  From 256 runs a die on they are less than 3 % of the tiles, and 32 is the better run (4096 rows of 4.3 GB
+// with refresh, 128 of 32,640 tiles left, 2.81 ms; in runs of 34, none left, 3.05).
+inline int32_t die_run_of(int64_t tiles, int32_t about)
+{
+    if (tiles < 6 * about) return tiles >= 16 ? static_cast<int32_t>(tiles / 8) : 1;
+    int32_t best = about;
+    if (tiles < 256 * about)
+        for (int32_t run = about * 3 / 4; run <= about * 5 / 4; ++run)
+            if (tiles % (8 * run) < tiles % (8 * best)) best = run;
+    return best;
+}
+
 // The rest of a plan whose tiles and kernel are chosen.
 inline bool fill_in(GridPlan *plan, const void *X, int64_t esize, const GridAsk &ask)
 {
@@ -312,8 +326,12 @@ inline bool fill_in(GridPlan *plan, const void *X, int64_t esize, const GridAsk 
     // 128 MiB 58.6 -> 52.8 us, 250 MiB 113 -> 89); below the L2s' 32 MiB the non-temporal ones are
     // ahead again (16 MiB: 12.5 against 13.8), they leave no dirty lines to be written back at the end.
     p.streaming = whole_lines && (!cached || state_bytes <= 24.0 * (1 << 20)) ? 1 : 0;
-    p.die_run = whole_lines && wb > 128 ? 1 : 32;
-    if (p.tiles < 8 * p.die_run) p.die_run = p.tiles >= 16 ? static_cast<int32_t>(p.tiles / 8) : 1;
+    // Rows a multiple of 256 KiB apart meet in the same memory channels, and dies that are further apart in the row spread over more of
+    // them: 4096 rows, 6 rounds, runs of 32 : 256, 1.1 GB binary32 676 : 640 us, 2.1 GB bfloat16 1,298 : 1,201, with refresh 1,613 :
+    // 1,462; 1024 rows in runs of 32 : 64, 0.5 GB 270 : 258, 16 GB 8,700 : 8,470 (256 8,780).  Others: 4096 rows of 262,208
+    // 32 : 256 1,180 : 1,187, of 49,152 binary32 567 : 606.
+    const bool same_channels = p.row_bytes % (256 * 1024) == 0;
+    p.die_run = whole_lines && wb > 128 ? 1 : die_run_of(p.tiles, same_channels && wb <= 32 ? 256 : same_channels && wb <= 128 ? 64 : 32);
     // rounds of one pass: as many bitmaps as fit next to the tile
     const int64_t waves = p.threads / 64, columns = part / esize;
     if (p.means) {

@@ -383,3 +383,37 @@ def test_the_gpu_tests_take_every_kernel(tmp_path):
     built = set(run_host(tmp_path, BUILT).stdout.splitlines())
     taken = {got.split("|")[1] for got in out}
     assert taken == built, sorted(built - taken)
+
+
+RUNS = r"""
+#include <cstdio>
+#include <vector>
+#include "grid_plan.h"
+using namespace moshpit;
+
+int main()
+{
+    for (int32_t about : {32, 64, 256})
+        for (int64_t tiles = 1; tiles < 400 * about; tiles += tiles < 3000 ? 1 : 37) {
+            const int32_t run = die_run_of(tiles, about);
+            const int64_t span = 8 * int64_t(run), rest = tiles % span;
+            const bool few = tiles < 6 * about, many = tiles >= 256 * about;
+            if (run < 1 || run > about * 5 / 4) return std::printf("run %d of %lld tiles\n", run, (long long)tiles), 1;
+            // (the best of about / 2 + 1 lengths leaves no more than the one asked for)
+            if (few ? (tiles >= 16 && rest >= 8) : many ? run != about : rest > tiles % (8 * int64_t(about)))
+                return std::printf("run %d of %lld tiles leaves %lld\n", run, (long long)tiles, (long long)rest), 1;
+            // the order in which a kernel takes tiles (tile_of) has every tile once
+            std::vector<char> seen(tiles, 0);
+            for (int64_t i = 0; i < tiles; ++i) {
+                const int64_t q = i / span, r = i - q * span, at = run == 1 || (q + 1) * span > tiles ? i : q * span + (r & 7) * run + (r >> 3);
+                if (at < 0 || at >= tiles || seen[at]++) return std::printf("tile %lld of %lld\n", (long long)at, (long long)tiles), 1;
+            }
+        }
+    return 0;
+}
+"""
+
+
+def test_runs_of_tiles_per_die(tmp_path):
+    got = run_host(tmp_path, RUNS)
+    assert got.returncode == 0, got.stdout
