@@ -82,6 +82,11 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
             const int64_t per = (work_items + 7) >> 3;
             w = (w0 & 7) * per + (w0 >> 3);
             if (w >= work_items) break;
+        } else if (order > 1) {
+            // runs of 2^order: a die takes so many of every eight times as many, and an eighth of what is left at the end
+            const int64_t span = int64_t(8) << order, first = w0 & ~(span - 1), r = w0 - first, left = work_items - first;
+            const int64_t run = (left < span ? left : span) >> 3;
+            if (r < 8 * run) w = first + (r & 7) * run + (r >> 3);
         }
         const int64_t g = w / tiles;
         const int64_t tile = w - g * tiles;
@@ -376,17 +381,17 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // more waves 8 x 8 x 8 x 200,000 binary32, 410 MB, 140 -> 122 us, 12 x 12 x 500,000 102 -> 95, 5 x 5 x 5 x 700,000 115 -> 107,
     // 16 x 16 x 16 x 65,536 bfloat16, 537 MB, 184 -> 175; 8 x 8 x 5,000,000, 640 MB, 213 : 215.
     const bool cached_list = geom.index != nullptr && whole_lines && !cached && touched <= 544.0 * (1 << 20);
-    // binary32 rows off the cache lines, of a state too large for the last-level cache: such rounds in
-    // which (nearly) every peer takes part, in groups of the grid, have rules of their own below
+    // Rounds of the grid over rows off the cache lines, of a state too large for the last-level cache, deal work items to the dies in runs
+    // of 32: the first and last lines of a row's part meet in one L2, and the waves in flight still stream a handful of groups.
+    const bool runs = !whole_lines && !cached && geom.index == nullptr && geom.grad == nullptr;
     const bool full = (alive == nullptr && geom.bits == nullptr) || geom.present >= 0.97f;
-    // (more than 16 rows as soon as it is too large, 24 x 24 x 303,819, 668 MiB, everybody present 284 -> 266 us,
-    // 10 % absent 256 -> 247; fewer from 800 MiB on: 12 x 12 x 1,215,277, 668 MiB, 258 us by the general rules, 273)
+    // (binary32, more than 16 rows as soon as it is too large, 24 x 24 x 303,819, 668 MiB, SGD step; fewer from 800 MiB on)
     const bool large_odd = !whole_lines && dtype == 0 && !cached && (geom.M > 16 || touched > 800.0 * (1 << 20));
-    const bool all_odd = large_odd && full && geom.index == nullptr && geom.grad == nullptr;
     // (the SGD step on groups of up to 8 rows streams so few rows at once that non-temporal accesses
-    // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms; so does a round of
-    // groups of 7 or 8 binary32 rows with everybody present: 8 x 8 x 7,812,501 731 against 769 us)
-    const bool lines_meet = !whole_lines && (geom.grad == nullptr || geom.M > 8) && !(all_odd && geom.M > 6 && geom.M <= 8);
+    // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms.  So do groups of up to 6 rows in runs,
+    // 3^4 of 3 GB binary32 1,042 : 1,123 us, 5 x 5 x 5 bfloat16 1,051 : 1,101, and 8 of large binary32 states, 8 x 8 x 12,000,007 985 : 1,015, but
+    // 500 MB 167 : 153)
+    const bool lines_meet = !whole_lines && (geom.grad != nullptr ? geom.M > 8 : !(runs && (geom.M <= 6 || (geom.M <= 8 && large_odd))));
     const bool nt = tune.nt >= 0 ? tune.nt != 0 : (cached ? whole_lines && touched <= 24.0 * (1 << 20) : !lines_meet && !cached_list);
     const int block = (tune.block == 64 || tune.block == 128 || tune.block == 256) ? tune.block : 64;
     // Block order (measured on MI355X over row sizes of 128 KiB .. 32 MiB, groups of 16 and of
@@ -418,21 +423,17 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
             // With gradients from 9 rows on (16 x 16 x 976,563 binary32, everybody present: 626 us in the plain order,
             // 588 in eighths), but up to 24 binary32 rows of less state, up to 16 with a mask until a little later, in
             // the plain one (16 x 16 x 488,281 with a mask 279 and 284, 12 x 12 x 1,736,111 531 and 549, 24 x 24 x
-            // 303,819 385 and 398; twice that state is 6 % ahead in eighths).  Without gradients more than 16 binary32
-            // rows (32 x 32 x 488,281 with a mask in device memory 758 us in the plain order, 720 in eighths; as bits
-            // 772 and 717), more than 28 bfloat16 rows (24 x 24 x 868,055 343 and 362, but 32 x 32 x 1,445,344 1245
-            // and 1147), and 3 or 4 binary32 rows with a mask as bits (4 x 4 x 4 x 7,812,501 657 and 636; not 2^6 x
-            // 7,812,501 578 and 607; not bfloat16 4 x 4 x 4 x 7,812,501 333 and 352).
+            // 303,819 385 and 398; twice that state is 6 % ahead in eighths).  Peer lists from more than 16 binary32
+            // rows or 28 bfloat16 rows on.  Others in runs, 0.5 to 3 GB, with 10 % absent (in whichever of the other two was
+            // the better before): 8 x 8 x 12,000,007 1,043 -> 985 us, 16 x 16 x 2,929,687 1,051 -> 1,027, 16 x 16 x 16 x 366,211 bfloat16 1,106 -> 1,016,
+            // 32 x 32 x 732,422 1,092 -> 1,029, 20 x 20 x 312,500, everybody present, 196 -> 173; groups of 2 to 40 rows 1.02 to 1.14
+            // times as fast, of 8 binary32 rows with everybody present 1.00.
             if (geom.grad != nullptr)
                 order = geom.M > 8 && (geom.M > 24 || dtype == 1 || touched > (full || geom.M > 16 ? 1600.0 : 2200.0) * (1 << 20)) ? 1 : 0;
+            else if (geom.index != nullptr)
+                order = geom.M > 28 || (dtype == 0 && geom.M > 16) ? 1 : 0;
             else
-                order = geom.M > 28 || (dtype == 0 && (geom.M > 16 || (geom.M > 2 && geom.M <= 4 && geom.bits != nullptr))) ? 1 : 0;
-            // Everybody present: 5 x 5 x 5 x 2,000,001 380 us in the plain order, 368 in eighths; 17 and 18 rows (a
-            // chunk of 16 and a short one) 17 x 17 x 2,595,156 1244 and 1189; 24 x 24 x 1,302,084 1161 and 1217;
-            // 32 x 32 x 732,422 1323 and 1228, 64 x 64 x 91,553 662 and 610.  A mask in device memory: 20 x 20 x
-            // 937,501 528 and 575, 24 x 24 x 651,042 531 and 553, 28 x 28 x 478,317 567 and 553.
-            if (all_odd && geom.M > 4) order = geom.M <= 6 || geom.M == 17 || geom.M == 18 || geom.M > 28 ? 1 : 0;
-            else if (large_odd && geom.M > 16 && geom.M <= 24 && geom.grad == nullptr && geom.index == nullptr && geom.bits == nullptr) order = 0;
+                order = 5;
         } else if (geom.index == nullptr) {
             const int64_t member_stride = geom.S * row_bytes;
             const int64_t MiB = 1 << 20;
@@ -471,17 +472,16 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         // ordinary accesses (see above): more in flight, 8 for bfloat16 rows off the cache lines
         if (cached) wpc = geom.M > 8 ? 12 : 16;
         else if (cached_list) wpc = geom.M > 8 ? 8 : 10;
-        else if (lines_meet && rows * cols <= 4) wpc = 16;
+        else if (!whole_lines && geom.grad == nullptr && rows * cols <= 4) wpc = 16;
+        // (in runs, a mask as bits: 8 x 8 x 12,000,007 3 waves 985 us, 6 waves 1,022; 16 x 16 x 488,281 3 waves 168, 8 waves 153; 20 x 20 x
+        // 625,000 bfloat16 4 waves 175, 8 waves 159; 9 x 9 x 6,172,839 8 waves 706, 11 waves 675, 14 x 14 as fast with either; 32 x 32 x 732,422 3 waves 1,029, 8 waves 1,059; 40 x 40 x 312,455 bfloat16
+        // 4 waves 348, 8 waves 360)
+        else if (runs && geom.M > 6) wpc = geom.M > 24 ? (dtype == 0 ? 3 : 4) : geom.M <= 8 && large_odd ? 3 : geom.M > 8 && geom.M <= 11 ? 11 : 8;
         else if (!whole_lines && dtype == 1 && geom.M > 8 && geom.M <= 16) wpc = 128 / rows;
         else if (large_odd && geom.grad != nullptr && geom.M > 8 && geom.M <= 16) wpc = 5;
-        // (8 x 8 x 3,906,251 371 us with 3 waves; 16 x 16 x 976,563 5 waves 405, 3 waves 384; 5 x 5 x 5 x
-        // 2,000,001 8 waves in eighths 368, 12 waves 376)
-        else if (all_odd && geom.M > 4 && geom.M <= 28) wpc = order == 0 ? 3 : 8;
-        // a wave whose mask came with its arguments starts loading sooner: fewer do (8 x 8 peers x
-        // 12,000,007 binary32: 3 waves 5.3 TB/s, 4 waves 5.0; 16 x 16 x 2,000,001: 5.3 and 4.9)
-        else if (!whole_lines && dtype == 0 && geom.bits != nullptr && geom.M > 4 && geom.M <= 16) wpc = 52 / kib_per_wave;
-        // (a mask in device memory: 16 x 16 x 16 x 61,035 5 waves 344, 7 waves 358 us)
-        else if (large_odd && !all_odd && geom.grad == nullptr && geom.index == nullptr && geom.M > 8) wpc = 5;
+        // (5 x 5 x 5 x 2,000,001 8 waves 343 us, 4 waves 352; a wave whose mask came with its arguments starts loading sooner)
+        else if (runs && large_odd && full && geom.M > 4) wpc = 8;
+        else if (runs && dtype == 0 && geom.bits != nullptr && geom.M > 4) wpc = 52 / kib_per_wave;
         if (wpc > 32) wpc = 32;
     }
 

@@ -49,7 +49,7 @@ hipError_t launch_sort_items(SortItem *items, int64_t n_padded, hipStream_t stre
 // waves_per_cu = resident waves per compute unit (enforced through the
 // launch's LDS reservation), order = how work items are dealt to the blocks (0: in
 // order, column tiles fastest; 1: each of the 8 dies streams through an eighth of the
-// list).  0 / -1 mean "choose from the shape".
+// list; more, chosen only: runs of 2^order per die).  0 / -1 mean "choose from the shape".
 struct MeanTuning {
     int cols = 0;
     int unroll = 0;
