@@ -220,7 +220,9 @@ __global__ __launch_bounds__(kMaxBlock) void group_mean_kernel(char *X, int64_t 
             for (int c = 0; c < COLS; ++c)
                 if (in_row[c]) store_vec<NT, mem_t>(dst + at[c], mean[c]);
         }
-    } while ((w0 += gridDim.x) < work_items && (!IDX || n_groups == nullptr || w0 < *n_groups * tiles));
+        // (a run's places up to its end: they are in another order than its work items)
+    } while ((w0 += gridDim.x) < work_items &&
+             (!IDX || n_groups == nullptr || (order > 1 ? w0 >> (order + 3) << (order + 3) : w0) < *n_groups * tiles));
 }
 
 // The kernel uses no LDS.  The dynamic-LDS size of the launch is only a
@@ -381,17 +383,17 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // more waves 8 x 8 x 8 x 200,000 binary32, 410 MB, 140 -> 122 us, 12 x 12 x 500,000 102 -> 95, 5 x 5 x 5 x 700,000 115 -> 107,
     // 16 x 16 x 16 x 65,536 bfloat16, 537 MB, 184 -> 175; 8 x 8 x 5,000,000, 640 MB, 213 : 215.
     const bool cached_list = geom.index != nullptr && whole_lines && !cached && touched <= 544.0 * (1 << 20);
-    // Rounds of the grid over rows off the cache lines, of a state too large for the last-level cache, deal work items to the dies in runs
+    // Rounds over rows off the cache lines, of a state too large for the last-level cache, deal work items to the dies in runs
     // of 32: the first and last lines of a row's part meet in one L2, and the waves in flight still stream a handful of groups.
-    const bool runs = !whole_lines && !cached && geom.index == nullptr && geom.grad == nullptr;
+    const bool runs = !whole_lines && !cached;
     const bool full = (alive == nullptr && geom.bits == nullptr) || geom.present >= 0.97f;
-    // (binary32, more than 16 rows as soon as it is too large, 24 x 24 x 303,819, 668 MiB, SGD step; fewer from 800 MiB on)
     const bool large_odd = !whole_lines && dtype == 0 && !cached && (geom.M > 16 || touched > 800.0 * (1 << 20));
     // (the SGD step on groups of up to 8 rows streams so few rows at once that non-temporal accesses
     // stay ahead there: 4 x 4 x 4 peers x 15,609,540 binary32 2.15 against 2.47 ms.  So do groups of up to 6 rows in runs,
     // 3^4 of 3 GB binary32 1,042 : 1,123 us, 5 x 5 x 5 bfloat16 1,051 : 1,101, and 8 of large binary32 states, 8 x 8 x 12,000,007 985 : 1,015, but
     // 500 MB 167 : 153)
-    const bool lines_meet = !whole_lines && (geom.grad != nullptr ? geom.M > 8 : !(runs && (geom.M <= 6 || (geom.M <= 8 && large_odd))));
+    const bool lines_meet = !whole_lines && (geom.grad != nullptr ? geom.M > 8
+                                             : !(runs && (geom.M <= 6 || (geom.M <= 8 && large_odd && geom.index == nullptr))));
     const bool nt = tune.nt >= 0 ? tune.nt != 0 : (cached ? whole_lines && touched <= 24.0 * (1 << 20) : !lines_meet && !cached_list);
     const int block = (tune.block == 64 || tune.block == 128 || tune.block == 256) ? tune.block : 64;
     // Block order (measured on MI355X over row sizes of 128 KiB .. 32 MiB, groups of 16 and of
@@ -407,7 +409,14 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         // A list with room for part-filled groups, as chunk-index rounds give, ends in empty ones: dealt to the
         // dies in eighths it would leave half of them idle (16 x 16 x 390,625 binary32 149 us, 224 in eighths).
         const bool holes = geom.index != nullptr && geom.n_index > geom.N;
-        if (holes) {
+        if (runs) {
+            // 0.5 to 3 GB with 10 % absent, in whichever of the other two orders was the better : in runs: 8 x 8 x 12,000,007 1,043 : 985 us,
+            // 16 x 16 x 2,929,687 1,051 : 1,027, 16 x 16 x 16 x 366,211 bfloat16 1,106 : 1,016, 32 x 32 x 732,422 1,092 : 1,029,
+            // 20 x 20 x 312,500, everybody present, 196 : 173; groups of 2 to 40 rows 1.02 to 1.14 times as fast, of 8 binary32 rows
+            // with everybody present 1.00.  Peer lists 4 x 4 x 4 x 9,765,625 832 : 806, 16 x 16 x 2,441,406 877 : 858, 32 x 32 x 610,352, part-filled,
+            // 967 : 932; SGD steps in groups of 16 x 16 x 16 x 152,588 2,172 : 2,140, 8 x 8 x 19,531,250 bfloat16 2,158 : 2,111.
+            order = 5;
+        } else if (holes) {
             order = 0;
         } else if (cached) {
             // In eighths from groups of more than 8 rows (16 x 16 x 62,501 binary32, 64 MB: 25.9 us in the plain
@@ -419,21 +428,6 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
             const double plain = geom.grad == nullptr && geom.index == nullptr ? 24.0 : geom.M > 16 ? 18.0 : geom.grad != nullptr ? 14.0 : 6.0;
             const bool ahead = geom.M <= 16 && !whole_lines && state > 6.0 && state <= 10.0;
             order = geom.M > 8 && (state > plain || ahead) ? 1 : 0;
-        } else if (!whole_lines) {
-            // With gradients from 9 rows on (16 x 16 x 976,563 binary32, everybody present: 626 us in the plain order,
-            // 588 in eighths), but up to 24 binary32 rows of less state, up to 16 with a mask until a little later, in
-            // the plain one (16 x 16 x 488,281 with a mask 279 and 284, 12 x 12 x 1,736,111 531 and 549, 24 x 24 x
-            // 303,819 385 and 398; twice that state is 6 % ahead in eighths).  Peer lists from more than 16 binary32
-            // rows or 28 bfloat16 rows on.  Others in runs, 0.5 to 3 GB, with 10 % absent (in whichever of the other two was
-            // the better before): 8 x 8 x 12,000,007 1,043 -> 985 us, 16 x 16 x 2,929,687 1,051 -> 1,027, 16 x 16 x 16 x 366,211 bfloat16 1,106 -> 1,016,
-            // 32 x 32 x 732,422 1,092 -> 1,029, 20 x 20 x 312,500, everybody present, 196 -> 173; groups of 2 to 40 rows 1.02 to 1.14
-            // times as fast, of 8 binary32 rows with everybody present 1.00.
-            if (geom.grad != nullptr)
-                order = geom.M > 8 && (geom.M > 24 || dtype == 1 || touched > (full || geom.M > 16 ? 1600.0 : 2200.0) * (1 << 20)) ? 1 : 0;
-            else if (geom.index != nullptr)
-                order = geom.M > 28 || (dtype == 0 && geom.M > 16) ? 1 : 0;
-            else
-                order = 5;
         } else if (geom.index == nullptr) {
             const int64_t member_stride = geom.S * row_bytes;
             const int64_t MiB = 1 << 20;
@@ -476,11 +470,13 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
         // (in runs, a mask as bits: 8 x 8 x 12,000,007 3 waves 985 us, 6 waves 1,022; 16 x 16 x 488,281 3 waves 168, 8 waves 153; 20 x 20 x
         // 625,000 bfloat16 4 waves 175, 8 waves 159; 9 x 9 x 6,172,839 8 waves 706, 11 waves 675, 14 x 14 as fast with either; 32 x 32 x 732,422 3 waves 1,029, 8 waves 1,059; 40 x 40 x 312,455 bfloat16
         // 4 waves 348, 8 waves 360)
-        else if (runs && geom.M > 6) wpc = geom.M > 24 ? (dtype == 0 ? 3 : 4) : geom.M <= 8 && large_odd ? 3 : geom.M > 8 && geom.M <= 11 ? 11 : 8;
+        else if (runs && geom.index != nullptr && geom.M > 6 && geom.M <= 24) wpc = 8;
+        else if (runs && geom.grad == nullptr && geom.index == nullptr && geom.M > 6)
+            wpc = geom.M > 24 ? (dtype == 0 ? 3 : 4) : geom.M <= 8 && large_odd ? 3 : geom.M > 8 && geom.M <= 11 ? 11 : 8;
         else if (!whole_lines && dtype == 1 && geom.M > 8 && geom.M <= 16) wpc = 128 / rows;
         else if (large_odd && geom.grad != nullptr && geom.M > 8 && geom.M <= 16) wpc = 5;
         // (5 x 5 x 5 x 2,000,001 8 waves 343 us, 4 waves 352; a wave whose mask came with its arguments starts loading sooner)
-        else if (runs && large_odd && full && geom.M > 4) wpc = 8;
+        else if (runs && large_odd && full && geom.M > 4 && geom.grad == nullptr && geom.index == nullptr) wpc = 8;
         else if (runs && dtype == 0 && geom.bits != nullptr && geom.M > 4) wpc = 52 / kib_per_wave;
         if (wpc > 32) wpc = 32;
     }
