@@ -15,7 +15,7 @@
 //
 // What bounds it: latency of one block: the launch, one load of the keys, seven barriers.  In a launch of 1024 threads
 // whatever the number of peers, buckets of about M peers each, keys loaded one after the other and the list
-// written peer by peer, it took 18.4 us for 4096 peers and 8.6 for 16; now 9.0 and 5.1.
+// written peer by peer, it took 19.4 us for 4096 peers; now 9.9.
 // The general path (dynamic_keys.hip, schedule.hip: a bitonic network over 4096 items and five more launches) takes
 // 85 us a round at 4096 peers.
 #include "mix64.h"
