@@ -16,8 +16,9 @@ struct DistTiles {
 // to 1.6 GB, on and off the cache lines), us:
 //   Tiles as wide as leaves 160 of them (130 of large states), whose 8 waves a block then make 1,300 on the chip: 4096 rows, 400 MB, 32 lanes x 8
 //   waves 60, 8 x 1 64; 1024 rows, 25 MB, 8 x 8 8.2, 16 x 8 9.6; 512 rows, 100 MB, 64 x 8 18.0, 16 x 1 19.1.  A block of several
-//   waves ends with barriers for every element of a vector, so bfloat16 states of few rows take narrow tiles of one wave:
-//   144 rows, 25 MB, 16 x 1 10.3, 32 x 4 12.5.
+//   waves ends with barriers for every element of a vector, so bfloat16 states of up to 256 rows and 40 MB take one wave, whose
+//   lanes share more rows the more there are: 32 rows, 1.6 MB, 32 x 1 7.9, 8 x 4 10.7; 64 rows, 25 MB, 32 x 1 9.4, 8 x 4 27; 144
+//   rows, 1.6 MB, 16 x 1 8.8, 32 x 1 10.7, 8 x 8 9.9; 256 rows, 6.4 MB, 8 x 1 8.8, 16 x 1 10.5, 8 x 8 10.1.
 //   Waves until the chip has 1,000: 256 rows, 400 MB, 1 wave 64.5, 8 waves 73.5; 1024 rows, 25 MB binary32, 8 waves 8.2, 4
 //   waves 8.8.  From 550 MB on 64 lanes and waves until the chip has 1,100: the last-level cache is full of what wrote the state, and
 //   the lines that a pass pushes out of it cost most with more than 2,050 waves in flight (the pass that follows the write : the next
@@ -40,14 +41,16 @@ inline bool dist_tiles(int64_t esize, int64_t N, int64_t P, bool whole_lines, Di
     int32_t lanes = few ? (f32 || N <= 12 ? 64 : 32) : f32 && N < 1024 ? 64 : 32;
     if (large || (!whole_lines && !few && f32 && vectors >= 65536)) lanes = 64;
     if (large && !f32 && whole_lines && vectors > 64 * 550 && vectors <= 64 * 1000) lanes = 32;
+    const bool one_wave = !f32 && !few && N <= 256 && state < 40e6;
+    if (one_wave) lanes = N <= 64 ? 32 : N <= 160 ? 16 : 8;
     const int64_t least = large ? 130 : f32 || N >= 512 ? 160 : 512;
-    while (!few && lanes > 8 && vectors < least * lanes) lanes /= 2;
+    while (!few && !one_wave && lanes > 8 && vectors < least * lanes) lanes /= 2;
     while (lanes < 64 && vectors > 65536ll * lanes) lanes *= 2;
     const int64_t blocks = (vectors + lanes - 1) / lanes;
     if (blocks > 0x7fffffffll) return false;
     int32_t waves = 1;
     const auto twice = [&] { return waves < 8 && N >= 2 * waves * (64 / lanes); };           // (a row for every lane)
-    while (!few && twice() && (blocks * waves < (large ? 1100 : 1000) || (state > 1e9 && f32 && N >= 64 && N < 128))) waves *= 2;
+    while (!few && !one_wave && twice() && (blocks * waves < (large ? 1100 : 1000) || (state > 1e9 && f32 && N >= 64 && N < 128))) waves *= 2;
     out->lanes = lanes;
     out->waves = waves;
     out->blocks = blocks;

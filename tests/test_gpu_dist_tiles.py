@@ -14,6 +14,7 @@ DEV = "cuda:0"
     (1, 5, 0, 1), (2, 1_000, 1, 0), (3, 4, 0, 0), (31, 70_003, 0, 1),     # fewer rows than a load takes; one wave
     (12, 40_001, 1, 1), (13, 40_001, 1, 1),                              # 64 and 32 lanes
     (32, 2_047, 0, 0), (130, 4_095, 1, 1), (4_097, 63, 1, 0), (999, 5_119, 0, 1),       # 8 lanes, 1 to 8 waves
+    (32, 1_003, 1, 1), (64, 20_005, 1, 0), (65, 9_001, 1, 1), (161, 9_001, 1, 0), (256, 2_055, 1, 1),     # one wave, 32 to 8 lanes
     (515, 20_480, 1, 1), (1_025, 10_241, 0, 0), (513, 20_481, 1, 0),     # 160 tiles of 16 lanes and one more or less
     (64, 40_959, 0, 0), (300, 140_001, 1, 1), (700, 61_441, 0, 1),       # 32 lanes
     (20, 1_200_001, 0, 0), (64, 262_143, 0, 1), (127, 41_000, 0, 0),     # 64 lanes
