@@ -1,12 +1,15 @@
 """The one-launch random orders (up to 4096 peers) against the oracle: permutations, chunk-index
 keys over many rounds with failures (keys with more than M and with no members), and rounds in
 random groups with a mask."""
+import os
+import re
 import time
 
 import numpy as np
 import pytest
 import torch
 
+import __graft_entry__ as entry
 from oracle import moshpit_oracle as orc
 from paper_2103_03239_amd import binding
 from parity_util import assert_state_close
@@ -85,6 +88,75 @@ def test_keys_that_have_come_together(M, d):
     assert crowded <= apart + 100e-6
     # at most 7 additions in a row and a division in the four rounds that average anything, each within 2^-24
     assert_state_close(X.cpu().double().numpy(), ref, 4 * 8 * 2.0 ** -24, f"keys together {M}^{d}")
+
+
+def fullest_bucket(N, M, d, packed, seed, t, alive):
+    """Participants of a chunk-index round in the kernel's fullest bucket: by key and as many of the order key's upper bits
+    as give at most one bucket to a peer (their next power of two)."""
+    def mix(x):
+        x = x ^ (x >> np.uint64(32))
+        x = x * np.uint64(0x9E3779B97F4A7C15)
+        x = x ^ (x >> np.uint64(29))
+        x = x * np.uint64(0x6A09E667F3BCC909)
+        return x ^ (x >> np.uint64(32))
+
+    with np.errstate(over="ignore"):
+        order = mix(mix(np.uint64(seed) + np.uint64(0xD1B54A32D192ED03) * np.uint64(t + 1)) ^ np.arange(N, dtype=np.uint64))
+    assert np.array_equal(np.argsort(order, kind="stable"), orc.random_permutation(seed, t, N))
+    n_keys, most, bits = M ** (d - 1), 64, 0
+    while most < N:
+        most *= 2
+    while n_keys << (bits + 1) <= most:
+        bits += 1
+    bucket = packed << bits
+    if bits > 0:
+        bucket = bucket + (order >> np.uint64(64 - bits)).astype(np.int64)
+    return int(np.bincount(bucket[np.asarray(alive) != 0], minlength=1).max())
+
+
+def crowded_from():
+    """Members of a bucket above which the kernel spreads them over slots."""
+    source = open(os.path.join(entry.CSRC, "small_order.hip")).read()
+    return int(re.search(r"constexpr int32_t kCrowded = (\d+);", source).group(1))
+
+
+# 16 x 16 x 16 and 4^6 spread 4096 peers of one key over 16 and 4 buckets, 2^12 over 2; 2^10 and 4^5 are launched with a peer to a thread
+@pytest.mark.parametrize("M,d", [(16, 3), (4, 6), (2, 12), (2, 10), (4, 5)])
+def test_crowded_buckets(M, d):
+    """Keys come together until a bucket holds so many peers that its members are spread over slots, with all, some and few
+    of them taking part; keys and the averages of every group as the oracle has them."""
+    N, P, seed, limit = M ** d, 4, 90 + M, crowded_from()
+    print(f"crowded M={M} d={d}", flush=True)
+    r = np.random.default_rng(M + d)
+    X = torch.rand(N, P, device=DEV) + 1.0
+    ref = X.cpu().double().numpy().copy()
+    keys = orc.dynamic_init(N, M, d)
+    weights = M ** np.arange(d - 1)
+    t = 0
+    with binding.Moshpit(N, P, M, d, binding.F32) as m:
+        m.bind_state(X)
+        for share in (1.0, 0.6, 0.9):
+            while True:
+                packed = keys.reshape(N, -1) @ weights
+                alive = (r.random(N) < share).astype(np.uint8)
+                if fullest_bucket(N, M, d, packed, seed, t, alive) > limit:
+                    break
+                # peers alone in their groups: each gets chunk 0 and keeps its row
+                alone = np.zeros(N, dtype=np.uint8)
+                some = r.permutation(np.flatnonzero(packed))
+                alone[some[np.unique(packed[some], return_index=True)[1]]] = 1
+                m.dynamic_round(t, seed, alone)
+                keys[alone != 0] = np.pad(keys[alone != 0][:, 1:], ((0, 0), (0, 1)))
+                t += 1
+                assert t < 2500
+            m.dynamic_round(t, seed, alive)
+            orc.dynamic_round(ref, M, d, keys, seed, t, alive)
+            assert np.array_equal(m.dynamic_keys(), keys.reshape(N, -1)), t
+            t += 1
+        m.sync()
+    print(f"  3 crowded rounds of {t}", flush=True)
+    # at most 7 additions in a row and a division in each of the crowded rounds, the others average nothing
+    assert_state_close(X.cpu().double().numpy(), ref, 3 * 8 * 2.0 ** -24, f"crowded {M}^{d}")
 
 
 @pytest.mark.parametrize("M,d,P", [(2, 3, 2_100_003), (3, 2, 2_800_000), (16, 2, 131_072)])
