@@ -293,10 +293,14 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
     // kLds: those of round r from the registers to LDS
     auto write_words = [&](int32_t r) {
         if constexpr (TAB == kLds) {
-            // (Where no distortion is wanted the quotients are left as they are: with shifts the two blocks of a compute unit fall
-            // into step, 32 x 32 x 4,194,304, 8 rounds, 8,870 us on every one of four states, 8,150 with the divisions)
-            const int32_t in = DIST ? r & (kRegisters * per_register - 1) : r % (kRegisters * per_register);
-            const int32_t q = DIST ? in >> per_shift : in / per_register;
+            // (Quotients where the binary32 tile of 32 x 32 has two parts: slower by the divisions, its two blocks a compute unit fall into step less
+            // often.  us, quotients : shifts, 8 rounds, 20 % absent: 4,194,304 elements 8,110 : 8,650, on one of six states
+            // 9,060 : 8,970, 4,190,208 7,630 : 8,300, 3,145,728 7,510 : 7,370, 2,097,152 4,010 : 3,910, 6 rounds 3,930 : 4,020; 16 rounds
+            // 12,750 : 12,280 and 6,800 : 6,580.  All other kernels, 60 MB to 17 GB, 8 and 16 rounds: shifts 0 to 9 % ahead on 34 shapes,
+            // 16 x 16 x 976,576, 16 rounds, 590 : 539; none behind.)
+            constexpr bool kQuotients = DT == 0 && SPLIT == 4 && HALF != 0 && !DIST;
+            const int32_t in = kQuotients ? r % (kRegisters * per_register) : r & (kRegisters * per_register - 1);
+            const int32_t q = kQuotients ? in / per_register : in >> per_shift;
             if (r > 0 && in == 0) fetch_words(r);
             if (tid >> words_shift == in - q * per_register) {
                 lds_put(base + p.words_at + (r & 1) * 4 * words + (tid & (words - 1)) * 4, static_cast<uint32_t>(entry_words[q]));
