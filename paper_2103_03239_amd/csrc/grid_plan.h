@@ -38,6 +38,7 @@ struct GridPlan {
     int32_t part;                    // bytes of a row in LDS
     int32_t means_at, means_bytes, zero_at, rcp_at, words_at;
     int32_t words_shift;             // log2 of N / 2: 32-bit words that a round's places take
+    int32_t sharers;                 // waves that share a distortion (with tables in LDS half of them, an even number)
     int32_t dist_barrier;            // a barrier behind every distortion (a refresh, or LDS has room for one round's terms only)
     int32_t mean_step[kGridMaxAxes];      // bytes between the means that the rows of a group were given by the round before
     // filled in by the caller
@@ -72,16 +73,21 @@ struct GridAsk {
 
 inline int64_t mean_place_stride(const GridPlan &p) { return static_cast<int64_t>(p.threads) * kPhaseSlots * p.phases; }
 
-// Waves of a block that share a distortion: half of them, the halves in turn, or all.
-#ifdef __HIPCC__
-__host__ __device__
-#endif
-inline int32_t dist_sharers(int32_t waves) { return waves % 2 == 0 ? waves / 2 : waves; }
-
-// The distortions' LDS: two rounds' sums of the sharing waves, a column each and one of squares, and the totals of a pass.
-inline int64_t dist_sums_bytes(int64_t waves, int64_t columns, int64_t rounds)
+// The distortions' LDS: the sums of the waves that share one (a half of the block's, the halves in turn; one of each where there is one
+// wave), a column each and one of squares, and the totals of a pass.
+inline int64_t dist_sums_bytes(int64_t waves, int64_t sharers, int64_t columns, int64_t rounds)
 {
-    return 2 * dist_sharers(static_cast<int32_t>(waves)) * (columns + 1) * 8 + (rounds + 1) * 8;
+    return (waves > 1 ? 2 : 1) * sharers * (columns + 1) * 8 + (rounds + 1) * 8;
+}
+
+// How many share it.  Of an odd number of waves one takes none (when all of them did, with two rounds' sums: 12 x 12 bfloat16 of 1 GB, 5
+// waves, had 2 blocks a compute unit, 30 rounds 4,830 us, and has 3, 3,150; 13 x 13 x 13 binary32 took two column parts instead of
+// one, 10 rounds 2,010 -> 1,130; 20 x 20 of 1 GB, 30 rounds 2,840 -> 2,200).  One less where that makes room for passes of 24 rounds (13 x 13 x 13
+// binary32, 3 of 9 waves, 24 rounds of 1 GB in one pass 2,010 us, in two with 4 waves 2,640).
+inline int32_t dist_sharers(int64_t waves, int64_t columns, int64_t room)
+{
+    const int32_t half = waves > 1 ? static_cast<int32_t>(waves / 2) : 1;
+    return half > 1 && dist_sums_bytes(waves, half, columns, 24) > room && dist_sums_bytes(waves, half - 1, columns, 24) <= room ? half - 1 : half;
 }
 
 // two rounds' places and moves, and the terms of one or two distortions
@@ -126,7 +132,7 @@ inline int64_t means_lds_bytes(const GridPlan &p, bool tables, int32_t rounds, b
     int64_t at = p.words_at + mean_words_bytes(p, tables, dist);
     *sums_at = static_cast<int32_t>(at);
     const int64_t waves = p.threads / 64;
-    if (dist) at += dist_sums_bytes(waves, p.part / esize, rounds);
+    if (dist) at += dist_sums_bytes(waves, p.sharers, p.part / esize, rounds);
     return at;
 }
 
@@ -259,11 +265,17 @@ inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
             q.dist_barrier = barrier ? 1 : 0;
             const int64_t bytes = lay_out_means(&q, part, ask.absent, ask.distortions);
             q.red_offset = static_cast<int32_t>(bytes);
-            return bytes + (ask.distortions ? dist_sums_bytes(waves, part / esize, 4) : 0) <= kLdsPerBlock;
+            q.sharers = ask.absent && part >= kLeastLdsPart ? static_cast<int32_t>(waves / 2) : dist_sharers(waves, part / esize, kLdsPerBlock - bytes);
+            return bytes + (ask.distortions ? dist_sums_bytes(waves, q.sharers, part / esize, 4) : 0) <= kLdsPerBlock;
         };
         const bool room = (!(ask.distortions && ask.refresh) && fits(false)) || fits(ask.distortions);
         if (ask.absent && (q.M != 8 * q.split || (phases == 2 && part == 32) || (ask.distortions && esize == 2 && part >= 64))) return false;
-        if (room) {
+        // (bfloat16 curves with nobody absent over groups of up to 8, beyond the last-level cache: in two parts 16 waves share a compute unit,
+        // in one 14 or 12.  us, one part : two: 6 x 6 x 6 of 300 MB, 2 rounds 198 : 196, of 1 GB, 10 rounds 1,450 : 1,372; 7 x 7 x 7 of 300 MB,
+        // 5 rounds 326 : 310, of 1 GB, 2 rounds 636 : 587, 30 rounds 4,050 : 3,540, but 1 round 544 : 683; of 150 MB, 5 rounds 183 : 184)
+        const bool halve = ask.distortions && !ask.absent && esize == 2 && q.M <= 8 && !cached && phases == 1 && ask.rounds >= 2 &&
+                           blocks_by_lds(q.red_offset + dist_sums_bytes(waves, q.sharers, part / esize, 4)) <= 2;
+        if (room && !halve) {
             q.means = 1;
             *p = q;
             return true;
@@ -335,7 +347,7 @@ inline bool fill_in(GridPlan *plan, const void *X, int64_t esize, const GridAsk 
     // rounds of one pass: as many bitmaps as fit next to the tile
     const int64_t waves = p.threads / 64, columns = part / esize;
     if (p.means) {
-        const int64_t most = ask.distortions ? (kLdsPerBlock - p.red_offset - dist_sums_bytes(waves, columns, -1)) / 8 - 1 : 64;
+        const int64_t most = ask.distortions ? (kLdsPerBlock - p.red_offset - dist_sums_bytes(waves, p.sharers, columns, -1)) / 8 - 1 : 64;
         p.max_rounds = static_cast<int32_t>(most < 64 ? most : 64);
         return p.max_rounds >= 4;
     }

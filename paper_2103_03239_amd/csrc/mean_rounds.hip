@@ -192,7 +192,7 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
 
     // waves that take a distortion (see there), and the thread's first term of one
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = T >> 6;
-    const int32_t sharers = dist_sharers(waves), halves = waves / sharers;
+    const int32_t sharers = TAB == kLds ? waves / 2 : p.sharers, halves = TAB == kLds || waves > 1 ? 2 : 1;
     [[maybe_unused]] const int32_t first_term = (tid - (wave >= sharers ? sharers * 64 : 0)) >> wv_shift;
 
     // Tables.  Loads in the rounds would wait for the tile that the compute unit's other block is loading (a compute
@@ -546,13 +546,13 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
 
     // Distortion of the part in LDS after round r of the pass (r = -1: before the first): sum over
     // its columns of s2 - s1^2 / N, s1 and s2 the sums of the differences from one peer's row and of their
-    // squares in binary64 (the differences are exact).  There are far fewer terms than threads, so where the block has an even
-    // number of waves its halves take the rounds in turn (sharers of them a round): thread (k, vector c) of the half takes every
+    // squares in binary64 (the differences are exact).  There are far fewer terms than threads, so the halves of a
+    // block take the rounds in turn (sharers of its waves a round): thread (k, vector c) of the half takes every
     // parts-th term.  What the waves of a half leave in LDS is put together by its first wave after the next round's barrier, when the
     // other half is busy with that round's.
     const int32_t columns = NE << wv_shift;
-    double *red = reinterpret_cast<double *>(lds + p.red_offset), *totals = red + 2 * sharers * (columns + 1);
-    [[maybe_unused]] auto sums_of = [&](int32_t r) -> double * { return red + ((r + 1) & 1) * sharers * (columns + 1); };
+    double *red = reinterpret_cast<double *>(lds + p.red_offset), *totals = red + halves * sharers * (columns + 1);
+    [[maybe_unused]] auto sums_of = [&](int32_t r) -> double * { return red + (halves == 2 ? (r + 1) & 1 : 0) * sharers * (columns + 1); };
     [[maybe_unused]] auto first_wave = [&](int32_t r) -> int32_t { return halves == 2 ? ((r + 1) & 1) * sharers : 0; };
     [[maybe_unused]] auto distortion = [&](int i, int32_t seg, int32_t r) {
         if constexpr (DIST) {

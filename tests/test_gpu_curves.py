@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (6, 2, 1_546), (7, 2, 1_028),                                    # rows of 128 words, 64 threads idle or a part more
     (3, 4, 772), (9, 2, 520), (2, 7, 1_000),                         # rows of 64 words, 3 and 4 parts
     (5, 4, 260), (3, 6, 140), (6, 3, 524), (15, 2, 390),             # shorter rows; odd numbers of waves
+    (13, 3, 108), (23, 2, 1_030),                                    # 9 waves of which 3 share a distortion, 5 of which 2 do
 ])
 def test_against_binary64(M, d, bytes_, dtype, p):
     N, rounds, t0, seed = M ** d, 2 * d + 5, 1, 11 * M + d
