@@ -9,6 +9,7 @@ struct DistTiles {
     int32_t lanes, waves;        // 16-byte vectors of a row in a tile; waves of a block, which share its rows
     int64_t blocks;
     bool streaming;              // non-temporal loads
+    bool last_first;             // rows are taken from the last to the first
 };
 
 // Tiles for N rows of P elements; whole_lines: rows start on cache lines.  false: rows of less than a vector, or too many of
@@ -30,17 +31,25 @@ struct DistTiles {
 //   Never more than 65,536 tiles where they can be wider (their sums take one block 10 us).
 //   Non-temporal loads beyond 64 MB (4096 rows, 1.6 GB 231 : 250; 1024 rows, 25 MB 9.4 : 8.2), but where neighbours share cache lines
 //   only in 1 KiB tiles of 32 rows and more (1024 rows, 1.6 GB, 32 lanes 281 : 262, 64 lanes 248 : 258; 144 rows 256 : 269; 9 rows, 100 MB
-//   22.5 : 20.8), which such states take as soon as there are enough.
+//   22.5 : 20.8), which such states take as soon as there are enough.  From 350 MB on the last-level cache no longer helps rows off
+//   the lines either: 64 lanes and non-temporal loads, of 1024 rows (bfloat16 512) and more 32 lanes where there are 500 such tiles (the pass that
+//   follows the write : the next one, ordinary loads of 32 lanes against that: 256 rows, 450 MB bfloat16 96 : 84, 78 : 77, 370 MB 79 : 70, 65 : 64;
+//   2048 rows, 540 MB binary32 133 : 104, 116 : 102, in 64 lanes 126 : 116).
+//   Rows from the first to the last, but the other way round from 270 to 700 MB, of whose last rows the last-level cache holds many, and binary32 of
+//   700 rows, bfloat16 of 2048 rows and more (the pass that follows the write, first to last : last to first; 256 rows, 1 GB 189 : 194, 64 to
+//   576 rows of 0.7 to 4 GB 1 to 3 % on average; 576 rows, 360 MB binary32 63 : 59, 256 rows, 370 MB bfloat16 off the lines 79 : 75; 2048 rows
+//   of binary32 2 to 3 %, 4096 rows of 2.1 GB bfloat16 371 : 359, but 4 GB 657 : 683; the next pass within 1 % either way).
 inline bool dist_tiles(int64_t esize, int64_t N, int64_t P, bool whole_lines, DistTiles *out)
 {
     const int64_t row = P * esize;
     if (row < 16 || N > (int64_t(1) << 30)) return false;
     const int64_t vectors = (row + 15) / 16;
     const double state = static_cast<double>(N) * static_cast<double>(row);
-    const bool f32 = esize == 4, few = N < 32, large = !few && state > 5.5e8;
+    const bool f32 = esize == 4, few = N < 32, large = !few && state > 5.5e8, odd_lines = !few && !whole_lines && state > 3.5e8;
     int32_t lanes = few ? (f32 || N <= 12 ? 64 : 32) : f32 && N < 1024 ? 64 : 32;
     if (large || (!whole_lines && !few && f32 && vectors >= 65536)) lanes = 64;
     if (large && !f32 && whole_lines && vectors > 64 * 550 && vectors <= 64 * 1000) lanes = 32;
+    if (odd_lines && !large) lanes = N >= (f32 ? 1024 : 512) && vectors >= 500 * 32 ? 32 : 64;
     const bool one_wave = !f32 && !few && N <= 256 && state < 40e6;
     if (one_wave) lanes = N <= 64 ? 32 : N <= 160 ? 16 : 8;
     const int64_t least = large ? 130 : f32 || N >= 512 ? 160 : 512;
@@ -54,7 +63,8 @@ inline bool dist_tiles(int64_t esize, int64_t N, int64_t P, bool whole_lines, Di
     out->lanes = lanes;
     out->waves = waves;
     out->blocks = blocks;
-    out->streaming = state > 64e6 && (whole_lines || (lanes == 64 && !few));
+    out->streaming = state > 64e6 && (whole_lines || (lanes == 64 && !few) || odd_lines);
+    out->last_first = N >= (f32 ? 700 : 2048) || (state > 2.7e8 && state < 7e8);
     return true;
 }
 

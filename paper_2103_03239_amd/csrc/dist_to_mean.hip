@@ -179,7 +179,7 @@ constexpr int rows_lds_bytes(int lanes, int waves) { return waves == 1 ? 0 : (4 
 
 template <int DT, int LANES, bool NT>
 __global__ __launch_bounds__(8 * 64, 4) void dist_rows_kernel(const char *__restrict__ X, int64_t row_bytes, int64_t valid_bytes,
-                                                           int32_t N, double *__restrict__ partials)
+                                                           int32_t N, bool last_first, double *__restrict__ partials)
 {
     typedef Wide<DT, DT == 0 ? 4 : 8> V;
     typedef typename V::mem_t mem_t;
@@ -214,18 +214,17 @@ __global__ __launch_bounds__(8 * 64, 4) void dist_rows_kernel(const char *__rest
         }
         if constexpr (NE == 8) __builtin_amdgcn_sched_barrier(0);       // (two rows' doubles at once spill)
     };
-    // From the last row to the first: rounds and whoever fills a state end with the last rows, which the last-level cache
-    // then holds (4096 rows of a state just written, 2.1 GB bfloat16, 402 -> 380 us, 1024 rows of 4.3 GB binary32 794 -> 775).
-    const int32_t step = waves * kRows;
-    const int64_t step_bytes = step * row_bytes;
-    const char *from = col + (N - 1 - (wave * kRows + sub)) * row_bytes;
-    int32_t i = wave * kRows;                               // rows before the wave's next load
+    // From the last row to the first (see dist_tiles.h) or from the first to the last: row 0 is the one that is subtracted either way.
+    const int32_t step = waves * kRows, start = wave * kRows + sub;
+    const int64_t step_bytes = last_first ? -(step * row_bytes) : step * row_bytes;
+    const char *from = col + (last_first ? N - 1 - start : start) * row_bytes;
+    int32_t i = wave * kRows;                               // rows taken before the wave's next load
     for (; i + (kRowLoads - 1) * step + kRows <= N; i += kRowLoads * step) {
         mem_t buf[kRowLoads];
 #pragma unroll
         for (int u = 0; u < kRowLoads; ++u) {
             buf[u] = load_vec<NT, mem_t>(from);
-            from -= step_bytes;
+            from += step_bytes;
         }
         // All loads leave before the first row is added: the compiler's own order keeps fewer in flight (256 rows of 2.6 GB
         // bfloat16, tiles of 64 lanes and 8 waves, 416 -> 373 us; 4096 rows of 2.9 GB 483 -> 425).
@@ -234,12 +233,12 @@ __global__ __launch_bounds__(8 * 64, 4) void dist_rows_kernel(const char *__rest
         for (int u = 0; u < kRowLoads; ++u) add(buf[u]);
     }
     if (i < N) {
-        // (row 0, whose difference is 0, in the place of rows before the first)
+        // (row 0, whose difference is 0, in the place of rows that there are not)
         mem_t buf[kRowLoads];
 #pragma unroll
         for (int u = 0; u < kRowLoads; ++u) {
             buf[u] = load_vec<NT, mem_t>(i + u * step + sub < N ? from : col);
-            from -= step_bytes;
+            from += step_bytes;
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -312,7 +311,7 @@ hipError_t launch_rows(const char *X, int64_t row_bytes, int64_t valid_bytes, in
 {
     const auto kernel = t.streaming ? dist_rows_kernel<DT, LANES, true> : dist_rows_kernel<DT, LANES, false>;
     kernel<<<dim3(static_cast<uint32_t>(t.blocks)), dim3(t.waves * 64), rows_lds_bytes(LANES, t.waves), stream>>>(
-        X, row_bytes, valid_bytes, static_cast<int32_t>(N), partials);
+        X, row_bytes, valid_bytes, static_cast<int32_t>(N), t.last_first, partials);
     return hipGetLastError();
 }
 template <int DT>

@@ -21,6 +21,8 @@ DEV = "cuda:0"
     (300, 900_003, 0, 0), (700, 720_005, 1, 1), (300, 900_032, 0, 0),    # beyond 1 GB
     (2_900, 320_001, 1, 1), (700, 412_000, 1, 0), (700, 394_240, 1, 0),  # more than half a GB: 2 waves of 64 lanes or 1 of 32
     (90, 2_900_001, 0, 1), (40, 7_100_001, 1, 0), (4_096, 33_281, 0, 0),
+    (300, 335_001, 0, 1), (699, 290_001, 1, 1), (1_024, 97_900, 0, 1), (2_048, 49_003, 0, 1),    # off the lines beyond 350 MB: 64 and 32 lanes
+    (699, 20_003, 0, 0), (700, 20_003, 0, 0),                            # from the first row to the last and the other way
     (3, 8_300_003, 0, 1),                                                # tiles widened so that there are not too many
 ])
 def test_against_binary64(N, P, dtype, odd):
