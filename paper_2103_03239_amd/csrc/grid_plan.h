@@ -3,6 +3,7 @@
 // plain numbers, without GPU types.
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 
 namespace moshpit {
@@ -30,7 +31,7 @@ struct GridPlan {
     int32_t S[kGridMaxAxes], pad_step[kGridMaxAxes];
     uint32_t magic_s[kGridMaxAxes];
     int64_t row_bytes, valid_bytes, tiles;
-    double inv_n;                    // 1 / N
+    double peers, inv_n;             // N, 1 / N
     // means != 0: the kernel of mean_rounds.hip, and where its LDS holds what
     int32_t means;
     int32_t split;                   // lanes that share a group
@@ -72,6 +73,18 @@ struct GridAsk {
 // ---- LDS of the kernel that keeps one mean per group ---------------------------------------------
 
 inline int64_t mean_place_stride(const GridPlan &p) { return static_cast<int64_t>(p.threads) * kPhaseSlots * p.phases; }
+
+// a / n, rounded once, for a whole n and inv = 1 / n: two multiply-adds after the product instead of a division (Markstein,
+// "Computation of elementary functions on the IBM RISC System/6000 processor", 1990: a quotient within an ulp and a rounded
+// reciprocal give the rounded quotient).
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline double over(double a, double n, double inv)
+{
+    const double q = a * inv;
+    return fma(fma(-q, n, a), inv, q);
+}
 
 // The distortions' LDS: the sums of the waves that share one (a half of the block's, the halves in turn; one of each where there is one
 // wave), a column each and one of squares, and the totals of a pass.
@@ -443,7 +456,8 @@ inline bool plan_grid(int dtype, int64_t N, int32_t M, int32_t d, int64_t P, int
     p.M = M;
     p.d = d;
     p.groups = static_cast<int32_t>(N / M);
-    p.inv_n = 1.0 / static_cast<double>(N);
+    p.peers = static_cast<double>(N);
+    p.inv_n = 1.0 / p.peers;
     p.full_bitmap = M == 32 ? ~0u : (1u << M) - 1u;
     p.axis0 = static_cast<int32_t>(t0 % d);
     // Widest tile: rows of 512 bytes beat 1 KiB on 64 rows (2.55 against 2.73 ms), 256 bytes beat

@@ -238,9 +238,11 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
 #pragma unroll
                         for (int e = 0; e < kIn; ++e) {
                             if ((q & ~3) * 4 >= seg || (q & 3) * 4 + e * kEs < early) s1[e] = sq[e] = 0.0;
-                            v += parts == 1 ? sq[e] - s1[e] * s1[e] * p.inv_n : sq[e];
                             if (parts > 1) red[part * columns + q * kIn + e] = s1[e];
                         }
+                        const double s2 = kIn == 1 ? sq[0] : sq[0] + sq[kIn - 1];
+                        const double t2 = kIn == 1 ? s1[0] * s1[0] : fma(s1[0], s1[0], s1[kIn - 1] * s1[kIn - 1]);
+                        v += parts == 1 ? s2 - over(t2, p.peers, p.inv_n) : s2;
                     }
                 v = wave_sum(v);
                 if (lane == 0) squares[wave] = v;
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(PHASES == 1 ? 1024 : 512, 4) void grid_rounds_kerne
             }
             lds_barrier();
             if (wave == entry % waves) {
-                const double sum = finish_columns(red, parts, columns, squares, waves, p.inv_n);
+                const double sum = finish_columns(red, parts, columns, squares, waves, p.peers, p.inv_n);
                 if (lane == 0) p.partials[out_at] = sum;
             }
         }

@@ -642,7 +642,7 @@ __global__ __launch_bounds__(HALF == 0 ? 1024 : 512, 4) void mean_rounds_kernel(
     [[maybe_unused]] auto finish = [&](int32_t r) {
         if constexpr (DIST) {
             if (wave != first_wave(r) || !(r < 0 ? p.dist_before != 0 : ((p.dist_after >> r) & 1u) != 0)) return;
-            const double sum = finish_columns(sums_of(r), sharers, columns, sums_of(r) + sharers * columns, sharers, p.inv_n);
+            const double sum = finish_columns(sums_of(r), sharers, columns, sums_of(r) + sharers * columns, sharers, p.peers, p.inv_n);
             if (lane == 0) totals[r + 1] = sum;
         }
     };

@@ -119,19 +119,19 @@ template <int NE> __device__ __forceinline__ void column_sums(const double (&s1)
 #pragma unroll
         for (int e = 0; e < NE / 4; ++e) mine[e] = quarter[e];
 }
-// One wave: the sum over the columns, from what `parts` parts of the rows left in cols and `waves` waves in squares; inv = 1 / N.
+// One wave: the sum over the columns, from what `parts` parts of the rows left in cols and `waves` waves in squares; inv = 1 / n.
 // (columns outside the tile hold 0)
-__device__ __forceinline__ double finish_columns(const double *cols, int32_t parts, int32_t columns, const double *squares, int32_t waves, double inv)
+__device__ __forceinline__ double finish_columns(const double *cols, int32_t parts, int32_t columns, const double *squares, int32_t waves, double n, double inv)
 {
     const int32_t lane = threadIdx.x & 63;
-    double sum = lane < waves ? squares[lane] : 0.0;
+    double sum = lane < waves ? squares[lane] : 0.0, t2 = 0.0;
     for (int32_t q = lane; q < columns; q += 64) {
         double t1 = 0.0;
 #pragma unroll 4
         for (int32_t k = 0; k < parts; ++k) t1 += cols[k * columns + q];
-        sum -= t1 * t1 * inv;
+        t2 = fma(t1, t1, t2);
     }
-    return wave_sum(sum);
+    return wave_sum(sum - over(t2, n, inv));            // (one quotient a lane)
 }
 
 // CV consecutive columns of one row in LDS, widened to binary32.

@@ -429,3 +429,45 @@ int main()
 def test_runs_of_tiles_per_die(tmp_path):
     got = run_host(tmp_path, RUNS)
     assert got.returncode == 0, got.stdout
+
+
+QUOTIENTS = r"""
+#include <cstdio>
+#include <cstring>
+#include "grid_plan.h"
+using namespace moshpit;
+
+int main()
+{
+    long bad = 0, plain = 0;
+    uint64_t x = 0x1234567;
+    const auto draw = [&] { x ^= x << 13; x ^= x >> 7; x ^= x << 17; return x; };
+    for (int64_t n = 1; n <= kGridMaxPeers; ++n) {
+        const double inv = 1.0 / static_cast<double>(n);
+        const auto check = [&](double a) {
+            const double want = a / static_cast<double>(n), got = over(a, static_cast<double>(n), inv);
+            if (std::memcmp(&want, &got, 8) != 0 && ++bad < 20) std::printf("%a / %lld: %a, not %a\n", a, (long long)n, got, want);
+            plain += a * inv != want;
+        };
+        // squares of sums of differences of binary32 numbers, and the neighbours of products with n (quotients near a tie)
+        for (int k = 0; k < 3000; ++k) {
+            const uint64_t bits = ((1023 - 300 + draw() % 560) << 52) | (draw() >> 12);
+            double a;
+            std::memcpy(&a, &bits, 8);
+            check(a);
+            check(a * a);
+            check(nextafter(a * static_cast<double>(n), 0.0));
+            check(nextafter(a * static_cast<double>(n), HUGE_VAL));
+        }
+        check(0.0);
+    }
+    std::printf("%ld wrong; %ld products with the reciprocal are\n", bad, plain);
+    return bad != 0 || plain == 0;
+}
+"""
+
+
+def test_distortions_divide_by_the_peers(tmp_path):
+    """What a pass subtracts from the squares is the rounded quotient by N, as everywhere else, not a product with 1 / N."""
+    out = run_host(tmp_path, QUOTIENTS)
+    assert out.returncode == 0, out.stdout
