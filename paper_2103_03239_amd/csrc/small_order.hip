@@ -27,8 +27,10 @@ namespace {
 
 constexpr int kThreads = 1024;       // at most
 static_assert(kThreads == kFewPeers, "a peer to a thread: the short argument block");
-// (38 us a round with 2048 of 64 x 64 peers in one bucket, 36 with 64 to a bucket)
-constexpr int32_t kCrowded = 64;
+// Spreading costs 4096 peers 1.1 us a launch, 1024 0.8, counting 0.19 and 0.06 for every peer of the fullest bucket.  us, counted : spread: 4096
+// peers, fullest bucket 8 10.4 : 11.5, 13 12.0 : 11.6, 24 13.9 : 11.8, 64 (64 x 64 peers with one key) 26 : 12, 256 64 : 12; 1024 peers 4 6.7 :
+// 7.5, 20 7.4 : 7.5, 40 8.4 : 7.5, 500 31 : 8.  Where everybody takes part and keys are apart the fullest holds 8.
+constexpr int32_t kCrowded = 16;
 
 // Up to MAX peers, in up to MAX buckets.
 template <int MAX> struct Shared {

@@ -135,11 +135,11 @@ def test_crowded_buckets(M, d):
     t = 0
     with binding.Moshpit(N, P, M, d, binding.F32) as m:
         m.bind_state(X)
-        for share in (1.0, 0.6, 0.9):
+        for share, more_than in ((1.0, limit), (0.6, limit), (0.9, max(limit, 100))):
             while True:
                 packed = keys.reshape(N, -1) @ weights
                 alive = (r.random(N) < share).astype(np.uint8)
-                if fullest_bucket(N, M, d, packed, seed, t, alive) > limit:
+                if fullest_bucket(N, M, d, packed, seed, t, alive) > more_than:
                     break
                 # peers alone in their groups: each gets chunk 0 and keeps its row
                 alone = np.zeros(N, dtype=np.uint8)
