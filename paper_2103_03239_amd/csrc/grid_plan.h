@@ -247,13 +247,14 @@ inline int64_t blocks_by_lds(int64_t bytes) { return 128 / ((bytes + 1279) / 128
 //   nobody ever absent: ahead from 4 rounds on (16 x 16, 200 MB binary32, 6 rounds 70 : 80; 24 x 24, 1.5 GB bfloat16
 //     887 : 1,234; 32 x 32, 16 GB, 16 rounds 10,450 : 14,200), behind by up to 11 % for 2 or 3 (8 x 8 x 8, 1.5 GB
 //     bfloat16 715 : 643), by 3 to 9 % for 4 of 32 x 32 in binary32 (250 MB 108 : 99) and for small states of 8 x 8 peers in bfloat16 (8 MB, 8 rounds 12.8 : 12.5);
-//     with distortions ahead everywhere (16 x 16, 1 GB binary32, 5 rounds 602 : 860).  Groups of 2 to 4 save little.
+//     with distortions ahead from the first round in one part (8 x 8 x 8, 1 GB binary32, 5 rounds 660 : 838; two parts: see copies_ahead).  Groups of 2 to 4 save little.
 //   with failures, whose tables cost a launch and a wait: ahead from 5 rounds (4 on more than 1024 peers) of
 //     states beyond 32 MB on (32 x 32, 16 GB, 8 rounds 8,110 : 9,320, 4 rounds of 200 MB 85 : 83; 16 x 16 x 16, 1.5 GB
 //     bfloat16, 4 rounds 911 : 1,222, 16 rounds 1,570 : 2,640; 8 MB, 8 rounds 31 : 28; not taken although ahead: longer runs
 //     of small states, 8 MB, 16 rounds 38 : 54), and not for 8 x 8 peers, whose passes
 //     wait for memory (1.5 GB binary32, 8 rounds 652 : 631).  Places are 8 to a lane: groups of 8, 16 or 32.  The
-//     distortion of bfloat16 rows of 64 bytes and more spills (16 x 16, 1 GB, 5 rounds 1,616 : 1,341).
+//     distortion of bfloat16 rows of 64 bytes and more spills and is not built next to tables (time of M copies over it, 33 to 240 MB, 5 to 40
+//     rounds: 256 peers with 5 % absent 1.27 to 1.55, 20 % 1.07 to 1.35, 50 % 0.99; 1,024 with 20 % 1.5 to 1.7, 80 % 0.98; 512 of 0.5 to 2 GB 20 % 0.76 to 0.90).
 // A local step would take its registers: not with one.  Where both have a plan copies_ahead looks closer.
 inline bool choose_means(GridPlan *p, int64_t esize, const GridAsk &ask)
 {
@@ -392,12 +393,19 @@ inline bool copies_ahead(const GridPlan &copies, const GridPlan &means, int64_t 
     // absent peer.  Time with one mean per group over that with M copies, 60 to 1,500 MB:
     const bool short_of_time = rounds >= 8 || state < 100000000;
     const double moves = ask.averaged * (1.0 - ask.averaged);
-    if (ask.absent && copies.N <= 1024) {
-        if (ask.distortions) {
-            // (12 rounds, 1,024 peers: 70 % absent 0.98 to 1.05, 80 % 1.06 to 1.12; 256: 70 % 1.02 to 1.11, 50 % 0.95 to 0.96, of
-            // 60 MB 1.07; 512, 60 MB: 30 % 0.98, 50 % 1.11, 90 % 1.34)
-            if (ask.averaged < (M <= 8 ? 0.6 : M > 16 ? (state < 1000000000 ? 0.35 : 0.25) : state < 100000000 ? 0.55 : 0.4)) return true;
-        } else if (ask.refresh) {
+    if (ask.absent && ask.distortions) {
+        // (curves of 5 to 40 rounds.  256 peers, 33 to 130 MB: 30 % absent 0.93 to 1.03, 40 % 1.07, 50 % 1.09 to 1.16, from 190 MB on 60 % 0.93, 70 %
+        // 0.97 to 0.99, 80 % 1.02, 90 % 1.10 to 1.12; 512: 30 % 0.93 to 0.95, 40 % 1.05 to 1.08, 90 % 1.3 to 2; 1,024 within 256 MiB: 40 % 0.92
+        // to 0.97, 50 % 0.97 to 1.04, 60 % 1.04 to 1.11, beyond: 5 % 0.77, 20 % 1.04 to 1.08, 40 % 1.11 to 1.17, 50 % 1.19 to 1.23, 40 rounds 5 % 0.77, 50 % 1.05; 4,096: 40 % 0.68 to
+        // 0.99, 60 % 1.02 to 1.11 up to 12 rounds, 24 rounds 0.85, 70 % 1.05 to 1.18, 40 rounds 0.98, 95 % 1.05 to 1.28, bfloat16 80 % 0.90 to
+        // 1.06, 90 % 1.00 to 1.15, 95 % 1.03 to 1.10)
+        const bool cached = state <= 268435456;
+        const double least = M <= 8 ? 0.6 : M > 16 ? (ask.refresh ? 0.35 : cached ? 0.45 : rounds < 40 ? 0.81 : 0.5)
+                             : copies.N <= 1024 ? (state < 130000000 ? 0.65 : 0.25)
+                             : f32 ? (rounds < 24 ? 0.45 : 0.15) : rounds < 24 ? 0.15 : 0.0;
+        if (ask.averaged < least) return true;
+    } else if (ask.absent && copies.N <= 1024) {
+        if (ask.refresh) {
             // (512 peers, 12 rounds: 6 % of the groups live 0.92 to 1.07, 2 % 1.02 to 1.18, 6 rounds of 300 MB and more 0.86 to 0.98)
             if (M <= 8 && ask.live < 0.03 && short_of_time) return true;
         } else {
@@ -417,12 +425,12 @@ inline bool copies_ahead(const GridPlan &copies, const GridPlan &means, int64_t 
     }
     // The means cost a second column part that M copies do without.  8 x 8 x 8 peers of 1 GB: 5 rounds 440 : 421, 8 rounds 425 :
     // 502; with failures 5 rounds 457 : 433, 8 rounds 446 : 515 (and refresh: 5 rounds 458 : 554); with failures and curve, where few
-    // registers are left, 5 rounds 1,311 : 985, 40 rounds 5,560 : 5,470, 64 rounds 8,410 : 8,760.  Curves with nobody absent: 13 x 13 x 13
-    // of 1 GB 5 rounds 1,494 : 1,420, 3 GB, 8 rounds 5,690 : 6,070; 24 x 24 of 1 GB 5 rounds 1,290 : 1,180, 12 rounds 2,307 : 2,320.
+    // registers are left, 5 rounds 1,204 : 867, of 3 GB 20 rounds 8,220 : 7,080, 64 rounds 20,270 : 21,460.  Curves with nobody absent: 24 x 24 of 0.3 to 3 GB
+    // 1 round 0.81 to 0.83 times as fast, 2 rounds 0.88, 3 rounds 0.96, 5 rounds 1.04 to 1.07, 12 rounds 4,990 : 6,030.
     // (In bfloat16 M copies take longer: 8 x 8 x 8, 5 rounds with failures 460 : 542.)
     if (f32 && copies.phases == 1 && means.phases == 2) {
         if (ask.distortions) {
-            if (rounds < (ask.absent ? 40 : M > 16 ? 10 : M > 8 ? 8 : 0)) return true;
+            if (rounds < (ask.absent ? 40 : M > 16 ? 4 : 0)) return true;
         } else if (M <= 8 && !ask.refresh && rounds < 6) {
             return true;
         }
@@ -432,10 +440,10 @@ inline bool copies_ahead(const GridPlan &copies, const GridPlan &means, int64_t 
     // rounds 22.4 : 19.1, 64 rounds 138 : 127, bfloat16 27.9 : 25.2 (20 MB, one turn of each: 13.7 : 15.8); 8 x 8, 4 rounds 18.6 :
     // 15.9, 10 rounds 24.4 : 22.9, 32 rounds 49.0 : 48.8; 8 x 8 x 8, 4 rounds 18.3 : 15.7, 10 rounds 25.1 : 24.3, 16 rounds 32.0 : 32.7; 24 x 24 of 30 MB, 4 rounds 22.8 : 20.7, 16
     // rounds 45.0 : 43.5; with failures 8 x 8 x 8 of 33 MB, 5 rounds 40.9 : 38.4, 20 rounds 50.3 : 48.8.  Other groups of 9 to 16, other bfloat16 rows and distortions are worth more than a turn (9 x 9 of 33 MB, 4 rounds
-    // 20.2 : 24.2; 8 x 8 x 8 bfloat16, 4 rounds 23.2 : 25.2; curve of 8 x 8 x 8, 1 round 44.5 : 40.5, 2 rounds 47.9 : 45.9, 5 rounds
-    // 57.7 : 60.6).
+    // 20.2 : 24.2; 8 x 8 x 8 bfloat16, 4 rounds 23.2 : 25.2; curve of 8 x 8 x 8, 1 round 43.7 : 40.1, 2 rounds 0.96 times as fast, 5 rounds
+    // 53.8 : 56.5).
     const int32_t most = ask.absent ? (f32 && M <= 8 && !ask.refresh && !ask.distortions ? 20 : 0)
-                         : ask.distortions ? (f32 && M <= 8 ? 1 : 0) : M == 7 ? 64 : !f32 ? 0 : M > 16 ? 64 : M > 8 ? 0 : copies.N <= 64 ? 10 : 6;
+                         : ask.distortions ? (f32 && M <= 8 ? 2 : 0) : M == 7 ? 64 : !f32 ? 0 : M > 16 ? 64 : M > 8 ? 0 : copies.N <= 64 ? 10 : 6;
     if (rounds > most) return false;
     int32_t at = 0;
     const auto pass = [&](const GridPlan &p) { return rounds < p.max_rounds ? rounds : p.max_rounds; };

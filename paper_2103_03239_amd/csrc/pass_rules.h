@@ -179,13 +179,17 @@ inline double fused_pass_us(const RunSize &z, const Participation &w, int32_t ro
 // slower than the better way.
 // Passes with one mean per group are taken unless rounds are priced below them: over 801 runs under failures the way taken is
 // more than 5 % slower than the better one in 3.0 % and more than 15 % in 1.6 % then, 5.9 and 3.8 % at four fifths.
+// So are passes with distortions: over 2,191 curves on 18 grids (0.3 MB to 5 GB, 1 to 40 rounds, 0 to 95 % absent) rounds are taken though a pass is more
+// than 5 % faster in 0.9 %, a pass though rounds are in 0.4 % (0.3 and 1.5 % at four fifths; with the prices of the distortions before they
+// got cheaper 4.9 and 0.6 %).
 constexpr double kRoundsAhead = 0.8, kRoundsAheadOfMeans = 1.0;
 
 // A distortion on its own: two launches and the chain over the rows that a wave walks, or one read of the state where that takes
-// longer.  1,024 binary32 rows of 1.6, 25, 100 and 1,600 MB take 7.5, 8.2, 20 and 235 us, 4,096 bfloat16 rows 17, 19, 22 and 236.
+// longer.  1,024 binary32 rows of 1.6, 25, 100 and 1,600 MB take 7.5, 8.2, 20 and 235 us, 4,096 bfloat16 rows 17, 19, 22 and 236; between
+// rounds, whose launches it is queued among, 4 more of a small state.
 inline double distortion_us(const RunSize &z)
 {
-    const double chain = 6.5 + static_cast<double>(z.N) * (z.element_bytes == 2 ? 0.0027 : 0.0015), read = 4.0 + 0.165 * z.megabytes();
+    const double chain = 11.0 + static_cast<double>(z.N) * (z.element_bytes == 2 ? 0.0027 : 0.0015), read = 8.0 + 0.15 * z.megabytes();
     return chain > read ? chain : read;
 }
 
@@ -200,6 +204,7 @@ struct GridTiles {
     int32_t row_bytes = 0, parts = 1, threads = 0, lds_bytes = 0, max_rounds = 1;
     int64_t tiles = 0;
     bool means = false;                  // the kernel that keeps one mean per group; else M copies of it
+    bool curve = false;                  // distortions are wanted
 };
 inline GridTiles grid_tiles(const GridPlan &p, const GridAsk &ask, int64_t esize)
 {
@@ -210,6 +215,7 @@ inline GridTiles grid_tiles(const GridPlan &p, const GridAsk &ask, int64_t esize
     t.max_rounds = p.max_rounds;
     t.tiles = p.tiles;
     t.means = p.means != 0;
+    t.curve = ask.distortions;
     int32_t sums_at = 0;
     t.lds_bytes = p.tile_bytes + p.N;
     if (t.means) t.lds_bytes = static_cast<int32_t>(means_lds_bytes(p, ask.absent, ask.rounds < p.max_rounds ? ask.rounds : p.max_rounds, ask.distortions, esize, &sums_at));
@@ -217,7 +223,7 @@ inline GridTiles grid_tiles(const GridPlan &p, const GridAsk &ask, int64_t esize
 }
 inline bool rounds_ahead(double by_rounds, double by_passes, const GridTiles &t)
 {
-    return by_rounds < (t.means ? kRoundsAheadOfMeans : kRoundsAhead) * by_passes;
+    return by_rounds < (t.means || t.curve ? kRoundsAheadOfMeans : kRoundsAhead) * by_passes;
 }
 inline double grid_passes_us(const RunSize &z, const Participation &w, const GridTiles &t, int32_t rounds, int32_t distortions)
 {
@@ -239,7 +245,6 @@ inline double grid_passes_us(const RunSize &z, const Participation &w, const Gri
     const bool tables = t.means && w.failures;
     const double share = !t.means ? 0.63 + 0.37 * w.groups : tables ? (f32 ? kSome32 : kSome16)[kind] + kLive[kind] * w.groups : kEverybody[kind];
     const double fixed = tables ? 11.3 + 32.0 * static_cast<double>(z.N) / 4096.0 : 4.2 + 8.2 * static_cast<double>(z.N) / 4096.0;
-    const double distortion_share = !t.means ? 1.0 : tables ? (f32 ? 0.83 : 0.57) : (f32 ? 0.7 : 0.56);
     const double round_us = (turns > 1.0 ? turns : 1.0) * per_thread * item_us * share * t.parts;
     const bool narrow = t.row_bytes <= 64;
     const double read = t.row_bytes <= 32 ? 0.47 : narrow ? 0.36 : t.row_bytes <= 128 ? 0.25 : 0.17;
@@ -251,7 +256,13 @@ inline double grid_passes_us(const RunSize &z, const Participation &w, const Gri
         const int32_t n = left < t.max_rounds ? left : t.max_rounds;
         us += fixed + memory * (read + (w.failures ? masked * w.ever(n) : whole)) + n * round_us;
     }
-    return us + distortions * (6.3 + z.megabytes() * (t.parts == 1 ? 0.065 : 0.14) * (f32 ? 1.0 : 2.3) * distortion_share);
+    // A distortion, fitted to 2,200 curves: a barrier or two, and the terms of a tile: every row, every group, or groups and absent rows.
+    const double away = 1.0 - w.averaged;
+    const double latency = !t.means ? (f32 ? 2.0 : 2.3) : tables ? 1.5 : 1.0;
+    const double terms = !t.means ? (f32 ? 0.06 : t.row_bytes >= 256 ? 0.107 : 0.135)
+                         : tables ? (t.parts == 1 ? 0.006 + 0.115 * away : f32 ? 0.043 + 0.113 * away : 0.051 + 0.149 * away)
+                                  : (f32 ? 0.028 : 0.0465) * (t.parts == 1 ? 1.0 : 1.4);
+    return us + distortions * (latency + z.megabytes() * terms);
 }
 
 }  // namespace moshpit

@@ -259,27 +259,33 @@ MEASURED = [
     (8, 2, 0, 33, 4, 0, 0, 0, 0, 16.4, 19.1), (8, 2, 0, 33, 64, 0, 0, 0, 0, 120.6, 85.4), (8, 2, 0, 40, 6, 0, 0, 0, 0, 23.6, 22.0),
     (24, 2, 0, 30, 10, 0, 0, 0, 0, 32.1, 33.9), (24, 2, 0, 30, 32, 0, 0, 0, 0, 94.9, 75.9), (5, 3, 0, 36, 4, 0, 0, 0, 0, 20.2, 21.8),
     (5, 3, 0, 28, 4, 0, 0, 0, 0, 18.5, 15.0), (8, 3, 0, 28, 6, 0, 0, 0, 0, 18.6, 20.9), (9, 2, 0, 33, 4, 0, 0, 0, 0, 24.2, 20.2),
-    (8, 3, 0, 28, 1, 0, 0, 1, 0, 40.5, 44.5), (8, 3, 0, 28, 5, 0, 0, 1, 0, 60.6, 57.7), (8, 3, 1, 28, 4, 0, 0, 0, 0, 25.2, 23.2),
-    (24, 2, 1, 33, 8, 0, 0, 0, 0, 39.7, 36.5), (9, 2, 1, 30, 2, 0, 0, 1, 0, 74.1, 62.0), (8, 3, 1, 32, 32, 0, 0, 0, 0, 112.4, 82.5),
+    (8, 3, 0, 28, 1, 0, 0, 1, 0, 40.1, 43.7), (8, 3, 0, 28, 5, 0, 0, 1, 0, 56.5, 53.8), (8, 3, 1, 28, 4, 0, 0, 0, 0, 25.2, 23.2),
+    (24, 2, 1, 33, 8, 0, 0, 0, 0, 39.7, 36.5), (9, 2, 1, 30, 2, 0, 0, 1, 0, 68.7, 52.6), (8, 3, 1, 32, 32, 0, 0, 0, 0, 112.4, 82.5),
     # small states with failures
     (16, 3, 0, 33, 5, 10, 0, 0, 0, 55.3, 60.2), (16, 3, 1, 40, 8, 10, 0, 0, 0, 63.4, 66.5), (32, 2, 0, 36, 5, 10, 0, 0, 0, 28.1, 30.8),
     (8, 3, 0, 33, 5, 10, 0, 0, 0, 38.4, 40.9), (8, 3, 0, 44, 8, 10, 0, 0, 0, 40.1, 35.9), (16, 2, 0, 36, 5, 10, 0, 0, 0, 25.1, 23.7),
-    (8, 3, 0, 200, 5, 10, 0, 0, 1, 108.9, 86.5), (32, 2, 0, 40, 10, 10, 0, 1, 0, 124.3, 106.7), (16, 3, 0, 200, 5, 10, 0, 1, 0, 320.7, 226.0),
+    (8, 3, 0, 200, 5, 10, 0, 0, 1, 108.9, 86.5), (32, 2, 0, 40, 10, 10, 0, 1, 0, 106.2, 92.1), (16, 3, 0, 200, 5, 10, 0, 1, 0, 249, 209),
     # two column parts in place of one
     (8, 3, 0, 1000, 4, 0, 0, 0, 0, 420, 443), (8, 3, 0, 1000, 8, 0, 0, 0, 0, 502, 425), (8, 3, 0, 1000, 5, 10, 0, 0, 0, 433, 457),
-    (8, 3, 0, 1000, 8, 10, 0, 0, 0, 515, 446), (8, 3, 0, 1000, 5, 10, 0, 1, 0, 987, 1311), (8, 3, 0, 3000, 20, 10, 0, 1, 0, 8605, 9338), (8, 3, 0, 3000, 64, 10, 0, 1, 0, 26047, 24796),
-    (8, 3, 0, 1000, 5, 10, 0, 0, 1, 554, 458), (8, 3, 0, 200, 5, 10, 0, 1, 0, 222.8, 196.6), (8, 3, 0, 1000, 5, 0, 0, 1, 0, 961, 787),
-    (13, 3, 0, 1000, 5, 0, 0, 1, 0, 1244, 959), (13, 3, 0, 1000, 12, 0, 0, 1, 0, 2670, 2548), (13, 3, 0, 1000, 4, 0, 0, 0, 0, 776, 600),
-    (13, 3, 1, 1000, 2, 0, 0, 1, 0, 1778, 1370), (24, 2, 0, 1000, 5, 0, 0, 1, 0, 1180, 1290), (24, 2, 0, 1000, 40, 0, 0, 1, 0, 7329, 6360), (24, 2, 0, 3000, 12, 0, 0, 1, 0, 7185, 6663),
+    (8, 3, 0, 1000, 8, 10, 0, 0, 0, 515, 446), (8, 3, 0, 1000, 5, 10, 0, 1, 0, 867, 1204), (8, 3, 0, 3000, 20, 10, 0, 1, 0, 7080, 8215), (8, 3, 0, 3000, 64, 10, 0, 1, 0, 21464, 20267),
+    (8, 3, 0, 1000, 5, 10, 0, 0, 1, 554, 458), (8, 3, 0, 200, 5, 10, 0, 1, 0, 198.7, 170.4), (8, 3, 0, 1000, 5, 0, 0, 1, 0, 838, 660),
+    (13, 3, 0, 1000, 5, 0, 0, 1, 0, 1244, 959), (13, 3, 0, 1000, 12, 0, 0, 1, 0, 2196, 1313), (13, 3, 0, 1000, 4, 0, 0, 0, 0, 776, 600),
+    (13, 3, 1, 1000, 2, 0, 0, 1, 0, 1586, 1143), (24, 2, 0, 1000, 5, 0, 0, 1, 0, 1127, 1078), (24, 2, 0, 1000, 40, 0, 0, 1, 0, 6600, 4579), (24, 2, 0, 3000, 12, 0, 0, 1, 0, 6032, 4989),
     (24, 2, 0, 1000, 4, 0, 0, 0, 0, 532, 497), (32, 2, 0, 250, 4, 0, 0, 0, 0, 99, 108), (24, 2, 1, 1000, 8, 0, 0, 0, 0, 3055, 828),
     # who is absent (60 MB and more, 12 rounds unless stated): curves, refresh, groups without an average, half of the peers
-    (16, 2, 0, 300, 12, 30, 0, 1, 0, 542, 466), (16, 2, 0, 300, 12, 80, 0, 1, 0, 537, 602), (32, 2, 0, 1500, 12, 90, 0, 1, 0, 3209, 3519),
-    (8, 3, 0, 60, 12, 70, 0, 1, 0, 163, 192), (16, 3, 0, 300, 12, 90, 0, 1, 0, 817, 705),
+    (16, 2, 0, 300, 12, 30, 0, 1, 0, 521, 365), (16, 2, 0, 300, 12, 80, 0, 1, 0, 515, 527), (32, 2, 0, 1500, 12, 90, 0, 1, 0, 2530, 3692),
+    (8, 3, 0, 60, 12, 70, 0, 1, 0, 145, 198), (16, 3, 0, 300, 12, 90, 0, 1, 0, 602, 758),
     (8, 3, 1, 300, 12, 95, 0, 0, 1, 178, 204), (16, 2, 0, 300, 12, 95, 0, 0, 1, 143, 125),
     (8, 3, 1, 1500, 12, 95, 0, 0, 0, 845, 1184), (8, 3, 1, 300, 12, 80, 0, 0, 0, 306, 293), (8, 3, 0, 300, 12, 90, 0, 0, 0, 170, 193),
     (16, 2, 0, 300, 12, 30, 1, 0, 0, 94, 117), (32, 2, 1, 1500, 12, 10, 1, 0, 0, 746, 822), (32, 2, 1, 1500, 12, 95, 0, 0, 0, 1253, 1048),
     (8, 3, 0, 300, 12, 50, 0, 0, 0, 212, 233), (16, 3, 0, 60, 12, 70, 0, 0, 0, 84, 94), (16, 3, 1, 300, 12, 50, 0, 0, 0, 346, 394),
     (16, 3, 1, 300, 6, 50, 0, 0, 0, 311, 277),
+    # curves: two parts with a mean per group; few rounds, many absent
+    (24, 2, 0, 438.8, 2, 0, 0, 1, 0, 320, 365), (16, 2, 0, 205.5, 24, 50, 0, 1, 0, 674, 549),
+    (16, 2, 0, 80.4, 12, 50, 0, 1, 0, 163, 185.8), (32, 2, 0, 58, 12, 30, 0, 1, 0, 144.7, 126.9),
+    (16, 3, 0, 182.4, 5, 70, 0, 1, 0, 238, 266), (16, 3, 0, 55, 24, 60, 0, 1, 0, 311, 266),
+    (16, 3, 1, 184.1, 5, 95, 0, 1, 0, 329, 360), (16, 3, 1, 191.1, 8, 50, 0, 1, 0, 469, 419),
+    (8, 3, 0, 219.5, 8, 50, 0, 1, 0, 298, 323),
 ]
 
 
@@ -316,6 +322,8 @@ WAYS = [
     (32, 2, 1, 304, 6, 95, 0, 0, 0, 110, 149), (16, 2, 0, 735, 12, 95, 0, 0, 0, 412, 304), (16, 2, 1, 307, 6, 90, 0, 0, 0, 177, 133),
     (32, 2, 0, 105, 16, 90, 0, 0, 0, 148, 95), (32, 2, 1, 835, 10, 95, 0, 0, 0, 730, 561), (16, 3, 1, 1327, 12, 80, 0, 0, 0, 1947, 1334),
     (16, 3, 0, 2151, 10, 70, 0, 0, 0, 2772, 1584), (16, 2, 1, 191, 7, 90, 0, 0, 0, 143, 95), (16, 2, 0, 39, 10, 80, 0, 0, 0, 70, 32),
+    (16, 3, 1, 84.31, 2, 0, 0, 1, 0, 171.4, 87), (16, 3, 1, 139.4, 2, 0, 0, 1, 0, 237, 120.3),
+    (32, 2, 1, 904.98, 1, 0, 0, 1, 0, 688, 442), (16, 3, 1, 94.7, 5, 40, 0, 1, 0, 339, 184.9),
 ]
 
 
