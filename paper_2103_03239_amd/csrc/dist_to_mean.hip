@@ -14,16 +14,18 @@
 // rows.  Their per-column sums meet across lanes and in LDS, and the block writes ONE partial.  A second
 // one-block kernel adds the partials in a fixed order, so the result does not depend on scheduling.
 //
-// What bounds it (MI355X): HBM where there are enough tiles (6.8 to 6.9 TB/s from 1.6 GB on); below, the
-// walk along the rows, so tiles get narrower until the chip has waves enough (dist_tiles.h).  A tile was
-// 64 vectors wide whatever the state's shape, with a wave for 256 rows of it.  us, both kernels, then and now:
-//   1024 rows, 25 MB            binary32 44.6 -> 8.2     bfloat16 75 -> 11.2
-//   256 rows, 6.4 MB            39.9 -> 7.4              69 -> 9.3
-//   4096 rows, 100 MB           82 -> 19.5               110 -> 22
-//   512 rows, 400 MB            64 -> 61                 93 -> 65
-//   4096 rows, 1.6 GB           253 -> 232               273 -> 236
-//   4096 rows, 2.1 GB                                    344 -> 314
-//   16 rows, 1.6 GB             321 -> 243               328 -> 272   (the sum of 97,657 partials: 60 us of it)
+// What bounds it (MI355X): HBM where there are enough tiles (6.3 to 6.9 TB/s from 1.6 GB on, 5.3 to 5.9 in the pass that follows a
+// write, whose lines it pushes out of the last-level cache); below, the walk along the rows, so tiles get narrower until the chip has
+// waves enough (dist_tiles.h).  A tile was 64 vectors wide whatever the state's shape, with a wave for 256 rows of it.  us, both kernels, repeated
+// passes (the pass after a write), then and now:
+//   1024 rows, 25 MB            binary32 26 -> 7.8 (34 -> 13)      bfloat16 52 -> 11 (56 -> 15)
+//   256 rows, 6.4 MB            22 -> 7.1 (32 -> 10)               33 -> 8.2 (53 -> 12)
+//   4096 rows, 100 MB           79 -> 19 (60 -> 23)                111 -> 22 (102 -> 25)
+//   512 rows, 400 MB            64 -> 62 (73 -> 66)                100 -> 64 (95 -> 66)
+//   4096 rows, 1.6 GB           266 -> 245 (311 -> 297)            291 -> 256 (327 -> 307)
+//   4096 rows, 2.1 GB           350 -> 333 (414 -> 369)            353 -> 339 (384 -> 394)
+//   16 rows, 1.6 GB             328 -> 245 (391 -> 305)            330 -> 245 (379 -> 303)
+//   1024 rows, 17 GB            2,588 -> 2,497 (2,929 -> 2,910)
 // dist_partial_kernel takes a row mask, and rows of less than 16 bytes.
 #include <mutex>
 

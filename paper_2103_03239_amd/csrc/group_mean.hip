@@ -382,7 +382,7 @@ hipError_t launch_group_mean(void *X, int dtype, int64_t P, int64_t row_stride, 
     // Peer lists, whose rows lie apart and come back in other groups, hold on to it longer, with ordinary accesses and more waves.  Time of
     // non-temporal accesses over that, chunk-index and random rounds with 10 % absent, both types: groups of 3 to 8 (8 x 8 x 8, 5 x 5 x 5, 4 x 4 x 4,
     // 3^4) at 315 MiB 1.07 to 1.18, 448 1.03 to 1.08, 512 0.99 to 1.03, 534 0.99 to 1.01, 553 0.98 to 1.02, 610 0.96 to 1.01; of 12 to 32 (12 x 12, 16 x 16, 16 x 16 x 16,
-    // 32 x 32) at 448 MiB 1.04 to 1.12, 512 0.99 to 1.09, 553 1.01 to 1.07, 610 0.98 to 1.05, 572 1.01 to 1.07, 686 0.96 to 1.04.
+    // 32 x 32) at 448 MiB 1.04 to 1.12, 512 0.99 to 1.09, 553 1.01 to 1.07, 572 1.01 to 1.07, 610 0.98 to 1.05, 686 0.96 to 1.04.
     const bool cached_list = geom.index != nullptr && whole_lines && !cached && touched <= (geom.M > 8 ? 600.0 : 544.0) * (1 << 20);
     // Rounds over rows off the cache lines, of a state too large for the last-level cache, deal work items to the dies in runs
     // of 32: the first and last lines of a row's part meet in one L2, and the waves in flight still stream a handful of groups.

@@ -49,7 +49,8 @@ def test_permutation_and_keys(M, d):
 @pytest.mark.parametrize("M,d", [(16, 2), (8, 3), (64, 2)])
 def test_keys_that_have_come_together(M, d):
     """Rounds in which every peer is alone in its group leave it chunk 0, until all peers share one key:
-    the next order ranks them all in one bucket, at about the price of any other."""
+    the next order ranks them among each other at about the price of any other (test_crowded_buckets has the
+    grids whose buckets hold hundreds then)."""
     N, P, seed = M ** d, 4, 40 + M
     print(f"keys together M={M} d={d}", flush=True)
     r = np.random.default_rng(M)
@@ -84,7 +85,7 @@ def test_keys_that_have_come_together(M, d):
             one_round(t + k, None)
         apart = min(took[-2:])
     print(f"  {1e6 * crowded:.0f} us a round, {1e6 * apart:.0f} with keys apart", flush=True)
-    # counting one bucket of 2048 took 240 us more
+    # counting among the 2048 of a key took 240 us more
     assert crowded <= apart + 100e-6
     # at most 7 additions in a row and a division in the four rounds that average anything, each within 2^-24
     assert_state_close(X.cpu().double().numpy(), ref, 4 * 8 * 2.0 ** -24, f"keys together {M}^{d}")
