@@ -96,7 +96,8 @@ inline int64_t dist_sums_bytes(int64_t waves, int64_t sharers, int64_t columns, 
 // How many share it.  Of an odd number of waves one takes none (when all of them did, with two rounds' sums: 12 x 12 bfloat16 of 1 GB, 5
 // waves, had 2 blocks a compute unit, 30 rounds 4,830 us, and has 3, 3,150; 13 x 13 x 13 binary32 took two column parts instead of
 // one, 10 rounds 2,010 -> 1,130; 20 x 20 of 1 GB, 30 rounds 2,840 -> 2,200).  One less where that makes room for passes of 24 rounds (13 x 13 x 13
-// binary32, 3 of 9 waves, 24 rounds of 1 GB in one pass 2,010 us, in two with 4 waves 2,640).
+// binary32, 3 of 9 waves, 24 rounds of 1 GB in one pass 2,010 us, in two with 4 waves 2,640; 16 x 16 bfloat16, 3 of 8 waves, which leave one
+// column part room, where 4 took two: 10 rounds of 1 GB 1,148 -> 1,005, of 100 MB 145 -> 143).
 inline int32_t dist_sharers(int64_t waves, int64_t columns, int64_t room)
 {
     const int32_t half = waves > 1 ? static_cast<int32_t>(waves / 2) : 1;
