@@ -401,10 +401,16 @@ inline bool copies_ahead(const GridPlan &copies, const GridPlan &means, int64_t 
         // 0.99, 60 % 1.02 to 1.11 up to 12 rounds, 24 rounds 0.85, 70 % 1.05 to 1.18, 40 rounds 0.98, 95 % 1.05 to 1.28, bfloat16 80 % 0.90 to
         // 1.06, 90 % 1.00 to 1.15, 95 % 1.03 to 1.10)
         const bool cached = state <= 268435456;
-        const double least = M <= 8 ? 0.6 : M > 16 ? (ask.refresh ? 0.35 : cached ? 0.45 : rounds < 40 ? 0.81 : 0.5)
+        const double least = M <= 8 ? 0.6 : M > 16 ? (cached ? 0.45 : rounds < 40 ? 0.81 : 0.5)
                              : copies.N <= 1024 ? (state < 130000000 ? 0.65 : 0.25)
                              : f32 ? (rounds < 24 ? 0.45 : 0.15) : rounds < 24 ? 0.15 : 0.0;
-        if (ask.averaged < least) return true;
+        // (with returning peers, whose rows M copies have to move; curves of 5 to 24 rounds by the peers averaged: 512 peers within 256 MiB 54 % 0.89 to
+        // 0.97, 43 % 1.00 to 1.07, 33 % 1.07 to 1.22, beyond 54 % 1.22 to 1.28; 256 peers, 38 to 120 MB 67 % 0.93, 54 % 1.02, 43 % 1.06, from 190 MB
+        // on 25 % 0.89 to 0.91, 11 % 0.95 to 1.00, 5 % 1.08; 1,024 within 256 MiB 33 % 0.95, 25 % 1.02 to 1.06, beyond 54 % 0.88 to 0.99, 43 % 1.00 to
+        // 1.04, 25 % 1.12 to 1.18; 4,096 33 % 0.83 to 0.96, 25 % 1.07, 11 % 1.05 to 1.11, bfloat16 18 % 0.97, 5 % 0.99 to 1.10)
+        const double with_refresh = M <= 8 ? (cached ? 0.45 : 0.6) : M > 16 ? (cached ? 0.28 : 0.45)
+                                    : copies.N <= 1024 ? (state < 130000000 ? 0.55 : 0.08) : f32 ? 0.28 : 0.1;
+        if (ask.averaged < (ask.refresh ? with_refresh : least)) return true;
     } else if (ask.absent && copies.N <= 1024) {
         if (ask.refresh) {
             // (512 peers, 12 rounds: 6 % of the groups live 0.92 to 1.07, 2 % 1.02 to 1.18, 6 rounds of 300 MB and more 0.86 to 0.98)

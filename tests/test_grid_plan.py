@@ -286,6 +286,10 @@ MEASURED = [
     (16, 3, 0, 182.4, 5, 70, 0, 1, 0, 238, 266), (16, 3, 0, 55, 24, 60, 0, 1, 0, 311, 266),
     (16, 3, 1, 184.1, 5, 95, 0, 1, 0, 329, 360), (16, 3, 1, 191.1, 8, 50, 0, 1, 0, 469, 419),
     (8, 3, 0, 219.5, 8, 50, 0, 1, 0, 298, 323),
+    # curves with returning peers
+    (8, 3, 0, 80.2, 12, 50, 0, 1, 1, 203, 248), (16, 2, 0, 79.9, 5, 50, 0, 1, 1, 111, 126.4),
+    (16, 2, 0, 217.4, 8, 50, 0, 1, 1, 326, 281), (32, 2, 0, 470.5, 8, 60, 0, 1, 1, 791, 897),
+    (16, 3, 0, 187.3, 24, 20, 0, 1, 1, 928, 590), (16, 3, 0, 376.9, 8, 90, 0, 1, 1, 665, 764),
 ]
 
 
